@@ -5,8 +5,8 @@
 // Every quantity is computed with the operations of the host setup in the
 // same order, and this file is compiled without floating-point contraction,
 // so the boxes and the map equal those of fpts_setup on the same nodes bit
-// for bit.  One wave per element: sums whose order fixes the rounding run
-// in one lane; the Chebyshev-grid evaluations of the bounds run across
+// for bit.  One wave per element: sums whose order fixes the rounding take
+// a lane each; the Chebyshev-grid evaluations of the bounds run across
 // lanes (each lane one grid point, the reduction is a min/max).
 #include <cmath>
 #include <vector>
@@ -31,144 +31,163 @@ __device__ __forceinline__ void wave_minmax(double &lo, double &hi)
     }
 }
 
-// Bound of u(r) = sum_i u_i phi_i(r) (eqs. eq_1D_bound_final_1/2): linear
-// Legendre part removed, basis bounds at the M Chebyshev points.  u in LDS,
-// sc: LDS scratch of the wave.  Result uniform over the wave.
-__device__ void bound1_w(const BoundTables &T, const double *u, double *sc, int lane,
-                         double &lo, double &hi)
-{
-    const int N = T.N, M = T.M;
-    if (lane == 0) {
-        double a0 = 0.0, a1 = 0.0;
-        for (int i = 0; i < N; ++i) {
-            a0 += u[i] * T.mom0[i];
-            a1 += u[i] * T.mom1[i];
+// The functions whose bounds make an element's box, per coordinate: the
+// edges of a quad (4), the faces of a hex (6), the whole patch of a surface
+// quad, the whole curve of a line element (1); each a function of BD = 1 or
+// 2 parameters.  Function fn belongs to coordinate fn % D and side fn / D.
+template <int D, int R, int N>
+struct Sides {
+    static constexpr int BD = (R == 3 || (R == 2 && D == 3)) ? 2 : 1;
+    static constexpr int NS = R == 3 ? 6 : (R == 2 && D == 2) ? 4 : 1;   // sides
+    static constexpr int NF = NS * D;
+    static constexpr int PTS = BD == 2 ? N * N : N;   // nodes of a side
+    static constexpr int NP = R == 3 ? N * N * N : R == 2 ? N * N : N;
+    // bounds of two parameters: the sides go to G groups of NQ functions,
+    // one group per lane and grid point; LDS keeps a node's NQ values
+    // together (an even number of doubles, for 16-byte reads)
+    static constexpr int G = R == 3 ? 2 : 1;
+    static constexpr int NQ = NF / G;
+    static constexpr int PQ = (NQ + 1) / 2 * 2;
+    static constexpr int VALS = BD == 2 ? PTS * G * PQ : PTS * NF;
+    static constexpr int MOM = BD == 2 ? 4 : 2;       // Legendre moments per function
+    // node of the element at node idx of side sd
+    __device__ static __forceinline__ int node(int sd, int idx)
+    {
+        if (NS == 1) return idx;
+        const int q = (sd & 1) ? N - 1 : 0, t = sd >> 1;
+        if (R == 3) {
+            const int x0 = idx % N, x1 = idx / N;
+            return t == 0   ? x0 + N * (x1 + N * q)
+                   : t == 1 ? x0 + N * (q + N * x1)
+                            : q + N * (x0 + N * x1);
         }
-        sc[0] = a0 * 0.5;
-        sc[1] = a1 * 1.5;
+        return t == 0 ? idx + N * q : q + N * idx;
     }
-    __syncthreads();
-    const double a0 = sc[0], a1 = sc[1];
-    double l = INFINITY, h = -INFINITY;
-    if (lane < M) {
-        const int j = lane;
-        l = a0 + a1 * T.eta[j];
-        h = l;
-        for (int i = 0; i < N; ++i) {
-            const double w = u[i] - (a0 + a1 * T.z[i]);
-            const double x = w * T.vlo[i * M + j], y = w * T.vhi[i * M + j];
-            l += mn(x, y);
-            h += mx(x, y);
-        }
-    }
-    wave_minmax(l, h);
-    lo = l;
-    hi = h;
-    __syncthreads();
-}
-
-// Bound of u(r,s) = sum_ij u_ij phi_i(r) phi_j(s), u indexed i + N j (eqs.
-// eq_2D_function_bound_1/2), bilinear Legendre part removed.  w: LDS [N*N].
-__device__ void bound2_w(const BoundTables &T, const double *u, double *w, double *sc,
-                         int lane, double &lo, double &hi)
-{
-    const int N = T.N, M = T.M;
-    if (lane == 0) {
-        double a00 = 0, a10 = 0, a01 = 0, a11 = 0;
-        for (int j = 0; j < N; ++j)
-            for (int i = 0; i < N; ++i) {
-                const double x = u[i + N * j];
-                a00 += x * T.mom0[i] * T.mom0[j];
-                a10 += x * T.mom1[i] * T.mom0[j];
-                a01 += x * T.mom0[i] * T.mom1[j];
-                a11 += x * T.mom1[i] * T.mom1[j];
-            }
-        sc[0] = a00 * 0.25;
-        sc[1] = a10 * 0.75;
-        sc[2] = a01 * 0.75;
-        sc[3] = a11 * 2.25;
-    }
-    __syncthreads();
-    const double a00 = sc[0], a10 = sc[1], a01 = sc[2], a11 = sc[3];
-    for (int idx = lane; idx < N * N; idx += kLanes) {
+    // where the value of function (side sd, coordinate c) at node idx is kept
+    __device__ static __forceinline__ int at(int sd, int c, int idx)
+    {
+        if (BD == 1) return (sd * D + c) * PTS + idx;
         const int i = idx % N, j = idx / N;
-        w[idx] = u[idx] - (a00 + a10 * T.z[i] + a01 * T.z[j] + a11 * T.z[i] * T.z[j]);
+        return ((i * N + j) * G + (sd & (G - 1))) * PQ + (sd / G) * D + c;
     }
-    __syncthreads();
-    double l = INFINITY, h = -INFINITY;
-    for (int gp = lane; gp < M * M; gp += kLanes) {
-        const int k = gp % M, ll = gp / M;
-        const double b = a00 + a10 * T.eta[k] + a01 * T.eta[ll] + a11 * T.eta[k] * T.eta[ll];
-        double sl = b, sh = b;
-        for (int i = 0; i < N; ++i) {
-            const double ulo = T.vlo[i * M + k], uhi = T.vhi[i * M + k];
-            for (int j = 0; j < N; ++j) {
-                const double x = w[i + N * j];
-                const double vlo = T.vlo[j * M + ll], vhi = T.vhi[j * M + ll];
-                const double p1 = ulo * vlo, p2 = ulo * vhi, p3 = uhi * vlo, p4 = uhi * vhi;
-                const double pn = mn(mn(p1, p2), mn(p3, p4));
-                const double px = mx(mx(p1, p2), mx(p3, p4));
-                sl += x >= 0.0 ? x * pn : x * px;
-                sh += x >= 0.0 ? x * px : x * pn;
-            }
-        }
-        l = mn(l, sl);
-        h = mx(h, sh);
-    }
-    wave_minmax(l, h);
-    lo = l;
-    hi = h;
-    __syncthreads();
-}
+};
 
-// Bound of one coordinate function f[NP] (LDS): the edges of a quad, the
-// faces of a hex, the whole patch of a surface quad, the whole curve of a
-// line element.
-__device__ void bound_fun_w(const BoundTables &T, int D, int R, const double *f, double *buf,
-                            double *w, double *sc, int lane, double &lo, double &hi)
+// Bounds of an element's NF side functions, whose nodal values are in
+// val (LDS), reduced to lo / hi per coordinate (uniform over the wave): the
+// (bi)linear Legendre part removed, basis bounds at the M Chebyshev points
+// of each parameter (eqs. eq_1D_bound_final_1/2, eq_2D_function_bound_1/2).
+// The moments are sums whose order fixes the rounding: one lane per
+// (function, moment).  The grid evaluations are one lane per grid point and
+// group of functions, so that the products of the basis bounds at a node are
+// formed once for the NQ functions of the group.
+template <int D, int R, int N>
+__device__ __forceinline__ void side_bounds(const BoundTables &T, double *val, double *mom,
+                                            int lane, double (&lo)[3], double (&hi)[3])
 {
-    const int N = T.N;
-    double a, b;
-    lo = INFINITY;
-    hi = -INFINITY;
-    if (R == 2 && D == 2) {
-        for (int e = 0; e < 2; ++e) {
-            const int q = e ? N - 1 : 0;
-            for (int i = lane; i < N; i += kLanes) buf[i] = f[i + N * q];
-            __syncthreads();
-            bound1_w(T, buf, sc, lane, a, b);
-            lo = mn(lo, a);
-            hi = mx(hi, b);
-            for (int j = lane; j < N; j += kLanes) buf[j] = f[q + N * j];
-            __syncthreads();
-            bound1_w(T, buf, sc, lane, a, b);
-            lo = mn(lo, a);
-            hi = mx(hi, b);
+    typedef Sides<D, R, N> S;
+    constexpr int M = 2 * N;
+    __syncthreads();
+    for (int id = lane; id < S::NF * S::MOM; id += kLanes) {
+        const int q = id % S::MOM, fn = id / S::MOM, sd = fn / D, c = fn % D;
+        double a = 0.0;
+        if constexpr (S::BD == 2) {
+            const double *m0 = (q & 1) ? T.mom1 : T.mom0, *m1 = (q & 2) ? T.mom1 : T.mom0;
+#pragma unroll 2
+            for (int j = 0; j < N; ++j)
+#pragma unroll
+                for (int i = 0; i < N; ++i) a += val[S::at(sd, c, i + N * j)] * m0[i] * m1[j];
+            mom[id] = a * (q == 0 ? 0.25 : q == 3 ? 2.25 : 0.75);
+        } else {
+            const double *m0 = q ? T.mom1 : T.mom0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) a += val[S::at(sd, c, i)] * m0[i];
+            mom[id] = a * (q ? 1.5 : 0.5);
         }
-    } else if (R == 3) {
-        for (int e = 0; e < 2; ++e) {
-            const int q = e ? N - 1 : 0;
-            for (int t = 0; t < 3; ++t) {
-                for (int idx = lane; idx < N * N; idx += kLanes) {
-                    const int x0 = idx % N, x1 = idx / N;
-                    buf[idx] = t == 0   ? f[x0 + N * (x1 + N * q)]
-                               : t == 1 ? f[x0 + N * (q + N * x1)]
-                                        : f[q + N * (x0 + N * x1)];
+    }
+    __syncthreads();
+    for (int id = lane; id < S::NF * S::PTS; id += kLanes) {
+        const int fn = id / S::PTS, idx = id % S::PTS, sd = fn / D, c = fn % D;
+        const double *a = mom + fn * S::MOM;
+        const int k = S::at(sd, c, idx);
+        if constexpr (S::BD == 2) {
+            const int i = idx % N, j = idx / N;
+            val[k] = val[k] - (a[0] + a[1] * T.z[i] + a[2] * T.z[j] + a[3] * T.z[i] * T.z[j]);
+        } else {
+            val[k] = val[k] - (a[0] + a[1] * T.z[idx]);
+        }
+    }
+    __syncthreads();
+    double l[D], h[D];
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+        l[c] = INFINITY;
+        h[c] = -INFINITY;
+    }
+    if constexpr (S::BD == 2) {
+#pragma unroll 1
+        for (int it = lane; it < M * M * S::G; it += kLanes) {
+            const int gp = it / S::G, grp = it % S::G, k = gp % M, ll = gp / M;
+            double sl[S::NQ], sh[S::NQ], vlo[N], vhi[N];
+#pragma unroll
+            for (int f = 0; f < S::NQ; ++f) {
+                const double *a = mom + ((f / D * S::G + grp) * D + f % D) * 4;
+                sl[f] = a[0] + a[1] * T.eta[k] + a[2] * T.eta[ll] + a[3] * T.eta[k] * T.eta[ll];
+                sh[f] = sl[f];
+            }
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                vlo[j] = T.vlo[j * M + ll];
+                vhi[j] = T.vhi[j * M + ll];
+            }
+            const double *w = val + grp * S::PQ;
+#pragma unroll 1
+            for (int i = 0; i < N; ++i) {
+                const double ulo = T.vlo[i * M + k], uhi = T.vhi[i * M + k];
+#pragma unroll
+                for (int j = 0; j < N; ++j, w += S::G * S::PQ) {
+                    const double p1 = ulo * vlo[j], p2 = ulo * vhi[j], p3 = uhi * vlo[j],
+                                 p4 = uhi * vhi[j];
+                    const double pn = fmin(fmin(p1, p2), fmin(p3, p4));
+                    const double px = fmax(fmax(p1, p2), fmax(p3, p4));
+                    // the smaller of w pn and w px is w pn for w >= 0, w px else
+#pragma unroll
+                    for (int f = 0; f < S::NQ; ++f) {
+                        const double a = w[f] * pn, b = w[f] * px;
+                        sl[f] += fmin(a, b);
+                        sh[f] += fmax(a, b);
+                    }
                 }
-                __syncthreads();
-                bound2_w(T, buf, w, sc, lane, a, b);
-                lo = mn(lo, a);
-                hi = mx(hi, b);
+            }
+#pragma unroll
+            for (int f = 0; f < S::NQ; ++f) {
+                l[f % D] = mn(l[f % D], sl[f]);
+                h[f % D] = mx(h[f % D], sh[f]);
             }
         }
-    } else if (R == 2) {
-        bound2_w(T, f, w, sc, lane, a, b);
-        lo = mn(lo, a);
-        hi = mx(hi, b);
     } else {
-        bound1_w(T, f, sc, lane, a, b);
-        lo = mn(lo, a);
-        hi = mx(hi, b);
+        for (int it = lane; it < M * S::NF; it += kLanes) {
+            const int fn = it / M, j = it % M, cc = fn % D;
+            double a = mom[2 * fn] + mom[2 * fn + 1] * T.eta[j], b = a;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const double w = val[fn * S::PTS + i];
+                const double x = w * T.vlo[i * M + j], y = w * T.vhi[i * M + j];
+                a += mn(x, y);
+                b += mx(x, y);
+            }
+#pragma unroll
+            for (int c = 0; c < D; ++c)
+                if (cc == c) {
+                    l[c] = mn(l[c], a);
+                    h[c] = mx(h[c], b);
+                }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+        wave_minmax(l[c], h[c]);
+        lo[c] = l[c];
+        hi[c] = h[c];
     }
 }
 
@@ -229,65 +248,88 @@ __device__ bool invert_d(int D, const double *A, double *I)
 }
 
 // AABB and OBB record (lo, hi, OBB centre, OBB inverse transform) and
-// centre of every element; one wave per element.
+// centre of every element; one wave per element, striding.  Bound by FP64
+// vector arithmetic: for a hex (2N)^2 grid points x N^2 nodes x 18 functions
+// x 2 boxes x 6 operations (no contraction: the host's rounding).  Only the
+// side functions' values are kept in LDS; the nodes stream through it one
+// slab (k) at a time for the centre sums, whose order fixes the rounding (one
+// lane per sum).
+template <int D, int R, int N>
 __global__ __launch_bounds__(kLanes) void k_elem_boxes(const BoundTables *Tg, const double *nodes,
-                                                      int64_t nel, int D, int R, double tol,
-                                                      double *box, double *xc_out)
+                                                      int64_t nel, double tol, double *box,
+                                                      double *xc_out)
 {
-    extern __shared__ double lds[];
+    typedef Sides<D, R, N> S;
+    constexpr int NP = S::NP, W = 3 * D + D * D;
+    constexpr int SLAB = R == 1 ? N : N * N, NSLAB = NP / SLAB;   // nodes of a slab
+    constexpr int PER = (D * SLAB + kLanes - 1) / kLanes;
+    static_assert(D * SLAB <= 3 * kMaxN * kMaxN, "slab");
+    __shared__ __align__(16) double val[S::VALS];
+    __shared__ double mom[S::NF * S::MOM], slab[D * SLAB], sc[16];
     const BoundTables &T = *Tg;
-    const int N = T.N, NP = (R == 3) ? N * N * N : (R == 2) ? N * N : N, W = 3 * D + D * D;
     const int lane = threadIdx.x;
-    double *xe = lds;              // [D][NP]
-    double *f = xe + D * NP;       // [NP]
-    double *buf = f + NP;          // [N*N]
-    double *w = buf + N * N;       // [N*N]
-    double *sc = w + N * N;        // scratch (16)
     for (int64_t e = blockIdx.x; e < nel; e += gridDim.x) {
-        for (int idx = lane; idx < D * NP; idx += kLanes) xe[idx] = nodes[e * D * NP + idx];
-        __syncthreads();
+        const double *xe = nodes + e * D * NP;
+        // centre and centre Jacobian: lane 4 c + q sums coordinate c times
+        // phi phi phi (q = 0) or its derivative along direction q - 1
+        {
+            double pre[PER];
+            auto fetch = [&](int ks) __attribute__((always_inline)) {
+#pragma unroll
+                for (int u = 0; u < PER; ++u) {
+                    const int i = u * kLanes + lane;
+                    pre[u] = i < D * SLAB ? xe[i / SLAB * NP + ks * SLAB + i % SLAB] : 0.0;
+                }
+            };
+            const int c = lane >> 2, q = lane & 3;
+            const double *w0 = q == 1 ? T.d0 : T.v0, *w1 = q == 2 ? T.d0 : T.v0,
+                         *w2 = q == 3 ? T.d0 : T.v0;
+            double acc = 0.0;
+            fetch(0);
+#pragma unroll 1
+            for (int ks = 0; ks < NSLAB; ++ks) {
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < PER; ++u) {
+                    const int i = u * kLanes + lane;
+                    if (i < D * SLAB) slab[i] = pre[u];
+                }
+                __syncthreads();
+                if (ks + 1 < NSLAB) fetch(ks + 1);
+                if (c < D && q <= R) {
+                    const double *u = slab + c * SLAB;
+                    if constexpr (R == 1) {
+#pragma unroll
+                        for (int i = 0; i < N; ++i) acc += u[i] * w0[i];
+                    } else {
+#pragma unroll 2
+                        for (int j = 0; j < N; ++j)
+#pragma unroll
+                            for (int i = 0; i < N; ++i) {
+                                double b = w0[i] * w1[j];
+                                if (R == 3) b *= w2[ks];
+                                acc += u[i + N * j] * b;
+                            }
+                    }
+                }
+            }
+            __syncthreads();
+            if (lane < 16) sc[lane] = acc;   // lanes without a sum: 0
+            __syncthreads();
+        }
+        double xc[3] = {0, 0, 0}, G[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+        for (int c = 0; c < D; ++c) {
+            xc[c] = sc[4 * c];
+            for (int a = 0; a < R; ++a) G[c][a] = sc[4 * c + 1 + a];
+        }
         double lo[3], hi[3], one[3] = {1, 1, 1};
-        for (int c = 0; c < D; ++c)
-            bound_fun_w(T, D, R, xe + c * NP, buf, w, sc, lane, lo[c], hi[c]);
+        for (int idx = lane; idx < S::NS * S::PTS; idx += kLanes) {
+            const int sd = idx / S::PTS, k = idx % S::PTS, nd = S::node(sd, k);
+#pragma unroll
+            for (int c = 0; c < D; ++c) val[S::at(sd, c, k)] = xe[c * NP + nd];
+        }
+        side_bounds<D, R, N>(T, val, mom, lane, lo, hi);
         finish_d(D, R, tol, lo, hi, one);
-        // centre and centre Jacobian, in one lane (summation order)
-        if (lane == 0) {
-            double xc[3] = {0, 0, 0}, G[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-            for (int idx = 0; idx < NP; ++idx) {
-                const int ii = idx % N, jj = (idx / N) % N, kk = idx / (N * N);
-                double b0 = T.v0[ii] * T.v0[jj], br = T.d0[ii] * T.v0[jj],
-                       bs = T.v0[ii] * T.d0[jj], bt = 0.0;
-                if (R == 1) {
-                    b0 = T.v0[ii];
-                    br = T.d0[ii];
-                    bs = 0.0;
-                }
-                if (R == 3) {
-                    bt = b0 * T.d0[kk];
-                    b0 *= T.v0[kk];
-                    br *= T.v0[kk];
-                    bs *= T.v0[kk];
-                }
-                for (int c = 0; c < D; ++c) {
-                    const double xv = xe[c * NP + idx];
-                    xc[c] += xv * b0;
-                    G[c][0] += xv * br;
-                    G[c][1] += xv * bs;
-                    if (R == 3) G[c][2] += xv * bt;
-                }
-            }
-            for (int c = 0; c < 3; ++c) {
-                sc[4 + c] = xc[c];
-                for (int a = 0; a < 3; ++a) sc[7 + 3 * c + a] = G[c][a];
-            }
-        }
-        __syncthreads();
-        double xc[3], G[3][3];
-        for (int c = 0; c < 3; ++c) {
-            xc[c] = sc[4 + c];
-            for (int a = 0; a < 3; ++a) G[c][a] = sc[7 + 3 * c + a];
-        }
-        __syncthreads();
         double Jc[9] = {0}, Ji[9] = {0}, len[3] = {1, 1, 1};
         if (R == D) {
             for (int a = 0; a < D; ++a)
@@ -311,15 +353,21 @@ __global__ __launch_bounds__(kLanes) void k_elem_boxes(const BoundTables *Tg, co
         const bool inv = invert_d(D, Jc, Ji);
         double tl[3], th[3];
         if (inv) {
-            for (int c = 0; c < D; ++c) {
-                for (int idx = lane; idx < NP; idx += kLanes) {
-                    double s = 0.0;
-                    for (int q = 0; q < D; ++q) s += Ji[c * D + q] * (xe[q * NP + idx] - xc[q]);
-                    f[idx] = s;
+            __syncthreads();   // the AABB's reads of val come first
+            for (int idx = lane; idx < S::NS * S::PTS; idx += kLanes) {
+                const int sd = idx / S::PTS, k = idx % S::PTS, nd = S::node(sd, k);
+                double x[D];
+#pragma unroll
+                for (int q = 0; q < D; ++q) x[q] = xe[q * NP + nd];
+#pragma unroll
+                for (int c = 0; c < D; ++c) {
+                    double t = 0.0;
+#pragma unroll
+                    for (int q = 0; q < D; ++q) t += Ji[c * D + q] * (x[q] - xc[q]);
+                    val[S::at(sd, c, k)] = t;
                 }
-                __syncthreads();
-                bound_fun_w(T, D, R, f, buf, w, sc, lane, tl[c], th[c]);
             }
+            side_bounds<D, R, N>(T, val, mom, lane, tl, th);
             finish_d(D, R, tol, tl, th, len);
         }
         if (lane == 0) {
@@ -430,6 +478,25 @@ __global__ __launch_bounds__(256) void k_map_sort(const int *off, int64_t ncell,
     }
 }
 
+typedef void (*BoxKernel)(const BoundTables *, const double *, int64_t, double, double *,
+                          double *);
+template <int D, int R>
+BoxKernel pick_boxes(int N)
+{
+    switch (N) {
+    case 2: return k_elem_boxes<D, R, 2>;
+    case 3: return k_elem_boxes<D, R, 3>;
+    case 4: return k_elem_boxes<D, R, 4>;
+    case 5: return k_elem_boxes<D, R, 5>;
+    case 6: return k_elem_boxes<D, R, 6>;
+    case 7: return k_elem_boxes<D, R, 7>;
+    case 8: return k_elem_boxes<D, R, 8>;
+    case 9: return k_elem_boxes<D, R, 9>;
+    case 10: return k_elem_boxes<D, R, 10>;
+    default: return nullptr;
+    }
+}
+
 template <typename T>
 struct DevBuf {
     T *p = nullptr;
@@ -441,7 +508,7 @@ struct DevBuf {
 
 int device_setup(fpts_mesh *m, hipStream_t s)
 {
-    const int D = m->D, R = m->R, N = m->N, NP = m->NP, W = box_words(D);
+    const int D = m->D, R = m->R, N = m->N, W = box_words(D);
     BoundTables bt;
     bound_tables(m, &bt);
     DevBuf<BoundTables> dt;
@@ -449,10 +516,13 @@ int device_setup(fpts_mesh *m, hipStream_t s)
     if (hipMemcpyAsync(dt.p, &bt, sizeof(bt), hipMemcpyHostToDevice, s) != hipSuccess)
         return FPTS_EDEVICE;
     // boxes and centres
-    const size_t lds = sizeof(double) * (D * NP + NP + 2 * N * N + 16);
     const int grid = (int)std::min<int64_t>(m->nel, (int64_t)m->cus * 16);
-    hipLaunchKernelGGL(k_elem_boxes, dim3(grid), dim3(kLanes), lds, s, dt.p, m->d_nodes,
-                       (int64_t)m->nel, D, R, m->p.bbox_tol, m->d_box, m->d_xc);
+    const BoxKernel kb = D == 2 ? (R == 2 ? pick_boxes<2, 2>(N) : pick_boxes<2, 1>(N))
+                         : R == 3 ? pick_boxes<3, 3>(N)
+                                  : R == 2 ? pick_boxes<3, 2>(N) : pick_boxes<3, 1>(N);
+    if (!kb) return FPTS_EINVAL;
+    hipLaunchKernelGGL(kb, dim3(grid), dim3(kLanes), 0, s, dt.p, m->d_nodes, (int64_t)m->nel,
+                       m->p.bbox_tol, m->d_box, m->d_xc);
     if (hipGetLastError() != hipSuccess) return FPTS_EDEVICE;
     // union box
     const int ublocks = (int)std::min<int64_t>((m->nel + 255) / 256, 1024);
