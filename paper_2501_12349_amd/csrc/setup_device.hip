@@ -91,16 +91,23 @@ __device__ __forceinline__ void side_bounds(const BoundTables &T, double *val, d
         const int q = id % S::MOM, fn = id / S::MOM, sd = fn / D, c = fn % D;
         double a = 0.0;
         if constexpr (S::BD == 2) {
-            const double *m0 = (q & 1) ? T.mom1 : T.mom0, *m1 = (q & 2) ? T.mom1 : T.mom0;
-#pragma unroll 2
+            double m0[N], m1[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                m0[i] = (q & 1) ? T.mom1[i] : T.mom0[i];
+                m1[i] = (q & 2) ? T.mom1[i] : T.mom0[i];
+            }
+            const double *u = val + S::at(sd, c, 0);
+#pragma unroll
             for (int j = 0; j < N; ++j)
 #pragma unroll
-                for (int i = 0; i < N; ++i) a += val[S::at(sd, c, i + N * j)] * m0[i] * m1[j];
+                for (int i = 0; i < N; ++i)
+                    a += u[(i * N + j) * S::G * S::PQ] * m0[i] * m1[j];
             mom[id] = a * (q == 0 ? 0.25 : q == 3 ? 2.25 : 0.75);
         } else {
-            const double *m0 = q ? T.mom1 : T.mom0;
 #pragma unroll
-            for (int i = 0; i < N; ++i) a += val[S::at(sd, c, i)] * m0[i];
+            for (int i = 0; i < N; ++i)
+                a += val[S::at(sd, c, i)] * (q ? T.mom1[i] : T.mom0[i]);
             mom[id] = a * (q ? 1.5 : 0.5);
         }
     }
@@ -282,9 +289,12 @@ __global__ __launch_bounds__(kLanes) void k_elem_boxes(const BoundTables *Tg, co
                 }
             };
             const int c = lane >> 2, q = lane & 3;
-            const double *w0 = q == 1 ? T.d0 : T.v0, *w1 = q == 2 ? T.d0 : T.v0,
-                         *w2 = q == 3 ? T.d0 : T.v0;
-            double acc = 0.0;
+            double w0[N], w1[N], acc = 0.0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                w0[i] = q == 1 ? T.d0[i] : T.v0[i];
+                w1[i] = q == 2 ? T.d0[i] : T.v0[i];
+            }
             fetch(0);
 #pragma unroll 1
             for (int ks = 0; ks < NSLAB; ++ks) {
@@ -296,18 +306,19 @@ __global__ __launch_bounds__(kLanes) void k_elem_boxes(const BoundTables *Tg, co
                 }
                 __syncthreads();
                 if (ks + 1 < NSLAB) fetch(ks + 1);
+                const double w2 = q == 3 ? T.d0[ks] : T.v0[ks];
                 if (c < D && q <= R) {
                     const double *u = slab + c * SLAB;
                     if constexpr (R == 1) {
 #pragma unroll
                         for (int i = 0; i < N; ++i) acc += u[i] * w0[i];
                     } else {
-#pragma unroll 2
+#pragma unroll
                         for (int j = 0; j < N; ++j)
 #pragma unroll
                             for (int i = 0; i < N; ++i) {
                                 double b = w0[i] * w1[j];
-                                if (R == 3) b *= w2[ks];
+                                if (R == 3) b *= w2;
                                 acc += u[i + N * j] * b;
                             }
                     }
