@@ -80,6 +80,19 @@ constexpr int kOverflowCount = 3;   // int counter of the overflowed points
 constexpr int kSlotTotal = 4;   // 64-bit running total of the second search's slots (ints 4, 5)
 constexpr int kHintPasses = 8;  // Newton passes of the hinted search
 
+// Pairs per task of the primary Newton pass at most, a multiple of kChunk:
+// about four tasks for each of the launch's waves (8 per CU), so that the
+// last ones to finish leave little of the chip idle; an element's queue is
+// kept whole below that (its nodes are staged, and its last pairs drained
+// with lanes idle, once).  kChunk where the arrays of another task map
+// would not fit the workspace (few points per element).
+int newton_task_len(const fpts_mesh *m, int64_t n)
+{
+    if (n < 2 * (m->nel + 1)) return kChunk;
+    const int64_t per = n / ((int64_t)m->cus * 8 * 4);
+    return (int)std::min<int64_t>(std::max<int64_t>((per + kChunk - 1) / kChunk, 1), 16) * kChunk;
+}
+
 void clear_events(fpts_mesh *m)
 {
     for (auto &v : m->ev) {
@@ -342,10 +355,21 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
                                         sorted, s));
     }
     {   // phase C: Newton on the primary candidates, results straight to the outputs
+        const int len = newton_task_len(m, n);
+        int *newt_off = chunk_off, *newt_task = task_elem;
+        if (m->R >= 2 && len > kChunk) {
+            // (bin_prim and pbin are free by now, and hold n entries each)
+            newt_off = bin_prim;
+            newt_task = pbin;
+            chk(launch_exclusive_scan(elem_cnt, newt_off, nel, len, tmp, tb, s));
+            chk(launch_task_map(newt_off, nel, newt_task, s));
+        }
         NewtonIO io{sorted, elem_off, chunk_off, nullptr, d_code, d_elem, d_r, n, d_dist,
-                    counters + kNewtonCounters, stats, task_elem, w.tb_elem, rs, n};
+                    counters + kNewtonCounters, stats, task_elem, newt_off, newt_task,
+                    w.tb_elem, rs, n};
         io.pts4 = pts4;
         if (m->R >= 2) {
+            io.node = rank;   // free by now
             io.start = start;
             io.start_stride = n;
             // pairs that reach a face leave the primary kernel's waves
@@ -376,7 +400,8 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
             chk(launch_park_bin(1, park_meta, counters + kParkCount, n, nullptr, park_off,
                                 park_rank, park_sorted, m->cus, s));
             NewtonIO fio{park_sorted, park_off, park_choff, nullptr, d_code, d_elem, d_r, n,
-                         d_dist, nullptr, stats + 2 * kStats, park_task, w.tb_park, rs, n};
+                         d_dist, nullptr, stats + 2 * kStats, park_task, nullptr, nullptr,
+                         w.tb_park, rs, n};
             fio.pts4 = pts4;
             fio.park_meta = park_meta;
             fio.park_r = park_r;
@@ -405,7 +430,7 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
                            w.cap2, nullptr, nullptr, s));
         NewtonIO io{sorted2, elem_off2, chunk_off2, slot_pt, res_code, nullptr, res_r, w.cap2,
                     res_dist, counters + 2 * kNewtonCounters, stats + kStats, task_elem2,
-                    w.tb_elem2};
+                    nullptr, nullptr, w.tb_elem2};
         io.pts4 = pts4;
         // the other candidates are few and near element faces: plain FP64
         // in both modes (an FP32 phase would not pay for its launches)
@@ -416,7 +441,7 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
             // points whose other candidates did not fit the slots (none in
             // the common case: the kernel reads the count and returns)
             NewtonIO oio{olist, nullptr, nullptr, nullptr, d_code, d_elem, d_r, n, d_dist,
-                         nullptr, stats + kStats, nullptr, w.ov_grid};
+                         nullptr, stats + kStats, nullptr, nullptr, nullptr, w.ov_grid};
             oio.pts4 = pts4;
             oio.ocount = counters + kOverflowCount;
             oio.cellpt = cellpt;
@@ -867,8 +892,8 @@ int fpts_lpt_step(fpts_mesh *m, const fpts_lpt_params *p, int64_t n, int first, 
         // passes tell, and the full Find takes it (kHintPasses; a warm
         // start converges in three or four)
         NewtonIO io{sorted, elem_off, chunk_off, nullptr, d_code, d_elem, d_r, n, d_dist,
-                    counters + kNewtonCounters, stats, task_elem, w.tb_elem, nullptr, 0,
-                    keep, kHintPasses};
+                    counters + kNewtonCounters, stats, task_elem, chunk_off, task_elem,
+                    w.tb_elem, nullptr, 0, keep, kHintPasses};
         chk(launch_newton(m, precision, n, d_x, io, 2, s));
         chk(launch_hint(m, 1, n, d_code, d_elem, d_r, cand, nullptr, nullptr, keep, s));
     }

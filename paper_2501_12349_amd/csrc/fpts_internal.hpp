@@ -220,6 +220,10 @@ struct NewtonIO {
     int *counter;           // element-queue counters (zeroed before the launch)
     unsigned long long *stats;
     const int *task_elem;   // task -> element of the nearest-node task grid
+    // the primary pass's Newton tasks (one or more per element, of even
+    // parts of its queue): offsets per element, task -> element
+    const int *newt_off;
+    const int *newt_task;
     int64_t task_bound;     // tasks of that grid at most
     // optional (fused find + interpolate, primary pass): results that settle
     // their point -- INTERIOR at least kSettleGuard inside -- also go to
@@ -234,10 +238,12 @@ struct NewtonIO {
     // optional: the points packed per point, [n][pt_stride(D)] (read instead
     // of the [D][n] coordinates: one cache line per gathered point)
     const double *pts4;
-    // optional: the starts of the Newton kernel (nearest node, or the FP32
-    // phase's result in mixed mode) at the pair's position q in `list`,
-    // start[k * start_stride + q], instead of in r: written and read in list
-    // order, without a gather
+    // optional: the nearest nodes (packed indices) of the pairs by list
+    // position, the starts of the Newton kernel; null: the starts are points
+    int *node;
+    // optional: the starts that are points (the FP32 phase's results in
+    // mixed mode) at the pair's position q in `list`, start[k * start_stride
+    // + q], instead of in r: written and read in list order, without a gather
     double *start;
     int64_t start_stride;
     // optional (primary FP64 pass): a pair whose next pass needs second

@@ -3,27 +3,35 @@
 // contraction on the matrix cores.  Instantiated in kernels_newton.hip
 // (hex, quad and surface kinds); kernels_eval.hip shares its LDS layout.
 //
-// Task = one element and the queue of its pairs.  The wave stages the
-// element's nodal coordinates in LDS and serves 16 pairs at a time, one per
-// slot; slot s owns lanes s, s+16, s+32, s+48 (g = lane / 16 picks the
-// quarter).  When a slot's pair is done it takes the next pair of the queue.
+// Task = one element and a queue of its pairs.  The wave stages the
+// element's nodal coordinates in LDS and serves up to 64 pairs at a time,
+// one per lane: a lane holds its pair's state and runs its Newton update.
+// When a lane's pair is done it takes the next pair of the queue.
 //
-// One map evaluation for the 16 slots at their reference points q_s:
-//   stage 1 (MFMA, v_mfma_{f64,f32}_16x16x4):
+// The map is evaluated for 16 pairs (a column group) at a time.  The lanes
+// that need an evaluation hand their reference points q over in LDS, packed
+// without gaps; in column group cg, column s belongs to the four lanes
+// s, s+16, s+32, s+48 (g = lane / 16 picks the quarter):
+//   stage 1 (MFMA, v_mfma_{f64,f32}_16x16x4, f64_4x4x4):
 //       C[row][s] = sum_i X[c][i][row] phi_i(q_s,0)   (and phi' / phi'')
 //     where row = (j, k) flattened (hex) or j (quad); A = node rows from LDS,
-//     B = the slot's bases (lane provides phi_i for i = 4 ks + g), so the
-//     16 MFMA columns are the 16 slots and lane l receives four rows of each
-//     16-row tile (which four depends on the instruction) for its own slot.
+//     B = the column's bases (lane provides phi_i for i = 4 ks + g), so the
+//     16 MFMA columns are the 16 pairs and lane l receives rows of its own
+//     column (four of each 16-row tile, one of each 4-row tile).
 //   stage 2+3 (VALU): each lane weights its rows with phi_j(s) phi_k(t) (and
-//     derivatives) of its slot, read from a per-slot LDS table (for N = 4, 8
-//     summed over k first, then weighted per j), and the four lanes of a
-//     slot are summed by lane swaps, four values at a time.  Each sum is
-//     formed once and broadcast, so the four lanes hold bit-identical values
-//     and run the Newton update redundantly and in step.
+//     derivatives) of its column, read from an LDS table (for N = 4, 8
+//     summed over k first, then weighted per j).
+//   The sums over a column's four lanes are formed by transposition: the
+//   16-lane swaps of two column groups and the 32-lane swap of two such
+//   results leave the totals of column 16 cg + s in lane 16 cg + s.
+// Why 16 columns of evaluation but 64 lanes of iteration: FP64 MFMA and
+// vector FMA run at the same rate on gfx950, so the evaluation gains nothing
+// from wider groups, while the update of a pair (some 400 FP64 instructions)
+// would be issued four times if the four lanes of a column shared one pair.
+// The totals of a column do not depend on which group or column it is, so a
+// pair's iterates do not depend on the pairs beside it.
 // Second derivatives (beta = 1 passes on faces/edges, eq. eq_newton_hessian)
-// are computed in a separate sweep contracted with the slot's residual dx,
-// run when enough slots wait for it (or nothing else can proceed).
+// are computed in a separate sweep contracted with the pair's residual dx.
 //
 // Mixed precision: the FP32 phase runs every pair of the element on FP32
 // nodes stored as offsets from the element centre (points shifted the same
@@ -55,6 +63,14 @@ __device__ __forceinline__ V4<float>::type mfma16(float a, float b, V4<float>::t
 {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
+
+// four 4x4x4 products side by side: A rows 4 (the same four for every block),
+// columns 16, one row of the result per lane quarter
+__device__ __forceinline__ double mfma4(double a, double b, double c)
+{
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ float mfma4(float, float, float c) { return c; }   // FP64 covers only
 
 template <typename T> __device__ inline T eps_of();
 template <> __device__ inline double eps_of<double>() { return DBL_EPSILON; }
@@ -195,6 +211,30 @@ __device__ __forceinline__ void slot_sum_all(T (&v)[K])
     if constexpr (K % 2 == 1) v[K - 1] = slot_sum(v[K - 1]);
 }
 
+// Column sums by transposition.  fold16: x and y hold the partial sums of
+// two column groups; the result holds, in row r of the wave, the sum over
+// rows r & ~1 and r | 1 of x (r even) or of y (r odd).  fold32 of two such
+// results completes them: row r holds the four-row total of group r.  Every
+// total is (row 0 + row 1) + (row 2 + row 3), whichever group it is.
+template <typename T, int K>
+__device__ __forceinline__ void fold16(T (&x)[K], const T (&y)[K])
+{
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const Two<T> p = swap16(x[k], y[k]);
+        x[k] = p.a + p.b;
+    }
+}
+template <typename T, int K>
+__device__ __forceinline__ void fold32(T (&x)[K], const T (&y)[K])
+{
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const Two<T> p = swap32(x[k], y[k]);
+        x[k] = p.a + p.b;
+    }
+}
+
 // Contraction row of the 16x16 output tile m held by lane quarter g in item
 // qq: 16 m + g + 4 qq.  The FP64 instruction interleaves the tile's rows that
 // way (item qq of quarter g is tile row g + 4 qq); the FP32 one gives each
@@ -214,6 +254,26 @@ struct Shape {
     static constexpr int ROWS = (R == 3) ? N * N : N;   // contraction rows
     static constexpr int MT = (ROWS + 15) / 16;         // 16-row tiles
     static constexpr int KS = (N + 3) / 4;              // 4-wide K steps
+};
+
+// Sweep 1's cover of the contraction without (most of) its padding.  FP64:
+// the rows beyond the last whole 16-row tile go to 4-row tiles
+// (v_mfma_f64_4x4x4 on four column quarters: 16 columns, a quarter of the
+// time), and where N is 1 or 2 above a multiple of 4 the last node indices
+// are added by vector FMAs (8 or 16 per tile and coordinate against two
+// MFMAs of 64 cycles, which would be padding but for them).  N = 6: 1610
+// instead of 2520 cycles of stage 1 per 16 pairs; N = 10: 6.5k instead of
+// 8.4k.  FP32: 16-row tiles and K steps rounded up (its MFMA is twice as
+// fast against the vector FMA, and has no 4-row form of this shape).
+template <typename T, int D, int R, int N>
+struct Cover {
+    typedef Shape<D, R, N> S;
+    static constexpr bool F64 = std::is_same<T, double>::value;
+    static constexpr int LEFT = S::ROWS % 16;
+    static constexpr int QT = F64 && LEFT <= 12 ? (LEFT + 3) / 4 : 0;   // 4-row tiles
+    static constexpr int FT = QT || !LEFT ? S::ROWS / 16 : S::MT;        // 16-row tiles
+    static constexpr int KR = F64 && (N % 4 == 1 || N % 4 == 2) ? N % 4 : 0;   // by FMA
+    static constexpr int KM = KR ? N / 4 : S::KS;                        // K steps by MFMA
 };
 
 // Where node (coordinate c, contraction row `row`, first index i) of the
@@ -313,29 +373,17 @@ __device__ __forceinline__ void basis_table(T x, T *tab, int slot, bool write)
     }
 }
 
-// Pairs staged per refill of a wave's slots (coordinates, start and id).
-// 32 keeps the FP64 LDS footprint of hexes with N <= 8 within 20 KB, so that
-// eight waves fit a CU.
-constexpr int kCache = 32;
-
-// LDS layout of one wave: nodes [D][NP] of type T, then the per-slot basis
-// tables of directions 1 and 2 (s, t): [2][3][N][16] of type T.
+// LDS layout of one wave: nodes [D][NP] of type T, the basis tables of one
+// column group, [R][2][N][16] (sweep 2: [R - 1][3][N][16]), then the points
+// of the pairs to evaluate, [R][64] (sweep 2: [R + D][16]).  FP64 hexes with
+// N <= 8 stay within 20 KB, so that eight waves fit a CU.
 template <typename T, int D, int R, int N>
 struct Lds {
     static constexpr int NODES = NodeLds<T, D, R, N>::SIZE;
-    static constexpr int TAB = 3 * N * 16;
-    // pair cache: kCache x (point coordinates D, start r R) of type T, then
-    // kCache item ids and kCache start-node indices
-    static constexpr int CACHE = kCache * (D + R);
-    static constexpr size_t bytes()
-    {
-        return sizeof(T) * (NODES + 2 * TAB + CACHE) + sizeof(int) * 2 * kCache;
-    }
-    __device__ static int *citem(void *lds)
-    {
-        return reinterpret_cast<int *>(reinterpret_cast<char *>(lds) + bytes() -
-                                       sizeof(int) * 2 * kCache);
-    }
+    static constexpr int TAB = (R == 3 ? 6 : 4) * N * 16;
+    static constexpr int QB = 64 * R;
+    static_assert(16 * (R + D) <= QB, "sweep 2 points");
+    static constexpr size_t bytes() { return sizeof(T) * (NODES + TAB + QB); }
 };
 
 // Rows of the differentiation matrix at the GLL nodes: v[a][m] = phi_m'(z_a),
@@ -371,6 +419,22 @@ constexpr DiffRows<T, N> make_diff()
 template <typename T, int N>
 __device__ const DiffRows<T, N> kDiff = make_diff<T, N>();
 
+// The GLL nodes, indexed per lane.
+template <typename T, int N>
+struct NodeRow {
+    T v[N];
+};
+template <typename T, int N>
+constexpr NodeRow<T, N> make_nodes()
+{
+    constexpr gll::Table<N> G = gll::Nodes<N>::t;
+    NodeRow<T, N> r{};
+    for (int i = 0; i < N; ++i) r.v[i] = T(G.z[i]);
+    return r;
+}
+template <typename T, int N>
+__device__ const NodeRow<T, N> kNodes = make_nodes<T, N>();
+
 // Stage 2+3 factored by j for hexes whose 16-row tiles hold whole (j, k)
 // blocks (N = 4, 8): a lane's rows 16 m + g + 4 qq have j = g + 4 (qq % NJ)
 // whatever m is, so the k-weights are summed per j first and the j-weights
@@ -381,40 +445,48 @@ struct Factor {
     static constexpr int NJ = N / 4 > 0 ? N / 4 : 1;   // the lane's distinct j
 };
 
-// Sweep 1 for all 16 slots: x(q) and G = dx/dr of each slot's point.
+// Sweep 1 for column group cg: each lane's partial sums of x(q) and
+// G = dx/dr of its column (v: X[c], then G[c][a]); the column's totals are
+// the sums over its four lanes.
 template <typename T, int D, int R, int N>
-__device__ __forceinline__ void sweep1(const T *xl, T *tab, int lane, const T (&q)[R], T (&X)[D],
-                                       T (&G)[D][R])
+__device__ __forceinline__ void sweep1(const T *xl, T *tab, const T *qb, int cg, int lane,
+                                       T (&v)[D * (R + 1)])
 {
     typedef Shape<D, R, N> S;
+    typedef Cover<T, D, R, N> C;
     typedef Factor<R, N> F;
+    typedef NodeLds<T, D, R, N> NL;
     typedef typename V4<T>::type v4;
     const int slot = lane & 15, g = lane >> 4;
-    // per-slot tables [direction][kind][i][slot] (kinds phi, phi'): lane
-    // quarter g builds direction g of its slot, so the R tables of all 16
-    // slots are built at once
-    wave_lds_sync();   // the previous sweep's reads of the tables come first
+    // per-column tables [direction][kind][i][column] (kinds phi, phi'): lane
+    // quarter g builds direction g of its column, so the R tables of all 16
+    // columns are built at once
+    wave_lds_sync();   // qb is written; the previous group's reads of the tables come first
     {
-        // q[g] by exact arithmetic selection (one weight is 1, the others
-        // 0), which keeps q in registers
-        const T w0 = T(g != 1 && g != 2), w1 = T(g == 1), w2 = T(R == 3 && g == 2);
-        T x = q[0] * w0;
-        x = fma(q[1], w1, x);
-        if (R == 3) x = fma(q[R == 3 ? 2 : 0], w2, x);
+        const T x = qb[(g < R ? g : 0) * 64 + 16 * cg + slot];
         basis_table<T, N, false>(x, tab + (g < R ? g : 0) * 2 * N * 16, slot, g < R);
     }
     wave_lds_sync();
     const T *tr = tab, *ts = tab + 2 * N * 16, *tt = tab + 4 * N * 16;
-    // B operand: this lane's bases in direction 0 for i = 4 ks + g
-    T b0[S::KS], b1[S::KS];
+    // B operand: this lane's bases in direction 0 for i = 4 ks + g, and the
+    // bases of the indices left to FMAs
+    T b0[C::KM > 0 ? C::KM : 1], b1[C::KM > 0 ? C::KM : 1];
+    T e0[C::KR > 0 ? C::KR : 1], e1[C::KR > 0 ? C::KR : 1];
 #pragma unroll
-    for (int ks = 0; ks < S::KS; ++ks) {
+    for (int ks = 0; ks < C::KM; ++ks) {
         const int i = 4 * ks + g;
-        b0[ks] = i < N ? tr[(0 * N + i) * 16 + slot] : T(0);
-        b1[ks] = i < N ? tr[(1 * N + i) * 16 + slot] : T(0);
+        const bool ok = N % 4 == 0 || C::KR > 0 || i < N;
+        b0[ks] = ok ? tr[(0 * N + i) * 16 + slot] : T(0);
+        b1[ks] = ok ? tr[(1 * N + i) * 16 + slot] : T(0);
+    }
+#pragma unroll
+    for (int u = 0; u < C::KR; ++u) {
+        e0[u] = tr[(0 * N + 4 * C::KM + u) * 16 + slot];
+        e1[u] = tr[(1 * N + 4 * C::KM + u) * 16 + slot];
     }
     // the lane's partial sums: X, G directly, or (factored) per j the
     // k-weighted sums Zv = sum_k C0 t_k, Zd = sum_k C1 t_k, Zt = sum_k C0 t'_k
+    T X[D], G[D][R];
     T Zv[F::NJ][D], Zd[F::NJ][D], Zt[F::NJ][D];
 #pragma unroll
     for (int c = 0; c < D; ++c) {
@@ -428,27 +500,52 @@ __device__ __forceinline__ void sweep1(const T *xl, T *tab, int lane, const T (&
             Zt[js][c] = T(0);
         }
     }
-    constexpr bool kFullA = (N % 4 == 0) && (S::ROWS % 16 == 0);
-    // one row tile; the first is issued on its own, where the partial sums
-    // are still the constant 0 (no registers to clear for the loop)
+    // C0, C1 of one contraction row of the lane, weighted into the sums
+    auto add_row = [&](int row, const T (&c0)[D], const T (&c1)[D]) __attribute__((always_inline)) {
+        if constexpr (R == 3) {
+            const int j = row % N, k = row / N;
+            const T sv = ts[(0 * N + j) * 16 + slot], sd = ts[(1 * N + j) * 16 + slot];
+            const T tv = tt[(0 * N + k) * 16 + slot], td = tt[(1 * N + k) * 16 + slot];
+            const T w00 = sv * tv, w10 = sd * tv, w01 = sv * td;
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                X[c] = fma(c0[c], w00, X[c]);
+                G[c][0] = fma(c1[c], w00, G[c][0]);
+                G[c][1] = fma(c0[c], w10, G[c][1]);
+                G[c][R - 1] = fma(c0[c], w01, G[c][R - 1]);
+            }
+        } else {
+            const T sv = ts[(0 * N + row) * 16 + slot], sd = ts[(1 * N + row) * 16 + slot];
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                X[c] = fma(c0[c], sv, X[c]);
+                G[c][0] = fma(c1[c], sv, G[c][0]);
+                G[c][1] = fma(c0[c], sd, G[c][1]);
+            }
+        }
+    };
+    // A entries outside the element (rows or node indices of the padding)
+    // meet a zero B entry or land in rows that are dropped; the clamped
+    // address keeps the read inside the node block
+    constexpr bool kFullA = (N % 4 == 0 || C::KR > 0);
+    // one 16-row tile (factored: the first is issued on its own, where the
+    // partial sums are still the constant 0, no registers to clear)
     auto tile = [&](int m) __attribute__((always_inline)) {
         v4 acc0[D], acc1[D];
+        constexpr bool kRows = S::ROWS % 16 == 0 || C::QT > 0;   // the tile's rows all exist
+        const int arow = a_row<T>(m, slot);   // A-operand row of this lane
 #pragma unroll
         for (int c = 0; c < D; ++c) {
             acc0[c] = v4{0, 0, 0, 0};
             acc1[c] = v4{0, 0, 0, 0};
         }
-        const int arow = a_row<T>(m, slot);   // A-operand row of this lane
 #pragma unroll
-        for (int ks = 0; ks < S::KS; ++ks) {
+        for (int ks = 0; ks < C::KM; ++ks) {
             const int ai = 4 * ks + g;      // A-operand column (node index i)
-            const bool aok = kFullA || (arow < S::ROWS && ai < N);
+            const bool aok = (kFullA && kRows) || ((kRows || arow < S::ROWS) && (kFullA || ai < N));
 #pragma unroll
             for (int c = 0; c < D; ++c) {
-                // out-of-range A entries meet a zero B entry (ai >= N) or
-                // land in output rows that are dropped (arow >= ROWS); the
-                // clamped address keeps the read inside the node block
-                const T a = xl[aok ? NodeLds<T, D, R, N>::at(c, arow, ai) : 0];
+                const T a = xl[aok ? NL::at(c, arow, ai) : 0];
                 acc0[c] = mfma16(a, b0[ks], acc0[c]);
                 acc1[c] = mfma16(a, b1[ks], acc1[c]);
             }
@@ -456,43 +553,80 @@ __device__ __forceinline__ void sweep1(const T *xl, T *tab, int lane, const T (&
 #pragma unroll
         for (int qq = 0; qq < 4; ++qq) {
             const int row = out_row(m, g, qq);
-            if (S::ROWS % 16 != 0 && row >= S::ROWS) continue;
+            if (!kRows && row >= S::ROWS) continue;
+            T c0[D], c1[D];
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                c0[c] = acc0[c][qq];
+                c1[c] = acc1[c][qq];
+#pragma unroll
+                for (int u = 0; u < C::KR; ++u) {
+                    const T a = xl[NL::at(c, row, 4 * C::KM + u)];
+                    c0[c] = fma(a, e0[u], c0[c]);
+                    c1[c] = fma(a, e1[u], c1[c]);
+                }
+            }
             if constexpr (F::ON) {
                 const int k = (16 * m + 4 * qq) / N, js = qq % F::NJ;   // row / N (g < 4)
                 const T tv = tt[(0 * N + k) * 16 + slot], td = tt[(1 * N + k) * 16 + slot];
 #pragma unroll
                 for (int c = 0; c < D; ++c) {
-                    Zv[js][c] = fma(acc0[c][qq], tv, Zv[js][c]);
-                    Zd[js][c] = fma(acc1[c][qq], tv, Zd[js][c]);
-                    Zt[js][c] = fma(acc0[c][qq], td, Zt[js][c]);
-                }
-            } else if constexpr (R == 3) {
-                const int j = row % N, k = row / N;
-                const T sv = ts[(0 * N + j) * 16 + slot], sd = ts[(1 * N + j) * 16 + slot];
-                const T tv = tt[(0 * N + k) * 16 + slot], td = tt[(1 * N + k) * 16 + slot];
-                const T w00 = sv * tv, w10 = sd * tv, w01 = sv * td;
-#pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    X[c] = fma(acc0[c][qq], w00, X[c]);
-                    G[c][0] = fma(acc1[c][qq], w00, G[c][0]);
-                    G[c][1] = fma(acc0[c][qq], w10, G[c][1]);
-                    G[c][2] = fma(acc0[c][qq], w01, G[c][2]);
+                    Zv[js][c] = fma(c0[c], tv, Zv[js][c]);
+                    Zd[js][c] = fma(c1[c], tv, Zd[js][c]);
+                    Zt[js][c] = fma(c0[c], td, Zt[js][c]);
                 }
             } else {
-                const int j = row;
-                const T sv = ts[(0 * N + j) * 16 + slot], sd = ts[(1 * N + j) * 16 + slot];
-#pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    X[c] = fma(acc0[c][qq], sv, X[c]);
-                    G[c][0] = fma(acc1[c][qq], sv, G[c][0]);
-                    G[c][1] = fma(acc0[c][qq], sd, G[c][1]);
-                }
+                add_row(row, c0, c1);
             }
         }
     };
-    tile(0);
+    if constexpr (F::ON) {
+        tile(0);
 #pragma unroll 1
-    for (int m = 1; m < S::MT; ++m) tile(m);
+        for (int m = 1; m < C::FT; ++m) tile(m);
+    } else {
+        // (one copy: with the row weights of two the registers spill)
+#pragma unroll 1
+        for (int m = 0; m < C::FT; ++m) tile(m);
+    }
+    // one 4-row tile: lane quarter g receives row g, all quarters of the
+    // columns read the same four A rows
+    if constexpr (C::QT > 0) {
+#pragma unroll 1
+        for (int t = 0; t < C::QT; ++t) {
+            const int base = 16 * C::FT + 4 * t;
+            const bool whole = S::ROWS % 4 == 0 || base + 4 <= S::ROWS;
+            const int arow = base + (slot & 3), row = base + g;
+            T c0[D], c1[D];
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                c0[c] = T(0);
+                c1[c] = T(0);
+            }
+#pragma unroll
+            for (int ks = 0; ks < C::KM; ++ks) {
+                const int ai = 4 * ks + g;
+                const bool aok = (whole || arow < S::ROWS) && (kFullA || ai < N);
+#pragma unroll
+                for (int c = 0; c < D; ++c) {
+                    const T a = xl[aok ? NL::at(c, arow, ai) : 0];
+                    c0[c] = mfma4(a, b0[ks], c0[c]);
+                    c1[c] = mfma4(a, b1[ks], c1[c]);
+                }
+            }
+            if (whole || row < S::ROWS) {
+#pragma unroll
+                for (int u = 0; u < C::KR; ++u)
+#pragma unroll
+                    for (int c = 0; c < D; ++c) {
+                        const T a = xl[NL::at(c, row, 4 * C::KM + u)];
+                        c0[c] = fma(a, e0[u], c0[c]);
+                        c1[c] = fma(a, e1[u], c1[c]);
+                    }
+                add_row(row, c0, c1);
+            }
+        }
+    }
     if constexpr (F::ON) {
 #pragma unroll
         for (int js = 0; js < F::NJ; ++js) {
@@ -503,35 +637,35 @@ __device__ __forceinline__ void sweep1(const T *xl, T *tab, int lane, const T (&
                 X[c] = fma(Zv[js][c], sv, X[c]);
                 G[c][0] = fma(Zd[js][c], sv, G[c][0]);
                 G[c][1] = fma(Zv[js][c], sd, G[c][1]);
-                G[c][2] = fma(Zt[js][c], sv, G[c][2]);
+                G[c][R - 1] = fma(Zt[js][c], sv, G[c][R - 1]);
             }
         }
     }
-    T v[D * (R + 1)];
 #pragma unroll
     for (int c = 0; c < D; ++c) {
         v[c] = X[c];
 #pragma unroll
         for (int a = 0; a < R; ++a) v[D + c * R + a] = G[c][a];
     }
-    slot_sum_all(v);
-#pragma unroll
-    for (int c = 0; c < D; ++c) {
-        X[c] = v[c];
-#pragma unroll
-        for (int a = 0; a < R; ++a) G[c][a] = v[D + c * R + a];
-    }
 }
 
-// Sweep 2: S_ab = sum_c dx_c d2x_c/dr_a dr_b at each slot's q.
+// Sweep 2: S_ab = sum_c dx_c d2x_c/dr_a dr_b for 16 columns, whose points q
+// and residuals dx are in qb ([R + D][16]); the four lanes of a column all
+// receive its totals.
 template <typename T, int D, int R, int N>
-__device__ __forceinline__ void sweep2(const T *xl, T *tab, int lane, const T (&q)[R],
-                                       const T (&dx)[D], T (&Sout)[kSym<R>])
+__device__ __forceinline__ void sweep2(const T *xl, T *tab, const T *qb, int lane,
+                                       T (&Sout)[kSym<R>])
 {
     typedef Shape<D, R, N> S;
     typedef Factor<R, N> F;
     typedef typename V4<T>::type v4;
     const int slot = lane & 15, g = lane >> 4;
+    wave_lds_sync();   // qb is written
+    T q[R], dx[D];
+#pragma unroll
+    for (int k = 0; k < R; ++k) q[k] = qb[k * 16 + slot];
+#pragma unroll
+    for (int c = 0; c < D; ++c) dx[c] = qb[(R + c) * 16 + slot];
     T b0[S::KS], b1[S::KS], b2[S::KS];
 #pragma unroll
     for (int ks = 0; ks < S::KS; ++ks) {
@@ -764,44 +898,63 @@ enum { S_FREE = 0, S_INIT = 1, S_STEP = 2, S_WAIT = 3 };
 // kPrimary, with the polish step and the double-batch refill).
 enum { kPrimary = 0, kResolve = 1, kFace = 2, kPolish = 3 };
 
-// per-slot counters are kept by the slot's leader lane, per-wave (sweep)
-// counters by lane 0
+// Free lanes that make a second refill and plan within a trip worth their
+// instructions (some 250 FP64, against lanes idle for one trip).
+constexpr int kReplan = 16;
+// park_meta flag beside the pass count: no iteration state was saved
+constexpr int kParkNoState = 1 << 30;
+
+// per-wave counters (scalar registers: counts of ballots)
 struct Counters {
-    unsigned long long pairs = 0, passes = 0, evals = 0, evals_h2 = 0, passes32 = 0,
-                       evals32 = 0, evals_h2_exec = 0, sweeps = 0, sweeps_h2 = 0, sweeps32 = 0,
-                       evals32_node = 0;
+    unsigned pairs = 0, passes = 0, evals = 0, evals_h2 = 0, passes32 = 0, evals32 = 0,
+             evals_h2_exec = 0, sweeps = 0, sweeps_h2 = 0, sweeps32 = 0, evals32_node = 0;
 };
 
+// Adds the wave's counters to the pass's.
+__device__ __forceinline__ void add_counters(const Counters &cn, unsigned long long *stats,
+                                             int lane)
+{
+    const unsigned v[11] = {cn.pairs,    cn.passes,  cn.evals,         cn.evals_h2,
+                            cn.passes32, cn.evals32, cn.evals_h2_exec, cn.sweeps,
+                            cn.sweeps_h2, cn.sweeps32, cn.evals32_node};
+#pragma unroll
+    for (int k = 0; k < 11; ++k)
+        if (lane == 0 && v[k]) atomicAdd(&stats[k], (unsigned long long)v[k]);
+}
+
+// How a pair's start is given: the packed index of a GLL node per list
+// position (io.node; the nearest node), or a point r (io.start per list
+// position, or io.r per item).
+enum { kStartNode = 0, kStartPoint = 1, kStartEither = 2 };
+
 // Run the iteration of Section 3.2.1 for every pair of element e (its queue
-// [q0, q1) in io.list), in precision T, 16 slots at a time.  FINAL: write
+// [q0, q1) in io.list), in precision T, one pair per lane.  FINAL: write
 // code/elem/dist/r (FP64 phase); otherwise write r only (FP32 phase of mixed
-// mode).  Each trip evaluates either sweep 1 at the slots' query points
-// (start points of new pairs, trial points of the others) or, when enough
-// slots wait for it, sweep 2 at the waiting slots' current points.
+// mode).  Each trip refills free lanes, plans the trial points of the
+// stepping ones, and evaluates the map (sweep 1) where that is due; waiting
+// lanes get their second derivatives (sweep 2) before the trip's plan.
 // stage(): stages the element's nodes in LDS (a no-op where the caller
-// staged them: kResolve, before it wrote the starts, and kFace).
+// staged them: kResolve, which found its starts from them, and kFace).
+// given_node: kResolve, the start node of the pair at list position
+// q0 + lane.
 template <typename T, int D, int R, int N, bool FINAL, int KIND, typename Stage>
 __device__ __forceinline__ void run_element(const NewtonArgs &a, int e, int q0, int q1,
-                                            const T *xl, T *tab, T *cache, int *citem, int lane,
-                                            int max_iter, T tol, const double *shift,
+                                            const T *xl, T *tab, T *qb, int lane, int max_iter,
+                                            T tol, const double *shift, int given_node,
                                             Counters &cn, Stage &&stage)
 {
-    const int slot = lane & 15;
-    const bool leader = lane < 16;
+    typedef unsigned long long u64;
+    constexpr int K = D * (R + 1);
+    constexpr int START = KIND == kPolish || KIND == kFace ? kStartPoint
+                          : FINAL                          ? kStartNode
+                                                           : kStartEither;
+    // the waves of the primary pass hand pairs that need second derivatives
+    // on (to the face kernel; FP32: to the FP64 phase)
+    constexpr bool kHandOn = KIND == kPrimary || KIND == kPolish;
     const NewtonIO &io = a.io;
-    int state = S_FREE, item = 0, pass = 0, pos = 0;
-    // start node of the slot's pair (packed index, -1: the start is not a
-    // node or not used); fresh: the slot's start was evaluated at its node
-    // this trip.  Only the FP32 phase of mixed mode evaluates starts at their
-    // nodes: its pairs take about two evaluations, so the start is half of
-    // them; in FP64 (three to four) the extra refill-and-plan round per trip
-    // cost more than the sweeps it saved (measured on hex48).
-    constexpr bool kNodeStart = KIND != kFace && !FINAL;
-    int nodeix = -1;
-    bool fresh = false;
-    int *cnode = citem + kCache;
-    T xs[D], r[R], q[R], dx[D], Hs[kSym<R>], alpha = T(1), pred = T(0), dmax = T(0),
-        xnorm = T(0);
+    int state = S_FREE, item = 0, pass = 0, pos = 0, node = -1;
+    bool fresh = false;   // evaluated at its start node this trip, not planned yet
+    T xs[D], r[R], q[R], dx[D], Hs[kSym<R>], alpha = T(1), pred = T(0), xnorm = T(0);
     Obj<T, D, R> cur;
 #pragma unroll
     for (int c = 0; c < D; ++c) {
@@ -812,284 +965,250 @@ __device__ __forceinline__ void run_element(const NewtonArgs &a, int e, int q0, 
     for (int k = 0; k < R; ++k) {
         r[k] = T(0);
         q[k] = T(0);
+        cur.g[k] = T(0);
     }
 #pragma unroll
-    for (int k = 0; k < kSym<R>; ++k) Hs[k] = T(0);
+    for (int k = 0; k < kSym<R>; ++k) {
+        Hs[k] = T(0);
+        cur.Hgn[k] = T(0);
+    }
     cur.f = T(0);
-#pragma unroll
-    for (int k = 0; k < R; ++k) cur.g[k] = T(0);
-#pragma unroll
-    for (int k = 0; k < kSym<R>; ++k) cur.Hgn[k] = T(0);
     bool hb_ok = false;
-    int head = q0, cstart = q0, cend = q0;
-    // Refill free slots from the element's queue, through a cache of the
-    // next kCache pairs (one coalesced load per kCache pairs).  Wave-uniform.
-    // When the staged batch runs out before every free slot has a pair, the
-    // next batch is staged at once where pairs take one or two evaluations
-    // (the FP32 phase and the polish phase of mixed mode: their slots turn
-    // over every trip); with three to four evaluations per pair (FP64) the
-    // slot waits for the next trip instead (the loop cost more there than
-    // the idle slots, measured on hex48).
-    constexpr int batches = (!FINAL || KIND == kPolish) ? 2 : 1;
-    // The pair ids, points and starts of a batch of the queue (lane l: list
-    // position b0 + l) are loaded into registers by fetch and written to the
-    // cache when the batch is staged.  The batches follow each other in
-    // list order, so where an element's queue spans many batches (the
-    // primary and polish passes) the next batch is fetched as soon as the
-    // current one is staged, and its loads complete behind the sweeps.
-    // The starts are read at the pair's list position (io.start: issued at
-    // once, beside the chain list -> point) or with its item (io.r; kFace:
-    // the list holds park indices, and the point, the saved iterate and the
-    // rest of the pair's state come from the park record).  Plain loads, as
-    // an earlier kernel wrote them -- except in kResolve, whose wave wrote
-    // its starts moments ago (agent-scope loads, which bypass L1).
-    constexpr bool kAhead = KIND == kPrimary || KIND == kPolish;
-    int nb_it = 0;
-    double nb_pc[D], nb_sv[R];
-    auto fetch = [&](int b0) __attribute__((always_inline)) {
-        auto load_start = [&](const double *src) __attribute__((always_inline)) {
-            if constexpr (KIND == kResolve)
-                return __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            else
-                return *src;
-        };
+    // Staged pairs: lane l holds the pair at list position cstart + l of the
+    // batch [cstart, cend).  Batches of 64 follow each other in list order;
+    // in the primary and polish passes, whose queues span several, the next
+    // batch's data are loaded while the current one is handed out, and the
+    // list entries of the one after are loaded with them, so that a batch's
+    // gathers do not wait for its list.  (kFace: the list holds park
+    // indices, and the point and the saved iterate come from the park
+    // record.)
+    struct Batch {
+        int it, node;
+        double x[D], s[START == kStartNode ? 1 : R];
+    };
+    constexpr bool kAhead = kHandOn;
+    int head = q0, cstart = q0, cend = min(q1, q0 + kWave);
+    auto load_item = [&](int b0) __attribute__((always_inline)) {
         const int idx = b0 + lane;
-        nb_it = 0;
+        return idx < q1 ? io.list[idx] : 0;
+    };
+    auto load_batch = [&](int b0, int it, Batch &b) __attribute__((always_inline)) {
+        const int idx = b0 + lane;
+        b.it = it;
+        b.node = -1;
+        if (idx < q1) {
+            int p;
+            if constexpr (KIND == kFace) p = io.park_meta[it].x;
+            else p = io.slot_pt ? io.slot_pt[it] : it;
+            if constexpr (KIND == kResolve) {
+                b.node = given_node;
+            } else if constexpr (START != kStartPoint) {
+                if (START == kStartNode || io.node) b.node = io.node[idx];
+            }
 #pragma unroll
-        for (int c = 0; c < D; ++c) nb_pc[c] = 0.0;
+            for (int c = 0; c < D; ++c) b.x[c] = point_coord<D>(a, p, c);
+            if constexpr (START != kStartNode) {
+                if (START == kStartPoint || !io.node) {
+                    const double *src = KIND == kFace ? io.park_r + it
+                                        : io.start    ? io.start + idx
+                                                      : io.r + it;
+                    const size_t st = KIND == kFace ? (size_t)io.park_cap
+                                      : io.start    ? (size_t)io.start_stride
+                                                    : (size_t)io.ostride;
 #pragma unroll
-        for (int k = 0; k < R; ++k) nb_sv[k] = 0.0;
-        if (lane < kCache && idx < q1) {
-            const bool by_pos = KIND != kFace && io.start != nullptr;
+                    for (int k = 0; k < R; ++k) b.s[k] = src[k * st];
+                }
+            }
+        }
+    };
+    Batch cb = {}, nb = {};
+    int it2 = 0;   // list entries of the batch after next
+    // the first batch is loaded before the nodes are staged, so that the two
+    // wait together
+    load_batch(q0, load_item(q0), cb);
+    if constexpr (kAhead) {
+        if (cend < q1) {
+            load_batch(cend, load_item(cend), nb);
+            it2 = load_item(cend + kWave);
+        }
+    }
+    stage();
+    // Free lanes take the next pairs of the queue (wave-uniform control).
+    auto refill = [&]() __attribute__((always_inline)) {
+#pragma unroll 1
+        for (;;) {
+            const u64 freem = __ballot(state == S_FREE);
+            if (!freem || head >= q1) return;
+            if (kAhead && head >= cend) {
+                cb = nb;
+                cstart = cend;
+                cend = min(q1, cend + kWave);
+                if (cend < q1) {
+                    load_batch(cend, it2, nb);
+                    it2 = load_item(cend + kWave);
+                }
+            }
+            const int src = head - cstart + __popcll(freem & ((1ull << lane) - 1));
+            const bool take = state == S_FREE && src < cend - cstart;
+            const int from = min(src, kWave - 1);
+            const int it = __shfl(cb.it, from);
+            const int nd = START == kStartPoint ? -1 : __shfl(cb.node, from);
+            T x[D], s[R];
+#pragma unroll
+            for (int c = 0; c < D; ++c)
+                x[c] = T(__shfl(cb.x[c], from) - (shift ? shift[c] : 0.0));
 #pragma unroll
             for (int k = 0; k < R; ++k)
-                if (by_pos) nb_sv[k] = load_start(io.start + (size_t)k * io.start_stride + idx);
-            nb_it = io.list[idx];
-            int p;
-            if constexpr (KIND == kFace) p = io.park_meta[nb_it].x;
-            else p = io.slot_pt ? io.slot_pt[nb_it] : nb_it;
+                s[k] = START == kStartNode ? T(0) : T(__shfl(cb.s[START == kStartNode ? 0 : k], from));
+            if (take) {
+                item = it;
+                node = nd;
+                pos = cstart + src;
+                T xn = T(0);
 #pragma unroll
-            for (int c = 0; c < D; ++c) nb_pc[c] = point_coord<D>(a, p, c);
-            if (!by_pos) {
+                for (int c = 0; c < D; ++c) {
+                    xs[c] = x[c];
+                    xn = fma(x[c], x[c], xn);
+                }
+                xnorm = sqrt_scale(xn);
+                if (START != kStartPoint && nd >= 0) {
+                    const int ix[3] = {nd % N, (nd / N) % N, nd / (N * N)};
+#pragma unroll
+                    for (int k = 0; k < R; ++k) r[k] = kNodes<T, N>.v[ix[k]];
+                } else {
+#pragma unroll
+                    for (int k = 0; k < R; ++k) r[k] = s[k];
+                }
+#pragma unroll
+                for (int k = 0; k < R; ++k) q[k] = r[k];
+                state = S_INIT;
+                pass = 0;
+                alpha = T(1);
+                hb_ok = false;
+                if constexpr (KIND == kFace) {
+                    // resumed where it was parked: same point, radius and
+                    // pass count (the pair was counted by the primary pass)
+                    const int4 mt = io.park_meta[it];
+                    pass = mt.w & ~kParkNoState;
+                    alpha = T(io.park_r[(size_t)R * io.park_cap + it]);
+                    if (it < io.park_state_cap && !(mt.w & kParkNoState)) {
+                        // with the state the evaluation at r left: the
+                        // pair waits for its second derivatives at once
+                        const double *ps = io.park_state + (size_t)it * kParkState;
+                        cur.f = T(ps[0]);
+#pragma unroll
+                        for (int j = 0; j < R; ++j) cur.g[j] = T(ps[1 + j]);
+#pragma unroll
+                        for (int j = 0; j < kSym<R>; ++j) cur.Hgn[j] = T(ps[1 + R + j]);
+#pragma unroll
+                        for (int c = 0; c < D; ++c) dx[c] = T(ps[1 + R + kSym<R> + c]);
+                        state = S_WAIT;
+                    }
+                    item = mt.x;
+                    pos = mt.y;
+                }
+            }
+            const int taken = min(__popcll(freem), cend - head);
+            if (FINAL && KIND != kFace) cn.pairs += taken;
+            head += taken;
+        }
+    };
+    // A pair is done: results out, lane free.
+    auto finish = [&](bool converged) __attribute__((always_inline)) {
+        if (FINAL) {
+            if (io.conv) io.conv[item] = converged ? 1 : 0;
+            bool inside = true;
+#pragma unroll
+            for (int k = 0; k < R; ++k) inside = inside && (fabs(r[k]) < T(1));
+            if (R < D) inside = inside && (cur.f < T(a.eps_d));
+            io.code[item] = inside ? FPTS_INTERIOR : FPTS_BORDER;
+            if (io.elem) io.elem[item] = e;
+            io.dist[item] = sqrt((double)cur.f);
+            if (io.rs) {
+                double mg = 1.0;
+#pragma unroll
+                for (int k = 0; k < R; ++k) mg = fmin(mg, 1.0 - fabs((double)r[k]));
+                const bool settles = inside && mg > kSettleGuard;
 #pragma unroll
                 for (int k = 0; k < R; ++k)
-                    nb_sv[k] = load_start(KIND == kFace ? io.park_r + (size_t)k * io.park_cap + nb_it
-                                                        : io.r + (size_t)k * io.ostride + nb_it);
+                    io.rs[(size_t)k * io.rs_stride + pos] =
+                        settles ? (double)r[k] : __builtin_nan("");
             }
         }
-    };
-    // the primary and polish passes fetch the first batch before the nodes
-    // are staged, so that the two wait together (the face kernel would spill
-    // registers for it; kResolve writes its starts after staging)
-    constexpr bool kEarly = kAhead;
-    if constexpr (kEarly) fetch(q0);
-    stage();
-    auto refill = [&]() {
-#pragma unroll 1
-        for (int round = 0; round < batches; ++round) {
-            const unsigned long long freem = __ballot(leader && state == S_FREE);
-            const int nfree = __popcll(freem);
-            if (!nfree || head >= q1) return;
-            if (head >= cend) {
-                // the next batch starts where the staged one ended
-                wave_lds_sync();   // earlier reads of the cache come first
-                cstart = head;
-                cend = min(q1, head + kCache);
-                if constexpr (!kAhead) {
-                    if (!kEarly || cstart != q0) fetch(cstart);
-                }
-                const int idx = cstart + lane;
-                if (lane < kCache && idx < cend) {
-                    citem[lane] = nb_it;
 #pragma unroll
-                    for (int c = 0; c < D; ++c)
-                        cache[c * kCache + lane] = T(nb_pc[c] - (shift ? shift[c] : 0.0));
-#pragma unroll
-                    for (int k = 0; k < R; ++k) cache[(D + k) * kCache + lane] = T(nb_sv[k]);
-                    // a start that is a GLL node (every nearest-node start): its
-                    // packed index, so that the start is evaluated from the node
-                    // block directly (kFace resumes from parked iterates)
-                    int node = -1;
-                    if constexpr (kNodeStart) {
-                        constexpr gll::Table<N> G = gll::Nodes<N>::t;
-                        int mul = 1;
-                        node = 0;
-#pragma unroll
-                        for (int k = 0; k < R; ++k) {
-                            const T v = cache[(D + k) * kCache + lane];
-                            int ik = -1;
-#pragma unroll
-                            for (int m = 0; m < N; ++m)
-                                if (v == T(G.z[m])) ik = m;
-                            node = (node < 0 || ik < 0) ? -1 : node + mul * ik;
-                            mul *= N;
-                        }
-                    }
-                    cnode[lane] = node;
-                }
-                if constexpr (kAhead)
-                    if (cend < q1) fetch(cend);
-                wave_lds_sync();
-            }
-            if (state == S_FREE) {
-                const int rank = __popcll(freem & ((1ull << slot) - 1));
-                const int idx = head + rank;
-                if (idx < cend) {
-                    const int c0 = idx - cstart;
-                    item = citem[c0];
-                    nodeix = cnode[c0];
-                    pos = idx;
-#pragma unroll
-                    for (int c = 0; c < D; ++c) xs[c] = cache[c * kCache + c0];
-#pragma unroll
-                    for (int k = 0; k < R; ++k) {
-                        r[k] = cache[(D + k) * kCache + c0];
-                        q[k] = r[k];
-                    }
-                    T xn = T(0);
-#pragma unroll
-                    for (int c = 0; c < D; ++c) xn = fma(xs[c], xs[c], xn);
-                    xnorm = sqrt_scale(xn);
-                    state = S_INIT;
-                    pass = 0;
-                    alpha = T(1);
-                    hb_ok = false;
-                    if constexpr (KIND == kFace) {
-                        // resumed where it was parked: same point, radius and
-                        // pass count (the pair was counted by the primary pass)
-                        const int4 mt = io.park_meta[item];
-                        pass = mt.w;
-                        alpha = T(io.park_r[(size_t)R * io.park_cap + item]);
-                        if (item < io.park_state_cap) {
-                            // with the state the evaluation at r left: the
-                            // pair waits for its second derivatives at once
-                            const double *ps = io.park_state + (size_t)item * kParkState;
-                            cur.f = T(ps[0]);
-#pragma unroll
-                            for (int j = 0; j < R; ++j) cur.g[j] = T(ps[1 + j]);
-#pragma unroll
-                            for (int j = 0; j < kSym<R>; ++j) cur.Hgn[j] = T(ps[1 + R + j]);
-#pragma unroll
-                            for (int c = 0; c < D; ++c) dx[c] = T(ps[1 + R + kSym<R> + c]);
-                            state = S_WAIT;
-                        }
-                        item = mt.x;
-                        pos = mt.y;
-                    } else if (leader && FINAL) {
-                        cn.pairs++;
-                    }
-                }
-            }
-            head = min(head + nfree, cend);
-        }
-    };
-    // A pair is done: results out, slot free.
-    auto finish = [&](bool converged) {
-        if (leader) {
-            if (FINAL && io.conv) io.conv[item] = converged ? 1 : 0;
-            if (FINAL) {
-                bool inside = true;
-#pragma unroll
-                for (int k = 0; k < R; ++k) inside = inside && (fabs(r[k]) < T(1));
-                if (R < D) inside = inside && (cur.f < T(a.eps_d));
-                io.code[item] = inside ? FPTS_INTERIOR : FPTS_BORDER;
-                if (io.elem) io.elem[item] = e;
-                io.dist[item] = sqrt((double)cur.f);
-                if (io.rs) {
-                    double mg = 1.0;
-#pragma unroll
-                    for (int k = 0; k < R; ++k) mg = fmin(mg, 1.0 - fabs((double)r[k]));
-                    const bool settles = inside && mg > kSettleGuard;
-#pragma unroll
-                    for (int k = 0; k < R; ++k)
-                        io.rs[(size_t)k * io.rs_stride + pos] =
-                            settles ? (double)r[k] : __builtin_nan("");
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < R; ++k) {
-                if (!FINAL && io.start)   // the FP64 phase's start
-                    io.start[(size_t)k * io.start_stride + pos] = (double)r[k];
-                else
-                    io.r[(size_t)k * io.ostride + item] = (double)r[k];
-            }
+        for (int k = 0; k < R; ++k) {
+            if (!FINAL && io.start)   // the FP64 phase's start
+                io.start[(size_t)k * io.start_stride + pos] = (double)r[k];
+            else
+                io.r[(size_t)k * io.ostride + item] = (double)r[k];
         }
         state = S_FREE;
     };
-    // Slots whose new pair starts at a GLL node: the map there is the node
+    // Lanes whose new pair starts at a GLL node: the map there is the node
     // itself and dx/dr_d = sum_m phi_m'(z_{a_d}) x[.. m ..] (an N-term sum
     // along direction d through the node), read from the node block: no
-    // sweep.  Quarter g < R sums direction g, quarter R reads the node; the
-    // slot's four lanes are then summed (three of each four terms are zero).
-    // Such slots go to S_STEP with the objective at the start, as an
-    // evaluation by sweep 1 would leave them.  Returns whether any did.
-    auto node_init = [&]() -> bool {
-        if constexpr (!kNodeStart) {
-            return false;
-        } else {
+    // sweep.  They go to S_STEP with the objective at the start, as an
+    // evaluation by sweep 1 would leave them.
+    auto node_init = [&]() __attribute__((always_inline)) {
+        fresh = false;
+        if constexpr (START != kStartPoint) {
             typedef NodeLds<T, D, R, N> NL;
-            const bool mine = state == S_INIT && nodeix >= 0;
-            if (!__ballot(leader && mine)) return false;
-            const int g = lane >> 4;
-            const int a0 = nodeix % N, a1 = (nodeix / N) % N, a2 = R == 3 ? nodeix / (N * N) : 0;
-            T v[D * (R + 1)];
-#pragma unroll
-            for (int k = 0; k < D * (R + 1); ++k) v[k] = T(0);
-            if (mine && g < R) {
-                const int ag = g == 0 ? a0 : g == 1 ? a1 : a2;
-                T dphi[N];
-#pragma unroll
-                for (int m = 0; m < N; ++m) dphi[m] = kDiff<T, N>.v[ag][m];
-#pragma unroll
-                for (int m = 0; m < N; ++m) {
-                    const int ii = g == 0 ? m : a0, jj = g == 1 ? m : a1, kk = g == 2 ? m : a2;
-                    const int base = NL::at(0, R == 3 ? jj + N * kk : jj, ii);
-#pragma unroll
-                    for (int c = 0; c < D; ++c)
-                        v[D + c * R + g] = fma(dphi[m], xl[base + c * NL::RP], v[D + c * R + g]);
-                }
-            } else if (mine && g == R) {
-                const int base = NL::at(0, R == 3 ? a1 + N * a2 : a1, a0);
-#pragma unroll
-                for (int c = 0; c < D; ++c) v[c] = xl[base + c * NL::RP];
-            }
-            slot_sum_all(v);
+            const bool mine = state == S_INIT && node >= 0;
+            const u64 minem = __ballot(mine);
+            if (!minem) return;
             if (mine) {
+                const int a0 = node % N, a1 = (node / N) % N, a2 = R == 3 ? node / (N * N) : 0;
                 T X[D], Gm[D][R];
+                const int row = R == 3 ? a1 + N * a2 : a1;
 #pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    X[c] = v[c];
+                for (int c = 0; c < D; ++c) X[c] = xl[NL::at(c, row, a0)];
 #pragma unroll
-                    for (int k = 0; k < R; ++k) Gm[c][k] = v[D + c * R + k];
+                for (int d = 0; d < R; ++d) {
+                    const int ad = d == 0 ? a0 : d == 1 ? a1 : a2;
+                    T s[D];
+#pragma unroll
+                    for (int c = 0; c < D; ++c) s[c] = T(0);
+#pragma unroll
+                    for (int m = 0; m < N; ++m) {
+                        const T w = kDiff<T, N>.v[ad][m];
+                        const int ii = d == 0 ? m : a0, jj = d == 1 ? m : a1, kk = d == 2 ? m : a2;
+                        const int at = NL::at(0, R == 3 ? jj + N * kk : jj, ii);
+#pragma unroll
+                        for (int c = 0; c < D; ++c) s[c] = fma(w, xl[at + c * NL::RP], s[c]);
+                    }
+#pragma unroll
+                    for (int c = 0; c < D; ++c) Gm[c][d] = s[c];
                 }
                 objective<T, D, R>(xs, X, Gm, cur, dx);
                 hb_ok = false;
                 state = S_STEP;
                 fresh = true;
-                if (leader) {
-                    cn.evals32++;
-                    cn.evals32_node++;
-                }
             }
-            return true;
+            const int cnt = __popcll(minem);
+            if (FINAL) cn.evals += cnt;
+            else {
+                cn.evals32 += cnt;
+                cn.evals32_node += cnt;
+            }
         }
     };
-    // Trial point of each stepping slot (only the fresh ones when asked):
+    // Trial point of each stepping lane (only the fresh ones when asked):
     // the Newton step of Section 3.2.1 on the free coordinates, clipped to
     // the trust region and the box; a step below the tolerance ends the
-    // iteration.  Returns, per lane, whether its slot's pair ended.
-    auto plan = [&](bool only_fresh) -> bool {
+    // iteration.  Returns the lanes whose pair ended.
+    auto plan = [&](bool only_fresh) __attribute__((always_inline)) -> u64 {
         bool ended = false;
         if (state == S_STEP && (!only_fresh || fresh)) {
             const bool beta = (pass > 0) && on_face(r);
-            if (beta && !hb_ok) {
+            if (!kHandOn && beta && !hb_ok) {
                 // a face pass needs second derivatives at r: dx at r is
-                // current (r was evaluated last), so wait for sweep 2
+                // current, so wait for sweep 2
                 state = S_WAIT;
             } else {
                 T H[kSym<R>];
 #pragma unroll
-                for (int k = 0; k < kSym<R>; ++k) H[k] = beta ? cur.Hgn[k] - Hs[k] : cur.Hgn[k];
+                for (int k = 0; k < kSym<R>; ++k)
+                    H[k] = !kHandOn && beta ? cur.Hgn[k] - Hs[k] : cur.Hgn[k];
                 // held: at a bound of the box with the gradient pointing
                 // out of it (r = +-1 exactly, so r g has the sign test)
                 bool held[R];
@@ -1098,13 +1217,12 @@ __device__ __forceinline__ void run_element(const NewtonArgs &a, int e, int q0, 
                     held[k] = (fabs(r[k]) == T(1)) & (r[k] * cur.g[k] > T(0));
                 T x[R];
                 bool ok = solve_free<T, R>(H, cur.g, held, x);
-                if (!ok && beta) {
+                if (!kHandOn && !ok && beta) {
 #pragma unroll
                     for (int k = 0; k < kSym<R>; ++k) H[k] = cur.Hgn[k];
                     ok = solve_free<T, R>(H, cur.g, held, x);
                 }
-                T dr[R];
-                dmax = T(0);
+                T dr[R], dmax = T(0);
 #pragma unroll
                 for (int k = 0; k < R; ++k) {
                     T d = ok ? x[k] : T(0);
@@ -1124,167 +1242,154 @@ __device__ __forceinline__ void run_element(const NewtonArgs &a, int e, int q0, 
                     dHd = fma(dr[k], w, dHd);
                 }
                 pred = T(2) * gd - dHd;
-                if (dmax < tol) {
-                    // converged: the step is taken without evaluating the
-                    // map at q; the squared residual there is the model's,
-                    // f - pred, whose error is third order in the step
+                // converged: the step is taken without evaluating the
+                // map at q; the squared residual there is the model's,
+                // f - pred, whose error is third order in the step.
+                // Mixed mode (polish): the first FP64 step from the FP32
+                // result is small and stays inside, so the start is within
+                // about kPolishTol of the solution and Newton's step
+                // leaves an error of second order in it; that step ends
+                // the iteration, too.
+                ended = dmax < tol;
+                if constexpr (KIND == kPolish && R == D)
+                    ended = ended || (io.polish && pass == 0 && dmax <= T(kPolishTol) &&
+                                      !on_face(r) && !on_face(q));
+                if (ended) {
                     ++pass;
-                    if (leader) {
-                        if (FINAL) cn.passes++;
-                        else cn.passes32++;
-                    }
 #pragma unroll
                     for (int k = 0; k < R; ++k) r[k] = q[k];
                     cur.f = fmax(cur.f - pred, T(0));
                     finish(true);
-                    ended = true;
-                } else if (KIND == kPolish && R == D && io.polish && pass == 0 &&
-                           dmax <= T(kPolishTol) && !on_face(r) && !on_face(q)) {
-                    // mixed mode: the first FP64 step from the FP32 result
-                    // is small and stays inside, so the start is within
-                    // about kPolishTol of the solution and Newton's step
-                    // leaves an error of second order in it; that step ends
-                    // the iteration, with the model residual f - pred
-                    ++pass;
-                    if (leader) cn.passes++;
-#pragma unroll
-                    for (int k = 0; k < R; ++k) r[k] = q[k];
-                    cur.f = fmax(cur.f - pred, T(0));
-                    finish(true);
-                    ended = true;
                 }
             }
         }
-        return ended;
+        const u64 em = __ballot(ended);
+        if (FINAL) cn.passes += __popcll(em);
+        else cn.passes32 += __popcll(em);
+        return em;
+    };
+    // Second derivatives of the waiting lanes, 16 at a time.
+    auto second = [&](u64 waitm) __attribute__((always_inline)) {
+        const int rank = __popcll(waitm & ((1ull << lane) - 1));
+        const int nw = __popcll(waitm);
+#pragma unroll 1
+        for (int w0 = 0; w0 < nw; w0 += 16) {
+            const bool mine = state == S_WAIT && rank >= w0 && rank < w0 + 16;
+            wave_lds_sync();   // earlier reads of qb come first
+            if (mine) {
+#pragma unroll
+                for (int k = 0; k < R; ++k) qb[k * 16 + rank - w0] = r[k];
+#pragma unroll
+                for (int c = 0; c < D; ++c) qb[(R + c) * 16 + rank - w0] = dx[c];
+            }
+            T Sn[kSym<R>];
+            sweep2<T, D, R, N>(xl, tab, qb, lane, Sn);
+#pragma unroll
+            for (int k = 0; k < kSym<R>; ++k) {
+                const T v = __shfl(Sn[k], (rank - w0) & 15);
+                if (mine) Hs[k] = v;
+            }
+            if (mine) {
+                hb_ok = true;
+                state = S_STEP;
+            }
+            cn.sweeps_h2++;
+        }
+        cn.evals_h2 += nw;
+        cn.evals_h2_exec += nw;
+    };
+    // Sweep 1 at q for the lanes of evalm: their X and G in z.
+    auto evaluate = [&](u64 evalm, T (&z)[K]) __attribute__((always_inline)) {
+        const int ncg = (__popcll(evalm) + 15) >> 4;
+        const int rank = __popcll(evalm & ((1ull << lane) - 1));
+        wave_lds_sync();   // earlier reads of qb come first
+        if ((evalm >> lane) & 1) {
+#pragma unroll
+            for (int k = 0; k < R; ++k) qb[k * 64 + rank] = q[k];
+        }
+        T x[K], y[K];
+#pragma unroll 1
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll 1
+            for (int cg = 2 * h; cg < min(ncg, 2 * h + 2); ++cg) {
+                if (cg & 1) {
+#pragma unroll
+                    for (int k = 0; k < K; ++k) x[k] = y[k];
+                }
+                sweep1<T, D, R, N>(xl, tab, qb, cg, lane, y);
+            }
+            // (a single group of the two: its totals come out in both rows)
+            if (2 * h + 1 >= ncg) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) x[k] = y[k];
+            }
+            fold16(x, y);
+            if (h == 0) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) z[k] = x[k];
+                if (ncg <= 2) break;
+            }
+        }
+        fold32(z, x);
+        if (evalm & (evalm + 1)) {
+            // the lanes are not the first ones: column j's totals go to the
+            // j-th lane
+#pragma unroll
+            for (int k = 0; k < K; ++k) z[k] = __shfl(z[k], rank);
+        }
+        if (FINAL) cn.sweeps += ncg;
+        else cn.sweeps32 += ncg;
     };
     const int guard = (q1 - q0 + 16) * (2 * max_iter + 4);
     for (int trip = 0; trip < guard; ++trip) {
-        if constexpr (KIND == kPrimary || KIND == kPolish) {
-            // pairs whose next pass needs second derivatives leave the wave:
-            // FP64 parks them (the face kernel resumes them, many to a wave),
-            // FP32 ends its phase there (the FP64 phase takes over)
-            const unsigned long long pm = __ballot(leader && state == S_WAIT);
-            if (pm) {
-                // (a launch without a park buffer -- the hinted search of
-                // particle tracking -- ends such pairs unconverged)
-                if (FINAL && io.park_meta) {
-                    int base = 0;
-                    if (lane == 0) base = atomicAdd(io.park_count, __popcll(pm));
-                    base = __shfl(base, 0);
-                    if (state == S_WAIT) {
-                        // park_cap is the pass's pair count: every pair is
-                        // parked at most once, so k < park_cap
-                        const int k = base + __popcll(pm & ((1ull << slot) - 1));
-                        if (leader && k < io.park_cap) {
-                            io.park_meta[k] = make_int4(item, pos, e, pass);
-#pragma unroll
-                            for (int j = 0; j < R; ++j)
-                                io.park_r[(size_t)j * io.park_cap + k] = (double)r[j];
-                            io.park_r[(size_t)R * io.park_cap + k] = (double)alpha;
-                            static_assert(1 + R + kSym<R> + D <= kParkState, "park state");
-                            if (k < io.park_state_cap) {
-                                // the state at r, as the evaluation there left it
-                                double *ps = io.park_state + (size_t)k * kParkState;
-                                ps[0] = (double)cur.f;
-#pragma unroll
-                                for (int j = 0; j < R; ++j) ps[1 + j] = (double)cur.g[j];
-#pragma unroll
-                                for (int j = 0; j < kSym<R>; ++j)
-                                    ps[1 + R + j] = (double)cur.Hgn[j];
-#pragma unroll
-                                for (int c = 0; c < D; ++c)
-                                    ps[1 + R + kSym<R> + c] = (double)dx[c];
-                            }
-                        }
-                        state = S_FREE;
-                    }
-                } else {
-                    if (state == S_WAIT) finish(false);
-                }
-            }
+        refill();
+        node_init();
+        if (!__ballot(state != S_FREE)) break;
+        if constexpr (!kHandOn) {
+            const u64 waitm = __ballot(state == S_WAIT);
+            if (waitm) second(waitm);
         }
-        // free slots take new pairs (those starting at a node are evaluated
-        // there), then the trial points of the stepping slots; the slots
-        // whose pairs that ends take new pairs at once, and those starting
-        // at a node get their first trial point too (a second round), so no
-        // slot idles in this trip's sweep.  One copy of each step.
-        bool done = false;
-        for (int round = 0;; round = 1) {
+        // lanes whose pair ends take new pairs at once, and get their first
+        // trial point in the same trip, when that many of them are free
+        const u64 em = plan(false);
+        if (__popcll(em) >= kReplan && head < q1) {
             refill();
-            fresh = false;
-            const bool any = node_init();
-            if (round == 0) {
-                const unsigned long long waitm = __ballot(leader && state == S_WAIT);
-                const unsigned long long stepm =
-                    __ballot(leader && (state == S_STEP || state == S_INIT));
-                if (!waitm && !stepm) {
-                    done = true;
-                    break;
-                }
-                // a slot that waits for second derivatives gets them at
-                // once: holding it back to batch more waiting slots (4 or
-                // 8) costs more in idle slots than the batching saves
-                // (measured on hex48); it is then planned with the others
-                // and takes part in this trip's sweep 1
-                if (KIND != kPrimary && KIND != kPolish && waitm != 0) {
-                    T Sn[kSym<R>];
-                    sweep2<T, D, R, N>(xl, tab, lane, r, dx, Sn);
-                    if (lane == 0) {
-                        if (FINAL) cn.sweeps_h2++;
-                        else cn.sweeps32++;
-                    }
-                    if (state == S_WAIT) {
-#pragma unroll
-                        for (int k = 0; k < kSym<R>; ++k) Hs[k] = Sn[k];
-                        hb_ok = true;
-                        state = S_STEP;
-                        if (leader && FINAL) cn.evals_h2++;
-                    }
-                    if (leader && FINAL && state != S_FREE) cn.evals_h2_exec++;
-                }
-            } else if (!any) {
-                break;
-            }
-            const bool ended = plan(round == 1);
-            if (round == 1 || !__ballot(leader && ended)) break;
+            node_init();
+            plan(true);
         }
-        if (done) break;
-        if (state != S_INIT && state != S_STEP) {
-#pragma unroll
-            for (int k = 0; k < R; ++k) q[k] = r[k];
-        }
-        if (!__ballot(leader && (state == S_INIT || state == S_STEP))) continue;
+        const u64 evalm = __ballot(state == S_INIT || state == S_STEP);
+        if (!evalm) continue;
+        T z[K];
+        evaluate(evalm, z);
         T X[D], Gm[D][R], dxn[D];
-        sweep1<T, D, R, N>(xl, tab, lane, q, X, Gm);
-        if (lane == 0) {
-            if (FINAL) cn.sweeps++;
-            else cn.sweeps32++;
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            X[c] = z[c];
+#pragma unroll
+            for (int k = 0; k < R; ++k) Gm[c][k] = z[D + c * R + k];
         }
         Obj<T, D, R> nw;
         objective<T, D, R>(xs, X, Gm, nw, dxn);
+        const u64 initm = __ballot(state == S_INIT), stepm = __ballot(state == S_STEP);
+        // a resumed pair re-evaluates the point it was parked at (the
+        // same values as before): not a new evaluation of the iteration
+        const int ne = __popcll(stepm) + (KIND != kFace ? __popcll(initm) : 0);
+        if (FINAL) {
+            cn.evals += ne;
+            cn.passes += __popcll(stepm);
+        } else {
+            cn.evals32 += ne;
+            cn.passes32 += __popcll(stepm);
+        }
+        bool park = false, at_r = true;
         if (state == S_INIT) {
             cur = nw;
 #pragma unroll
             for (int c = 0; c < D; ++c) dx[c] = dxn[c];
             hb_ok = false;
             state = S_STEP;
-            // a resumed pair re-evaluates the point it was parked at (the
-            // same values as before): not a new evaluation of the iteration
-            if (leader && KIND != kFace) {
-                if (FINAL) cn.evals++;
-                else cn.evals32++;
-            }
         } else if (state == S_STEP) {
             ++pass;
-            if (leader) {
-                if (FINAL) {
-                    cn.evals++;
-                    cn.passes++;
-                } else {
-                    cn.evals32++;
-                    cn.passes32++;
-                }
-            }
             // trust-region test (the step is at least the tolerance here)
             bool accept;
             const T decr = cur.f - nw.f;
@@ -1309,8 +1414,62 @@ __device__ __forceinline__ void run_element(const NewtonArgs &a, int e, int q0, 
                 for (int c = 0; c < D; ++c) dx[c] = dxn[c];
                 hb_ok = false;
             }
-            if (pass >= max_iter) finish(false);
-            else if (accept && on_face(r)) state = S_WAIT;   // next pass: beta = 1
+            if (pass >= max_iter) {
+                finish(false);
+            } else if (on_face(r)) {
+                // the next pass takes second derivatives (beta = 1)
+                if (kHandOn) {
+                    park = true;
+                    at_r = accept;
+                } else if (accept) {
+                    state = S_WAIT;
+                }
+            }
+        }
+        if constexpr (kHandOn) {
+            // pairs whose next pass needs second derivatives leave the wave:
+            // FP64 parks them (the face kernel resumes them, many to a wave),
+            // FP32 ends its phase there (the FP64 phase takes over).  A
+            // launch without a park buffer -- the hinted search of particle
+            // tracking -- ends such pairs unconverged.
+            const u64 pm = __ballot(park);
+            if (pm) {
+                if (FINAL && io.park_meta) {
+                    int base = 0;
+                    if (lane == 0) base = atomicAdd(io.park_count, __popcll(pm));
+                    base = __builtin_amdgcn_readfirstlane(base);
+                    // park_cap is the pass's pair count: every pair is
+                    // parked at most once, so k < park_cap
+                    const int k = base + __popcll(pm & ((1ull << lane) - 1));
+                    if (park && k < io.park_cap) {
+                        // a rejected step leaves r at its start node, where
+                        // the objective came from the node block: the face
+                        // kernel evaluates it anew, whichever k it got
+                        io.park_meta[k] =
+                            make_int4(item, pos, e, at_r ? pass : pass | kParkNoState);
+#pragma unroll
+                        for (int j = 0; j < R; ++j)
+                            io.park_r[(size_t)j * io.park_cap + k] = (double)r[j];
+                        io.park_r[(size_t)R * io.park_cap + k] = (double)alpha;
+                        static_assert(1 + R + kSym<R> + D <= kParkState, "park state");
+                        if (at_r && k < io.park_state_cap) {
+                            // the state at r, as the evaluation there left it
+                            double *ps = io.park_state + (size_t)k * kParkState;
+                            ps[0] = (double)cur.f;
+#pragma unroll
+                            for (int j = 0; j < R; ++j) ps[1 + j] = (double)cur.g[j];
+#pragma unroll
+                            for (int j = 0; j < kSym<R>; ++j) ps[1 + R + j] = (double)cur.Hgn[j];
+#pragma unroll
+                            for (int c = 0; c < D; ++c)
+                                ps[1 + R + kSym<R> + c] = (double)dxn[c];
+                        }
+                    }
+                    if (park) state = S_FREE;
+                } else if (park) {
+                    finish(false);
+                }
+            }
         }
     }
 }
@@ -1386,14 +1545,14 @@ __device__ __forceinline__ void stage_nodes(T *lds, const T *src, int lane)
 // -2 z_j, |x_j|^2 of every node j, element-local; padding columns score a
 // large constant) and A rows [4][64] (x, y, z, 1 of each pair).  FP64 reads
 // B from rows precomputed at setup (L2-resident per element), so its LDS
-// holds only A and the item ids; FP32 builds B in LDS from the FP32 nodes.
+// holds only A; FP32 builds B in LDS from the FP32 nodes.
 template <typename T, int D, int R, int N>
 struct NearLds {
     static constexpr int NPAD = (Shape<D, R, N>::NP + 31) / 32 * 32;   // even tile count
     static constexpr bool B_IN_LDS = std::is_same<T, float>::value;
     static constexpr size_t bytes()
     {
-        return sizeof(T) * (4 * ((B_IN_LDS ? NPAD : 0) + 64) + 64) + sizeof(int) * 64;
+        return sizeof(T) * (4 * ((B_IN_LDS ? NPAD : 0) + 64) + 64);
     }
 };
 
@@ -1435,14 +1594,12 @@ __device__ __forceinline__ void nearest_body(const NewtonArgs &a)
     typedef NearLds<typename std::conditional<MIXED, float, double>::type, D, R, N> L;
     typedef typename std::conditional<MIXED, float, double>::type T;
     typedef typename V4<T>::type v4;
-    constexpr gll::Table<N> GT = gll::Nodes<N>::t;
     constexpr int NT = L::NPAD / 16;   // node tiles (even)
     const T kBig = MIXED ? T(1e30f) : T(1e300);
     extern __shared__ double lds_raw[];
     T *Bt = reinterpret_cast<T *>(lds_raw);                  // [4][NPAD] (FP32)
     T *Pt = Bt + (L::B_IN_LDS ? 4 * L::NPAD : 0);            // [4][64]
     T *Xx = Pt + 4 * 64;                                     // [64] |x|^2
-    int *items = reinterpret_cast<int *>(Xx + 64);           // [64]
     const int lane = threadIdx.x, col = lane & 15, g = lane >> 4;
     const NewtonIO &io = a.io;
     const int total = io.chunk_off[a.nel];
@@ -1501,7 +1658,6 @@ __device__ __forceinline__ void nearest_body(const NewtonArgs &a)
         // A rows of the pairs
         {
             const bool has = lane < cnt;
-            items[lane] = item;
             T pa[4] = {T(0), T(0), T(0), T(0)};
 #pragma unroll
             for (int c = 0; c < D; ++c) pa[c] = has ? T(px[c] - xc[c]) : T(0);
@@ -1516,21 +1672,9 @@ __device__ __forceinline__ void nearest_body(const NewtonArgs &a)
         wave_lds_sync();
         const int itemn = more ? pair_of(begn, cntn) : 0;   // next task, level 2
         const int ntile = (cnt + 15) >> 4;   // pair tiles of this task (wave-uniform)
-        // the start of the pair at task position pl: node bi's reference point
+        // the start of the pair at task position pl: node bi
         auto write_start = [&](int bi, int pl) __attribute__((always_inline)) {
-            const int it = items[pl];
-            const int ii[3] = {bi % N, (bi / N) % N, bi / (N * N)};
-#pragma unroll
-            for (int k = 0; k < R; ++k) {
-                double v = GT.z[0];
-#pragma unroll
-                for (int m = 1; m < N; ++m)
-                    if (ii[k] == m) v = GT.z[m];
-                if (io.start)
-                    io.start[(size_t)k * io.start_stride + beg + pl] = v;
-                else
-                    io.r[(size_t)k * io.ostride + it] = v;
-            }
+            io.node[beg + pl] = bi;
         };
         double pxn[D];
         if constexpr (!MIXED) {
@@ -1732,30 +1876,17 @@ __device__ __forceinline__ int nearest_staged(const double *xl, const double (&x
     return bi;
 }
 
-// Reference coordinate k of node `node` (packed index i + N j + N^2 l): the
-// GLL point of its k-th index.
-template <int N>
-__device__ __forceinline__ double node_coord(int node, int k)
-{
-    constexpr gll::Table<N> GT = gll::Nodes<N>::t;
-    const int ik = k == 0 ? node % N : k == 1 ? (node / N) % N : node / (N * N);
-    double v = GT.z[0];
-#pragma unroll
-    for (int m = 1; m < N; ++m)
-        if (ik == m) v = GT.z[m];
-    return v;
-}
-
-// Newton over the element queue in precision T: one wave per element (task
-// counter io.counter[8] for the FP64 kernel, [9] for the FP32 phase of mixed
-// mode), over the elements that have pairs.  The start of every pair is
-// read from io.start (or io.r): the nearest node, or the FP32 result in
-// mixed mode.
-// TASKS: the waves stride over the 64-pair tasks of io.task_elem instead
-// (no counter).  The other candidates of unsettled points are a few pairs
-// scattered over many elements; a counter would be stepped once per element
-// of the mesh, mostly past empty queues, one same-address atomic after the
-// other.  The parked pairs of the face kernel are likewise spread thinly.
+// Newton over the element queues in precision T.  Tasks are the parts of an
+// element's queue: io.newt_off[e] .. io.newt_off[e + 1] - 1 are element e's,
+// io.newt_task[t] is task t's element, and the element's pairs are divided
+// evenly among its tasks.  The primary and polish passes and the FP32 phase
+// take tasks from a counter (io.counter[8] for the FP64 kernels, [9] for the
+// FP32 phase of mixed mode), a few per wave of unequal cost; one task per
+// element would leave most waves idle at the end where elements hold many
+// pairs (2 million particles in 3888 elements, N = 8: 2.37 ms so).
+// TASKS: the waves stride over the 64-pair tasks of io.task_elem instead.
+// The other candidates of unsettled points and the parked pairs of the face
+// kernel are a few pairs scattered over many elements.
 // kResolve finds the starts of its pairs itself, from the nodes it stages
 // anyway: a separate nearest-node pass would read every such element's
 // node data once more for about one pair each, and score that pair on
@@ -1764,106 +1895,85 @@ template <typename T, int D, int R, int N, bool TASKS, int KIND>
 __device__ __forceinline__ void newton_body(const NewtonArgs &a)
 {
     typedef Shape<D, R, N> S;
+    typedef Lds<T, D, R, N> L;
     constexpr bool FINAL = std::is_same<T, double>::value;
     extern __shared__ double lds_raw[];
-    int *citem = Lds<T, D, R, N>::citem(lds_raw);
     const int lane = threadIdx.x;
     const NewtonIO &io = a.io;
     T *xl = reinterpret_cast<T *>(lds_raw);
-    T *tab = xl + Lds<T, D, R, N>::NODES;
-    T *cache = tab + 2 * Lds<T, D, R, N>::TAB;
+    T *tab = xl + L::NODES;
+    T *qb = tab + L::TAB;
     Counters cn;
-    const int total = TASKS ? io.chunk_off[a.nel] : 0;
-    int ticket = -1;   // (lane 0) the element counter's value for the next element
-    for (int t = TASKS ? task_of_block() : 0;; t += gridDim.x) {
-        int e = 0, q0, q1;
+    const int *off = TASKS ? io.chunk_off : io.newt_off;
+    const int *elem = TASKS ? io.task_elem : io.newt_task;
+    const int total = off[a.nel];
+    int *ctr = io.counter + (FINAL ? 8 : 9);
+    // the ticket of the wave's next task is taken one task ahead, so that
+    // its atomic completes while the current one is processed (every ticket
+    // below the total is processed by the wave that took it)
+    auto take = [&]() __attribute__((always_inline)) {
+        int v = 0;
+        if (lane == 0) v = atomicAdd(ctr, 1);
+        return v;
+    };
+    int ticket = TASKS ? task_of_block() : take();
+    for (;;) {
+        const int t = __builtin_amdgcn_readfirstlane(ticket);
+        if (t >= total) break;
+        ticket = TASKS ? t + (int)gridDim.x : take();
+        const int e = __builtin_amdgcn_readfirstlane(elem[t]);
+        int q0 = io.elem_off[e], q1 = io.elem_off[e + 1];
         if constexpr (TASKS) {
-            if (t >= total) break;
-            e = __builtin_amdgcn_readfirstlane(io.task_elem[t]);
-            q0 = io.elem_off[e] + (t - io.chunk_off[e]) * kChunk;
-            q1 = min(io.elem_off[e + 1], q0 + kChunk);
+            q0 += (t - off[e]) * kChunk;
+            q1 = min(q1, q0 + kChunk);
         } else {
-            if (lane == 0) {
-                // the element of the ticket taken before, or the next one with
-                // a non-empty queue; then the ticket for the wave's next
-                // element, taken now so that its atomic completes while this
-                // element is staged (every ticket below nel is processed by
-                // the wave that took it)
-                int *ctr = io.counter + (FINAL ? 8 : 9);
-                e = ticket < 0 ? atomicAdd(ctr, 1) : ticket;
-                while (e < a.nel && io.elem_off[e + 1] <= io.elem_off[e]) e = atomicAdd(ctr, 1);
-                ticket = e < a.nel ? atomicAdd(ctr, 1) : a.nel;
-            }
-            e = __builtin_amdgcn_readfirstlane(__shfl(e, 0));
-            if (e >= a.nel) break;
-            q0 = io.elem_off[e];
-            q1 = io.elem_off[e + 1];
+            // part t - off[e] of the queue's nt even parts
+            const int nt = off[e + 1] - off[e], per = (q1 - q0 + nt - 1) / nt;
+            q0 += (t - off[e]) * per;
+            q1 = min(q1, q0 + per);
         }
         __syncthreads();
         if constexpr (FINAL) {
-            // kResolve: lane l < q1 - q0 (at most kChunk = 64) loads pair
-            // q0 + l (slot id, point) before the nodes are staged
-            int it = 0;
-            double px[D];
-#pragma unroll
-            for (int d = 0; d < D; ++d) px[d] = 0.0;
+            const double *src = a.nodes + (size_t)e * D * S::NP;
             if constexpr (KIND == kResolve) {
+                // lane l < q1 - q0 (at most kChunk = 64) loads pair q0 + l
+                // (slot id, point) before the nodes are staged
                 static_assert(kChunk <= kWave, "one lane per pair of a task");
+                double px[D];
+#pragma unroll
+                for (int d = 0; d < D; ++d) px[d] = 0.0;
                 if (lane < q1 - q0) {
-                    it = io.list[q0 + lane];
-                    const int p = io.slot_pt[it];
+                    const int p = io.slot_pt[io.list[q0 + lane]];
 #pragma unroll
                     for (int d = 0; d < D; ++d) px[d] = point_coord<D>(a, p, d);
                 }
-            }
-            const double *src = a.nodes + (size_t)e * D * S::NP;
-            if constexpr (KIND == kResolve) {
                 stage_nodes<double, D, R, N>(xl, src, lane);
+                int node = 0;
                 for (int j = 0; j < q1 - q0; ++j) {
                     double x[D];
 #pragma unroll
                     for (int d = 0; d < D; ++d) x[d] = __shfl(px[d], j);
                     const int bi = nearest_staged<D, R, N>(xl, x, lane);
-                    const int itj = __shfl(it, j);
-                    if (lane < R) io.r[(size_t)lane * io.ostride + itj] = node_coord<N>(bi, lane);
+                    if (lane == j) node = bi;
                 }
-                // the refill reads the starts back with loads that bypass
-                // L1; this wave's stores only have to be complete (a
-                // device-scope fence would also write back and invalidate
-                // the L2, once per task)
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                run_element<double, D, R, N, true, KIND>(a, e, q0, q1, xl, tab, cache, citem,
-                                                         lane, a.max_iter, a.tol, nullptr, cn,
-                                                         [] {});
-            } else if constexpr (KIND == kFace) {
-                stage_nodes<double, D, R, N>(xl, src, lane);
-                run_element<double, D, R, N, true, KIND>(a, e, q0, q1, xl, tab, cache, citem,
-                                                         lane, a.max_iter, a.tol, nullptr, cn,
+                run_element<double, D, R, N, true, KIND>(a, e, q0, q1, xl, tab, qb, lane,
+                                                         a.max_iter, a.tol, nullptr, node, cn,
                                                          [] {});
             } else {
-                // the primary and polish passes stage the nodes after their
-                // first batch of pairs has been fetched
+                // the nodes are staged after the first batch of pairs has
+                // been asked for
                 run_element<double, D, R, N, true, KIND>(
-                    a, e, q0, q1, xl, tab, cache, citem, lane, a.max_iter, a.tol, nullptr, cn,
+                    a, e, q0, q1, xl, tab, qb, lane, a.max_iter, a.tol, nullptr, 0, cn,
                     [&] { stage_nodes<double, D, R, N>(xl, src, lane); });
             }
         } else {
             const float *src = a.nodes32 + (size_t)e * D * S::NP;
             run_element<float, D, R, N, false, KIND>(
-                a, e, q0, q1, xl, tab, cache, citem, lane, a.max_iter32, a.tol32,
-                a.xc + (size_t)e * D, cn, [&] { stage_nodes<float, D, R, N>(xl, src, lane); });
+                a, e, q0, q1, xl, tab, qb, lane, a.max_iter32, a.tol32, a.xc + (size_t)e * D, 0,
+                cn, [&] { stage_nodes<float, D, R, N>(xl, src, lane); });
         }
     }
-    unsigned long long v[11] = {cn.pairs,  cn.passes,        cn.evals,  cn.evals_h2,
-                                cn.passes32, cn.evals32,     cn.evals_h2_exec,
-                                cn.sweeps, cn.sweeps_h2, cn.sweeps32, cn.evals32_node};
-#pragma unroll
-    for (int k = 0; k < 11; ++k) {
-        unsigned long long x = v[k];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-        if (lane == 0 && x) atomicAdd(&io.stats[k], x);
-    }
+    add_counters(cn, io.stats, lane);
 }
 
 // The primary pass and the pass over the other candidates of unsettled
@@ -1921,10 +2031,9 @@ k_resolve_overflow(NewtonArgs a, HashView h)
 {
     typedef Shape<D, R, N> S;
     extern __shared__ double lds_raw[];
-    int *citem = Lds<double, D, R, N>::citem(lds_raw);
     double *xl = lds_raw;
     double *tab = xl + Lds<double, D, R, N>::NODES;
-    double *cache = tab + 2 * Lds<double, D, R, N>::TAB;
+    double *qb = tab + Lds<double, D, R, N>::TAB;
     const int lane = threadIdx.x, b = blockIdx.x, G = gridDim.x;
     const NewtonIO &io = a.io;
     const int cnt = *io.ocount;
@@ -1966,16 +2075,12 @@ k_resolve_overflow(NewtonArgs a, HashView h)
             __syncthreads();
             stage_nodes<double, D, R, N>(xl, a.nodes + (size_t)e * D * S::NP, lane);
             const int bi = nearest_staged<D, R, N>(xl, x, lane);
-            if (lane == 0) {
-#pragma unroll
-                for (int k = 0; k < R; ++k) la.io.r[(size_t)k * G + b] = node_coord<N>(bi, k);
-            }
-            // lane 0 wrote the queue entry and the start and reads them back
-            // in the refill (same lane, program order)
-            run_element<double, D, R, N, true, kResolve>(la, e, b, b + 1, xl, tab, cache, citem,
-                                                        lane, a.max_iter, a.tol, nullptr, cn,
+            // lane 0 wrote the queue entry and reads it back (same lane,
+            // program order)
+            run_element<double, D, R, N, true, kResolve>(la, e, b, b + 1, xl, tab, qb, lane,
+                                                        a.max_iter, a.tol, nullptr, bi, cn,
                                                         [] {});
-            // slot 0's leader (lane 0) wrote the result
+            // lane 0, the pair's lane, wrote the result
             int cd = 0;
             double dd = 0.0, rr[R];
             if (lane == 0) {
@@ -2011,23 +2116,15 @@ k_resolve_overflow(NewtonArgs a, HashView h)
             for (int k = 0; k < R; ++k) io.r[(size_t)k * io.ostride + p] = br[k];
         }
     }
-    unsigned long long v[11] = {cn.pairs,  cn.passes,        cn.evals,  cn.evals_h2,
-                                cn.passes32, cn.evals32,     cn.evals_h2_exec,
-                                cn.sweeps, cn.sweeps_h2, cn.sweeps32, cn.evals32_node};
-#pragma unroll
-    for (int k = 0; k < 11; ++k) {
-        unsigned long long xv = v[k];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) xv += __shfl_xor(xv, o);
-        if (lane == 0 && xv) atomicAdd(&io.stats[k], xv);
-    }
+    add_counters(cn, io.stats, lane);
 }
 
 typedef void (*KernelFn)(NewtonArgs);
 typedef void (*OverflowFn)(NewtonArgs, HashView);
 
 struct Kernels {
-    KernelFn nearest = nullptr, newton32 = nullptr, newton = nullptr, face = nullptr;
+    KernelFn nearest = nullptr, newton32 = nullptr, newton = nullptr, warm = nullptr,
+             face = nullptr;
     OverflowFn overflow = nullptr;
     size_t lds_nearest = 0, lds_newton32 = 0, lds_newton = 0;
 };
@@ -2041,11 +2138,11 @@ Kernels pick_kernels(int N, bool resolve)
     case NN:                                                                                \
         k.nearest = resolve ? nullptr : k_nearest<D, R, NN, MIXED>;                          \
         k.newton = resolve ? k_newton_resolve<D, R, NN> : k_newton<D, R, NN>;               \
+        k.warm = k_newton_polish<D, R, NN>;                                                 \
         k.face = k_newton_face<D, R, NN>;                                                   \
         k.overflow = k_resolve_overflow<D, R, NN>;                                          \
         if (MIXED && !resolve) {                                                            \
             k.newton32 = k_newton32<D, R, NN>;                                              \
-            k.newton = k_newton_polish<D, R, NN>;                                           \
         }                                                                                   \
         k.lds_nearest = NearLds<TN, D, R, NN>::bytes();                                     \
         k.lds_newton32 = Lds<float, D, R, NN>::bytes();                                     \
@@ -2115,7 +2212,10 @@ hipError_t launch_newton_kind(const fpts_mesh *m, bool mixed, int64_t n, const d
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(k.newton, dim3(m->cus * 8), dim3(64), k.lds_newton, s, a);
+        // starts given as points (the FP32 phase's results, or the hinted
+        // search of particle tracking) take the warm-start kernel
+        const KernelFn kn = resolve || (io.node && !mixed) ? k.newton : k.warm;
+        hipLaunchKernelGGL(kn, dim3(m->cus * 8), dim3(64), k.lds_newton, s, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
