@@ -1307,6 +1307,26 @@ __device__ __forceinline__ void run_element(const NewtonArgs &a, int e, int q0, 
 #pragma unroll
             for (int k = 0; k < R; ++k) qb[k * 64 + rank] = q[k];
         }
+        if constexpr (!kHandOn) {
+            // (kFace, kResolve: mostly a single group, and no registers left
+            // for the other groups' sums: a group's totals go to all four
+            // lanes of a column, and to the lanes from there)
+            T y[K];
+#pragma unroll 1
+            for (int cg = 0; cg < ncg; ++cg) {
+                sweep1<T, D, R, N>(xl, tab, qb, cg, lane, y);
+                slot_sum_all(y);
+                const bool mine = (rank >> 4) == cg;
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const T v = __shfl(y[k], rank & 15);
+                    if (mine) z[k] = v;
+                }
+            }
+            if (FINAL) cn.sweeps += ncg;
+            else cn.sweeps32 += ncg;
+            return;
+        }
         T x[K], y[K];
 #pragma unroll 1
         for (int h = 0; h < 2; ++h) {
