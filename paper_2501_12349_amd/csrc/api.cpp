@@ -84,11 +84,12 @@ constexpr int kHintPasses = 8;  // Newton passes of the hinted search
 // about four tasks for each of the launch's waves (8 per CU), so that the
 // last ones to finish leave little of the chip idle; an element's queue is
 // kept whole below that (its nodes are staged, and its last pairs drained
-// with lanes idle, once).  kChunk where the arrays of another task map
-// would not fit the workspace (few points per element).
-int newton_task_len(const fpts_mesh *m, int64_t n)
+// with lanes idle, once).  kChunk for line meshes, whose kernel takes
+// 64-pair tasks, and where the arrays of the cells' tasks would not hold
+// another map of the elements' (a local map of fewer cells than elements).
+int newton_task_len(const fpts_mesh *m, int64_t n, int64_t ncell)
 {
-    if (n < 2 * (m->nel + 1)) return kChunk;
+    if (m->R < 2 || m->nel > ncell) return kChunk;
     const int64_t per = n / ((int64_t)m->cus * 8 * 4);
     return (int)std::min<int64_t>(std::max<int64_t>((per + kChunk - 1) / kChunk, 1), 16) * kChunk;
 }
@@ -168,7 +169,6 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     w.scan_blocks = scan_tmp_blocks(
         std::max<int64_t>(std::max<int64_t>(std::max<int64_t>(n, m->nel), ncell), w.bin_hist_n));
     const size_t I = sizeof(int);
-    w.cell_cnt = c.take(I * ncell);
     w.cell_poff = c.take(I * (ncell + 1));
     w.cell_choff = c.take(I * (ncell + 1));
     w.cellpt = c.take(I * n);
@@ -176,15 +176,12 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     w.cand = c.take(sizeof(int2) * n);
     w.rank = c.take(I * n);
     w.bin_prim = c.take(I * n);
-    w.elem_cnt = c.take(I * m->nel);
     w.elem_off = c.take(I * (m->nel + 1));
     w.chunk_off = c.take(I * (m->nel + 1));
     w.sorted = c.take(I * n);
     w.ulist = c.take(I * n);
     w.uoff = c.take(I * n);
     w.ucnt = c.take(I * n);
-    w.elem_cnt2 = c.take(I * m->nel);
-    w.elem_fill2 = c.take(I * m->nel);
     w.elem_off2 = c.take(I * (m->nel + 1));
     w.chunk_off2 = c.take(I * (m->nel + 1));
     w.slot_pt = c.take(I * w.cap2);
@@ -209,7 +206,6 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     // meshes; those beyond the capacity are re-evaluated by the face kernel
     w.park_state_cap = std::min<int64_t>(n, n / 8 + 1024);
     w.park_state = c.take(sizeof(double) * kParkState * w.park_state_cap);
-    w.park_cnt = c.take(I * m->nel);
     w.park_off = c.take(I * (m->nel + 1));
     w.park_choff = c.take(I * (m->nel + 1));
     w.park_rank = c.take(I * n);
@@ -222,6 +218,14 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     w.ov_dbl = c.take(sizeof(double) * (m->R + 1) * w.ov_grid);
     w.bin_hist = c.take(I * (w.bin_hist_n + 1));
     w.bin_pairs = c.take(w.bin_shift < 0 ? 1 : sizeof(int2) * n);
+    // zeroed at the start of a call: [zero, total).  The counters stay last:
+    // an Interpolate in the same workspace leaves them readable.
+    w.zero = c.at;
+    w.cell_cnt = c.take(I * ncell);
+    w.elem_cnt = c.take(I * m->nel);
+    w.elem_cnt2 = c.take(I * m->nel);
+    w.elem_fill2 = c.take(I * m->nel);
+    w.park_cnt = c.take(I * m->nel);
     w.counters = c.take(I * kCounters);
     w.stats = c.take(sizeof(unsigned long long) * 3 * kStats);
     w.total = c.at;
@@ -232,7 +236,10 @@ EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n)
 {
     EvalWs w;
     Cursor c;
+    // zeroed before the points are binned: [0, zero_end)
     w.elem_cnt = c.take(sizeof(int) * m->nel);
+    w.scount = c.take(sizeof(int));
+    w.zero_end = c.at;
     w.elem_off = c.take(sizeof(int) * (m->nel + 1));
     w.rank = c.take(sizeof(int) * std::max<int64_t>(n, 1));
     w.chunk_off = c.take(sizeof(int) * (m->nel + 1));
@@ -241,7 +248,6 @@ EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n)
     w.tb_elem = task_bound(n, m->nel);
     w.task_elem = c.take(sizeof(int) * w.tb_elem);
     w.slist = c.take(sizeof(int) * std::max<int64_t>(n, 1));
-    w.scount = c.take(sizeof(int));
     w.total = c.at;
     return w;
 }
@@ -308,62 +314,54 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
     double *ov_dbl = at<double>(d_ws, w.ov_dbl);
     unsigned long long *stats = at<unsigned long long>(d_ws, w.stats);
     const int64_t nel = m->nel, ncell = w.ncell, tb = w.scan_blocks;
+    // the primary Newton pass's tasks (the cells' task arrays are free once
+    // the candidates are located, and as long as those of the elements)
+    const int len = newton_task_len(m, n, ncell);
+    int *newt_off = len > kChunk ? cell_choff : chunk_off;
+    int *newt_task = len > kChunk ? task_cell : task_elem;
     hipError_t e = hipSuccess;
     auto chk = [&](hipError_t x) {
         if (e == hipSuccess) e = x;
     };
     {   // phases A and B: bin points by cell, candidates and primaries
         Span sp(m, 0, s);
-        chk(launch_fill_i32(cell_cnt, ncell, 0, s));
-        chk(launch_fill_i32(elem_cnt, nel, 0, s));
-        chk(launch_fill_i32(elem_cnt2, nel, 0, s));
-        chk(launch_fill_i32(elem_fill2, nel, 0, s));
-        chk(launch_fill_i32(park_cnt, nel, 0, s));
-        chk(launch_fill_i32(counters, kCounters, 0, s));
-        if (rest) chk(launch_fill_i32(rest->count, 1, 0, s));
-        chk(launch_fill_i32(reinterpret_cast<int *>(stats), 6 * kStats, 0, s));
+        chk(launch_zero2(at<int>(d_ws, w.zero), (w.total - w.zero) / sizeof(int),
+                         rest ? rest->zero : nullptr, rest ? rest->zero_n : 0, s));
         if (w.bin_shift >= 0) {
             int *bh = at<int>(d_ws, w.bin_hist);
             int2 *pairs = at<int2>(d_ws, w.bin_pairs);
             const int *npairs = bh + w.bin_hist_n;   // the scan's total
             chk(launch_bin_tiles(m, n, d_pts, pts4, keep, cellpt, cand, d_code, d_elem, d_r,
                                  d_dist, w.bin_shift, bh, s));
-            chk(launch_exclusive_scan(bh, bh, w.bin_hist_n, 1, tmp, tb, s));
+            chk(launch_unit_scan(UnitScan{bh, w.bin_hist_n, tmp, bh}, tb, s));
             chk(launch_bin_coarse(m, n, cellpt, w.bin_shift, bh, pairs, s));
             chk(launch_bin_rank(n, npairs, w.bin_shift, pairs, cell_cnt, rank, s));
-            chk(launch_exclusive_scan(cell_cnt, cell_poff, ncell, 1, tmp, tb, s));
-            chk(launch_exclusive_scan(cell_cnt, cell_choff, ncell, kChunk, tmp, tb, s));
-            chk(launch_task_map(cell_choff, ncell, task_cell, s));
+            chk(launch_unit_scan(
+                UnitScan{cell_cnt, ncell, tmp, cell_poff, cell_choff, task_cell}, tb, s));
             chk(launch_bin_scatter(n, npairs, pairs, rank, cell_poff, pbin, m->cus, s));
         } else {
             chk(launch_cell_bin(m, 0, n, d_pts, pts4, keep, cellpt, cell_cnt, nullptr, rank,
                                 nullptr, cand, d_code, d_elem, d_r, d_dist, s));
-            chk(launch_exclusive_scan(cell_cnt, cell_poff, ncell, 1, tmp, tb, s));
-            chk(launch_exclusive_scan(cell_cnt, cell_choff, ncell, kChunk, tmp, tb, s));
-            chk(launch_task_map(cell_choff, ncell, task_cell, s));
+            chk(launch_unit_scan(
+                UnitScan{cell_cnt, ncell, tmp, cell_poff, cell_choff, task_cell}, tb, s));
             chk(launch_cell_bin(m, 1, n, d_pts, nullptr, keep, cellpt, nullptr, cell_poff, rank,
                                 pbin, nullptr, d_code, d_elem, d_r, d_dist, s));
         }
         chk(launch_locate_cells(m, n, d_pts, pts4, pbin, cell_poff, cell_choff, ncell, task_cell,
                                 w.tb_cell, cand, elem_cnt, rank, bin_prim, d_code,
                                 d_elem, d_r, d_dist, s));
-        chk(launch_exclusive_scan(elem_cnt, elem_off, nel, 1, tmp, tb, s));
-        chk(launch_exclusive_scan(elem_cnt, chunk_off, nel, kChunk, tmp, tb, s));
-        chk(launch_task_map(chunk_off, nel, task_elem, s));
+        UnitScan es{elem_cnt, nel, tmp, elem_off, chunk_off, task_elem};
+        if (len > kChunk) {
+            es.off2 = newt_off;
+            es.task2 = newt_task;
+            es.len2 = len;
+        }
+        chk(launch_unit_scan(es, tb, s));
         // the binned points number cell_poff[ncell]
         chk(launch_primary_scatter_bins(n, cell_poff + ncell, pbin, bin_prim, rank, elem_off,
                                         sorted, s));
     }
     {   // phase C: Newton on the primary candidates, results straight to the outputs
-        const int len = newton_task_len(m, n);
-        int *newt_off = chunk_off, *newt_task = task_elem;
-        if (m->R >= 2 && len > kChunk) {
-            // (bin_prim and pbin are free by now, and hold n entries each)
-            newt_off = bin_prim;
-            newt_task = pbin;
-            chk(launch_exclusive_scan(elem_cnt, newt_off, nel, len, tmp, tb, s));
-            chk(launch_task_map(newt_off, nel, newt_task, s));
-        }
         NewtonIO io{sorted, elem_off, chunk_off, nullptr, d_code, d_elem, d_r, n, d_dist,
                     counters + kNewtonCounters, stats, task_elem, newt_off, newt_task,
                     w.tb_elem, rs, n};
@@ -394,9 +392,8 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
             Span sp(m, 7, s);
             chk(launch_park_bin(0, park_meta, counters + kParkCount, n, park_cnt, nullptr,
                                 park_rank, nullptr, m->cus, s));
-            chk(launch_exclusive_scan(park_cnt, park_off, nel, 1, tmp, tb, s));
-            chk(launch_exclusive_scan(park_cnt, park_choff, nel, kChunk, tmp, tb, s));
-            chk(launch_task_map(park_choff, nel, park_task, s));
+            chk(launch_unit_scan(UnitScan{park_cnt, nel, tmp, park_off, park_choff, park_task},
+                                 tb, s));
             chk(launch_park_bin(1, park_meta, counters + kParkCount, n, nullptr, park_off,
                                 park_rank, park_sorted, m->cus, s));
             NewtonIO fio{park_sorted, park_off, park_choff, nullptr, d_code, d_elem, d_r, n,
@@ -414,7 +411,7 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
     {   // phase D: other candidates of unsettled points, then the selection rule
         Span sp(m, 3, s);
         // counters[0]: listed points, counters[1]: slots handed out
-        const EvalRest none{nullptr, nullptr, nullptr, 0};
+        const EvalRest none{};
         chk(launch_unsettled(m, n, cellpt, cand, d_code, d_r, ulist, counters,
                              rest ? *rest : none, s));
         unsigned long long *slot_total =
@@ -422,9 +419,8 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
         chk(launch_resolve(m, 0, n, d_pts, cellpt, cand, ulist, counters, uoff, ucnt,
                            slot_total, elem_cnt2, nullptr, nullptr, nullptr, nullptr, nullptr,
                            w.cap2, olist, counters + kOverflowCount, s));
-        chk(launch_exclusive_scan(elem_cnt2, elem_off2, nel, 1, tmp, tb, s));
-        chk(launch_exclusive_scan(elem_cnt2, chunk_off2, nel, kChunk, tmp, tb, s));
-        chk(launch_task_map(chunk_off2, nel, task_elem2, s));
+        chk(launch_unit_scan(UnitScan{elem_cnt2, nel, tmp, elem_off2, chunk_off2, task_elem2},
+                             tb, s));
         chk(launch_resolve(m, 1, n, d_pts, cellpt, cand, ulist, counters, uoff, ucnt,
                            nullptr, nullptr, elem_off2, elem_fill2, slot_pt, slot_elem, sorted2,
                            w.cap2, nullptr, nullptr, s));
@@ -637,12 +633,11 @@ int fpts_eval_order(fpts_mesh *m, int64_t n, const int32_t *d_code, const int32_
     };
     {
         Span sp(m, 4, s);
-        chk(launch_fill_i32(elem_cnt, m->nel, 0, s));
+        chk(launch_zero2(elem_cnt, m->nel, nullptr, 0, s));
         chk(launch_eval_bin(m, 0, n, d_code, d_elem, nullptr, nullptr, n_fields, d_out, elem_cnt,
                             nullptr, rank, nullptr, s));
-        chk(launch_exclusive_scan(elem_cnt, elem_off, m->nel, 1, tmp, tb, s));
-        chk(launch_exclusive_scan(elem_cnt, chunk_off, m->nel, kChunk, tmp, tb, s));
-        chk(launch_task_map(chunk_off, m->nel, task_elem, s));
+        chk(launch_unit_scan(
+            UnitScan{elem_cnt, m->nel, tmp, elem_off, chunk_off, task_elem}, tb, s));
         chk(launch_eval_bin(m, 1, n, d_code, d_elem, nullptr, nullptr, n_fields, d_out, nullptr,
                             elem_off,
                             rank, sorted, s));
@@ -877,13 +872,10 @@ int fpts_lpt_step(fpts_mesh *m, const fpts_lpt_params *p, int64_t n, int first, 
     };
     {
         Span sp(m, 0, s);
-        chk(launch_fill_i32(elem_cnt, m->nel, 0, s));
-        chk(launch_fill_i32(counters, kCounters, 0, s));
-        chk(launch_fill_i32(reinterpret_cast<int *>(stats), 6 * kStats, 0, s));
+        chk(launch_zero2(at<int>(sub, w.zero), (w.total - w.zero) / sizeof(int), nullptr, 0, s));
         chk(launch_hint(m, 0, n, d_code, d_elem, d_r, cand, elem_cnt, rank, nullptr, s));
-        chk(launch_exclusive_scan(elem_cnt, elem_off, m->nel, 1, tmp, w.scan_blocks, s));
-        chk(launch_exclusive_scan(elem_cnt, chunk_off, m->nel, kChunk, tmp, w.scan_blocks, s));
-        chk(launch_task_map(chunk_off, m->nel, task_elem, s));
+        chk(launch_unit_scan(UnitScan{elem_cnt, m->nel, tmp, elem_off, chunk_off, task_elem},
+                             w.scan_blocks, s));
         chk(launch_primary_scatter(n, m->nel, cand, elem_off, rank, sorted, s));
     }
     {
@@ -935,9 +927,12 @@ int fpts_find_eval(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code
     // interpolation pass are listed by the find's marking pass (in slist,
     // which only the line-mesh path uses otherwise)
     const bool listed = m->R >= 2;
-    const EvalRest rest{at<int>(ews, v.slist), at<int>(ews, v.scount), d_out, n_fields};
+    // (the second pass's counts are zeroed with the find's)
+    const EvalRest rest{at<int>(ews, 0), (int64_t)(v.zero_end / sizeof(int)),
+                        listed ? at<int>(ews, v.slist) : nullptr, at<int>(ews, v.scount), d_out,
+                        n_fields};
     int st = find_impl(m, n, d_pts, d_code, d_elem, d_r, d_dist, precision, d_ws, w.total,
-                       stream, nullptr, rs, listed ? &rest : nullptr);
+                       stream, nullptr, rs, &rest);
     if (st != FPTS_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     const int2 *cand = at<int2>(d_ws, w.cand);
@@ -971,21 +966,17 @@ int fpts_find_eval(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code
         // give the same bits
         const bool split = m->R == 1;
         Span sp(m, 4, s);
-        chk(launch_fill_i32(elem_cnt, m->nel, 0, s));
         if (listed) {
             chk(launch_eval_bin_list(m, 0, slist, scount, n, d_elem, elem_cnt, nullptr, erank,
                                      nullptr, s));
         } else {
-            chk(launch_fill_i32(scount, 1, 0, s));
             chk(launch_eval_bin(m, 0, n, d_code, d_elem, d_r, cand, n_fields, d_out, elem_cnt,
                                 nullptr, erank, nullptr, s));
         }
         if (split)
             chk(launch_eval_split(m, n, d_elem, erank, elem_cnt, nullptr, nullptr, nullptr,
                                   nullptr, 0, s));
-        chk(launch_exclusive_scan(elem_cnt, eoff, m->nel, 1, tmp, tb, s));
-        chk(launch_exclusive_scan(elem_cnt, choff, m->nel, kChunk, tmp, tb, s));
-        chk(launch_task_map(choff, m->nel, etask, s));
+        chk(launch_unit_scan(UnitScan{elem_cnt, m->nel, tmp, eoff, choff, etask}, tb, s));
         if (split)
             chk(launch_eval_split(m, n, d_elem, erank, elem_cnt, eoff, esorted, slist, scount, 1,
                                   s));

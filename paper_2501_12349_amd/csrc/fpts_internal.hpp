@@ -49,8 +49,8 @@ struct HashView {
 // runs task (b mod 8) * (G / 8) + b / 8 of a grid of G blocks (G a multiple
 // of 8): each XCD works through a contiguous range of tasks and the tasks of
 // one unit share its L2; a block continues with tasks t + G, t + 2G, ...
-// Task -> unit comes from a map filled after the task offsets are scanned
-// (launch_task_map).
+// Task -> unit comes from a map filled as the task offsets are scanned
+// (launch_unit_scan).
 constexpr int kXcd = 8;
 // a primary result settles its point when INTERIOR at least this far inside
 // the reference box (no other element can then hold the point inside)
@@ -171,14 +171,17 @@ __device__ inline bool box_pass(P rec, const double *x, double &depth)
     return in && (depth <= 1.0);
 }
 
-// fused find + interpolate (list null otherwise): the points the pass over
-// the primary list does not interpolate (list, *count of them; count zeroed
-// by the find), and NaN values for NOT_FOUND points
+// fused find + interpolate: ints zeroed with the find's own counts (zero,
+// zero_n of them, *count among them); unless list is null, the points the
+// pass over the primary list does not interpolate (list, *count of them), and
+// NaN values for NOT_FOUND points
 struct EvalRest {
-    int *list;
-    int *count;
-    double *out;
-    int n_fields;
+    int *zero = nullptr;
+    int64_t zero_n = 0;
+    int *list = nullptr;
+    int *count = nullptr;
+    double *out = nullptr;
+    int n_fields = 0;
 };
 
 // cand[p] (find workspace): (number of candidates that pass the box tests,
@@ -189,7 +192,7 @@ struct FindWs {
         elem_off2, chunk_off2, slot_pt, slot_elem, sorted2, res_r, res_dist, res_code,
         task_cell, task_elem, task_elem2, scan_tmp, counters, stats, pts4, start, park_meta,
         park_r, park_state, park_cnt, park_off, park_choff, park_rank, park_sorted, park_task,
-        olist, ov_int, ov_dbl, bin_hist, bin_pairs, total;
+        olist, ov_int, ov_dbl, bin_hist, bin_pairs, zero, total;
     int64_t cap2;           // capacity for second-pass (point, candidate) pairs
     int64_t scan_blocks;
     int64_t ncell;
@@ -202,7 +205,7 @@ struct FindWs {
 
 struct EvalWs {
     size_t elem_cnt, elem_off, rank, chunk_off, scan_tmp, sorted, task_elem, slist, scount,
-        total;
+        zero_end, total;
     int64_t tb_elem;
 };
 
@@ -372,9 +375,23 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n);
 EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n);
 
 // launchers (kernels_*.hip); all return hipError_t of the last launch
-hipError_t launch_fill_i32(int *p, int64_t count, int value, hipStream_t s);
-hipError_t launch_exclusive_scan(const int *in, int *out, int64_t n, int ceil_div,
-                                 int *tmp, int64_t tmp_blocks, hipStream_t s);
+// zeroes two ranges of ints (counts may be 0) in one launch
+hipError_t launch_zero2(int *a, int64_t na, int *b, int64_t nb, hipStream_t s);
+// Exclusive scans over the counts of n >= 1 units (cnt 16-byte aligned):
+// off[0..n] of the counts (off may alias cnt); unless null, choff[0..n] of
+// their 64-item tasks with the map task -> unit, and off2[0..n] of their
+// tasks of up to len2 items with the map task2.  tile_sum: scan_tmp_blocks(n)
+// ints of scratch.
+struct UnitScan {
+    const int *cnt;
+    int64_t n;
+    int *tile_sum;
+    int *off;
+    int *choff = nullptr, *task = nullptr;
+    int *off2 = nullptr, *task2 = nullptr;
+    int len2 = 1;
+};
+hipError_t launch_unit_scan(UnitScan u, int64_t tmp_blocks, hipStream_t s);
 int64_t scan_tmp_blocks(int64_t n);
 // phase A: pass 0 counts points per cell (and writes NOT_FOUND for points
 // outside the map), keeping each point's rank among its cell's points; pass 1
@@ -422,8 +439,6 @@ hipError_t launch_hint(const fpts_mesh *m, int pass, int64_t n, const int32_t *c
                        int *rank, int *keep, hipStream_t s);
 // phase B: candidates of each point from its cell's list (one wave per 64
 // points of one cell), primary = deepest inside its OBB
-// task -> unit map of a task grid over nunit units with task offsets chunk_off
-hipError_t launch_task_map(const int *chunk_off, int64_t nunit, int *task_unit, hipStream_t s);
 // Parked pairs binned by element: pass 0 counts them per element (elem_cnt,
 // zeroed before) and keeps each one's rank, pass 1 writes park index k at
 // sorted[elem_off[elem] + rank[k]]; *count pairs (at most cap).

@@ -3,102 +3,178 @@
 // OBB tests (eqs. eq_AABB_test, eq_OBB_test); the primary candidate of each
 // point is bucketed by element for Newton; points the primary does not
 // settle get their other candidates in a second pass and the selection rule
-// of Section 3.2.  Also the int32 exclusive scan and fill kernels used by
-// find and eval.
+// of Section 3.2.  Also the scan and fill kernels used by find and eval.
 #include "fpts_internal.hpp"
 
 namespace fpts {
 namespace {
 
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 8;
-constexpr int kScanTile = kScanThreads * kScanItems;
-
-__global__ void k_fill_i32(int *p, int64_t count, int value)
+// Zeroes [a, a + na) and [b, b + nb).
+__global__ __launch_bounds__(256) void k_zero2(int *a, int64_t na, int *b, int64_t nb)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < count; i += stride) p[i] = value;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < na + nb; i += stride) {
+        if (i < na) a[i] = 0;
+        else b[i - na] = 0;
+    }
 }
 
-__device__ inline int scan_in(const int *in, int64_t i, int64_t n, int ceil_div)
+// Exclusive scans of the counts of a bucketing, all in one pass over them:
+// off (items before each unit), choff (64-item tasks before it, with the
+// map task -> unit) and off2 (tasks of up to len2 items, with their map).
+// A block scans a tile of 8192 counts; where there are several tiles,
+// k_unit_sums has left their sums in tile_sum (3 per tile) and every block
+// adds up those before its own (no block waits for another).  A kernel of a
+// few microseconds costs about 4.6 us of the stream on this GPU whatever it
+// does, so the three scans and their maps as kernels of their own (eight
+// launches) took 37 us per bucketing, six bucketings per call.
+constexpr int kUsThreads = 1024;
+constexpr int kUsItems = 8;
+constexpr int kUsTile = kUsThreads * kUsItems;
+constexpr int kUsWaves = kUsThreads / kWave;
+
+__device__ __forceinline__ int tasks_of(int cnt, int len) { return (cnt + len - 1) / len; }
+
+__device__ __forceinline__ void load_counts(const UnitScan &u, int64_t base, int (&v)[kUsItems])
 {
-    if (i >= n) return 0;
-    int v = in[i];
-    return ceil_div > 1 ? (v + ceil_div - 1) / ceil_div : v;
+    if (base + kUsItems <= u.n) {
+        const int4 *p = reinterpret_cast<const int4 *>(u.cnt + base);   // 256-byte aligned arrays
+        const int4 x = p[0], y = p[1];
+        v[0] = x.x;
+        v[1] = x.y;
+        v[2] = x.z;
+        v[3] = x.w;
+        v[4] = y.x;
+        v[5] = y.y;
+        v[6] = y.z;
+        v[7] = y.w;
+    } else {
+#pragma unroll
+        for (int k = 0; k < kUsItems; ++k) v[k] = base + k < u.n ? u.cnt[base + k] : 0;
+    }
 }
 
-// Block-wide exclusive scan of one value per thread; returns the block total.
-__device__ inline int block_exclusive(int v, int &excl)
+__device__ __forceinline__ void sum_counts(const UnitScan &u, const int (&v)[kUsItems],
+                                           int (&s)[3])
 {
-    __shared__ int warp_tot[kScanThreads / kWave];
+    s[0] = s[1] = s[2] = 0;
+#pragma unroll
+    for (int k = 0; k < kUsItems; ++k) {
+        s[0] += v[k];
+        if (u.choff) s[1] += tasks_of(v[k], kChunk);
+        if (u.off2) s[2] += tasks_of(v[k], u.len2);
+    }
+}
+
+// Block sums of three values, in every thread.
+__device__ __forceinline__ void block_sum3(int (&s)[3], int (*red)[kUsWaves])
+{
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    int incl = v;
 #pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        int t = __shfl_up(incl, o, kWave);
-        if (lane >= o) incl += t;
-    }
-    if (lane == kWave - 1) warp_tot[wid] = incl;
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int o = kWave / 2; o > 0; o >>= 1) s[q] += __shfl_xor(s[q], o, kWave);
     __syncthreads();
-    int base = 0, total = 0;
+    if (lane == 0) {
 #pragma unroll
-    for (int w = 0; w < kScanThreads / kWave; ++w) {
-        int t = warp_tot[w];
-        if (w < wid) base += t;
-        total += t;
+        for (int q = 0; q < 3; ++q) red[q][wid] = s[q];
     }
     __syncthreads();
-    excl = base + incl - v;
-    return total;
-}
-
-// Pass 1: per tile, local exclusive scan into out and the tile total.
-__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const int *in, int *out, int64_t n,
-                                                            int ceil_div, int *tile_sum)
-{
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    int v[kScanItems], s = 0;
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        v[k] = scan_in(in, base + k, n, ceil_div);
-        s += v[k];
-    }
-    int excl;
-    int tot = block_exclusive(s, excl);
+    for (int q = 0; q < 3; ++q) {
+        s[q] = 0;
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        if (base + k < n) out[base + k] = excl;
-        excl += v[k];
+        for (int w = 0; w < kUsWaves; ++w) s[q] += red[q][w];
     }
-    if (threadIdx.x == 0) tile_sum[blockIdx.x] = tot;
+    __syncthreads();
 }
 
-// Pass 2: one block scans the tile totals (exclusive) and writes the grand
-// total to out[n].
-__global__ __launch_bounds__(kScanThreads) void k_scan_sums(int *tile_sum, int64_t tiles, int *out,
-                                                           int64_t n)
+__global__ __launch_bounds__(kUsThreads) void k_unit_sums(UnitScan u)
 {
-    int carry = 0;
-    for (int64_t b = 0; b < tiles; b += kScanThreads) {
-        int64_t i = b + threadIdx.x;
-        int v = i < tiles ? tile_sum[i] : 0;
-        int excl;
-        int tot = block_exclusive(v, excl);
-        if (i < tiles) tile_sum[i] = carry + excl;
-        carry += tot;
-    }
-    if (threadIdx.x == 0) out[n] = carry;
+    __shared__ int red[3][kUsWaves];
+    int v[kUsItems], s[3];
+    load_counts(u, (int64_t)blockIdx.x * kUsTile + (int64_t)threadIdx.x * kUsItems, v);
+    sum_counts(u, v, s);
+    block_sum3(s, red);
+    if (threadIdx.x < 3) u.tile_sum[3 * (int64_t)blockIdx.x + threadIdx.x] = s[threadIdx.x];
 }
 
-// Pass 3: add the tile offsets.
-__global__ __launch_bounds__(kScanThreads) void k_scan_add(int *out, int64_t n, const int *tile_sum)
+// The maps' entries of the wave's units: task[base ..] = unit, cnt of them.
+// Units with many tasks are written by the whole wave.
+__device__ __forceinline__ void write_tasks(int *task, int base, int cnt, int unit)
 {
-    const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    const int add = tile_sum[blockIdx.x];
-    for (int k = threadIdx.x; k < kScanTile; k += kScanThreads) {
-        int64_t i = base + k;
-        if (i < n) out[i] += add;
+    constexpr int kOwn = 8;
+    const int lane = threadIdx.x & (kWave - 1);
+    if (cnt <= kOwn)
+        for (int t = 0; t < cnt; ++t) task[base + t] = unit;
+    unsigned long long big = __ballot(cnt > kOwn);
+    while (big) {
+        const int l = __builtin_ctzll(big);
+        big &= big - 1;
+        const int b = __shfl(base, l), c = __shfl(cnt, l), un = __shfl(unit, l);
+        for (int t = lane; t < c; t += kWave) task[b + t] = un;
+    }
+}
+
+__global__ __launch_bounds__(kUsThreads) void k_unit_scan(UnitScan u)
+{
+    __shared__ int red[3][kUsWaves];
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    const int64_t base = (int64_t)blockIdx.x * kUsTile + (int64_t)threadIdx.x * kUsItems;
+    // items and tasks of the earlier tiles
+    int pre[3] = {0, 0, 0};
+    if (blockIdx.x > 0) {
+        for (int64_t i = threadIdx.x; i < blockIdx.x; i += kUsThreads)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) pre[q] += u.tile_sum[3 * i + q];
+        block_sum3(pre, red);
+    }
+    int v[kUsItems], s[3];
+    load_counts(u, base, v);
+    sum_counts(u, v, s);
+    // exclusive scan of the threads' sums over the block
+    int at[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        int incl = s[q];
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int t = __shfl_up(incl, o, kWave);
+            if (lane >= o) incl += t;
+        }
+        at[q] = incl - s[q];
+        if (lane == kWave - 1) red[q][wid] = incl;
+    }
+    __syncthreads();
+    // totals of the earlier waves: lane w holds wave w's
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        int t = lane < wid ? red[q][lane] : 0;
+#pragma unroll
+        for (int o = kUsWaves / 2; o > 0; o >>= 1) t += __shfl_xor(t, o, kWave);
+        at[q] += pre[q] + __shfl(t, 0, kWave);
+    }
+#pragma unroll
+    for (int k = 0; k < kUsItems; ++k) {
+        const int64_t i = base + k;
+        const bool in = i < u.n;
+        const int t1 = in && u.choff ? tasks_of(v[k], kChunk) : 0;
+        const int t2 = in && u.off2 ? tasks_of(v[k], u.len2) : 0;
+        if (in) {
+            u.off[i] = at[0];
+            if (u.choff) u.choff[i] = at[1];
+            if (u.off2) u.off2[i] = at[2];
+        }
+        if (u.choff) write_tasks(u.task, at[1], t1, (int)i);
+        if (u.off2) write_tasks(u.task2, at[2], t2, (int)i);
+        at[0] += in ? v[k] : 0;
+        at[1] += t1;
+        at[2] += t2;
+        if (i == u.n - 1) {
+            u.off[u.n] = at[0];
+            if (u.choff) u.choff[u.n] = at[1];
+            if (u.off2) u.off2[u.n] = at[2];
+        }
     }
 }
 
@@ -313,15 +389,6 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_scatter(const int *total_p,
         const int2 cp = pairs[i];
         pbin[cell_poff[cp.x] + rank[i]] = cp.y;
     }
-}
-
-// task -> unit map: the tasks of unit u are chunk_off[u] .. chunk_off[u+1]-1
-__global__ __launch_bounds__(256) void k_task_map(const int *chunk_off, int nunit,
-                                                 int *task_unit)
-{
-    const int u = blockIdx.x * blockDim.x + threadIdx.x;
-    if (u >= nunit) return;
-    for (int t = chunk_off[u]; t < chunk_off[u + 1]; ++t) task_unit[t] = u;
 }
 
 // Phase B: one wavefront per task of up to 64 points of one cell (task
@@ -791,30 +858,29 @@ __global__ __launch_bounds__(256) void k_park_bin(int pass, const int4 *meta, co
 
 }  // namespace
 
-hipError_t launch_fill_i32(int *p, int64_t count, int value, hipStream_t s)
+hipError_t launch_zero2(int *a, int64_t na, int *b, int64_t nb, hipStream_t s)
 {
-    if (count <= 0) return hipSuccess;
-    int grid = (int)std::min<int64_t>(grid_for(count, 256), 4096);
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid), dim3(256), 0, s, p, count, value);
+    if (na + nb <= 0) return hipSuccess;
+    const int grid = (int)std::min<int64_t>((na + nb + 1023) / 1024, 4096);
+    hipLaunchKernelGGL(k_zero2, dim3(grid), dim3(256), 0, s, a, na, b, nb);
     return hipGetLastError();
 }
 
-int64_t scan_tmp_blocks(int64_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
+int64_t scan_tmp_blocks(int64_t n) { return 3 * ((n + kUsTile - 1) / kUsTile) + 1; }
 
-// out[0..n] = exclusive scan of in[0..n) (optionally ceil(in/ceil_div)),
-// out[n] = total.  `out` may alias `in` only when ceil_div <= 1.
-hipError_t launch_exclusive_scan(const int *in, int *out, int64_t n, int ceil_div, int *tmp,
-                                 int64_t tmp_blocks, hipStream_t s)
+hipError_t launch_unit_scan(UnitScan u, int64_t tmp_blocks, hipStream_t s)
 {
-    const int64_t tiles = (n + kScanTile - 1) / kScanTile;
-    if (tiles + 1 > tmp_blocks) return hipErrorInvalidValue;
-    if (tiles > 0)
-        hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)tiles), dim3(kScanThreads), 0, s, in, out,
-                           n, ceil_div, tmp);
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanThreads), 0, s, tmp, tiles, out, n);
-    if (tiles > 0)
-        hipLaunchKernelGGL(k_scan_add, dim3((unsigned)tiles), dim3(kScanThreads), 0, s, out, n,
-                           tmp);
+    const int64_t tiles = (u.n + kUsTile - 1) / kUsTile;
+    if (u.n < 1 || 3 * tiles > tmp_blocks || ((uintptr_t)u.cnt & 15) != 0)
+        return hipErrorInvalidValue;
+    // a single tile: as many threads as it has counts for (a block of few
+    // waves is launched and synchronised sooner)
+    int threads = kUsThreads;
+    if (tiles > 1)
+        hipLaunchKernelGGL(k_unit_sums, dim3((unsigned)tiles), dim3(kUsThreads), 0, s, u);
+    else
+        threads = (int)((u.n + kUsItems * kWave - 1) / (kUsItems * kWave)) * kWave;
+    hipLaunchKernelGGL(k_unit_scan, dim3((unsigned)tiles), dim3(threads), 0, s, u);
     return hipGetLastError();
 }
 
@@ -904,14 +970,6 @@ hipError_t launch_bin_scatter(int64_t n, const int *total, const int2 *pairs, co
     const int grid = xcd_grid(std::min<int64_t>(grid_for(n, kBinThreads), (int64_t)cus * 16));
     hipLaunchKernelGGL(k_bin_scatter, dim3(grid), dim3(kBinThreads), 0, s, total, pairs, rank,
                        cell_poff, pbin);
-    return hipGetLastError();
-}
-
-hipError_t launch_task_map(const int *chunk_off, int64_t nunit, int *task_unit, hipStream_t s)
-{
-    if (nunit <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_task_map, dim3(grid_for(nunit, 256)), dim3(256), 0, s, chunk_off,
-                       (int)nunit, task_unit);
     return hipGetLastError();
 }
 

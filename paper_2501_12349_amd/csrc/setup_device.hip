@@ -575,13 +575,11 @@ int device_setup(fpts_mesh *m, hipStream_t s)
     const int64_t tb = scan_tmp_blocks(ncell);
     if (!cnt.alloc(ncell + 1) || !fill.alloc(ncell) || !tmp.alloc(tb)) return FPTS_ENOMEM;
     const int eg = (int)((m->nel + 255) / 256);
-    if (launch_fill_i32(cnt.p, ncell, 0, s) != hipSuccess ||
-        launch_fill_i32(fill.p, ncell, 0, s) != hipSuccess)
-        return FPTS_EDEVICE;
+    if (launch_zero2(cnt.p, ncell, fill.p, ncell, s) != hipSuccess) return FPTS_EDEVICE;
     hipLaunchKernelGGL(k_map, dim3(eg), dim3(256), 0, s, v, m->d_box, (int64_t)m->nel, 0, cnt.p,
                        nullptr, nullptr, nullptr);
     if (hipGetLastError() != hipSuccess ||
-        launch_exclusive_scan(cnt.p, m->d_cell_off, ncell, 1, tmp.p, tb, s) != hipSuccess)
+        launch_unit_scan(UnitScan{cnt.p, ncell, tmp.p, m->d_cell_off}, tb, s) != hipSuccess)
         return FPTS_EDEVICE;
     m->cell_off.resize(ncell + 1);
     if (hipMemcpyAsync(m->cell_off.data(), m->d_cell_off, sizeof(int) * (ncell + 1),
