@@ -23,8 +23,10 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH,
           "-Wno-unused-command-line-argument",
           "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
-SOURCES = ["kernels_newton.hip",
-           "kernels_newton_line.hip",
+# "file@NAME" compiles the file with -DNAME: the Newton kernels of the three
+# element kinds are one file and three objects (they take longest)
+SOURCES = ["kernels_newton.hip@FPTS_HEX", "kernels_newton.hip@FPTS_SURF",
+           "kernels_newton.hip@FPTS_QUAD", "kernels_newton_line.hip",
            "kernels_find.hip", "kernels_eval.hip", "setup_device.hip", "lpt.hip", "api.cpp", "setup.cpp",
            "serve.cpp"]
 # the device setup reproduces the host setup's rounding and the particle
@@ -33,10 +35,11 @@ EXTRA = {"setup_device.hip": ["-ffp-contract=off"], "lpt.hip": ["-ffp-contract=o
 
 
 def _compile(src):
-    path = os.path.join(CSRC, src)
+    name, _, define = src.partition("@")
+    path = os.path.join(CSRC, name)
     obj = os.path.join(BUILD, src + ".o")
-    lang = ["-x", "hip"]
-    cmd = [HIPCC] + COMMON + EXTRA.get(src, []) + lang + ["-c", path, "-o", obj]
+    lang = ["-x", "hip"] + (["-D" + define] if define else [])
+    cmd = [HIPCC] + COMMON + EXTRA.get(name, []) + lang + ["-c", path, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("hipcc failed for %s:\n%s\n%s" % (src, " ".join(cmd), r.stderr))

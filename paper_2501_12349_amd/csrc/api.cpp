@@ -70,11 +70,12 @@ T *at(void *base, size_t off)
     return reinterpret_cast<T *>(static_cast<char *>(base) + off);
 }
 
-constexpr int kCounters = 64;   // ints: 0 the second search's list count, 2 to 5 below;
-                                 // from 16 on the Newton passes' element-queue counters
-constexpr int kNewtonCounters = 16;   // each Newton pass owns 16 counters from here on
-static_assert(3 * kNewtonCounters <= kCounters, "the two Newton passes need disjoint counters");
-constexpr int kStats = 16;      // unsigned long long: Newton counters per pass
+// ints: 0 the second search's list count, 2 to 6 below; from kNewtonFirst on
+// the primary Newton pass's task counters (a cache line apart)
+constexpr int kNewtonFirst = 32;
+constexpr int kCounters = kNewtonFirst + kNewtonCounters;
+constexpr int kPassStats = kStats * kStatCopies;   // 64-bit counters per pass, all copies
+constexpr int kStateSlots = 6;  // int counter of the reserved park states
 constexpr int kParkCount = 2;   // int counter of the parked pairs
 constexpr int kOverflowCount = 3;   // int counter of the overflowed points
 constexpr int kSlotTotal = 4;   // 64-bit running total of the second search's slots (ints 4, 5)
@@ -208,12 +209,11 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     w.park_state = c.take(sizeof(double) * kParkState * w.park_state_cap);
     w.park_off = c.take(I * (m->nel + 1));
     w.park_choff = c.take(I * (m->nel + 1));
-    w.park_rank = c.take(I * n);
     w.park_sorted = c.take(I * n);
     w.tb_park = task_bound(n, m->nel);
     w.park_task = c.take(I * w.tb_park);
     w.olist = c.take(I * n);
-    w.ov_grid = (int64_t)m->cus * 4;
+    w.ov_grid = (int64_t)m->cus * 3;
     w.ov_int = c.take(I * 3 * w.ov_grid);
     w.ov_dbl = c.take(sizeof(double) * (m->R + 1) * w.ov_grid);
     w.bin_hist = c.take(I * (w.bin_hist_n + 1));
@@ -224,10 +224,9 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     w.cell_cnt = c.take(I * ncell);
     w.elem_cnt = c.take(I * m->nel);
     w.elem_cnt2 = c.take(I * m->nel);
-    w.elem_fill2 = c.take(I * m->nel);
     w.park_cnt = c.take(I * m->nel);
     w.counters = c.take(I * kCounters);
-    w.stats = c.take(sizeof(unsigned long long) * 3 * kStats);
+    w.stats = c.take(sizeof(unsigned long long) * 3 * kPassStats);
     w.total = c.at;
     return w;
 }
@@ -291,7 +290,7 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
     int *elem_off = at<int>(d_ws, w.elem_off), *chunk_off = at<int>(d_ws, w.chunk_off);
     int *sorted = at<int>(d_ws, w.sorted), *ulist = at<int>(d_ws, w.ulist);
     int *uoff = at<int>(d_ws, w.uoff), *ucnt = at<int>(d_ws, w.ucnt);
-    int *elem_cnt2 = at<int>(d_ws, w.elem_cnt2), *elem_fill2 = at<int>(d_ws, w.elem_fill2);
+    int *elem_cnt2 = at<int>(d_ws, w.elem_cnt2);
     int *elem_off2 = at<int>(d_ws, w.elem_off2), *chunk_off2 = at<int>(d_ws, w.chunk_off2);
     int *slot_pt = at<int>(d_ws, w.slot_pt), *slot_elem = at<int>(d_ws, w.slot_elem);
     int *sorted2 = at<int>(d_ws, w.sorted2);
@@ -308,7 +307,7 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
     double *park_r = at<double>(d_ws, w.park_r);
     double *park_state = at<double>(d_ws, w.park_state);
     int *park_cnt = at<int>(d_ws, w.park_cnt), *park_off = at<int>(d_ws, w.park_off);
-    int *park_choff = at<int>(d_ws, w.park_choff), *park_rank = at<int>(d_ws, w.park_rank);
+    int *park_choff = at<int>(d_ws, w.park_choff);
     int *park_sorted = at<int>(d_ws, w.park_sorted), *park_task = at<int>(d_ws, w.park_task);
     int *olist = at<int>(d_ws, w.olist), *ov_int = at<int>(d_ws, w.ov_int);
     double *ov_dbl = at<double>(d_ws, w.ov_dbl);
@@ -363,7 +362,7 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
     }
     {   // phase C: Newton on the primary candidates, results straight to the outputs
         NewtonIO io{sorted, elem_off, chunk_off, nullptr, d_code, d_elem, d_r, n, d_dist,
-                    counters + kNewtonCounters, stats, task_elem, newt_off, newt_task,
+                    counters + kNewtonFirst, stats, task_elem, newt_off, newt_task,
                     w.tb_elem, rs, n};
         io.pts4 = pts4;
         if (m->R >= 2) {
@@ -375,29 +374,31 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
             io.park_r = park_r;
             io.park_cap = n;
             io.park_count = counters + kParkCount;
+            io.park_slots = counters + kStateSlots;
             io.park_state = park_state;
             io.park_state_cap = w.park_state_cap;
             io.polish = precision == FPTS_MIXED && m->R == m->D;
         }
-        {
+        // (the line kernel finds its starts itself)
+        if (m->R >= 2) {
             Span sp(m, 1, s);
             chk(launch_newton(m, precision, n, d_pts, io, 1, s));
         }
         {
             Span sp(m, 2, s);
-            chk(launch_newton(m, precision, n, d_pts, io, 2, s));
+            chk(launch_newton(m, precision, n, d_pts, io, m->R >= 2 ? 2 : 3, s));
         }
         if (m->R >= 2) {
             // the parked pairs, binned by element, go on in the face kernel
             Span sp(m, 7, s);
-            chk(launch_park_bin(0, park_meta, counters + kParkCount, n, park_cnt, nullptr,
-                                park_rank, nullptr, m->cus, s));
+            chk(launch_park_bin(0, park_meta, elem_off + nel, n, rank, park_cnt, nullptr,
+                                nullptr, m->cus, s));
             chk(launch_unit_scan(UnitScan{park_cnt, nel, tmp, park_off, park_choff, park_task},
                                  tb, s));
-            chk(launch_park_bin(1, park_meta, counters + kParkCount, n, nullptr, park_off,
-                                park_rank, park_sorted, m->cus, s));
+            chk(launch_park_bin(1, park_meta, elem_off + nel, n, rank, nullptr, park_off,
+                                park_sorted, m->cus, s));
             NewtonIO fio{park_sorted, park_off, park_choff, nullptr, d_code, d_elem, d_r, n,
-                         d_dist, nullptr, stats + 2 * kStats, park_task, nullptr, nullptr,
+                         d_dist, nullptr, stats + 2 * kPassStats, park_task, nullptr, nullptr,
                          w.tb_park, rs, n};
             fio.pts4 = pts4;
             fio.park_meta = park_meta;
@@ -417,15 +418,15 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
         unsigned long long *slot_total =
             reinterpret_cast<unsigned long long *>(counters + kSlotTotal);
         chk(launch_resolve(m, 0, n, d_pts, cellpt, cand, ulist, counters, uoff, ucnt,
-                           slot_total, elem_cnt2, nullptr, nullptr, nullptr, nullptr, nullptr,
+                           slot_total, elem_cnt2, nullptr, nullptr, nullptr, nullptr,
                            w.cap2, olist, counters + kOverflowCount, s));
         chk(launch_unit_scan(UnitScan{elem_cnt2, nel, tmp, elem_off2, chunk_off2, task_elem2},
                              tb, s));
         chk(launch_resolve(m, 1, n, d_pts, cellpt, cand, ulist, counters, uoff, ucnt,
-                           nullptr, nullptr, elem_off2, elem_fill2, slot_pt, slot_elem, sorted2,
+                           nullptr, elem_cnt2, elem_off2, slot_pt, slot_elem, sorted2,
                            w.cap2, nullptr, nullptr, s));
         NewtonIO io{sorted2, elem_off2, chunk_off2, slot_pt, res_code, nullptr, res_r, w.cap2,
-                    res_dist, counters + 2 * kNewtonCounters, stats + kStats, task_elem2,
+                    res_dist, nullptr, stats + kPassStats, task_elem2,
                     nullptr, nullptr, w.tb_elem2};
         io.pts4 = pts4;
         // the other candidates are few and near element faces: plain FP64
@@ -437,7 +438,7 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
             // points whose other candidates did not fit the slots (none in
             // the common case: the kernel reads the count and returns)
             NewtonIO oio{olist, nullptr, nullptr, nullptr, d_code, d_elem, d_r, n, d_dist,
-                         nullptr, stats + kStats, nullptr, nullptr, nullptr, w.ov_grid};
+                         nullptr, stats + kPassStats, nullptr, nullptr, nullptr, w.ov_grid};
             oio.pts4 = pts4;
             oio.ocount = counters + kOverflowCount;
             oio.cellpt = cellpt;
@@ -656,7 +657,7 @@ int fpts_find_stats_get(const fpts_mesh *m, int64_t n, const void *d_ws, int pas
 {
     if (!m || !d_ws || !out || n < 0 || pass < 0 || pass > 3) return FPTS_EINVAL;
     const FindWs w = find_ws_layout(m, n);
-    unsigned long long all[3 * kStats] = {0}, v[kStats] = {0};
+    unsigned long long all[3 * kPassStats] = {0}, v[kStats] = {0};
     hipStream_t s = (hipStream_t)stream;
     if (hipMemcpyAsync(all, static_cast<const char *>(d_ws) + w.stats, sizeof(all),
                        hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -669,7 +670,8 @@ int fpts_find_stats_get(const fpts_mesh *m, int64_t n, const void *d_ws, int pas
         return FPTS_EDEVICE;
     for (int k = 0; k < kStats; ++k)
         for (int q = 0; q < 3; ++q)
-            if (pass == 0 || pass == q + 1) v[k] += all[q * kStats + k];
+            if (pass == 0 || pass == q + 1)
+                for (int cp = 0; cp < kStatCopies; ++cp) v[k] += all[q * kPassStats + cp * kStats + k];
     out->overflow_points = ctr[kOverflowCount];
     out->parked_pairs = ctr[kParkCount];
     out->listed_points = ctr[0];
@@ -884,7 +886,7 @@ int fpts_lpt_step(fpts_mesh *m, const fpts_lpt_params *p, int64_t n, int first, 
         // passes tell, and the full Find takes it (kHintPasses; a warm
         // start converges in three or four)
         NewtonIO io{sorted, elem_off, chunk_off, nullptr, d_code, d_elem, d_r, n, d_dist,
-                    counters + kNewtonCounters, stats, task_elem, chunk_off, task_elem,
+                    counters + kNewtonFirst, stats, task_elem, chunk_off, task_elem,
                     w.tb_elem, nullptr, 0, keep, kHintPasses};
         chk(launch_newton(m, precision, n, d_x, io, 2, s));
         chk(launch_hint(m, 1, n, d_code, d_elem, d_r, cand, nullptr, nullptr, keep, s));

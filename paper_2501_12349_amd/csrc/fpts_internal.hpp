@@ -188,10 +188,10 @@ struct EvalRest {
 // primary element or -1) of point p
 struct FindWs {
     size_t cell_cnt, cell_poff, cell_choff, cellpt, pbin, cand, rank, bin_prim,
-        elem_cnt, elem_off, chunk_off, sorted, ulist, uoff, ucnt, elem_cnt2, elem_fill2,
+        elem_cnt, elem_off, chunk_off, sorted, ulist, uoff, ucnt, elem_cnt2,
         elem_off2, chunk_off2, slot_pt, slot_elem, sorted2, res_r, res_dist, res_code,
         task_cell, task_elem, task_elem2, scan_tmp, counters, stats, pts4, start, park_meta,
-        park_r, park_state, park_cnt, park_off, park_choff, park_rank, park_sorted, park_task,
+        park_r, park_state, park_cnt, park_off, park_choff, park_sorted, park_task,
         olist, ov_int, ov_dbl, bin_hist, bin_pairs, zero, total;
     int64_t cap2;           // capacity for second-pass (point, candidate) pairs
     int64_t scan_blocks;
@@ -220,8 +220,8 @@ struct NewtonIO {
     double *r;              // [R][ostride]
     int64_t ostride;
     double *dist;           // [item]
-    int *counter;           // element-queue counters (zeroed before the launch)
-    unsigned long long *stats;
+    int *counter;           // task counters, kNewtonCounters ints (zeroed before the launch)
+    unsigned long long *stats;   // kStatCopies copies of kStats counters
     const int *task_elem;   // task -> element of the nearest-node task grid
     // the primary pass's Newton tasks (one or more per element, of even
     // parts of its queue): offsets per element, task -> element
@@ -251,19 +251,21 @@ struct NewtonIO {
     int64_t start_stride;
     // optional (primary FP64 pass): a pair whose next pass needs second
     // derivatives (a pass on a face, eq. eq_newton_hessian) leaves its wave
-    // and is parked: park_meta[k] = {item, list position, element, passes
-    // so far}, park_r[j * park_cap + k] = r_j (j < R) and the trust-region
-    // radius alpha (j = R); *park_count counts the parked pairs (at most
-    // park_cap, one per pair of the pass).  The face kernel resumes them,
-    // binned by element, with list = park indices.
+    // and is parked at its list position q: node[q] = -1, park_meta[q] =
+    // {item, state slot, element, passes so far}, park_r[j * park_cap + q] =
+    // r_j (j < R) and the trust-region radius alpha (j = R); *park_count
+    // counts the parked pairs.  The face kernel resumes them, binned by
+    // element, with list = those positions.
     int4 *park_meta;
     double *park_r;
     int64_t park_cap;
     int *park_count;
-    // optional: the iteration state at r of parked pair k < park_state_cap,
-    // park_state[k * kParkState + j] (j: f, g[R], the Gauss-Newton Hessian
-    // [kSym<R>], dx[D]), so that the face kernel resumes without evaluating
-    // the map at r again; pairs parked beyond the capacity are re-evaluated
+    // the iteration state at r of the parked pair with state slot k <
+    // park_state_cap, park_state[k * kParkState + j] (j: f, g[R], the
+    // Gauss-Newton Hessian [kSym<R>], dx[D]), so that the face kernel resumes
+    // without evaluating the map at r again; pairs beyond the capacity are
+    // re-evaluated.  *park_slots: slots reserved so far
+    int *park_slots;
     double *park_state;
     int64_t park_state_cap;
     // mixed mode, FP64 phase of a volume mesh: when the first FP64 Newton
@@ -285,6 +287,15 @@ struct NewtonIO {
 // the solution one step leaves an error of order kappa * 1e-12, kappa the
 // element map's relative curvature (<< 1 for elements of a valid mesh).
 constexpr double kPolishTol = 1e-6;
+
+// Newton counters: kStats 64-bit counters per pass, in kStatCopies copies that
+// are added up when they are read (fpts_find_stats_get).
+constexpr int kStats = 16;
+constexpr int kStatCopies = 16;
+// Task counters of a Newton pass: one per XCD, a cache line apart, for the
+// FP64 kernel and for the FP32 phase.
+constexpr int kXcdCounter = 32;
+constexpr int kNewtonCounters = 2 * kXcd * kXcdCounter;
 
 // Doubles per saved park state (at most 1 + 3 + 6 + 3 used), one 128-byte
 // record per parked pair.
@@ -439,11 +450,12 @@ hipError_t launch_hint(const fpts_mesh *m, int pass, int64_t n, const int32_t *c
                        int *rank, int *keep, hipStream_t s);
 // phase B: candidates of each point from its cell's list (one wave per 64
 // points of one cell), primary = deepest inside its OBB
-// Parked pairs binned by element: pass 0 counts them per element (elem_cnt,
-// zeroed before) and keeps each one's rank, pass 1 writes park index k at
-// sorted[elem_off[elem] + rank[k]]; *count pairs (at most cap).
-hipError_t launch_park_bin(int pass, const int4 *meta, const int *count, int64_t cap,
-                           int *elem_cnt, const int *elem_off, int *rank, int *sorted, int cus,
+// Parked pairs binned by element, over the *total list positions q (at most
+// cap) of which those with node[q] < 0 hold one: pass 0 counts them per
+// element (elem_cnt, zeroed before) and keeps each one's rank (node[q] = -2 -
+// rank), pass 1 writes q at sorted[elem_off[elem] + rank].
+hipError_t launch_park_bin(int pass, const int4 *meta, const int *total, int64_t cap,
+                           int *node, int *elem_cnt, const int *elem_off, int *sorted, int cus,
                            hipStream_t s);
 // (counts primaries per element; in bin order, bin_prim[i] and rank[i] are
 // the primary of the point at bin position i and its rank in that bucket)
@@ -465,7 +477,8 @@ hipError_t launch_primary_scatter(int64_t n, int64_t nel, const int2 *cand,
 // phase D: list the points whose primary result does not settle them
 // (ulist, *ucount of them); pass 0 counts their other candidates and gives
 // each point a block of slots (uoff, ucnt, running total *slot_total), pass
-// 1 writes the (point, element) slots into element buckets; select2 applies
+// 1 writes the (point, element) slots into element buckets (counting
+// elem_cnt2 back down); select2 applies
 // the selection rule to every listed point
 hipError_t launch_unsettled(const fpts_mesh *m, int64_t n, const int *cellpt, const int2 *cand,
                             const int32_t *code, const double *r, int *ulist,
@@ -473,7 +486,7 @@ hipError_t launch_unsettled(const fpts_mesh *m, int64_t n, const int *cellpt, co
 hipError_t launch_resolve(const fpts_mesh *m, int pass, int64_t n, const double *pts,
                           const int *cellpt, const int2 *cand, const int *ulist,
                           const int *ucount, int *uoff, int *ucnt, unsigned long long *slot_total,
-                          int *elem_cnt2, const int *elem_off2, int *elem_fill2, int *slot_pt,
+                          int *elem_cnt2, const int *elem_off2, int *slot_pt,
                           int *slot_elem, int *sorted2, int64_t cap2, int *olist, int *ocount,
                           hipStream_t s);
 hipError_t launch_select2(const fpts_mesh *m, int64_t n, const int *ulist, const int *ucount,

@@ -690,8 +690,7 @@ __global__ __launch_bounds__(256) void k_resolve(HashView h, int pass, int n, co
                                                 int *uoff, int *ucnt,
                                                 unsigned long long *slot_total,
                                                 int *elem_cnt2, const int *elem_off2,
-                                                int *elem_fill2, int *slot_pt, int *slot_elem,
-                                                int *sorted2, int64_t cap2, int *olist,
+                                                int *slot_pt, int *slot_elem, int *sorted2, int64_t cap2, int *olist,
                                                 int *ocount)
 {
     const int cnt = *ucount;
@@ -753,7 +752,7 @@ __global__ __launch_bounds__(256) void k_resolve(HashView h, int pass, int n, co
                 const int sl = s0 + k;
                 slot_pt[sl] = p;
                 slot_elem[sl] = e;
-                sorted2[elem_off2[e] + atomicAdd(&elem_fill2[e], 1)] = sl;
+                sorted2[elem_off2[e] + atomicSub(&elem_cnt2[e], 1) - 1] = sl;
                 ++k;
             }
         }
@@ -834,24 +833,26 @@ __global__ __launch_bounds__(256) void k_hint(int pass, int n, int nel, int R,
 }
 
 // Parked pairs of the primary Newton pass, binned by element (their queue
-// for the face kernel).  A fixed grid strides over the *count records; the
-// loop bound is uniform per wavefront, as wave_inc needs.
-__global__ __launch_bounds__(256) void k_park_bin(int pass, const int4 *meta, const int *count,
-                                                 int cap, int *elem_cnt, const int *elem_off,
-                                                 int *rank, int *sorted)
+// for the face kernel).  A fixed grid strides over the pass's list
+// positions; the loop bound is uniform per wavefront, as wave_inc needs.
+__global__ __launch_bounds__(256) void k_park_bin(int pass, const int4 *meta, const int *total_p,
+                                                 int cap, int *node, int *elem_cnt,
+                                                 const int *elem_off, int *sorted)
 {
-    const int total = min(*count, cap);
+    const int total = min(*total_p, cap);
     const int lane = threadIdx.x & 63;
-    for (int k0 = blockIdx.x * blockDim.x + (threadIdx.x & ~63); k0 < total;
-         k0 += gridDim.x * blockDim.x) {
-        const int k = k0 + lane;
-        const bool active = k < total;
+    for (int64_t k0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63); k0 < total;
+         k0 += (int64_t)gridDim.x * blockDim.x) {
+        const int k = (int)k0 + lane;
+        const int nd = k < total ? node[k] : 0;
+        const bool active = nd < 0;
+        if (!__ballot(active)) continue;
         const int e = active ? meta[k].z : 0;
         if (pass == 0) {
             const int rk = wave_inc(elem_cnt, e, active);
-            if (active) rank[k] = rk;
+            if (active) node[k] = -2 - rk;
         } else if (active) {
-            sorted[elem_off[e] + rank[k]] = k;
+            sorted[elem_off[e] - 2 - nd] = k;
         }
     }
 }
@@ -884,14 +885,14 @@ hipError_t launch_unit_scan(UnitScan u, int64_t tmp_blocks, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_park_bin(int pass, const int4 *meta, const int *count, int64_t cap,
-                           int *elem_cnt, const int *elem_off, int *rank, int *sorted, int cus,
+hipError_t launch_park_bin(int pass, const int4 *meta, const int *total, int64_t cap,
+                           int *node, int *elem_cnt, const int *elem_off, int *sorted, int cus,
                            hipStream_t s)
 {
     if (cap <= 0) return hipSuccess;
-    const int grid = (int)std::min<int64_t>(grid_for(cap, 256), (int64_t)cus * 4);
-    hipLaunchKernelGGL(k_park_bin, dim3(grid), dim3(256), 0, s, pass, meta, count, (int)cap,
-                       elem_cnt, elem_off, rank, sorted);
+    const int grid = (int)std::min<int64_t>(grid_for(cap, 256), (int64_t)cus * 8);
+    hipLaunchKernelGGL(k_park_bin, dim3(grid), dim3(256), 0, s, pass, meta, total, (int)cap,
+                       node, elem_cnt, elem_off, sorted);
     return hipGetLastError();
 }
 
@@ -1031,7 +1032,7 @@ static int list_grid(const fpts_mesh *m, int64_t n)
 hipError_t launch_resolve(const fpts_mesh *m, int pass, int64_t n, const double *pts,
                           const int *cellpt, const int2 *cand, const int *ulist,
                           const int *ucount, int *uoff, int *ucnt, unsigned long long *slot_total,
-                          int *elem_cnt2, const int *elem_off2, int *elem_fill2, int *slot_pt,
+                          int *elem_cnt2, const int *elem_off2, int *slot_pt,
                           int *slot_elem, int *sorted2, int64_t cap2, int *olist, int *ocount,
                           hipStream_t s)
 {
@@ -1040,7 +1041,7 @@ hipError_t launch_resolve(const fpts_mesh *m, int pass, int64_t n, const double 
     auto k = m->D == 2 ? k_resolve<2> : k_resolve<3>;
     hipLaunchKernelGGL(k, dim3(list_grid(m, n)), dim3(256), 0, s, h, pass, (int)n, pts, cellpt,
                        cand, ulist, ucount, uoff, ucnt, slot_total, elem_cnt2, elem_off2,
-                       elem_fill2, slot_pt, slot_elem, sorted2, cap2, olist, ocount);
+                       slot_pt, slot_elem, sorted2, cap2, olist, ocount);
     return hipGetLastError();
 }
 

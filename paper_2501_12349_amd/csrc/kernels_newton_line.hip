@@ -247,12 +247,12 @@ __global__ __launch_bounds__(64) void k_newton_line(LineArgs a)
     n_passes = wave_sum(n_passes);
     n_evals = wave_sum(n_evals);
     n_h2 = wave_sum(n_h2);
-    if (lane == 0 && n_pairs) {
-        atomicAdd(&io.stats[0], n_pairs);
-        atomicAdd(&io.stats[1], n_passes);
-        atomicAdd(&io.stats[2], n_evals);
-        atomicAdd(&io.stats[3], n_h2);
-    }
+    // (to the block's copy, a lane per counter: every block's four atomics on
+    // the same addresses, some 16 ns each, held the kernel at 0.81 ms for
+    // 5.4M points)
+    if (lane < 4 && n_pairs)
+        atomicAdd(&io.stats[(blockIdx.x % kStatCopies) * kStats + lane],
+                  lane == 0 ? n_pairs : lane == 1 ? n_passes : lane == 2 ? n_evals : n_h2);
 }
 
 typedef void (*LineFn)(LineArgs);

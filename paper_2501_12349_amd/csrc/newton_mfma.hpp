@@ -903,6 +903,14 @@ enum { kPrimary = 0, kResolve = 1, kFace = 2, kPolish = 3 };
 constexpr int kReplan = 16;
 // park_meta flag beside the pass count: no iteration state was saved
 constexpr int kParkNoState = 1 << 30;
+// State slots a wave reserves at a time: one returning atomic on the pass's
+// counter for every trip that parks a pair held k_newton at 2.3 ms (N = 8,
+// 5M points: about 130 thousand of them at 16 ns).  Slots left over at the
+// end stay empty.
+constexpr int kParkReserve = 16;
+struct Reserve {
+    int next = 0, left = 0;
+};
 
 // per-wave counters (scalar registers: counts of ballots)
 struct Counters {
@@ -910,16 +918,20 @@ struct Counters {
              evals_h2_exec = 0, sweeps = 0, sweeps_h2 = 0, sweeps32 = 0, evals32_node = 0;
 };
 
-// Adds the wave's counters to the pass's.
+// Adds the wave's counters to the pass's: to the block's copy of them (an
+// atomic on one address takes some 16 ns whichever wave it comes from), one
+// lane per counter.
 __device__ __forceinline__ void add_counters(const Counters &cn, unsigned long long *stats,
                                              int lane)
 {
     const unsigned v[11] = {cn.pairs,    cn.passes,  cn.evals,         cn.evals_h2,
                             cn.passes32, cn.evals32, cn.evals_h2_exec, cn.sweeps,
                             cn.sweeps_h2, cn.sweeps32, cn.evals32_node};
+    unsigned x = 0;
 #pragma unroll
-    for (int k = 0; k < 11; ++k)
-        if (lane == 0 && v[k]) atomicAdd(&stats[k], (unsigned long long)v[k]);
+    for (int k = 0; k < 11; ++k) x = lane == k ? v[k] : x;
+    if (x)
+        atomicAdd(&stats[(blockIdx.x % kStatCopies) * kStats + lane], (unsigned long long)x);
 }
 
 // How a pair's start is given: the packed index of a GLL node per list
@@ -936,12 +948,12 @@ enum { kStartNode = 0, kStartPoint = 1, kStartEither = 2 };
 // stage(): stages the element's nodes in LDS (a no-op where the caller
 // staged them: kResolve, which found its starts from them, and kFace).
 // given_node: kResolve, the start node of the pair at list position
-// q0 + lane.
+// q0 + lane.  Returns the number of pairs parked.
 template <typename T, int D, int R, int N, bool FINAL, int KIND, typename Stage>
-__device__ __forceinline__ void run_element(const NewtonArgs &a, int e, int q0, int q1,
-                                            const T *xl, T *tab, T *qb, int lane, int max_iter,
-                                            T tol, const double *shift, int given_node,
-                                            Counters &cn, Stage &&stage)
+__device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, int q1,
+                                           const T *xl, T *tab, T *qb, int lane, int max_iter,
+                                           T tol, const double *shift, int given_node,
+                                           Reserve &reserve, Counters &cn, Stage &&stage)
 {
     typedef unsigned long long u64;
     constexpr int K = D * (R + 1);
@@ -998,7 +1010,7 @@ __device__ __forceinline__ void run_element(const NewtonArgs &a, int e, int q0, 
         b.node = -1;
         if (idx < q1) {
             int p;
-            if constexpr (KIND == kFace) p = io.park_meta[it].x;
+            if constexpr (KIND == kFace) p = io.park_meta[it].x;   // (it: its list position)
             else p = io.slot_pt ? io.slot_pt[it] : it;
             if constexpr (KIND == kResolve) {
                 b.node = given_node;
@@ -1023,6 +1035,7 @@ __device__ __forceinline__ void run_element(const NewtonArgs &a, int e, int q0, 
     };
     Batch cb = {}, nb = {};
     int it2 = 0;   // list entries of the batch after next
+    int parked = 0;
     // the first batch is loaded before the nodes are staged, so that the two
     // wait together
     load_batch(q0, load_item(q0), cb);
@@ -1091,10 +1104,10 @@ __device__ __forceinline__ void run_element(const NewtonArgs &a, int e, int q0, 
                     const int4 mt = io.park_meta[it];
                     pass = mt.w & ~kParkNoState;
                     alpha = T(io.park_r[(size_t)R * io.park_cap + it]);
-                    if (it < io.park_state_cap && !(mt.w & kParkNoState)) {
+                    if (!(mt.w & kParkNoState)) {
                         // with the state the evaluation at r left: the
                         // pair waits for its second derivatives at once
-                        const double *ps = io.park_state + (size_t)it * kParkState;
+                        const double *ps = io.park_state + (size_t)mt.y * kParkState;
                         cur.f = T(ps[0]);
 #pragma unroll
                         for (int j = 0; j < R; ++j) cur.g[j] = T(ps[1 + j]);
@@ -1105,7 +1118,7 @@ __device__ __forceinline__ void run_element(const NewtonArgs &a, int e, int q0, 
                         state = S_WAIT;
                     }
                     item = mt.x;
-                    pos = mt.y;
+                    pos = it;
                 }
             }
             const int taken = min(__popcll(freem), cend - head);
@@ -1455,24 +1468,33 @@ __device__ __forceinline__ void run_element(const NewtonArgs &a, int e, int q0, 
             const u64 pm = __ballot(park);
             if (pm) {
                 if (FINAL && io.park_meta) {
-                    int base = 0;
-                    if (lane == 0) base = atomicAdd(io.park_count, __popcll(pm));
-                    base = __builtin_amdgcn_readfirstlane(base);
-                    // park_cap is the pass's pair count: every pair is
-                    // parked at most once, so k < park_cap
-                    const int k = base + __popcll(pm & ((1ull << lane) - 1));
-                    if (park && k < io.park_cap) {
+                    // a record per list position, so that nothing has to be
+                    // counted; a state slot from the wave's reserve
+                    const int np = __popcll(pm);
+                    parked += np;
+                    if (np > reserve.left) {
+                        reserve.left = max(kParkReserve, np);
+                        int base = 0;
+                        if (lane == 0) base = atomicAdd(io.park_slots, reserve.left);
+                        reserve.next = __builtin_amdgcn_readfirstlane(base);
+                    }
+                    const int k = reserve.next + __popcll(pm & ((1ull << lane) - 1));
+                    reserve.next += np;
+                    reserve.left -= np;
+                    if (park) {
                         // a rejected step leaves r at its start node, where
                         // the objective came from the node block: the face
-                        // kernel evaluates it anew, whichever k it got
-                        io.park_meta[k] =
-                            make_int4(item, pos, e, at_r ? pass : pass | kParkNoState);
+                        // kernel evaluates it anew, whichever slot it got
+                        const bool save = at_r && k < io.park_state_cap;
+                        io.node[pos] = -1;
+                        io.park_meta[pos] =
+                            make_int4(item, k, e, save ? pass : pass | kParkNoState);
 #pragma unroll
                         for (int j = 0; j < R; ++j)
-                            io.park_r[(size_t)j * io.park_cap + k] = (double)r[j];
-                        io.park_r[(size_t)R * io.park_cap + k] = (double)alpha;
+                            io.park_r[(size_t)j * io.park_cap + pos] = (double)r[j];
+                        io.park_r[(size_t)R * io.park_cap + pos] = (double)alpha;
                         static_assert(1 + R + kSym<R> + D <= kParkState, "park state");
-                        if (at_r && k < io.park_state_cap) {
+                        if (save) {
                             // the state at r, as the evaluation there left it
                             double *ps = io.park_state + (size_t)k * kParkState;
                             ps[0] = (double)cur.f;
@@ -1492,6 +1514,7 @@ __device__ __forceinline__ void run_element(const NewtonArgs &a, int e, int q0, 
             }
         }
     }
+    return parked;
 }
 
 // Copies COUNT values of an element block from global memory to LDS (one
@@ -1899,11 +1922,14 @@ __device__ __forceinline__ int nearest_staged(const double *xl, const double (&x
 // Newton over the element queues in precision T.  Tasks are the parts of an
 // element's queue: io.newt_off[e] .. io.newt_off[e + 1] - 1 are element e's,
 // io.newt_task[t] is task t's element, and the element's pairs are divided
-// evenly among its tasks.  The primary and polish passes and the FP32 phase
-// take tasks from a counter (io.counter[8] for the FP64 kernels, [9] for the
-// FP32 phase of mixed mode), a few per wave of unequal cost; one task per
-// element would leave most waves idle at the end where elements hold many
-// pairs (2 million particles in 3888 elements, N = 8: 2.37 ms so).
+// evenly among its tasks: one task per element would leave most waves idle
+// at the end where elements hold many pairs (2 million particles in 3888
+// elements, N = 8: 2.37 ms so).  The primary and polish passes and the FP32
+// phase divide the tasks among the XCDs, a contiguous range each; a wave's
+// first task is its own place in its XCD's range, the others come from the
+// XCD's counter (io.counter, kXcdCounter ints apart; the FP32 phase's after
+// the FP64 kernels').  (One counter for all: an atomic on one address takes
+// some 16 ns, 1.05 ms for the 64 thousand tasks of 4M points, N = 4.)
 // TASKS: the waves stride over the 64-pair tasks of io.task_elem instead.
 // The other candidates of unsettled points and the parked pairs of the face
 // kernel are a few pairs scattered over many elements.
@@ -1926,17 +1952,24 @@ __device__ __forceinline__ void newton_body(const NewtonArgs &a)
     Counters cn;
     const int *off = TASKS ? io.chunk_off : io.newt_off;
     const int *elem = TASKS ? io.task_elem : io.newt_task;
-    const int total = off[a.nel];
-    int *ctr = io.counter + (FINAL ? 8 : 9);
+    const int all = off[a.nel];
+    // (the grid is a multiple of the XCD count)
+    const int xcd = blockIdx.x % kXcd, waves = gridDim.x / kXcd;
+    const int share = (all + kXcd - 1) / kXcd;
+    const int first = TASKS ? 0 : xcd * share;
+    const int total = TASKS ? all : min(all, first + share);
+    int *ctr = io.counter + ((FINAL ? 0 : kXcd) + xcd) * kXcdCounter;
     // the ticket of the wave's next task is taken one task ahead, so that
     // its atomic completes while the current one is processed (every ticket
-    // below the total is processed by the wave that took it)
+    // of the range is processed by the wave that took it)
     auto take = [&]() __attribute__((always_inline)) {
         int v = 0;
         if (lane == 0) v = atomicAdd(ctr, 1);
-        return v;
+        return first + waves + v;
     };
-    int ticket = TASKS ? task_of_block() : take();
+    int ticket = TASKS ? task_of_block() : first + (int)blockIdx.x / kXcd;
+    int parked = 0;
+    Reserve reserve;
     for (;;) {
         const int t = __builtin_amdgcn_readfirstlane(ticket);
         if (t >= total) break;
@@ -1977,22 +2010,24 @@ __device__ __forceinline__ void newton_body(const NewtonArgs &a)
                     if (lane == j) node = bi;
                 }
                 run_element<double, D, R, N, true, KIND>(a, e, q0, q1, xl, tab, qb, lane,
-                                                         a.max_iter, a.tol, nullptr, node, cn,
-                                                         [] {});
+                                                         a.max_iter, a.tol, nullptr, node,
+                                                         reserve, cn, [] {});
             } else {
                 // the nodes are staged after the first batch of pairs has
                 // been asked for
-                run_element<double, D, R, N, true, KIND>(
-                    a, e, q0, q1, xl, tab, qb, lane, a.max_iter, a.tol, nullptr, 0, cn,
+                parked += run_element<double, D, R, N, true, KIND>(
+                    a, e, q0, q1, xl, tab, qb, lane, a.max_iter, a.tol, nullptr, 0, reserve, cn,
                     [&] { stage_nodes<double, D, R, N>(xl, src, lane); });
             }
         } else {
             const float *src = a.nodes32 + (size_t)e * D * S::NP;
             run_element<float, D, R, N, false, KIND>(
                 a, e, q0, q1, xl, tab, qb, lane, a.max_iter32, a.tol32, a.xc + (size_t)e * D, 0,
-                cn, [&] { stage_nodes<float, D, R, N>(xl, src, lane); });
+                reserve, cn, [&] { stage_nodes<float, D, R, N>(xl, src, lane); });
         }
     }
+    if (KIND == kPrimary || KIND == kPolish)
+        if (FINAL && lane == 0 && parked) atomicAdd(io.park_count, parked);
     add_counters(cn, io.stats, lane);
 }
 
@@ -2074,6 +2109,7 @@ k_resolve_overflow(NewtonArgs a, HashView h)
     la.io.polish = 0;
     if (lane == 0) ov_item[b] = b;
     Counters cn;
+    Reserve none;
     for (int i = b; i < cnt; i += G) {
         const int p = io.list[i];
         const int prim = io.cand[p].y, c = io.cellpt[p];
@@ -2098,7 +2134,7 @@ k_resolve_overflow(NewtonArgs a, HashView h)
             // lane 0 wrote the queue entry and reads it back (same lane,
             // program order)
             run_element<double, D, R, N, true, kResolve>(la, e, b, b + 1, xl, tab, qb, lane,
-                                                        a.max_iter, a.tol, nullptr, bi, cn,
+                                                        a.max_iter, a.tol, nullptr, bi, none, cn,
                                                         [] {});
             // lane 0, the pair's lane, wrote the result
             int cd = 0;
@@ -2187,12 +2223,12 @@ Kernels pick_kernels(int N, bool resolve)
 
 // Launches on the caller's stream: nearest nodes (which & 1; task grid of
 // 64-pair tasks over io.chunk_off, io.task_elem; not for the *_resolve
-// kernels, which find them from the nodes they stage), then Newton (which & 2; element
-// tasks: in mixed mode the FP32 phase, counter io.counter[9], then the FP64
-// kernel, counter io.counter[8]); which & 4 runs the face kernel over the
-// parked pairs (io.list = park indices binned by element, io.elem_off /
-// chunk_off / task_elem their buckets and tasks).  io.counter[0..15] must be
-// zero.  A list with io.slot_pt set (other candidates) selects the *_resolve
+// kernels, which find them from the nodes they stage), then Newton (which & 2;
+// the tasks of io.newt_off, io.newt_task: in mixed mode the FP32 phase, then
+// the FP64 kernel); which & 4 runs the face kernel over the parked pairs
+// (io.list = their list positions binned by element, io.elem_off / chunk_off
+// / task_elem their buckets and tasks).  io.counter must be zero
+// (kNewtonCounters ints).  A list with io.slot_pt set (other candidates) selects the *_resolve
 // kernels, whose Newton strides over the 64-pair tasks like the nearest-node
 // kernel.
 template <int D, int R>
