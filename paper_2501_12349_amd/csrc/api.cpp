@@ -193,7 +193,7 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     w.res_code = c.take(I * w.cap2);
     w.tb_cell = task_bound(n, ncell);
     w.tb_elem = task_bound(n, m->nel);
-    w.tb_elem2 = task_bound(w.cap2, m->nel);
+    w.tb_elem2 = task_bound(w.cap2, m->nel, few_lanes(m->R, m->N));
     w.task_cell = c.take(I * w.tb_cell);
     w.task_elem = c.take(I * w.tb_elem);
     w.task_elem2 = c.take(I * w.tb_elem2);
@@ -210,7 +210,7 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     w.park_off = c.take(I * (m->nel + 1));
     w.park_choff = c.take(I * (m->nel + 1));
     w.park_sorted = c.take(I * n);
-    w.tb_park = task_bound(n, m->nel);
+    w.tb_park = task_bound(n, m->nel, few_lanes(m->R, m->N));
     w.park_task = c.take(I * w.tb_park);
     w.olist = c.take(I * n);
     w.ov_grid = (int64_t)m->cus * 3;
@@ -393,7 +393,8 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
             Span sp(m, 7, s);
             chk(launch_park_bin(0, park_meta, elem_off + nel, n, rank, park_cnt, nullptr,
                                 nullptr, m->cus, s));
-            chk(launch_unit_scan(UnitScan{park_cnt, nel, tmp, park_off, park_choff, park_task},
+            chk(launch_unit_scan(UnitScan{park_cnt, nel, tmp, park_off, park_choff, park_task,
+                                          few_lanes(m->R, m->N)},
                                  tb, s));
             chk(launch_park_bin(1, park_meta, elem_off + nel, n, rank, nullptr, park_off,
                                 park_sorted, m->cus, s));
@@ -420,7 +421,8 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
         chk(launch_resolve(m, 0, n, d_pts, cellpt, cand, ulist, counters, uoff, ucnt,
                            slot_total, elem_cnt2, nullptr, nullptr, nullptr, nullptr,
                            w.cap2, olist, counters + kOverflowCount, s));
-        chk(launch_unit_scan(UnitScan{elem_cnt2, nel, tmp, elem_off2, chunk_off2, task_elem2},
+        chk(launch_unit_scan(UnitScan{elem_cnt2, nel, tmp, elem_off2, chunk_off2, task_elem2,
+                                      few_lanes(m->R, m->N)},
                              tb, s));
         chk(launch_resolve(m, 1, n, d_pts, cellpt, cand, ulist, counters, uoff, ucnt,
                            nullptr, elem_cnt2, elem_off2, slot_pt, slot_elem, sorted2,

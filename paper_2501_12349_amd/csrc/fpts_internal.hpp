@@ -56,10 +56,19 @@ constexpr int kXcd = 8;
 // the reference box (no other element can then hold the point inside)
 constexpr double kSettleGuard = 1e-9;
 
-// Upper bound on the tasks of n items over nunit units.
-inline int64_t task_bound(int64_t n, int64_t nunit)
+// Elements that a wave of the face and resolve kernels takes at a time (they
+// hold some three to five pairs each), and the lanes of each: as many as
+// leave eight waves their node blocks in a CU's LDS.  Face + resolve kernel,
+// us: N = 4, 4M points 603 with one element, 298 with four; N = 6, 1.02M
+// points 218, 179 with two, 340 with four; N = 8, 5M points 1005 with one,
+// 1294 with two (32 KB a wave).
+constexpr int few_elems(int R, int N) { return R == 2 || N <= 5 ? 4 : N <= 7 ? 2 : 1; }
+constexpr int few_lanes(int R, int N) { return R == 1 ? kChunk : kWave / few_elems(R, N); }
+
+// Upper bound on the tasks of up to len of n items over nunit units.
+inline int64_t task_bound(int64_t n, int64_t nunit, int len = kChunk)
 {
-    return n / kChunk + std::min<int64_t>(n, nunit) + 1;
+    return n / len + std::min<int64_t>(n, nunit) + 1;
 }
 
 // Grid size (blocks) for a task bound: a multiple of the XCD count, at most
@@ -390,8 +399,8 @@ EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n);
 hipError_t launch_zero2(int *a, int64_t na, int *b, int64_t nb, hipStream_t s);
 // Exclusive scans over the counts of n >= 1 units (cnt 16-byte aligned):
 // off[0..n] of the counts (off may alias cnt); unless null, choff[0..n] of
-// their 64-item tasks with the map task -> unit, and off2[0..n] of their
-// tasks of up to len2 items with the map task2.  tile_sum: scan_tmp_blocks(n)
+// their tasks of up to len items with the map task -> unit, and off2[0..n] of
+// their tasks of up to len2 items with the map task2.  tile_sum: scan_tmp_blocks(n)
 // ints of scratch.
 struct UnitScan {
     const int *cnt;
@@ -399,6 +408,7 @@ struct UnitScan {
     int *tile_sum;
     int *off;
     int *choff = nullptr, *task = nullptr;
+    int len = kChunk;
     int *off2 = nullptr, *task2 = nullptr;
     int len2 = 1;
 };

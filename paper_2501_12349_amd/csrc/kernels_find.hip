@@ -20,8 +20,8 @@ __global__ __launch_bounds__(256) void k_zero2(int *a, int64_t na, int *b, int64
 }
 
 // Exclusive scans of the counts of a bucketing, all in one pass over them:
-// off (items before each unit), choff (64-item tasks before it, with the
-// map task -> unit) and off2 (tasks of up to len2 items, with their map).
+// off (items before each unit), choff (tasks of up to len items before it,
+// with the map task -> unit) and off2 (tasks of up to len2 items, with their map).
 // A block scans a tile of 8192 counts; where there are several tiles,
 // k_unit_sums has left their sums in tile_sum (3 per tile) and every block
 // adds up those before its own (no block waits for another).  A kernel of a
@@ -61,7 +61,7 @@ __device__ __forceinline__ void sum_counts(const UnitScan &u, const int (&v)[kUs
 #pragma unroll
     for (int k = 0; k < kUsItems; ++k) {
         s[0] += v[k];
-        if (u.choff) s[1] += tasks_of(v[k], kChunk);
+        if (u.choff) s[1] += tasks_of(v[k], u.len);
         if (u.off2) s[2] += tasks_of(v[k], u.len2);
     }
 }
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kUsThreads) void k_unit_scan(UnitScan u)
     for (int k = 0; k < kUsItems; ++k) {
         const int64_t i = base + k;
         const bool in = i < u.n;
-        const int t1 = in && u.choff ? tasks_of(v[k], kChunk) : 0;
+        const int t1 = in && u.choff ? tasks_of(v[k], u.len) : 0;
         const int t2 = in && u.off2 ? tasks_of(v[k], u.len2) : 0;
         if (in) {
             u.off[i] = at[0];

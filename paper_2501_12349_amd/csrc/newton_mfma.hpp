@@ -447,8 +447,12 @@ struct Factor {
 
 // Sweep 1 for column group cg: each lane's partial sums of x(q) and
 // G = dx/dr of its column (v: X[c], then G[c][a]); the column's totals are
-// the sums over its four lanes.
-template <typename T, int D, int R, int N>
+// the sums over its four lanes.  NB > 1: the columns belong to NB elements
+// (16 / NB consecutive columns each, the node blocks one after the other);
+// every row tile is then a 4-row one, whose four products take their A rows
+// from their own columns' element.  The row sums and their order are the
+// same (the MFMAs of both shapes round like a chain of FMAs).
+template <typename T, int D, int R, int N, int NB = 1>
 __device__ __forceinline__ void sweep1(const T *xl, T *tab, const T *qb, int cg, int lane,
                                        T (&v)[D * (R + 1)])
 {
@@ -457,7 +461,9 @@ __device__ __forceinline__ void sweep1(const T *xl, T *tab, const T *qb, int cg,
     typedef Factor<R, N> F;
     typedef NodeLds<T, D, R, N> NL;
     typedef typename V4<T>::type v4;
+    constexpr int FT = NB > 1 ? 0 : C::FT, QT = NB > 1 ? (S::ROWS + 3) / 4 : C::QT;
     const int slot = lane & 15, g = lane >> 4;
+    if (NB > 1) xl += slot / (16 / NB) * NL::SIZE;
     // per-column tables [direction][kind][i][column] (kinds phi, phi'): lane
     // quarter g builds direction g of its column, so the R tables of all 16
     // columns are built at once
@@ -580,52 +586,68 @@ __device__ __forceinline__ void sweep1(const T *xl, T *tab, const T *qb, int cg,
             }
         }
     };
-    if constexpr (F::ON) {
+    if constexpr (FT > 0 && F::ON) {
         tile(0);
 #pragma unroll 1
-        for (int m = 1; m < C::FT; ++m) tile(m);
-    } else {
+        for (int m = 1; m < FT; ++m) tile(m);
+    } else if constexpr (FT > 0) {
         // (one copy: with the row weights of two the registers spill)
 #pragma unroll 1
-        for (int m = 0; m < C::FT; ++m) tile(m);
+        for (int m = 0; m < FT; ++m) tile(m);
     }
     // one 4-row tile: lane quarter g receives row g, all quarters of the
-    // columns read the same four A rows
-    if constexpr (C::QT > 0) {
-#pragma unroll 1
-        for (int t = 0; t < C::QT; ++t) {
-            const int base = 16 * C::FT + 4 * t;
-            const bool whole = S::ROWS % 4 == 0 || base + 4 <= S::ROWS;
-            const int arow = base + (slot & 3), row = base + g;
-            T c0[D], c1[D];
+    // columns read the same four A rows (of their element)
+    auto quad = [&](int base, auto &&take) __attribute__((always_inline)) {
+        const bool whole = S::ROWS % 4 == 0 || base + 4 <= S::ROWS;
+        const int arow = base + (slot & 3), row = base + g;
+        T c0[D], c1[D];
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            c0[c] = T(0);
+            c1[c] = T(0);
+        }
+#pragma unroll
+        for (int ks = 0; ks < C::KM; ++ks) {
+            const int ai = 4 * ks + g;
+            const bool aok = (whole || arow < S::ROWS) && (kFullA || ai < N);
 #pragma unroll
             for (int c = 0; c < D; ++c) {
-                c0[c] = T(0);
-                c1[c] = T(0);
-            }
-#pragma unroll
-            for (int ks = 0; ks < C::KM; ++ks) {
-                const int ai = 4 * ks + g;
-                const bool aok = (whole || arow < S::ROWS) && (kFullA || ai < N);
-#pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    const T a = xl[aok ? NL::at(c, arow, ai) : 0];
-                    c0[c] = mfma4(a, b0[ks], c0[c]);
-                    c1[c] = mfma4(a, b1[ks], c1[c]);
-                }
-            }
-            if (whole || row < S::ROWS) {
-#pragma unroll
-                for (int u = 0; u < C::KR; ++u)
-#pragma unroll
-                    for (int c = 0; c < D; ++c) {
-                        const T a = xl[NL::at(c, row, 4 * C::KM + u)];
-                        c0[c] = fma(a, e0[u], c0[c]);
-                        c1[c] = fma(a, e1[u], c1[c]);
-                    }
-                add_row(row, c0, c1);
+                const T a = xl[aok ? NL::at(c, arow, ai) : 0];
+                c0[c] = mfma4(a, b0[ks], c0[c]);
+                c1[c] = mfma4(a, b1[ks], c1[c]);
             }
         }
+        if (whole || row < S::ROWS) {
+#pragma unroll
+            for (int u = 0; u < C::KR; ++u)
+#pragma unroll
+                for (int c = 0; c < D; ++c) {
+                    const T a = xl[NL::at(c, row, 4 * C::KM + u)];
+                    c0[c] = fma(a, e0[u], c0[c]);
+                    c1[c] = fma(a, e1[u], c1[c]);
+                }
+            take(row, c0, c1);
+        }
+    };
+    if constexpr (QT > 0 && F::ON) {
+#pragma unroll 1
+        for (int k = 0; k < N; ++k) {
+            const T tv = tt[(0 * N + k) * 16 + slot], td = tt[(1 * N + k) * 16 + slot];
+#pragma unroll
+            for (int js = 0; js < F::NJ; ++js)
+                quad(N * k + 4 * js, [&](int, const T (&c0)[D], const T (&c1)[D])
+                                         __attribute__((always_inline)) {
+#pragma unroll
+                    for (int c = 0; c < D; ++c) {
+                        Zv[js][c] = fma(c0[c], tv, Zv[js][c]);
+                        Zd[js][c] = fma(c1[c], tv, Zd[js][c]);
+                        Zt[js][c] = fma(c0[c], td, Zt[js][c]);
+                    }
+                });
+        }
+    } else if constexpr (QT > 0) {
+#pragma unroll 1
+        for (int t = 0; t < QT; ++t) quad(16 * FT + 4 * t, add_row);
     }
     if constexpr (F::ON) {
 #pragma unroll
@@ -651,15 +673,17 @@ __device__ __forceinline__ void sweep1(const T *xl, T *tab, const T *qb, int cg,
 
 // Sweep 2: S_ab = sum_c dx_c d2x_c/dr_a dr_b for 16 columns, whose points q
 // and residuals dx are in qb ([R + D][16]); the four lanes of a column all
-// receive its totals.
-template <typename T, int D, int R, int N>
+// receive its totals.  NB as in sweep 1 (one element: 16-row tiles).
+template <typename T, int D, int R, int N, int NB = 1>
 __device__ __forceinline__ void sweep2(const T *xl, T *tab, const T *qb, int lane,
                                        T (&Sout)[kSym<R>])
 {
     typedef Shape<D, R, N> S;
     typedef Factor<R, N> F;
     typedef typename V4<T>::type v4;
+    typedef NodeLds<T, D, R, N> NL;
     const int slot = lane & 15, g = lane >> 4;
+    if (NB > 1) xl += slot / (16 / NB) * NL::SIZE;
     wave_lds_sync();   // qb is written
     T q[R], dx[D];
 #pragma unroll
@@ -696,63 +720,105 @@ __device__ __forceinline__ void sweep2(const T *xl, T *tab, const T *qb, int lan
     for (int js = 0; js < F::NJ; ++js)
 #pragma unroll
         for (int a = 0; a < 6; ++a) Z[js][a] = T(0);
-    auto tile = [&](int m) __attribute__((always_inline)) {
-        // the slot's residual enters the B operand, so one accumulator per
-        // basis kind collects sum_c dx_c C_c[row][slot] over the coordinates
-        v4 acc0 = v4{0, 0, 0, 0}, acc1 = v4{0, 0, 0, 0}, acc2 = v4{0, 0, 0, 0};
-        const int arow = a_row<T>(m, slot);
-#pragma unroll
-        for (int ks = 0; ks < S::KS; ++ks) {
-            const int ai = 4 * ks + g;
-            const bool aok = ((N % 4 == 0) && (S::ROWS % 16 == 0)) || (arow < S::ROWS && ai < N);
-#pragma unroll
-            for (int c = 0; c < D; ++c) {
-                const T a = xl[aok ? NodeLds<T, D, R, N>::at(c, arow, ai) : 0];
-                acc0 = mfma16(a, dx[c] * b0[ks], acc0);
-                acc1 = mfma16(a, dx[c] * b1[ks], acc1);
-                acc2 = mfma16(a, dx[c] * b2[ks], acc2);
-            }
-        }
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-            const int row = out_row(m, g, qq);
-            if (S::ROWS % 16 != 0 && row >= S::ROWS) continue;
-            const T C0 = acc0[qq], C1 = acc1[qq], C2 = acc2[qq];
-            if constexpr (F::ON) {
-                const int k = (16 * m + 4 * qq) / N, js = qq % F::NJ;
-                const T tv = tt[(0 * N + k) * 16 + slot], td = tt[(1 * N + k) * 16 + slot];
-                const T tdd = tt[(2 * N + k) * 16 + slot];
-                Z[js][0] = fma(C2, tv, Z[js][0]);
-                Z[js][1] = fma(C0, tv, Z[js][1]);
-                Z[js][2] = fma(C0, tdd, Z[js][2]);
-                Z[js][3] = fma(C1, tv, Z[js][3]);
-                Z[js][4] = fma(C1, td, Z[js][4]);
-                Z[js][5] = fma(C0, td, Z[js][5]);
-            } else if constexpr (R == 3) {
-                const int j = row % N, k = row / N;
-                const T sv = tab[(0 * N + j) * 16 + slot], sd = tab[(1 * N + j) * 16 + slot];
-                const T sdd = tab[(2 * N + j) * 16 + slot];
-                const T tv = tt[(0 * N + k) * 16 + slot], td = tt[(1 * N + k) * 16 + slot];
-                const T tdd = tt[(2 * N + k) * 16 + slot];
-                Sa[0] = fma(C2, sv * tv, Sa[0]);    // rr
-                Sa[1] = fma(C0, sdd * tv, Sa[1]);   // ss
-                Sa[2] = fma(C0, sv * tdd, Sa[2]);   // tt
-                Sa[3] = fma(C1, sd * tv, Sa[3]);    // rs
-                Sa[4] = fma(C1, sv * td, Sa[4]);    // rt
-                Sa[5] = fma(C0, sd * td, Sa[5]);    // st
-            } else {
-                const int j = row;
-                const T sv = tab[(0 * N + j) * 16 + slot], sd = tab[(1 * N + j) * 16 + slot];
-                const T sdd = tab[(2 * N + j) * 16 + slot];
-                Sa[0] = fma(C2, sv, Sa[0]);         // rr
-                Sa[1] = fma(C0, sdd, Sa[1]);        // ss
-                Sa[2] = fma(C1, sd, Sa[2]);         // rs
-            }
+    // a row's C0, C1, C2 = sum_c dx_c C_c[row][column] per basis kind,
+    // weighted into the sums; js: the lane's j (factored), k likewise
+    auto add_row = [&](int row, int k, auto jsc, T C0, T C1, T C2) __attribute__((always_inline)) {
+        if constexpr (F::ON) {
+            constexpr int js = decltype(jsc)::value;
+            const T tv = tt[(0 * N + k) * 16 + slot], td = tt[(1 * N + k) * 16 + slot];
+            const T tdd = tt[(2 * N + k) * 16 + slot];
+            Z[js][0] = fma(C2, tv, Z[js][0]);
+            Z[js][1] = fma(C0, tv, Z[js][1]);
+            Z[js][2] = fma(C0, tdd, Z[js][2]);
+            Z[js][3] = fma(C1, tv, Z[js][3]);
+            Z[js][4] = fma(C1, td, Z[js][4]);
+            Z[js][5] = fma(C0, td, Z[js][5]);
+        } else if constexpr (R == 3) {
+            const int j = row % N, kk = row / N;
+            const T sv = tab[(0 * N + j) * 16 + slot], sd = tab[(1 * N + j) * 16 + slot];
+            const T sdd = tab[(2 * N + j) * 16 + slot];
+            const T tv = tt[(0 * N + kk) * 16 + slot], td = tt[(1 * N + kk) * 16 + slot];
+            const T tdd = tt[(2 * N + kk) * 16 + slot];
+            Sa[0] = fma(C2, sv * tv, Sa[0]);                                 // rr
+            Sa[1] = fma(C0, sdd * tv, Sa[1]);                                // ss
+            Sa[2] = fma(C0, sv * tdd, Sa[2]);                                // tt
+            Sa[kSym<R> - 3] = fma(C1, sd * tv, Sa[kSym<R> - 3]);             // rs
+            Sa[kSym<R> - 2] = fma(C1, sv * td, Sa[kSym<R> - 2]);             // rt
+            Sa[kSym<R> - 1] = fma(C0, sd * td, Sa[kSym<R> - 1]);             // st
+        } else {
+            const int j = row;
+            const T sv = tab[(0 * N + j) * 16 + slot], sd = tab[(1 * N + j) * 16 + slot];
+            const T sdd = tab[(2 * N + j) * 16 + slot];
+            Sa[0] = fma(C2, sv, Sa[0]);         // rr
+            Sa[1] = fma(C0, sdd, Sa[1]);        // ss
+            Sa[2] = fma(C1, sd, Sa[2]);         // rs
         }
     };
-    tile(0);
+    if constexpr (NB == 1) {
+        auto tile = [&](int m) __attribute__((always_inline)) {
+            // the column's residual enters the B operand, so one accumulator
+            // per basis kind collects the sum over the coordinates
+            v4 acc0 = v4{0, 0, 0, 0}, acc1 = v4{0, 0, 0, 0}, acc2 = v4{0, 0, 0, 0};
+            const int arow = a_row<T>(m, slot);
+#pragma unroll
+            for (int ks = 0; ks < S::KS; ++ks) {
+                const int ai = 4 * ks + g;
+                const bool aok =
+                    ((N % 4 == 0) && (S::ROWS % 16 == 0)) || (arow < S::ROWS && ai < N);
+#pragma unroll
+                for (int c = 0; c < D; ++c) {
+                    const T a = xl[aok ? NL::at(c, arow, ai) : 0];
+                    acc0 = mfma16(a, dx[c] * b0[ks], acc0);
+                    acc1 = mfma16(a, dx[c] * b1[ks], acc1);
+                    acc2 = mfma16(a, dx[c] * b2[ks], acc2);
+                }
+            }
+            auto part = [&](auto qqc) __attribute__((always_inline)) {
+                constexpr int qq = decltype(qqc)::value;
+                const int row = out_row(m, g, qq);
+                if (S::ROWS % 16 == 0 || row < S::ROWS)
+                    add_row(row, (16 * m + 4 * qq) / N, std::integral_constant<int, qq % F::NJ>(),
+                            acc0[qq], acc1[qq], acc2[qq]);
+            };
+            part(std::integral_constant<int, 0>());
+            part(std::integral_constant<int, 1>());
+            part(std::integral_constant<int, 2>());
+            part(std::integral_constant<int, 3>());
+        };
+        tile(0);
 #pragma unroll 1
-    for (int m = 1; m < S::MT; ++m) tile(m);
+        for (int m = 1; m < S::MT; ++m) tile(m);
+    } else {
+        auto quad = [&](int base, int k, auto jsc) __attribute__((always_inline)) {
+            const bool whole = S::ROWS % 4 == 0 || base + 4 <= S::ROWS;
+            const int arow = base + (slot & 3), row = base + g;
+            T C0 = T(0), C1 = T(0), C2 = T(0);
+#pragma unroll
+            for (int ks = 0; ks < S::KS; ++ks) {
+                const int ai = 4 * ks + g;
+                const bool aok = (whole || arow < S::ROWS) && (N % 4 == 0 || ai < N);
+#pragma unroll
+                for (int c = 0; c < D; ++c) {
+                    const T a = xl[aok ? NL::at(c, arow, ai) : 0];
+                    C0 = mfma4(a, dx[c] * b0[ks], C0);
+                    C1 = mfma4(a, dx[c] * b1[ks], C1);
+                    C2 = mfma4(a, dx[c] * b2[ks], C2);
+                }
+            }
+            if (whole || row < S::ROWS) add_row(row, k, jsc, C0, C1, C2);
+        };
+        if constexpr (F::ON) {
+#pragma unroll 1
+            for (int k = 0; k < N; ++k) {
+                quad(N * k, k, std::integral_constant<int, 0>());
+                if constexpr (F::NJ > 1) quad(N * k + 4, k, std::integral_constant<int, 1>());
+            }
+        } else {
+#pragma unroll 1
+            for (int t = 0; t < (S::ROWS + 3) / 4; ++t)
+                quad(4 * t, 0, std::integral_constant<int, 0>());
+        }
+    }
     if constexpr (F::ON) {
 #pragma unroll
         for (int js = 0; js < F::NJ; ++js) {
@@ -894,6 +960,7 @@ enum { S_FREE = 0, S_INIT = 1, S_STEP = 2, S_WAIT = 3 };
 // FP32 phase.  kResolve: the other candidates of unsettled points, second
 // derivatives in the wave.  kFace: the parked pairs, resumed from their
 // saved point, radius and pass count, second derivatives in the wave.
+// (kResolve and kFace: a few pairs per element, run_few.)
 // kPolish: the primary candidates in the FP64 phase of mixed mode (as
 // kPrimary, with the polish step and the double-batch refill).
 enum { kPrimary = 0, kResolve = 1, kFace = 2, kPolish = 3 };
@@ -934,6 +1001,38 @@ __device__ __forceinline__ void add_counters(const Counters &cn, unsigned long l
         atomicAdd(&stats[(blockIdx.x % kStatCopies) * kStats + lane], (unsigned long long)x);
 }
 
+// The map at GLL node `node` (packed index i + N j + N^2 k): r, the node's
+// reference point; X, the node itself; dx/dr_d = sum_m phi_m'(z_{a_d})
+// x[.. m ..], an N-term sum along direction d through the node, read from
+// the node block: no sweep.
+template <typename T, int D, int R, int N>
+__device__ __forceinline__ void node_map(const T *xl, int node, T (&r)[R], T (&X)[D], T (&G)[D][R])
+{
+    typedef NodeLds<T, D, R, N> NL;
+    const int a0 = node % N, a1 = (node / N) % N, a2 = R == 3 ? node / (N * N) : 0;
+    const int row = R == 3 ? a1 + N * a2 : a1;
+#pragma unroll
+    for (int c = 0; c < D; ++c) X[c] = xl[NL::at(c, row, a0)];
+#pragma unroll
+    for (int d = 0; d < R; ++d) {
+        const int ad = d == 0 ? a0 : d == 1 ? a1 : a2;
+        r[d] = kNodes<T, N>.v[ad];
+        T s[D];
+#pragma unroll
+        for (int c = 0; c < D; ++c) s[c] = T(0);
+#pragma unroll
+        for (int m = 0; m < N; ++m) {
+            const T w = kDiff<T, N>.v[ad][m];
+            const int ii = d == 0 ? m : a0, jj = d == 1 ? m : a1, kk = d == 2 ? m : a2;
+            const int at = NL::at(0, R == 3 ? jj + N * kk : jj, ii);
+#pragma unroll
+            for (int c = 0; c < D; ++c) s[c] = fma(w, xl[at + c * NL::RP], s[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < D; ++c) G[c][d] = s[c];
+    }
+}
+
 // How a pair's start is given: the packed index of a GLL node per list
 // position (io.node; the nearest node), or a point r (io.start per list
 // position, or io.r per item).
@@ -943,36 +1042,25 @@ enum { kStartNode = 0, kStartPoint = 1, kStartEither = 2 };
 // [q0, q1) in io.list), in precision T, one pair per lane.  FINAL: write
 // code/elem/dist/r (FP64 phase); otherwise write r only (FP32 phase of mixed
 // mode).  Each trip refills free lanes, plans the trial points of the
-// stepping ones, and evaluates the map (sweep 1) where that is due; waiting
-// lanes get their second derivatives (sweep 2) before the trip's plan.
-// stage(): stages the element's nodes in LDS (a no-op where the caller
-// staged them: kResolve, which found its starts from them, and kFace).
-// given_node: kResolve, the start node of the pair at list position
-// q0 + lane.  Returns the number of pairs parked.
+// stepping ones, and evaluates the map (sweep 1) where that is due; pairs
+// that need second derivatives leave the wave.  stage(): stages the
+// element's nodes in LDS.  Returns the number of pairs parked.
 template <typename T, int D, int R, int N, bool FINAL, int KIND, typename Stage>
 __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, int q1,
                                            const T *xl, T *tab, T *qb, int lane, int max_iter,
-                                           T tol, const double *shift, int given_node,
-                                           Reserve &reserve, Counters &cn, Stage &&stage)
+                                           T tol, const double *shift, Reserve &reserve,
+                                           Counters &cn, Stage &&stage)
 {
     typedef unsigned long long u64;
     constexpr int K = D * (R + 1);
-    constexpr int START = KIND == kPolish || KIND == kFace ? kStartPoint
-                          : FINAL                          ? kStartNode
-                                                           : kStartEither;
-    // the waves of the primary pass hand pairs that need second derivatives
-    // on (to the face kernel; FP32: to the FP64 phase)
-    constexpr bool kHandOn = KIND == kPrimary || KIND == kPolish;
+    constexpr int START = KIND == kPolish ? kStartPoint : FINAL ? kStartNode : kStartEither;
     const NewtonIO &io = a.io;
     int state = S_FREE, item = 0, pass = 0, pos = 0, node = -1;
     bool fresh = false;   // evaluated at its start node this trip, not planned yet
-    T xs[D], r[R], q[R], dx[D], Hs[kSym<R>], alpha = T(1), pred = T(0), xnorm = T(0);
+    T xs[D], r[R], q[R], alpha = T(1), pred = T(0), xnorm = T(0);
     Obj<T, D, R> cur;
 #pragma unroll
-    for (int c = 0; c < D; ++c) {
-        xs[c] = T(0);
-        dx[c] = T(0);
-    }
+    for (int c = 0; c < D; ++c) xs[c] = T(0);
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         r[k] = T(0);
@@ -980,25 +1068,17 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
         cur.g[k] = T(0);
     }
 #pragma unroll
-    for (int k = 0; k < kSym<R>; ++k) {
-        Hs[k] = T(0);
-        cur.Hgn[k] = T(0);
-    }
+    for (int k = 0; k < kSym<R>; ++k) cur.Hgn[k] = T(0);
     cur.f = T(0);
-    bool hb_ok = false;
     // Staged pairs: lane l holds the pair at list position cstart + l of the
     // batch [cstart, cend).  Batches of 64 follow each other in list order;
-    // in the primary and polish passes, whose queues span several, the next
-    // batch's data are loaded while the current one is handed out, and the
-    // list entries of the one after are loaded with them, so that a batch's
-    // gathers do not wait for its list.  (kFace: the list holds park
-    // indices, and the point and the saved iterate come from the park
-    // record.)
+    // the next batch's data are loaded while the current one is handed out,
+    // and the list entries of the one after are loaded with them, so that a
+    // batch's gathers do not wait for its list.
     struct Batch {
         int it, node;
         double x[D], s[START == kStartNode ? 1 : R];
     };
-    constexpr bool kAhead = kHandOn;
     int head = q0, cstart = q0, cend = min(q1, q0 + kWave);
     auto load_item = [&](int b0) __attribute__((always_inline)) {
         const int idx = b0 + lane;
@@ -1009,24 +1089,16 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
         b.it = it;
         b.node = -1;
         if (idx < q1) {
-            int p;
-            if constexpr (KIND == kFace) p = io.park_meta[it].x;   // (it: its list position)
-            else p = io.slot_pt ? io.slot_pt[it] : it;
-            if constexpr (KIND == kResolve) {
-                b.node = given_node;
-            } else if constexpr (START != kStartPoint) {
+            if constexpr (START != kStartPoint) {
                 if (START == kStartNode || io.node) b.node = io.node[idx];
             }
+            // (the items of the primary pass are the points)
 #pragma unroll
-            for (int c = 0; c < D; ++c) b.x[c] = point_coord<D>(a, p, c);
+            for (int c = 0; c < D; ++c) b.x[c] = point_coord<D>(a, it, c);
             if constexpr (START != kStartNode) {
                 if (START == kStartPoint || !io.node) {
-                    const double *src = KIND == kFace ? io.park_r + it
-                                        : io.start    ? io.start + idx
-                                                      : io.r + it;
-                    const size_t st = KIND == kFace ? (size_t)io.park_cap
-                                      : io.start    ? (size_t)io.start_stride
-                                                    : (size_t)io.ostride;
+                    const double *src = io.start ? io.start + idx : io.r + it;
+                    const size_t st = io.start ? (size_t)io.start_stride : (size_t)io.ostride;
 #pragma unroll
                     for (int k = 0; k < R; ++k) b.s[k] = src[k * st];
                 }
@@ -1039,11 +1111,9 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
     // the first batch is loaded before the nodes are staged, so that the two
     // wait together
     load_batch(q0, load_item(q0), cb);
-    if constexpr (kAhead) {
-        if (cend < q1) {
-            load_batch(cend, load_item(cend), nb);
-            it2 = load_item(cend + kWave);
-        }
+    if (cend < q1) {
+        load_batch(cend, load_item(cend), nb);
+        it2 = load_item(cend + kWave);
     }
     stage();
     // Free lanes take the next pairs of the queue (wave-uniform control).
@@ -1052,7 +1122,7 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
         for (;;) {
             const u64 freem = __ballot(state == S_FREE);
             if (!freem || head >= q1) return;
-            if (kAhead && head >= cend) {
+            if (head >= cend) {
                 cb = nb;
                 cstart = cend;
                 cend = min(q1, cend + kWave);
@@ -1084,45 +1154,17 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
                     xn = fma(x[c], x[c], xn);
                 }
                 xnorm = sqrt_scale(xn);
-                if (START != kStartPoint && nd >= 0) {
-                    const int ix[3] = {nd % N, (nd / N) % N, nd / (N * N)};
+                // (a start node's r is set where it is evaluated)
+                if (START != kStartNode) {
 #pragma unroll
-                    for (int k = 0; k < R; ++k) r[k] = kNodes<T, N>.v[ix[k]];
-                } else {
-#pragma unroll
-                    for (int k = 0; k < R; ++k) r[k] = s[k];
+                    for (int k = 0; k < R; ++k) r[k] = q[k] = s[k];
                 }
-#pragma unroll
-                for (int k = 0; k < R; ++k) q[k] = r[k];
                 state = S_INIT;
                 pass = 0;
                 alpha = T(1);
-                hb_ok = false;
-                if constexpr (KIND == kFace) {
-                    // resumed where it was parked: same point, radius and
-                    // pass count (the pair was counted by the primary pass)
-                    const int4 mt = io.park_meta[it];
-                    pass = mt.w & ~kParkNoState;
-                    alpha = T(io.park_r[(size_t)R * io.park_cap + it]);
-                    if (!(mt.w & kParkNoState)) {
-                        // with the state the evaluation at r left: the
-                        // pair waits for its second derivatives at once
-                        const double *ps = io.park_state + (size_t)mt.y * kParkState;
-                        cur.f = T(ps[0]);
-#pragma unroll
-                        for (int j = 0; j < R; ++j) cur.g[j] = T(ps[1 + j]);
-#pragma unroll
-                        for (int j = 0; j < kSym<R>; ++j) cur.Hgn[j] = T(ps[1 + R + j]);
-#pragma unroll
-                        for (int c = 0; c < D; ++c) dx[c] = T(ps[1 + R + kSym<R> + c]);
-                        state = S_WAIT;
-                    }
-                    item = mt.x;
-                    pos = it;
-                }
             }
             const int taken = min(__popcll(freem), cend - head);
-            if (FINAL && KIND != kFace) cn.pairs += taken;
+            if (FINAL) cn.pairs += taken;
             head += taken;
         }
     };
@@ -1157,43 +1199,20 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
         }
         state = S_FREE;
     };
-    // Lanes whose new pair starts at a GLL node: the map there is the node
-    // itself and dx/dr_d = sum_m phi_m'(z_{a_d}) x[.. m ..] (an N-term sum
-    // along direction d through the node), read from the node block: no
+    // Lanes whose new pair starts at a GLL node: evaluated there without a
     // sweep.  They go to S_STEP with the objective at the start, as an
     // evaluation by sweep 1 would leave them.
     auto node_init = [&]() __attribute__((always_inline)) {
         fresh = false;
         if constexpr (START != kStartPoint) {
-            typedef NodeLds<T, D, R, N> NL;
             const bool mine = state == S_INIT && node >= 0;
             const u64 minem = __ballot(mine);
             if (!minem) return;
             if (mine) {
-                const int a0 = node % N, a1 = (node / N) % N, a2 = R == 3 ? node / (N * N) : 0;
                 T X[D], Gm[D][R];
-                const int row = R == 3 ? a1 + N * a2 : a1;
-#pragma unroll
-                for (int c = 0; c < D; ++c) X[c] = xl[NL::at(c, row, a0)];
-#pragma unroll
-                for (int d = 0; d < R; ++d) {
-                    const int ad = d == 0 ? a0 : d == 1 ? a1 : a2;
-                    T s[D];
-#pragma unroll
-                    for (int c = 0; c < D; ++c) s[c] = T(0);
-#pragma unroll
-                    for (int m = 0; m < N; ++m) {
-                        const T w = kDiff<T, N>.v[ad][m];
-                        const int ii = d == 0 ? m : a0, jj = d == 1 ? m : a1, kk = d == 2 ? m : a2;
-                        const int at = NL::at(0, R == 3 ? jj + N * kk : jj, ii);
-#pragma unroll
-                        for (int c = 0; c < D; ++c) s[c] = fma(w, xl[at + c * NL::RP], s[c]);
-                    }
-#pragma unroll
-                    for (int c = 0; c < D; ++c) Gm[c][d] = s[c];
-                }
+                node_map<T, D, R, N>(xl, node, r, X, Gm);
+                T dx[D];
                 objective<T, D, R>(xs, X, Gm, cur, dx);
-                hb_ok = false;
                 state = S_STEP;
                 fresh = true;
             }
@@ -1212,16 +1231,8 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
     auto plan = [&](bool only_fresh) __attribute__((always_inline)) -> u64 {
         bool ended = false;
         if (state == S_STEP && (!only_fresh || fresh)) {
-            const bool beta = (pass > 0) && on_face(r);
-            if (!kHandOn && beta && !hb_ok) {
-                // a face pass needs second derivatives at r: dx at r is
-                // current, so wait for sweep 2
-                state = S_WAIT;
-            } else {
-                T H[kSym<R>];
-#pragma unroll
-                for (int k = 0; k < kSym<R>; ++k)
-                    H[k] = !kHandOn && beta ? cur.Hgn[k] - Hs[k] : cur.Hgn[k];
+            // (beta = 0: a pair on a face after its first pass has left)
+            {
                 // held: at a bound of the box with the gradient pointing
                 // out of it (r = +-1 exactly, so r g has the sign test)
                 bool held[R];
@@ -1229,12 +1240,7 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
                 for (int k = 0; k < R; ++k)
                     held[k] = (fabs(r[k]) == T(1)) & (r[k] * cur.g[k] > T(0));
                 T x[R];
-                bool ok = solve_free<T, R>(H, cur.g, held, x);
-                if (!kHandOn && !ok && beta) {
-#pragma unroll
-                    for (int k = 0; k < kSym<R>; ++k) H[k] = cur.Hgn[k];
-                    ok = solve_free<T, R>(H, cur.g, held, x);
-                }
+                const bool ok = solve_free<T, R>(cur.Hgn, cur.g, held, x);
                 T dr[R], dmax = T(0);
 #pragma unroll
                 for (int k = 0; k < R; ++k) {
@@ -1251,7 +1257,7 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
                     gd = fma(cur.g[k], dr[k], gd);
                     T w = T(0);   // (H dr)_k
 #pragma unroll
-                    for (int b = 0; b < R; ++b) w = fma(H[sym<R>(k, b)], dr[b], w);
+                    for (int b = 0; b < R; ++b) w = fma(cur.Hgn[sym<R>(k, b)], dr[b], w);
                     dHd = fma(dr[k], w, dHd);
                 }
                 pred = T(2) * gd - dHd;
@@ -1281,36 +1287,6 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
         else cn.passes32 += __popcll(em);
         return em;
     };
-    // Second derivatives of the waiting lanes, 16 at a time.
-    auto second = [&](u64 waitm) __attribute__((always_inline)) {
-        const int rank = __popcll(waitm & ((1ull << lane) - 1));
-        const int nw = __popcll(waitm);
-#pragma unroll 1
-        for (int w0 = 0; w0 < nw; w0 += 16) {
-            const bool mine = state == S_WAIT && rank >= w0 && rank < w0 + 16;
-            wave_lds_sync();   // earlier reads of qb come first
-            if (mine) {
-#pragma unroll
-                for (int k = 0; k < R; ++k) qb[k * 16 + rank - w0] = r[k];
-#pragma unroll
-                for (int c = 0; c < D; ++c) qb[(R + c) * 16 + rank - w0] = dx[c];
-            }
-            T Sn[kSym<R>];
-            sweep2<T, D, R, N>(xl, tab, qb, lane, Sn);
-#pragma unroll
-            for (int k = 0; k < kSym<R>; ++k) {
-                const T v = __shfl(Sn[k], (rank - w0) & 15);
-                if (mine) Hs[k] = v;
-            }
-            if (mine) {
-                hb_ok = true;
-                state = S_STEP;
-            }
-            cn.sweeps_h2++;
-        }
-        cn.evals_h2 += nw;
-        cn.evals_h2_exec += nw;
-    };
     // Sweep 1 at q for the lanes of evalm: their X and G in z.
     auto evaluate = [&](u64 evalm, T (&z)[K]) __attribute__((always_inline)) {
         const int ncg = (__popcll(evalm) + 15) >> 4;
@@ -1319,26 +1295,6 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
         if ((evalm >> lane) & 1) {
 #pragma unroll
             for (int k = 0; k < R; ++k) qb[k * 64 + rank] = q[k];
-        }
-        if constexpr (!kHandOn) {
-            // (kFace, kResolve: mostly a single group, and no registers left
-            // for the other groups' sums: a group's totals go to all four
-            // lanes of a column, and to the lanes from there)
-            T y[K];
-#pragma unroll 1
-            for (int cg = 0; cg < ncg; ++cg) {
-                sweep1<T, D, R, N>(xl, tab, qb, cg, lane, y);
-                slot_sum_all(y);
-                const bool mine = (rank >> 4) == cg;
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const T v = __shfl(y[k], rank & 15);
-                    if (mine) z[k] = v;
-                }
-            }
-            if (FINAL) cn.sweeps += ncg;
-            else cn.sweeps32 += ncg;
-            return;
         }
         T x[K], y[K];
 #pragma unroll 1
@@ -1378,10 +1334,6 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
         refill();
         node_init();
         if (!__ballot(state != S_FREE)) break;
-        if constexpr (!kHandOn) {
-            const u64 waitm = __ballot(state == S_WAIT);
-            if (waitm) second(waitm);
-        }
         // lanes whose pair ends take new pairs at once, and get their first
         // trial point in the same trip, when that many of them are free
         const u64 em = plan(false);
@@ -1404,9 +1356,7 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
         Obj<T, D, R> nw;
         objective<T, D, R>(xs, X, Gm, nw, dxn);
         const u64 initm = __ballot(state == S_INIT), stepm = __ballot(state == S_STEP);
-        // a resumed pair re-evaluates the point it was parked at (the
-        // same values as before): not a new evaluation of the iteration
-        const int ne = __popcll(stepm) + (KIND != kFace ? __popcll(initm) : 0);
+        const int ne = __popcll(stepm) + __popcll(initm);
         if (FINAL) {
             cn.evals += ne;
             cn.passes += __popcll(stepm);
@@ -1417,9 +1367,6 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
         bool park = false, at_r = true;
         if (state == S_INIT) {
             cur = nw;
-#pragma unroll
-            for (int c = 0; c < D; ++c) dx[c] = dxn[c];
-            hb_ok = false;
             state = S_STEP;
         } else if (state == S_STEP) {
             ++pass;
@@ -1443,23 +1390,16 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
 #pragma unroll
                 for (int k = 0; k < R; ++k) r[k] = q[k];
                 cur = nw;
-#pragma unroll
-                for (int c = 0; c < D; ++c) dx[c] = dxn[c];
-                hb_ok = false;
             }
             if (pass >= max_iter) {
                 finish(false);
             } else if (on_face(r)) {
                 // the next pass takes second derivatives (beta = 1)
-                if (kHandOn) {
-                    park = true;
-                    at_r = accept;
-                } else if (accept) {
-                    state = S_WAIT;
-                }
+                park = true;
+                at_r = accept;
             }
         }
-        if constexpr (kHandOn) {
+        {
             // pairs whose next pass needs second derivatives leave the wave:
             // FP64 parks them (the face kernel resumes them, many to a wave),
             // FP32 ends its phase there (the FP64 phase takes over).  A
@@ -1515,6 +1455,288 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
         }
     }
     return parked;
+}
+
+// The iteration for pairs of few-pair elements: the pairs parked on a face
+// (kFace) and the other candidates of unsettled points (kResolve), some
+// three to five per element.  NB elements to a wave (their node blocks one
+// after the other at xl), lanes b L .. b L + L - 1 (L = 64 / NB) for the pairs
+// of element b, a pair per lane and no refill; a column group takes 16 / NB
+// columns of each element, so that the sweeps and the updates of NB sparse
+// elements cost what those of one do.  Second derivatives in the wave.
+// has: the lane has a pair, of element e; item: where its results go; pos:
+// kFace, its list position (of its park record and of io.rs); node: kResolve,
+// its start node; xs: its point.
+template <int D, int R, int N, int KIND, int NB>
+__device__ __forceinline__ void run_few(const NewtonArgs &a, const double *xl, double *tab,
+                                        double *qb, int lane, bool has, int e, int item, int pos,
+                                        int node, const double (&xs)[D], Counters &cn)
+{
+    typedef unsigned long long u64;
+    typedef NodeLds<double, D, R, N> NL;
+    constexpr int K = D * (R + 1), L = kWave / NB, CB = 16 / NB;
+    const NewtonIO &io = a.io;
+    const int b = lane / L;
+    const int max_iter = a.max_iter;
+    int state = has ? S_INIT : S_FREE, pass = 0;
+    double r[R], q[R], dx[D], Hs[kSym<R>], alpha = 1.0, pred = 0.0;
+    Obj<double, D, R> cur;
+    bool hb_ok = false;
+    cur.f = 0.0;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        r[k] = 0.0;
+        q[k] = 0.0;
+        cur.g[k] = 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < kSym<R>; ++k) {
+        Hs[k] = 0.0;
+        cur.Hgn[k] = 0.0;
+    }
+#pragma unroll
+    for (int c = 0; c < D; ++c) dx[c] = 0.0;
+    double xn = 0.0;
+#pragma unroll
+    for (int c = 0; c < D; ++c) xn = fma(xs[c], xs[c], xn);
+    const double xnorm = sqrt_scale(xn);
+    if constexpr (KIND == kFace) {
+        if (has) {
+            // resumed where it was parked: same point, radius and pass count
+            // (the pair was counted by the primary pass)
+            const int4 mt = io.park_meta[pos];
+            pass = mt.w & ~kParkNoState;
+            alpha = io.park_r[(size_t)R * io.park_cap + pos];
+#pragma unroll
+            for (int k = 0; k < R; ++k) r[k] = io.park_r[(size_t)k * io.park_cap + pos];
+            if (!(mt.w & kParkNoState)) {
+                // with the state the evaluation at r left: the pair waits
+                // for its second derivatives at once
+                const double *ps = io.park_state + (size_t)mt.y * kParkState;
+                cur.f = ps[0];
+#pragma unroll
+                for (int j = 0; j < R; ++j) cur.g[j] = ps[1 + j];
+#pragma unroll
+                for (int j = 0; j < kSym<R>; ++j) cur.Hgn[j] = ps[1 + R + j];
+#pragma unroll
+                for (int c = 0; c < D; ++c) dx[c] = ps[1 + R + kSym<R> + c];
+                state = S_WAIT;
+            }
+        }
+    } else {
+        // the start is a node: evaluated from the node block
+        if (has) {
+            double X[D], Gm[D][R];
+            node_map<double, D, R, N>(xl + b * NL::SIZE, node, r, X, Gm);
+            objective<double, D, R>(xs, X, Gm, cur, dx);
+            state = S_STEP;
+        }
+        const int cnt = __popcll(__ballot(has));
+        cn.pairs += cnt;
+        cn.evals += cnt;
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) q[k] = r[k];
+    auto finish = [&](bool converged) __attribute__((always_inline)) {
+        bool inside = true;
+#pragma unroll
+        for (int k = 0; k < R; ++k) inside = inside && (fabs(r[k]) < 1.0);
+        if (R < D) inside = inside && (cur.f < a.eps_d);
+        if (io.conv) io.conv[item] = converged ? 1 : 0;
+        io.code[item] = inside ? FPTS_INTERIOR : FPTS_BORDER;
+        if (io.elem) io.elem[item] = e;
+        io.dist[item] = sqrt(cur.f);
+        if (KIND == kFace && io.rs) {
+            double mg = 1.0;
+#pragma unroll
+            for (int k = 0; k < R; ++k) mg = fmin(mg, 1.0 - fabs(r[k]));
+            const bool settles = inside && mg > kSettleGuard;
+#pragma unroll
+            for (int k = 0; k < R; ++k)
+                io.rs[(size_t)k * io.rs_stride + pos] = settles ? r[k] : __builtin_nan("");
+        }
+#pragma unroll
+        for (int k = 0; k < R; ++k) io.r[(size_t)k * io.ostride + item] = r[k];
+        state = S_FREE;
+    };
+    // A lane's place among the lanes of `mask` in its element, and the
+    // column groups they make: the element's columns of group cg are those
+    // of its lanes with places CB cg .. CB cg + CB - 1.
+    auto place = [&](u64 mask, int &ncg) __attribute__((always_inline)) {
+        constexpr u64 seg = L == 64 ? ~0ull : (1ull << (L & 63)) - 1;
+        int most = 0;
+#pragma unroll
+        for (int u = 0; u < NB; ++u) most = max(most, __popcll((mask >> (u * L)) & seg));
+        ncg = (most + CB - 1) / CB;
+        return __popcll((mask >> (b * L)) & seg & ((1ull << (lane & (L - 1))) - 1));
+    };
+    const int guard = 2 * max_iter + 8;
+    for (int trip = 0; trip < guard; ++trip) {
+        if (!__ballot(state != S_FREE)) break;
+        const u64 waitm = __ballot(state == S_WAIT);
+        if (waitm) {
+            int ncg;
+            const int rank = place(waitm, ncg);
+#pragma unroll 1
+            for (int cg = 0; cg < ncg; ++cg) {
+                const bool mine = state == S_WAIT && rank / CB == cg;
+                const int col = b * CB + rank % CB;
+                wave_lds_sync();   // earlier reads of qb come first
+                if (mine) {
+#pragma unroll
+                    for (int k = 0; k < R; ++k) qb[k * 16 + col] = r[k];
+#pragma unroll
+                    for (int c = 0; c < D; ++c) qb[(R + c) * 16 + col] = dx[c];
+                }
+                double Sn[kSym<R>];
+                sweep2<double, D, R, N, NB>(xl, tab, qb, lane, Sn);
+#pragma unroll
+                for (int k = 0; k < kSym<R>; ++k) {
+                    const double v = __shfl(Sn[k], col);
+                    if (mine) Hs[k] = v;
+                }
+                if (mine) {
+                    hb_ok = true;
+                    state = S_STEP;
+                }
+            }
+            cn.sweeps_h2 += ncg;
+            cn.evals_h2 += __popcll(waitm);
+            cn.evals_h2_exec += __popcll(waitm);
+        }
+        // trial points: the Newton step of Section 3.2.1 on the free
+        // coordinates, clipped to the trust region and the box; a step below
+        // the tolerance ends the iteration
+        bool ended = false;
+        if (state == S_STEP) {
+            const bool beta = (pass > 0) && on_face(r);
+            if (beta && !hb_ok) {
+                state = S_WAIT;   // dx at r is current: wait for sweep 2
+            } else {
+                double H[kSym<R>];
+#pragma unroll
+                for (int k = 0; k < kSym<R>; ++k) H[k] = beta ? cur.Hgn[k] - Hs[k] : cur.Hgn[k];
+                // held: at a bound of the box with the gradient pointing
+                // out of it (r = +-1 exactly, so r g has the sign test)
+                bool held[R];
+#pragma unroll
+                for (int k = 0; k < R; ++k)
+                    held[k] = (fabs(r[k]) == 1.0) & (r[k] * cur.g[k] > 0.0);
+                double x[R];
+                bool ok = solve_free<double, R>(H, cur.g, held, x);
+                if (!ok && beta) {
+#pragma unroll
+                    for (int k = 0; k < kSym<R>; ++k) H[k] = cur.Hgn[k];
+                    ok = solve_free<double, R>(H, cur.g, held, x);
+                }
+                double dr[R], dmax = 0.0;
+#pragma unroll
+                for (int k = 0; k < R; ++k) {
+                    double d = ok ? x[k] : 0.0;
+                    d = fmin(fmax(d, -alpha), alpha);
+                    const double t = fmin(fmax(r[k] + d, -1.0), 1.0);
+                    q[k] = t;
+                    dr[k] = t - r[k];
+                    dmax = fmax(dmax, fabs(dr[k]));
+                }
+                double gd = 0.0, dHd = 0.0;
+#pragma unroll
+                for (int k = 0; k < R; ++k) {
+                    gd = fma(cur.g[k], dr[k], gd);
+                    double w = 0.0;   // (H dr)_k
+#pragma unroll
+                    for (int u = 0; u < R; ++u) w = fma(H[sym<R>(k, u)], dr[u], w);
+                    dHd = fma(dr[k], w, dHd);
+                }
+                pred = 2.0 * gd - dHd;
+                if (dmax < a.tol) {
+                    // converged: the step is taken without evaluating the
+                    // map at q; the squared residual there is the model's,
+                    // f - pred, whose error is third order in the step
+                    ended = true;
+                    ++pass;
+#pragma unroll
+                    for (int k = 0; k < R; ++k) r[k] = q[k];
+                    cur.f = fmax(cur.f - pred, 0.0);
+                    finish(true);
+                }
+            }
+        }
+        cn.passes += __popcll(__ballot(ended));
+        const u64 stepm = __ballot(state == S_STEP), initm = __ballot(state == S_INIT);
+        const u64 evalm = stepm | initm;
+        if (!evalm) continue;
+        int ncg;
+        const int rank = place(evalm, ncg);
+        const int col = b * CB + rank % CB;
+        wave_lds_sync();   // earlier reads of qb come first
+        if ((evalm >> lane) & 1) {
+#pragma unroll
+            for (int k = 0; k < R; ++k) qb[k * 64 + rank / CB * 16 + col] = q[k];
+        }
+        double z[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) z[k] = 0.0;
+#pragma unroll 1
+        for (int cg = 0; cg < ncg; ++cg) {
+            double y[K];
+            sweep1<double, D, R, N, NB>(xl, tab, qb, cg, lane, y);
+            slot_sum_all(y);   // a column's totals in its four lanes
+            const bool mine = rank / CB == cg;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const double v = __shfl(y[k], col);
+                if (mine) z[k] = v;
+            }
+        }
+        cn.sweeps += ncg;
+        // a resumed pair re-evaluates the point it was parked at (the same
+        // values as before): not a new evaluation of the iteration
+        cn.evals += __popcll(stepm) + (KIND != kFace ? __popcll(initm) : 0);
+        cn.passes += __popcll(stepm);
+        double X[D], Gm[D][R], dxn[D];
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            X[c] = z[c];
+#pragma unroll
+            for (int k = 0; k < R; ++k) Gm[c][k] = z[D + c * R + k];
+        }
+        Obj<double, D, R> nw;
+        objective<double, D, R>(xs, X, Gm, nw, dxn);
+        bool moved = false;
+        if (state == S_INIT) {
+            moved = true;
+            state = S_STEP;
+        } else if (state == S_STEP) {
+            ++pass;
+            // trust-region test (the step is at least the tolerance here)
+            const double decr = cur.f - nw.f;
+            const double sf = sqrt_scale(cur.f);
+            const double noise = 64.0 * eps_of<double>() * sf * (xnorm + sf);
+            if (pred > 0.0 && pred <= noise) {
+                moved = true;
+            } else if (pred > 0.0 && decr >= 0.9 * pred) {
+                moved = true;
+                alpha *= 2.0;
+            } else if (pred > 0.0 && decr >= 0.01 * pred) {
+                moved = true;
+            } else {
+                alpha *= 0.25;
+            }
+            if (moved) {
+#pragma unroll
+                for (int k = 0; k < R; ++k) r[k] = q[k];
+            }
+        }
+        if (moved) {
+            cur = nw;
+#pragma unroll
+            for (int c = 0; c < D; ++c) dx[c] = dxn[c];
+            hb_ok = false;
+        }
+        if (((stepm >> lane) & 1) && pass >= max_iter) finish(false);
+        else if (moved && pass > 0 && on_face(r)) state = S_WAIT;   // next pass: beta = 1
+    }
 }
 
 // Copies COUNT values of an element block from global memory to LDS (one
@@ -1885,30 +2107,29 @@ __device__ __forceinline__ void nearest_body(const NewtonArgs &a)
     }
 }
 
-// Nearest node of x among the element's nodes staged in LDS (FP64, NodeLds
-// layout): the squared distance summed over the coordinates in order, the
-// lowest node index among equal distances (Section 3.2.1 starts Newton
-// there).  Wave-cooperative: each lane scans every 64th node, then the
-// lanes are reduced; every lane returns the index.
-template <int D, int R, int N>
-__device__ __forceinline__ int nearest_staged(const double *xl, const double (&x)[D], int lane)
+// Nearest node of x among an element's nodes staged in LDS at xl (FP64,
+// NodeLds layout), by a segment of L lanes together (j: the lane's place in
+// it): the squared distance summed over the coordinates in order, the lowest
+// node index among equal distances (Section 3.2.1 starts Newton there).
+template <int D, int R, int N, int L>
+__device__ __forceinline__ int nearest_staged(const double *xl, const double (&x)[D], int j)
 {
     double bd = __builtin_huge_val();
     int bi = 0;
-    for (int j = lane; j < Shape<D, R, N>::NP; j += kWave) {
+    for (int n = j; n < Shape<D, R, N>::NP; n += L) {
         double d2 = 0.0;
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            const double t = x[d] - xl[NodeLds<double, D, R, N>::at(d, j / N, j % N)];
+            const double t = x[d] - xl[NodeLds<double, D, R, N>::at(d, n / N, n % N)];
             d2 = fma(t, t, d2);
         }
         if (d2 < bd) {
             bd = d2;
-            bi = j;
+            bi = n;
         }
     }
 #pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
+    for (int o = 1; o < L; o <<= 1) {
         const double od = __shfl_xor(bd, o);
         const int oi = __shfl_xor(bi, o);
         if (od < bd || (od == bd && oi < bi)) {
@@ -1930,14 +2151,7 @@ __device__ __forceinline__ int nearest_staged(const double *xl, const double (&x
 // XCD's counter (io.counter, kXcdCounter ints apart; the FP32 phase's after
 // the FP64 kernels').  (One counter for all: an atomic on one address takes
 // some 16 ns, 1.05 ms for the 64 thousand tasks of 4M points, N = 4.)
-// TASKS: the waves stride over the 64-pair tasks of io.task_elem instead.
-// The other candidates of unsettled points and the parked pairs of the face
-// kernel are a few pairs scattered over many elements.
-// kResolve finds the starts of its pairs itself, from the nodes it stages
-// anyway: a separate nearest-node pass would read every such element's
-// node data once more for about one pair each, and score that pair on
-// matrix tiles of 16.
-template <typename T, int D, int R, int N, bool TASKS, int KIND>
+template <typename T, int D, int R, int N, int KIND>
 __device__ __forceinline__ void newton_body(const NewtonArgs &a)
 {
     typedef Shape<D, R, N> S;
@@ -1950,14 +2164,12 @@ __device__ __forceinline__ void newton_body(const NewtonArgs &a)
     T *tab = xl + L::NODES;
     T *qb = tab + L::TAB;
     Counters cn;
-    const int *off = TASKS ? io.chunk_off : io.newt_off;
-    const int *elem = TASKS ? io.task_elem : io.newt_task;
+    const int *off = io.newt_off, *elem = io.newt_task;
     const int all = off[a.nel];
     // (the grid is a multiple of the XCD count)
     const int xcd = blockIdx.x % kXcd, waves = gridDim.x / kXcd;
     const int share = (all + kXcd - 1) / kXcd;
-    const int first = TASKS ? 0 : xcd * share;
-    const int total = TASKS ? all : min(all, first + share);
+    const int first = xcd * share, total = min(all, first + share);
     int *ctr = io.counter + ((FINAL ? 0 : kXcd) + xcd) * kXcdCounter;
     // the ticket of the wave's next task is taken one task ahead, so that
     // its atomic completes while the current one is processed (every ticket
@@ -1967,73 +2179,111 @@ __device__ __forceinline__ void newton_body(const NewtonArgs &a)
         if (lane == 0) v = atomicAdd(ctr, 1);
         return first + waves + v;
     };
-    int ticket = TASKS ? task_of_block() : first + (int)blockIdx.x / kXcd;
+    int ticket = first + (int)blockIdx.x / kXcd;
     int parked = 0;
     Reserve reserve;
     for (;;) {
         const int t = __builtin_amdgcn_readfirstlane(ticket);
         if (t >= total) break;
-        ticket = TASKS ? t + (int)gridDim.x : take();
+        ticket = take();
         const int e = __builtin_amdgcn_readfirstlane(elem[t]);
+        // part t - off[e] of the queue's nt even parts
+        const int nt = off[e + 1] - off[e];
         int q0 = io.elem_off[e], q1 = io.elem_off[e + 1];
-        if constexpr (TASKS) {
-            q0 += (t - off[e]) * kChunk;
-            q1 = min(q1, q0 + kChunk);
-        } else {
-            // part t - off[e] of the queue's nt even parts
-            const int nt = off[e + 1] - off[e], per = (q1 - q0 + nt - 1) / nt;
-            q0 += (t - off[e]) * per;
-            q1 = min(q1, q0 + per);
-        }
+        const int per = (q1 - q0 + nt - 1) / nt;
+        q0 += (t - off[e]) * per;
+        q1 = min(q1, q0 + per);
         __syncthreads();
+        // the nodes are staged after the first batch of pairs has been asked
+        // for
         if constexpr (FINAL) {
             const double *src = a.nodes + (size_t)e * D * S::NP;
-            if constexpr (KIND == kResolve) {
-                // lane l < q1 - q0 (at most kChunk = 64) loads pair q0 + l
-                // (slot id, point) before the nodes are staged
-                static_assert(kChunk <= kWave, "one lane per pair of a task");
-                double px[D];
-#pragma unroll
-                for (int d = 0; d < D; ++d) px[d] = 0.0;
-                if (lane < q1 - q0) {
-                    const int p = io.slot_pt[io.list[q0 + lane]];
-#pragma unroll
-                    for (int d = 0; d < D; ++d) px[d] = point_coord<D>(a, p, d);
-                }
-                stage_nodes<double, D, R, N>(xl, src, lane);
-                int node = 0;
-                for (int j = 0; j < q1 - q0; ++j) {
-                    double x[D];
-#pragma unroll
-                    for (int d = 0; d < D; ++d) x[d] = __shfl(px[d], j);
-                    const int bi = nearest_staged<D, R, N>(xl, x, lane);
-                    if (lane == j) node = bi;
-                }
-                run_element<double, D, R, N, true, KIND>(a, e, q0, q1, xl, tab, qb, lane,
-                                                         a.max_iter, a.tol, nullptr, node,
-                                                         reserve, cn, [] {});
-            } else {
-                // the nodes are staged after the first batch of pairs has
-                // been asked for
-                parked += run_element<double, D, R, N, true, KIND>(
-                    a, e, q0, q1, xl, tab, qb, lane, a.max_iter, a.tol, nullptr, 0, reserve, cn,
-                    [&] { stage_nodes<double, D, R, N>(xl, src, lane); });
-            }
+            parked += run_element<double, D, R, N, true, KIND>(
+                a, e, q0, q1, xl, tab, qb, lane, a.max_iter, a.tol, nullptr, reserve, cn,
+                [&] { stage_nodes<double, D, R, N>(xl, src, lane); });
         } else {
             const float *src = a.nodes32 + (size_t)e * D * S::NP;
             run_element<float, D, R, N, false, KIND>(
-                a, e, q0, q1, xl, tab, qb, lane, a.max_iter32, a.tol32, a.xc + (size_t)e * D, 0,
+                a, e, q0, q1, xl, tab, qb, lane, a.max_iter32, a.tol32, a.xc + (size_t)e * D,
                 reserve, cn, [&] { stage_nodes<float, D, R, N>(xl, src, lane); });
         }
     }
-    if (KIND == kPrimary || KIND == kPolish)
-        if (FINAL && lane == 0 && parked) atomicAdd(io.park_count, parked);
+    if (FINAL && lane == 0 && parked) atomicAdd(io.park_count, parked);
     add_counters(cn, io.stats, lane);
 }
 
-// The primary pass and the pass over the other candidates of unsettled
-// points run the same Newton code under two kernel names, so that a kernel
-// trace reports them apart (the latter finds its starts itself).
+// The face and resolve kernels: waves stride over the tasks of io.task_elem
+// (up to few_lanes pairs of one element each; io.chunk_off their offsets per
+// element), up to NB of them at a time, consecutive ones.  kResolve finds the
+// starts of its pairs itself, from the nodes it stages anyway: a separate
+// nearest-node pass would read every such element's node data once more for
+// a few pairs, and score them on matrix tiles of 16.
+template <int D, int R, int N, int KIND>
+__device__ __forceinline__ void few_body(const NewtonArgs &a)
+{
+    typedef Shape<D, R, N> S;
+    typedef NodeLds<double, D, R, N> NL;
+    constexpr int NB = few_elems(R, N), L = few_lanes(R, N);
+    extern __shared__ double lds_raw[];
+    double *xl = lds_raw;
+    double *tab = xl + NB * NL::SIZE;
+    double *qb = tab + Lds<double, D, R, N>::TAB;
+    const int lane = threadIdx.x, b = lane / L, j = lane % L;
+    const NewtonIO &io = a.io;
+    Counters cn;
+    const int total = io.chunk_off[a.nel];
+    // elements per trip: fewer than NB where the launch's waves are more than
+    // total / NB (a wave with one element is done sooner than one with NB)
+    const int nb = min(NB, (total + (int)gridDim.x - 1) / (int)gridDim.x);
+    for (int64_t t0 = (int64_t)task_of_block() * nb; t0 < total; t0 += (int64_t)gridDim.x * nb) {
+        const int t = (int)t0 + b;
+        const bool on = b < nb && t < total;
+        const int e = on ? io.task_elem[t] : -1;
+        int q = 0;
+        bool has = false;
+        if (on) {
+            q = io.elem_off[e] + (t - io.chunk_off[e]) * L + j;
+            has = q < io.elem_off[e + 1];
+        }
+        // kFace: the list holds the pairs' positions in the primary list
+        const int pos = has ? io.list[q] : 0;
+        int item = pos, p = 0;
+        if (has) {
+            if constexpr (KIND == kFace) item = p = io.park_meta[pos].x;
+            else p = io.slot_pt[item];
+        }
+        double xs[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) xs[d] = has ? point_coord<D>(a, p, d) : 0.0;
+        __syncthreads();   // the previous elements' reads come first
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int eu = __builtin_amdgcn_readlane(e, u * L);
+            if (eu >= 0)
+                stage_nodes<double, D, R, N>(xl + u * NL::SIZE, a.nodes + (size_t)eu * D * S::NP,
+                                             lane);
+        }
+        int node = 0;
+        if constexpr (KIND == kResolve) {
+            // every segment finds its pairs' nearest nodes one after the other
+            const unsigned long long hm = __ballot(has);
+            int most = 0;
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                most = max(most, __popcll(L == 64 ? hm : (hm >> (u * L)) & ((1ull << (L & 63)) - 1)));
+            for (int k = 0; k < most; ++k) {
+                double x[D];
+#pragma unroll
+                for (int d = 0; d < D; ++d) x[d] = __shfl(xs[d], b * L + k);
+                const int bi = nearest_staged<D, R, N, L>(xl + b * NL::SIZE, x, j);
+                if (j == k) node = bi;
+            }
+        }
+        run_few<D, R, N, KIND, NB>(a, xl, tab, qb, lane, has, e, item, pos, node, xs, cn);
+    }
+    add_counters(cn, io.stats, lane);
+}
+
 // (at least three waves per SIMD: the register budget then stays within the
 // 256 VGPRs, and the compiler gives the MFMA results VGPRs, not AGPRs that
 // the selection would first have to copy out)
@@ -2046,31 +2296,31 @@ k_nearest(NewtonArgs a)
 template <int D, int R, int N>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_newton(NewtonArgs a)
 {
-    newton_body<double, D, R, N, false, kPrimary>(a);
+    newton_body<double, D, R, N, kPrimary>(a);
 }
 template <int D, int R, int N>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 k_newton_polish(NewtonArgs a)
 {
-    newton_body<double, D, R, N, false, kPolish>(a);
+    newton_body<double, D, R, N, kPolish>(a);
 }
 template <int D, int R, int N>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 k_newton_resolve(NewtonArgs a)
 {
-    newton_body<double, D, R, N, true, kResolve>(a);
+    few_body<D, R, N, kResolve>(a);
 }
 template <int D, int R, int N>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 k_newton_face(NewtonArgs a)
 {
-    newton_body<double, D, R, N, true, kFace>(a);
+    few_body<D, R, N, kFace>(a);
 }
 template <int D, int R, int N>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
 k_newton32(NewtonArgs a)
 {
-    newton_body<float, D, R, N, false, kPrimary>(a);
+    newton_body<float, D, R, N, kPrimary>(a);
 }
 
 // Phase D for the points whose other candidates found no room in the slot
@@ -2109,7 +2359,6 @@ k_resolve_overflow(NewtonArgs a, HashView h)
     la.io.polish = 0;
     if (lane == 0) ov_item[b] = b;
     Counters cn;
-    Reserve none;
     for (int i = b; i < cnt; i += G) {
         const int p = io.list[i];
         const int prim = io.cand[p].y, c = io.cellpt[p];
@@ -2130,12 +2379,8 @@ k_resolve_overflow(NewtonArgs a, HashView h)
                 continue;
             __syncthreads();
             stage_nodes<double, D, R, N>(xl, a.nodes + (size_t)e * D * S::NP, lane);
-            const int bi = nearest_staged<D, R, N>(xl, x, lane);
-            // lane 0 wrote the queue entry and reads it back (same lane,
-            // program order)
-            run_element<double, D, R, N, true, kResolve>(la, e, b, b + 1, xl, tab, qb, lane,
-                                                        a.max_iter, a.tol, nullptr, bi, none, cn,
-                                                        [] {});
+            const int bi = nearest_staged<D, R, N, kWave>(xl, x, lane);
+            run_few<D, R, N, kResolve, 1>(la, xl, tab, qb, lane, lane == 0, e, b, 0, bi, x, cn);
             // lane 0, the pair's lane, wrote the result
             int cd = 0;
             double dd = 0.0, rr[R];
@@ -2182,7 +2427,7 @@ struct Kernels {
     KernelFn nearest = nullptr, newton32 = nullptr, newton = nullptr, warm = nullptr,
              face = nullptr;
     OverflowFn overflow = nullptr;
-    size_t lds_nearest = 0, lds_newton32 = 0, lds_newton = 0;
+    size_t lds_nearest = 0, lds_newton32 = 0, lds_newton = 0, lds_few = 0;
 };
 
 template <int D, int R, bool MIXED>
@@ -2203,6 +2448,8 @@ Kernels pick_kernels(int N, bool resolve)
         k.lds_nearest = NearLds<TN, D, R, NN>::bytes();                                     \
         k.lds_newton32 = Lds<float, D, R, NN>::bytes();                                     \
         k.lds_newton = Lds<double, D, R, NN>::bytes();                                      \
+        k.lds_few = k.lds_newton + sizeof(double) * (few_elems(R, NN) - 1) *                \
+                                       NodeLds<double, D, R, NN>::SIZE;                     \
         break;
     switch (N) {
         FPTS_CASE(2)
@@ -2271,13 +2518,14 @@ hipError_t launch_newton_kind(const fpts_mesh *m, bool mixed, int64_t n, const d
         // starts given as points (the FP32 phase's results, or the hinted
         // search of particle tracking) take the warm-start kernel
         const KernelFn kn = resolve || (io.node && !mixed) ? k.newton : k.warm;
-        hipLaunchKernelGGL(kn, dim3(m->cus * 8), dim3(64), k.lds_newton, s, a);
+        hipLaunchKernelGGL(kn, dim3(m->cus * 8), dim3(64), resolve ? k.lds_few : k.lds_newton, s,
+                           a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if (which & 4) {
         if (!k.face) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k.face, dim3(m->cus * 8), dim3(64), k.lds_newton, s, a);
+        hipLaunchKernelGGL(k.face, dim3(m->cus * 8), dim3(64), k.lds_few, s, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
