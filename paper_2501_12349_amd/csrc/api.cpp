@@ -164,9 +164,7 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     const int64_t cmax = n * (int64_t)std::max(m->max_cell - 1, 1);
     w.cap2 = std::max<int64_t>(1, m->R == 1 ? cmax : std::min<int64_t>(cmax, n));
     w.bin_shift = bin_shift(ncell);
-    w.bin_hist_n = w.bin_shift < 0 ? 0
-                                    : ((ncell + (1ll << w.bin_shift) - 1) >> w.bin_shift) *
-                                          bin_tiles(n);
+    w.bin_hist_n = w.bin_shift < 0 ? 0 : bin_hist_size(n, ncell, w.bin_shift);
     w.scan_blocks = scan_tmp_blocks(
         std::max<int64_t>(std::max<int64_t>(std::max<int64_t>(n, m->nel), ncell), w.bin_hist_n));
     const size_t I = sizeof(int);
@@ -334,7 +332,7 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
                                  d_dist, w.bin_shift, bh, s));
             chk(launch_unit_scan(UnitScan{bh, w.bin_hist_n, tmp, bh}, tb, s));
             chk(launch_bin_coarse(m, n, cellpt, w.bin_shift, bh, pairs, s));
-            chk(launch_bin_rank(n, npairs, w.bin_shift, pairs, cell_cnt, rank, s));
+            chk(launch_bin_rank(m, n, npairs, w.bin_shift, pairs, cell_cnt, rank, s));
             chk(launch_unit_scan(
                 UnitScan{cell_cnt, ncell, tmp, cell_poff, cell_choff, task_cell}, tb, s));
             chk(launch_bin_scatter(n, npairs, pairs, rank, cell_poff, pbin, m->cus, s));

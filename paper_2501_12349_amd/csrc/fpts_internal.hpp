@@ -427,15 +427,15 @@ hipError_t launch_cell_bin(const fpts_mesh *m, int pass, int64_t n, const double
 // cells; bin_shift returns -1 beyond): cells grouped into buckets of
 // 2^shift cells, at most kBinMaxBuckets of them.  tiles: as pass 0 of
 // launch_cell_bin, and each tile's bucket histogram into bh[bucket * ntile
-// + tile] (ntile = bin_tiles(n); bh is then scanned in place, its total at
-// bh[nb * ntile]); coarse: (cell, id) pairs sorted by bucket from the
+// + tile] (bh is then scanned in place, its total at bh[nb * ntile]); coarse: (cell, id) pairs sorted by bucket from the
 // scanned bh; rank: each pair's rank in its cell (cell_cnt zeroed before,
 // complete after), *total pairs; scatter: pbin[cell_poff[c] + rank[i]] =
 // id of pair i.
 constexpr int64_t kBinMaxCells = (int64_t)1 << 24;
 constexpr int kBinMaxBuckets = 4096;
 int bin_shift(int64_t ncell);
-int64_t bin_tiles(int64_t n);
+// entries of bh: buckets times tiles
+int64_t bin_hist_size(int64_t n, int64_t ncell, int shift);
 inline int64_t bin_cells(const fpts_mesh *m)
 {
     int64_t c = 1;
@@ -448,8 +448,8 @@ hipError_t launch_bin_tiles(const fpts_mesh *m, int64_t n, const double *pts, do
                             int *bh, hipStream_t s);
 hipError_t launch_bin_coarse(const fpts_mesh *m, int64_t n, const int *cellpt, int shift,
                              const int *boff, int2 *pairs, hipStream_t s);
-hipError_t launch_bin_rank(int64_t n, const int *total, int shift, const int2 *pairs,
-                           int *cell_cnt, int *rank, hipStream_t s);
+hipError_t launch_bin_rank(const fpts_mesh *m, int64_t n, const int *total, int shift,
+                           const int2 *pairs, int *cell_cnt, int *rank, hipStream_t s);
 hipError_t launch_bin_scatter(int64_t n, const int *total, const int2 *pairs, const int *rank,
                               const int *cell_poff, int *pbin, int cus, hipStream_t s);
 // search hints: pass 0 makes the previous element of each previously

@@ -116,15 +116,19 @@ __device__ __forceinline__ void write_tasks(int *task, int base, int cnt, int un
     }
 }
 
-__global__ __launch_bounds__(kUsThreads) void k_unit_scan(UnitScan u)
+// (parts = 1 or kUsItems blocks scan each tile and write a share of the
+// results each: the scattered stores of the task maps of one tile keep one
+// CU's address unit busy for 20 us)
+__global__ __launch_bounds__(kUsThreads) void k_unit_scan(UnitScan u, int parts)
 {
     __shared__ int red[3][kUsWaves];
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    const int64_t base = (int64_t)blockIdx.x * kUsTile + (int64_t)threadIdx.x * kUsItems;
+    const int tile = blockIdx.x / parts, part = blockIdx.x % parts;
+    const int64_t base = (int64_t)tile * kUsTile + (int64_t)threadIdx.x * kUsItems;
     // items and tasks of the earlier tiles
     int pre[3] = {0, 0, 0};
-    if (blockIdx.x > 0) {
-        for (int64_t i = threadIdx.x; i < blockIdx.x; i += kUsThreads)
+    if (tile > 0) {
+        for (int64_t i = threadIdx.x; i < tile; i += kUsThreads)
 #pragma unroll
             for (int q = 0; q < 3; ++q) pre[q] += u.tile_sum[3 * i + q];
         block_sum3(pre, red);
@@ -160,17 +164,18 @@ __global__ __launch_bounds__(kUsThreads) void k_unit_scan(UnitScan u)
         const bool in = i < u.n;
         const int t1 = in && u.choff ? tasks_of(v[k], u.len) : 0;
         const int t2 = in && u.off2 ? tasks_of(v[k], u.len2) : 0;
-        if (in) {
+        const bool mine = parts == 1 || k == part;
+        if (in && mine) {
             u.off[i] = at[0];
             if (u.choff) u.choff[i] = at[1];
             if (u.off2) u.off2[i] = at[2];
         }
-        if (u.choff) write_tasks(u.task, at[1], t1, (int)i);
-        if (u.off2) write_tasks(u.task2, at[2], t2, (int)i);
+        if (u.choff && mine) write_tasks(u.task, at[1], t1, (int)i);
+        if (u.off2 && mine) write_tasks(u.task2, at[2], t2, (int)i);
         at[0] += in ? v[k] : 0;
         at[1] += t1;
         at[2] += t2;
-        if (i == u.n - 1) {
+        if (i == u.n - 1 && mine) {
             u.off[u.n] = at[0];
             if (u.choff) u.choff[u.n] = at[1];
             if (u.off2) u.off2[u.n] = at[2];
@@ -270,12 +275,12 @@ __global__ __launch_bounds__(256) void k_cell_bin(HashView h, int pass, int n, i
 // cell buckets one write at a random place per point.  Instead the cells
 // are grouped into coarse buckets of 2^shift consecutive cells (at most
 // kBinMaxBuckets buckets):
-//  tiles:   per tile of kBinTile points, bin_point and the tile's histogram
+//  tiles:   per tile of points, bin_point and the tile's histogram
 //           over the buckets (LDS atomics), stored bucket-major in bh; an
 //           exclusive scan of bh gives each (bucket, tile) its range;
 //  coarse:  each tile writes its points as (cell, id) pairs into those
 //           ranges: pairs sorted by bucket, one short run per (tile, bucket);
-//  rank:    windows of kBinTile consecutive pairs (cells of at most two
+//  rank:    windows of as many consecutive pairs (cells of at most two
 //           buckets, unless the buckets are sparse) count their cells in LDS
 //           and take one atomic per cell on cell_cnt for a block of ranks;
 //  scatter: after the scan of cell_cnt, pbin[cell_poff[c] + rank] = id in
@@ -284,9 +289,12 @@ __global__ __launch_bounds__(256) void k_cell_bin(HashView h, int pass, int n, i
 // The scatter's ranges go to the XCDs in contiguous blocks (task_of_block),
 // so that an XCD's writes stay within a few buckets and partly written cache
 // lines meet in one L2 (the same mapping for the tiles measured slower).
+// A tile or window is 256 threads times 4 to 32 items (bin_items): long runs
+// per bucket where there are many points, and enough blocks to fill the chip
+// where there are few (20 thousand points in tiles of 8192, three blocks, took
+// the tile pass 31 us).
 constexpr int kBinThreads = 256;
-constexpr int kBinItems = 32;
-constexpr int kBinTile = kBinThreads * kBinItems;
+constexpr int kBinItems = 32;   // at most
 
 template <int D>
 __global__ __launch_bounds__(kBinThreads) void k_bin_tiles(HashView h, int n, int R,
@@ -295,14 +303,14 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_tiles(HashView h, int n, in
                                                           int2 *cand,
                                                           int32_t *code, int32_t *elem, double *r,
                                                           double *dist, int shift, int nb,
-                                                          int ntile, int *bh)
+                                                          int ntile, int items, int *bh)
 {
     extern __shared__ int hist[];   // [nb]
     const int tile = blockIdx.x;
     for (int i = threadIdx.x; i < nb; i += kBinThreads) hist[i] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)tile * kBinTile;
-    for (int k = 0; k < kBinItems; ++k) {
+    const int64_t base = (int64_t)tile * items * kBinThreads;
+    for (int k = 0; k < items; ++k) {
         const int64_t q = base + (int64_t)k * kBinThreads + threadIdx.x;
         if (q < n) {
             const int c = bin_point<D>(h, (int)q, n, R, pts, pts4, keep, cellpt, cand, code,
@@ -316,16 +324,16 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_tiles(HashView h, int n, in
 }
 
 __global__ __launch_bounds__(kBinThreads) void k_bin_coarse(int n, const int *cellpt, int shift,
-                                                           int nb, int ntile, const int *boff,
-                                                           int2 *pairs)
+                                                           int nb, int ntile, int items,
+                                                           const int *boff, int2 *pairs)
 {
     extern __shared__ int off[];   // [nb] next free place of each bucket's range
     const int tile = blockIdx.x;
     for (int i = threadIdx.x; i < nb; i += kBinThreads)
         off[i] = boff[(int64_t)i * ntile + tile];
     __syncthreads();
-    const int64_t base = (int64_t)tile * kBinTile;
-    for (int k = 0; k < kBinItems; ++k) {
+    const int64_t base = (int64_t)tile * items * kBinThreads;
+    for (int k = 0; k < items; ++k) {
         const int64_t q = base + (int64_t)k * kBinThreads + threadIdx.x;
         if (q < n) {
             const int c = cellpt[q];
@@ -334,10 +342,12 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_coarse(int n, const int *ce
     }
 }
 
+template <int ITEMS>
 __global__ __launch_bounds__(kBinThreads) void k_bin_rank(const int *total_p, int shift,
                                                          const int2 *pairs, int *cell_cnt,
                                                          int *rank)
 {
+    constexpr int kBinItems = ITEMS, kBinTile = kBinThreads * ITEMS;
     extern __shared__ int cnt[];   // [2 << shift] cells of buckets hA, hA + 1
     const int total = *total_p;
     const int64_t w0 = (int64_t)task_of_block() * kBinTile;
@@ -587,7 +597,7 @@ __device__ inline bool settled(int nc, int32_t cd, const double (&rr)[3], int R)
 // order, *ucount of them.  The other candidates of the few listed points are
 // then handled by dense wavefronts: tested where they lie among all points,
 // their candidate loops (dependent loads) kept whole wavefronts waiting.
-// A block marks kMarkChunk consecutive points, gathers its listed points in
+// A block marks up to kMarkChunk consecutive points, gathers its listed points in
 // LDS and reserves their places with one atomic: device-scope atomics on one
 // address serialise (several ns each), so one per wavefront with a listed
 // point would take longer than the loads.  All of a point's loads are
@@ -614,7 +624,8 @@ __device__ inline void list_append(bool take, int p, int lane, int *lst, int &lc
 __global__ __launch_bounds__(256) void k_unsettled(int n, int R, const int *cellpt,
                                                   const int2 *cand,
                                                   const int32_t *code, const double *r,
-                                                  int *ulist, int *ucount, EvalRest rest)
+                                                  int *ulist, int *ucount, int items,
+                                                  EvalRest rest)
 {
     __shared__ int lst[kMarkChunk], elst[kMarkChunk];
     __shared__ int lcnt, ecnt, gbase, ebase;
@@ -624,8 +635,9 @@ __global__ __launch_bounds__(256) void k_unsettled(int n, int R, const int *cell
         ecnt = 0;
     }
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kMarkChunk;
-    for (int it = 0; it < kMarkChunk / 256; ++it) {
+    const int64_t base = (int64_t)blockIdx.x * items * 256;
+#pragma unroll 4
+    for (int it = 0; it < items; ++it) {
         const int64_t q = base + it * 256 + threadIdx.x;
         const int p = (int)q;
         bool todo = false, other = false;
@@ -661,28 +673,20 @@ __global__ __launch_bounds__(256) void k_unsettled(int n, int R, const int *cell
     for (int i = threadIdx.x; i < ec; i += 256) rest.list[ebase + i] = elst[i];
 }
 
-// Exclusive prefix sum of v over the lanes of a wavefront; total = the sum.
-__device__ __forceinline__ int wave_excl_sum(int v, int &total)
-{
-    const int lane = __lane_id();
-    int incl = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += t;
-    }
-    total = __shfl(incl, 63, 64);
-    return incl - v;
-}
+// Phase D over the listed points, a contiguous range of the list per block,
+// kResLanes lanes to a point: they test its cell's candidates side by side
+// (a point per lane walked some 20 of them one dependent load after the
+// other, twice: 50 us a pass whatever the number of points).  pass 0: count
+// each point's other candidates (ucnt) and give the point a block of that
+// many slots, uoff[i] .. uoff[i] + ucnt[i] - 1 (one atomic per block on
+// *slot_total), and count them per element; a point whose block would end
+// beyond the slot capacity cap2 gets none (ucnt[i] = 0, uoff[i] = -1) and
+// goes to the overflow list instead (olist, *ocount: searched one point per wavefront).
+// pass 1: write the slots (k-th other candidate in ascending id at uoff[i] +
+// k) and bucket them by element.
+constexpr int kResLanes = 16;
+constexpr int kResGroups = 256 / kResLanes;
 
-// Phase D over the listed points (grid-stride).  pass 0: count each point's
-// other candidates and give the point a block of that many slots, uoff[i] ..
-// uoff[i] + ucnt[i] - 1 (one atomic per wavefront on *slot_total), and count
-// them per element; a point whose block would end beyond the slot capacity
-// cap2 gets none (ucnt[i] = 0) and goes to the overflow list instead
-// (olist, *ocount: searched one point per wavefront).  pass 1: write the
-// slots (k-th other candidate in ascending id at uoff[i] + k) and bucket them
-// by element.
 template <int D>
 __global__ __launch_bounds__(256) void k_resolve(HashView h, int pass, int n, const double *pts,
                                                 const int *cellpt, const int2 *cand,
@@ -690,72 +694,113 @@ __global__ __launch_bounds__(256) void k_resolve(HashView h, int pass, int n, co
                                                 int *uoff, int *ucnt,
                                                 unsigned long long *slot_total,
                                                 int *elem_cnt2, const int *elem_off2,
-                                                int *slot_pt, int *slot_elem, int *sorted2, int64_t cap2, int *olist,
-                                                int *ocount)
+                                                int *slot_pt, int *slot_elem, int *sorted2,
+                                                int64_t cap2, int *olist, int *ocount)
 {
+    __shared__ int wsum[4];
+    __shared__ unsigned long long sbase;
     const int cnt = *ucount;
-    const int lane = threadIdx.x & 63;
-    const int stride = gridDim.x * blockDim.x;
-    // the loop condition is wave-uniform (the stride is a multiple of 64)
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i - lane < cnt; i += stride) {
-        const bool act = i < cnt;
-        int k = 0, p = 0, prim = -1, c = 0;
+    // (at least two points per group: the blocks' atomics on *slot_total, some
+    // 16 ns each, come one after the other)
+    const int per = max((int)((cnt + gridDim.x - 1) / gridDim.x), 2 * kResGroups);
+    const int i0 = min((int64_t)cnt, (int64_t)blockIdx.x * per);
+    const int i1 = min((int64_t)cnt, (int64_t)i0 + per);
+    if (i0 >= i1) return;   // the whole block
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    const int gl = threadIdx.x % kResLanes, grp = threadIdx.x / kResLanes;
+    const int shift = lane / kResLanes * kResLanes;   // the group's lanes in its wave
+    // calls hit(e, k) for the point's k-th other candidate e, in ascending
+    // id (every lane of the group takes part; the hitting lane calls);
+    // returns their number
+    auto others = [&](int i, auto &&hit) __attribute__((always_inline)) {
+        const int p = ulist[i], prim = cand[p].y, c = cellpt[p];
         double x[D];
 #pragma unroll
-        for (int d = 0; d < D; ++d) x[d] = 0.0;
-        if (act) {
-            p = ulist[i];
-            prim = cand[p].y;
-            c = cellpt[p];
-#pragma unroll
-            for (int d = 0; d < D; ++d) x[d] = pts[(size_t)d * n + p];
+        for (int d = 0; d < D; ++d) x[d] = pts[(size_t)d * n + p];
+        int k = 0;
+        const int q1 = h.cell_off[c + 1];
+        for (int q = h.cell_off[c]; q < q1; q += kResLanes) {
+            const int e = q + gl < q1 ? h.cell_el[q + gl] : prim;
+            double depth;
+            const bool ok =
+                e != prim && box_pass<D>(h.box + (size_t)e * (3 * D + D * D), x, depth);
+            const unsigned m =
+                (unsigned)(__ballot(ok) >> shift) & ((1u << kResLanes) - 1);
+            if (ok) hit(p, e, k + __popc(m & ((1u << gl) - 1)));
+            k += __popc(m);
         }
-        if (pass == 0) {
-            if (act) {
-                for (int q = h.cell_off[c]; q < h.cell_off[c + 1]; ++q) {
-                    const int e = h.cell_el[q];
-                    double depth;
-                    if (e != prim && box_pass<D>(h.box + (size_t)e * (3 * D + D * D), x, depth))
-                        ++k;
-                }
-            }
-            int tot;
-            const int ex = wave_excl_sum(k, tot);
-            unsigned long long base = 0;
-            if (lane == 0 && tot > 0) base = atomicAdd(slot_total, (unsigned long long)tot);
-            base = __shfl(base, 0, 64);
-            const bool fits = base + (unsigned long long)(ex + k) <= (unsigned long long)cap2;
-            if (act) {
-                uoff[i] = fits ? (int)(base + ex) : 0;
-                ucnt[i] = fits ? k : 0;
-            }
-            if (act && k > 0) {
-                if (fits) {
-                    for (int q = h.cell_off[c]; q < h.cell_off[c + 1]; ++q) {
-                        const int e = h.cell_el[q];
-                        double depth;
-                        if (e != prim &&
-                            box_pass<D>(h.box + (size_t)e * (3 * D + D * D), x, depth))
-                            atomicAdd(&elem_cnt2[e], 1);
-                    }
-                } else {
-                    olist[atomicAdd(ocount, 1)] = p;
-                }
-            }
-        } else if (act && ucnt[i] > 0) {
+        return k;
+    };
+    if (pass == 1) {
+        for (int i = i0 + grp; i < i1; i += kResGroups) {
+            if (ucnt[i] == 0) continue;
             const int s0 = uoff[i];
-            for (int q = h.cell_off[c]; q < h.cell_off[c + 1]; ++q) {
-                const int e = h.cell_el[q];
-                double depth;
-                if (e == prim || !box_pass<D>(h.box + (size_t)e * (3 * D + D * D), x, depth))
-                    continue;
-                const int sl = s0 + k;
-                slot_pt[sl] = p;
-                slot_elem[sl] = e;
-                sorted2[elem_off2[e] + atomicSub(&elem_cnt2[e], 1) - 1] = sl;
-                ++k;
-            }
+            others(i, [&](int p, int e, int k) __attribute__((always_inline)) {
+                slot_pt[s0 + k] = p;
+                slot_elem[s0 + k] = e;
+                sorted2[elem_off2[e] + atomicSub(&elem_cnt2[e], 1) - 1] = s0 + k;
+            });
         }
+        return;
+    }
+    int sum = 0;
+    for (int i = i0 + grp; i < i1; i += kResGroups) {
+        const int k = others(i, [&](int, int e, int) __attribute__((always_inline)) {
+            atomicAdd(&elem_cnt2[e], 1);
+        });
+        if (gl == 0) {
+            ucnt[i] = k;
+            sum += k;
+        }
+    }
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    if (lane == 0) wsum[wid] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int tot = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+        sbase = tot ? atomicAdd(slot_total, (unsigned long long)tot) : 0;
+    }
+    __syncthreads();
+    // the points' places in the block's slots, 256 at a time
+    unsigned long long base = sbase;
+    for (int c0 = i0; c0 < i1; c0 += 256) {
+        const int i = c0 + threadIdx.x;
+        const int k = i < i1 ? ucnt[i] : 0;
+        int incl = k;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int t = __shfl_up(incl, o);
+            if (lane >= o) incl += t;
+        }
+        __syncthreads();   // earlier reads of wsum come first
+        if (lane == kWave - 1) wsum[wid] = incl;
+        __syncthreads();
+        int before = incl - k, all = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            if (w < wid) before += wsum[w];
+            all += wsum[w];
+        }
+        const unsigned long long at = base + (unsigned long long)before;
+        const bool fits = at + (unsigned long long)k <= (unsigned long long)cap2;
+        if (i < i1) {
+            if (!fits) {
+                ucnt[i] = 0;
+                if (k > 0) olist[atomicAdd(ocount, 1)] = ulist[i];
+            }
+            uoff[i] = fits ? (int)at : k > 0 ? -1 : 0;
+        }
+        base += (unsigned long long)all;
+    }
+    if (base <= (unsigned long long)cap2) return;   // (base is uniform over the block)
+    // points without room: their candidates are counted back out
+    __syncthreads();
+    for (int i = i0 + grp; i < i1; i += kResGroups) {
+        if (uoff[i] >= 0) continue;
+        others(i, [&](int, int e, int) __attribute__((always_inline)) {
+            atomicSub(&elem_cnt2[e], 1);
+        });
     }
 }
 
@@ -881,7 +926,10 @@ hipError_t launch_unit_scan(UnitScan u, int64_t tmp_blocks, hipStream_t s)
         hipLaunchKernelGGL(k_unit_sums, dim3((unsigned)tiles), dim3(kUsThreads), 0, s, u);
     else
         threads = (int)((u.n + kUsItems * kWave - 1) / (kUsItems * kWave)) * kWave;
-    hipLaunchKernelGGL(k_unit_scan, dim3((unsigned)tiles), dim3(threads), 0, s, u);
+    // (in place, off aliasing cnt, a tile's counts are read by one block only)
+    const int parts = u.n >= 512 && u.off != u.cnt ? kUsItems : 1;
+    hipLaunchKernelGGL(k_unit_scan, dim3((unsigned)(tiles * parts)), dim3(threads), 0, s, u,
+                       parts);
     return hipGetLastError();
 }
 
@@ -920,7 +968,32 @@ int bin_shift(int64_t ncell)
     return shift;
 }
 
-int64_t bin_tiles(int64_t n) { return (n + kBinTile - 1) / kBinTile; }
+// items per thread of a tile: 32 from about 6 million points on, fewer
+// below so that some three blocks per CU have work, as long as the bucket
+// histograms (one per tile) stay below an eighth of the points.  (At 4
+// million points 8 items took the tile pass from 74 to 64 us, but the pass
+// that writes the shorter runs from 26 to 33.)
+static int bin_items(int64_t n, int nb)
+{
+    int items = kBinItems;
+    while (items > 4 && n < (int64_t)kBinThreads * items * 768 &&
+           (n / (kBinThreads * items / 2) + 1) * nb <= n / 8)
+        items /= 2;
+    return items;
+}
+static int64_t tiles_for(int64_t n, int items)
+{
+    return (n + (int64_t)kBinThreads * items - 1) / ((int64_t)kBinThreads * items);
+}
+static int bin_buckets(int64_t ncell, int shift)
+{
+    return (int)((ncell + (1ll << shift) - 1) >> shift);
+}
+int64_t bin_hist_size(int64_t n, int64_t ncell, int shift)
+{
+    const int nb = bin_buckets(ncell, shift);
+    return nb * tiles_for(n, bin_items(n, nb));
+}
 
 // a grid of at least `blocks` blocks, a multiple of the XCD count
 static unsigned xcd_grid(int64_t blocks)
@@ -935,12 +1008,12 @@ hipError_t launch_bin_tiles(const fpts_mesh *m, int64_t n, const double *pts, do
 {
     if (n <= 0) return hipSuccess;
     HashView h = hash_view(m);
-    const int64_t ncell = bin_cells(m);
-    const int nb = (int)((ncell + (1ll << shift) - 1) >> shift), ntile = (int)bin_tiles(n);
+    const int nb = bin_buckets(bin_cells(m), shift), items = bin_items(n, nb);
+    const int ntile = (int)tiles_for(n, items);
     auto k = m->D == 2 ? k_bin_tiles<2> : k_bin_tiles<3>;
     hipLaunchKernelGGL(k, dim3(ntile), dim3(kBinThreads), sizeof(int) * nb, s, h, (int)n, m->R,
                        pts, pts4, keep, cellpt, cand, code, elem, r, dist, shift, nb,
-                       ntile, bh);
+                       ntile, items, bh);
     return hipGetLastError();
 }
 
@@ -948,18 +1021,21 @@ hipError_t launch_bin_coarse(const fpts_mesh *m, int64_t n, const int *cellpt, i
                              const int *boff, int2 *pairs, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    const int64_t ncell = bin_cells(m);
-    const int nb = (int)((ncell + (1ll << shift) - 1) >> shift), ntile = (int)bin_tiles(n);
+    const int nb = bin_buckets(bin_cells(m), shift), items = bin_items(n, nb);
+    const int ntile = (int)tiles_for(n, items);
     hipLaunchKernelGGL(k_bin_coarse, dim3(ntile), dim3(kBinThreads), sizeof(int) * nb, s, (int)n,
-                       cellpt, shift, nb, ntile, boff, pairs);
+                       cellpt, shift, nb, ntile, items, boff, pairs);
     return hipGetLastError();
 }
 
-hipError_t launch_bin_rank(int64_t n, const int *total, int shift, const int2 *pairs,
-                           int *cell_cnt, int *rank, hipStream_t s)
+hipError_t launch_bin_rank(const fpts_mesh *m, int64_t n, const int *total, int shift,
+                           const int2 *pairs, int *cell_cnt, int *rank, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bin_rank, dim3(xcd_grid(bin_tiles(n))), dim3(kBinThreads),
+    const int items = bin_items(n, bin_buckets(bin_cells(m), shift));
+    auto k = items == 4 ? k_bin_rank<4> : items == 8 ? k_bin_rank<8>
+             : items == 16 ? k_bin_rank<16> : k_bin_rank<32>;
+    hipLaunchKernelGGL(k, dim3(xcd_grid(tiles_for(n, items))), dim3(kBinThreads),
                        sizeof(int) * (2 << shift), s, total, shift, pairs, cell_cnt, rank);
     return hipGetLastError();
 }
@@ -1017,8 +1093,13 @@ hipError_t launch_unsettled(const fpts_mesh *m, int64_t n, const int *cellpt, co
                             int *ucount, const EvalRest &rest, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_unsettled, dim3(grid_for(n, kMarkChunk)), dim3(256), 0, s, (int)n, m->R,
-                       cellpt, cand, code, r, ulist, ucount, rest);
+    // a block's items: 4096 where that still leaves two blocks per CU, else
+    // fewer (a block of 16 items per thread takes 19 us however few points
+    // there are)
+    const int items = (int)std::min<int64_t>(
+        std::max<int64_t>(n / ((int64_t)m->cus * 2 * 256), 1), kMarkChunk / 256);
+    hipLaunchKernelGGL(k_unsettled, dim3(grid_for(n, 256 * items)), dim3(256), 0, s, (int)n, m->R,
+                       cellpt, cand, code, r, ulist, ucount, items, rest);
     return hipGetLastError();
 }
 
@@ -1039,7 +1120,9 @@ hipError_t launch_resolve(const fpts_mesh *m, int pass, int64_t n, const double 
     if (n <= 0) return hipSuccess;
     HashView h = hash_view(m);
     auto k = m->D == 2 ? k_resolve<2> : k_resolve<3>;
-    hipLaunchKernelGGL(k, dim3(list_grid(m, n)), dim3(256), 0, s, h, pass, (int)n, pts, cellpt,
+    const int grid = std::max(
+        1, (int)std::min<int64_t>((n + kResGroups - 1) / kResGroups, (int64_t)m->cus * 4));
+    hipLaunchKernelGGL(k, dim3(grid), dim3(256), 0, s, h, pass, (int)n, pts, cellpt,
                        cand, ulist, ucount, uoff, ucnt, slot_total, elem_cnt2, elem_off2,
                        slot_pt, slot_elem, sorted2, cap2, olist, ocount);
     return hipGetLastError();
