@@ -197,7 +197,7 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     w.task_elem2 = c.take(I * w.tb_elem2);
     w.scan_tmp = c.take(I * w.scan_blocks);
     w.pts4 = c.take(m->R >= 2 ? sizeof(double) * pt_stride(m->D) * n : 1);
-    w.start = c.take(sizeof(double) * m->R * n);
+    w.rec = c.take(m->R >= 2 ? sizeof(double) * kRec * n : 1);
     // parked pairs of the primary pass (at most one per point)
     w.park_meta = c.take(sizeof(int4) * n);
     w.park_r = c.take(sizeof(double) * (m->R + 1) * n);
@@ -264,8 +264,8 @@ hipError_t launch_newton(const fpts_mesh *m, int precision, int64_t n, const dou
 namespace fpts {
 
 // fpts_find with an optional keep mask: points with keep[p] != 0 hold final
-// results on entry and are not searched; with rs the primary pass also
-// writes its settling results in list order (NewtonIO::rs).
+// results on entry and are not searched; with rs (line meshes) the primary
+// pass also writes its settling results in list order (NewtonIO::rs).
 int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int32_t *d_elem,
               double *d_r, double *d_dist, int precision, void *d_ws, size_t ws_bytes,
               void *stream, const int *keep, double *rs, const EvalRest *rest)
@@ -300,7 +300,7 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
     // the packed copy of the points: volume and surface meshes (the line
     // kernel reads the [D][n] coordinates)
     double *pts4 = m->R >= 2 ? at<double>(d_ws, w.pts4) : nullptr;
-    double *start = at<double>(d_ws, w.start);
+    double *rec = m->R >= 2 ? at<double>(d_ws, w.rec) : nullptr;
     int4 *park_meta = at<int4>(d_ws, w.park_meta);
     double *park_r = at<double>(d_ws, w.park_r);
     double *park_state = at<double>(d_ws, w.park_state);
@@ -361,12 +361,11 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
     {   // phase C: Newton on the primary candidates, results straight to the outputs
         NewtonIO io{sorted, elem_off, chunk_off, nullptr, d_code, d_elem, d_r, n, d_dist,
                     counters + kNewtonFirst, stats, task_elem, newt_off, newt_task,
-                    w.tb_elem, rs, n};
+                    w.tb_elem, m->R == 1 ? rs : nullptr};
         io.pts4 = pts4;
         if (m->R >= 2) {
             io.node = rank;   // free by now
-            io.start = start;
-            io.start_stride = n;
+            io.rec = rec;
             // pairs that reach a face leave the primary kernel's waves
             io.park_meta = park_meta;
             io.park_r = park_r;
@@ -398,8 +397,9 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
                                 park_sorted, m->cus, s));
             NewtonIO fio{park_sorted, park_off, park_choff, nullptr, d_code, d_elem, d_r, n,
                          d_dist, nullptr, stats + 2 * kPassStats, park_task, nullptr, nullptr,
-                         w.tb_park, rs, n};
+                         w.tb_park};
             fio.pts4 = pts4;
+            fio.rec = rec;
             fio.park_meta = park_meta;
             fio.park_r = park_r;
             fio.park_cap = n;
@@ -412,8 +412,11 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
         Span sp(m, 3, s);
         // counters[0]: listed points, counters[1]: slots handed out
         const EvalRest none{};
-        chk(launch_unsettled(m, n, cellpt, cand, d_code, d_r, ulist, counters,
-                             rest ? *rest : none, s));
+        if (m->R >= 2)
+            chk(launch_settle(m, n, cand, elem_off, rec, d_code, d_elem, d_r, d_dist, ulist,
+                              counters, rest ? *rest : none, s));
+        else
+            chk(launch_unsettled(m, n, cand, d_code, d_r, ulist, counters, s));
         unsigned long long *slot_total =
             reinterpret_cast<unsigned long long *>(counters + kSlotTotal);
         chk(launch_resolve(m, 0, n, d_pts, cellpt, cand, ulist, counters, uoff, ucnt,
@@ -887,7 +890,7 @@ int fpts_lpt_step(fpts_mesh *m, const fpts_lpt_params *p, int64_t n, int first, 
         // start converges in three or four)
         NewtonIO io{sorted, elem_off, chunk_off, nullptr, d_code, d_elem, d_r, n, d_dist,
                     counters + kNewtonFirst, stats, task_elem, chunk_off, task_elem,
-                    w.tb_elem, nullptr, 0, keep, kHintPasses};
+                    w.tb_elem, nullptr, keep, kHintPasses};
         chk(launch_newton(m, precision, n, d_x, io, 2, s));
         chk(launch_hint(m, 1, n, d_code, d_elem, d_r, cand, nullptr, nullptr, keep, s));
     }
@@ -903,7 +906,7 @@ size_t fpts_find_eval_workspace_size(const fpts_mesh *m, int64_t n)
     if (fw == 0) return 0;
     const size_t nn = (size_t)std::max<int64_t>(n, 1);
     return fw + align_up(eval_ws_layout(m, n).total) +
-           align_up(sizeof(double) * (size_t)m->R * nn);
+           (m->R == 1 ? align_up(sizeof(double) * nn) : 0);
 }
 
 int fpts_find_eval(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code,
@@ -920,11 +923,13 @@ int fpts_find_eval(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code
     if (((uintptr_t)d_ws & 255) != 0) return FPTS_EINVAL;
     const size_t need = fpts_find_eval_workspace_size(m, n);
     if (need == 0 || ws_bytes < need) return FPTS_EINVAL;
-    // [find workspace][interpolation workspace][R][n] results in list order
+    // [find workspace][interpolation workspace], and on line meshes [n]
+    // results in list order (the other meshes' are in the find workspace)
     const FindWs w = find_ws_layout(m, n);
     const EvalWs v = eval_ws_layout(m, n);
     void *ews = static_cast<char *>(d_ws) + w.total;
-    double *rs = at<double>(d_ws, w.total + align_up(v.total));
+    double *rs = m->R == 1 ? at<double>(d_ws, w.total + align_up(v.total)) : nullptr;
+    const double *rec = m->R == 1 ? nullptr : at<double>(d_ws, w.rec);
     // volume and surface meshes: the points left for the second
     // interpolation pass are listed by the find's marking pass (in slist,
     // which only the line-mesh path uses otherwise)
@@ -956,7 +961,7 @@ int fpts_find_eval(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code
         // list order (no re-binning, no gather of r)
         Span sp(m, 5, s);
         chk(launch_eval(m, n, nullptr, n_fields, field_nodes_1d, d_field, d_out, sorted,
-                        elem_off, chunk_off, task_elem, w.tb_elem, s, rs));
+                        elem_off, chunk_off, task_elem, w.tb_elem, s, rs, rec));
     }
     {
         // the rest (settled by the second search, BORDER, NOT_FOUND): the

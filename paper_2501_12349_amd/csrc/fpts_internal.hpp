@@ -193,13 +193,14 @@ struct EvalRest {
     int n_fields = 0;
 };
 
-// cand[p] (find workspace): (number of candidates that pass the box tests,
-// primary element or -1) of point p
+// cand[p] (find workspace): primary element of point p, or -1, in y; in x
+// the point's rank in its primary's bucket, times two, plus one when more
+// than one candidate passed the box tests (unsigned)
 struct FindWs {
     size_t cell_cnt, cell_poff, cell_choff, cellpt, pbin, cand, rank, bin_prim,
         elem_cnt, elem_off, chunk_off, sorted, ulist, uoff, ucnt, elem_cnt2,
         elem_off2, chunk_off2, slot_pt, slot_elem, sorted2, res_r, res_dist, res_code,
-        task_cell, task_elem, task_elem2, scan_tmp, counters, stats, pts4, start, park_meta,
+        task_cell, task_elem, task_elem2, scan_tmp, counters, stats, pts4, rec, park_meta,
         park_r, park_state, park_cnt, park_off, park_choff, park_sorted, park_task,
         olist, ov_int, ov_dbl, bin_hist, bin_pairs, zero, total;
     int64_t cap2;           // capacity for second-pass (point, candidate) pairs
@@ -237,12 +238,11 @@ struct NewtonIO {
     const int *newt_off;
     const int *newt_task;
     int64_t task_bound;     // tasks of that grid at most
-    // optional (fused find + interpolate, primary pass): results that settle
-    // their point -- INTERIOR at least kSettleGuard inside -- also go to
-    // rs[k * rs_stride + q] at the pair's position q in `list`; NaN marks
-    // the other positions
+    // optional (line meshes, fused find + interpolate, primary pass): results
+    // that settle their point -- INTERIOR at least kSettleGuard inside --
+    // also go to rs[q] at the pair's position q in `list`; NaN marks the
+    // other positions
     double *rs;
-    int64_t rs_stride;
     // optional: conv[item] = 1 when the step test ended the iteration, 0 when
     // the pass limit did; max_iter > 0 replaces the mesh's pass limit
     int *conv;
@@ -253,11 +253,14 @@ struct NewtonIO {
     // optional: the nearest nodes (packed indices) of the pairs by list
     // position, the starts of the Newton kernel; null: the starts are points
     int *node;
-    // optional: the starts that are points (the FP32 phase's results in
-    // mixed mode) at the pair's position q in `list`, start[k * start_stride
-    // + q], instead of in r: written and read in list order, without a gather
-    double *start;
-    int64_t start_stride;
+    // optional (primary and face passes of volume and surface meshes): the
+    // results by list position instead of in code, elem, r and dist: a
+    // 32-byte record rec[kRec q ..] = r[0..R), then in its last double the
+    // distance, with the sign bit set unless INTERIOR.  A result takes one
+    // write that way (in random point order the six arrays took a cache line
+    // each, some 30 G/s on this GPU) and launch_settle brings the records
+    // into point order.  Mixed mode: the FP32 phase's results, too.
+    double *rec;
     // optional (primary FP64 pass): a pair whose next pass needs second
     // derivatives (a pass on a face, eq. eq_newton_hessian) leaves its wave
     // and is parked at its list position q: node[q] = -1, park_meta[q] =
@@ -305,6 +308,8 @@ constexpr int kStatCopies = 16;
 // FP64 kernel and for the FP32 phase.
 constexpr int kXcdCounter = 32;
 constexpr int kNewtonCounters = 2 * kXcd * kXcdCounter;
+
+constexpr int kRec = 4;   // doubles per result record
 
 // Doubles per saved park state (at most 1 + 3 + 6 + 3 used), one 128-byte
 // record per parked pair.
@@ -490,9 +495,15 @@ hipError_t launch_primary_scatter(int64_t n, int64_t nel, const int2 *cand,
 // 1 writes the (point, element) slots into element buckets (counting
 // elem_cnt2 back down); select2 applies
 // the selection rule to every listed point
-hipError_t launch_unsettled(const fpts_mesh *m, int64_t n, const int *cellpt, const int2 *cand,
+hipError_t launch_unsettled(const fpts_mesh *m, int64_t n, const int2 *cand,
                             const int32_t *code, const double *r, int *ulist,
-                            int *ucount, const EvalRest &rest, hipStream_t s);
+                            int *ucount, hipStream_t s);
+// volume and surface meshes: the result records of the primary pass (by list
+// position, elem_off the primary buckets) written to the outputs in point
+// order, and the same marking with the interpolation's rest
+hipError_t launch_settle(const fpts_mesh *m, int64_t n, const int2 *cand, const int *elem_off,
+                         const double *rec, int32_t *code, int32_t *elem, double *r, double *dist,
+                         int *ulist, int *ucount, const EvalRest &rest, hipStream_t s);
 hipError_t launch_resolve(const fpts_mesh *m, int pass, int64_t n, const double *pts,
                           const int *cellpt, const int2 *cand, const int *ulist,
                           const int *ucount, int *uoff, int *ucnt, unsigned long long *slot_total,
@@ -535,7 +546,8 @@ hipError_t launch_eval_bin(const fpts_mesh *m, int pass, int64_t n, const int32_
 hipError_t launch_eval(const fpts_mesh *m, int64_t n, const double *r, int n_fields, int field_n,
                        const double *field, double *out, const int *sorted,
                        const int *elem_off, const int *chunk_off, const int *task_elem,
-                       int64_t task_bound, hipStream_t s, const double *rs = nullptr);
+                       int64_t task_bound, hipStream_t s, const double *rs = nullptr,
+                       const double *rec = nullptr);
 hipError_t launch_nodes32(const fpts_mesh *m, hipStream_t s);
 // score rows of the nearest-node contraction: per element and node j,
 // (-2 x_j, -2 y_j, -2 z_j, |x_j|^2) element-local (D = 2: (-2x, -2y, |x|^2, 0)),

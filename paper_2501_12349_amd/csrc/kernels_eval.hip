@@ -124,8 +124,11 @@ struct EvalArgs {
     const int *chunk_off;
     const int *task_elem;   // task -> element (task grid)
     Basis basis;
-    // fused mode (rs != null): `sorted` is the primary list of Find and
-    // r comes from rs[k * n + list position]; NaN there skips the point
+    // fused mode: `sorted` is the primary list of Find, and r comes from its
+    // results by list position -- rec (records of NewtonIO::rec; the points
+    // that they do not settle are skipped), or on line meshes rs (NaN there
+    // skips the point)
+    const double *rec;
     const double *rs;
     int f0;                 // first field of this launch (k_eval_mfma)
     // k_eval_mfma: walk the elements (every wave at most a few of them)
@@ -307,10 +310,22 @@ k_eval_mfma(EvalArgs a)
         bool has = idx < end;
         const int p = has ? a.sorted[idx] : 0;
         double rr[3] = {0.0, 0.0, 0.0};
+        if (a.rec) {
+            double mg = 1.0, sd = 0.0;
+            if (has) {
+                const double *rc = a.rec + (size_t)idx * kRec;
 #pragma unroll
-        for (int k = 0; k < R; ++k)
-            if (has) rr[k] = a.rs ? a.rs[(size_t)k * a.n + idx] : a.r[(size_t)k * a.n + p];
-        if (a.rs) has = has && !__builtin_isnan(rr[0]);
+                for (int k = 0; k < R; ++k) {
+                    rr[k] = rc[k];
+                    mg = fmin(mg, 1.0 - fabs(rr[k]));
+                }
+                sd = rc[kRec - 1];
+            }
+            has = has && !__builtin_signbit(sd) && mg > kSettleGuard;
+        } else if (has) {
+#pragma unroll
+            for (int k = 0; k < R; ++k) rr[k] = a.r[(size_t)k * a.n + p];
+        }
         const int ngrp = (end - beg + 15) >> 4;
         for (int grp = 0; grp < ngrp; ++grp) {
             const int pl = 16 * grp + slot;   // task position of this slot's point
@@ -671,7 +686,7 @@ hipError_t launch_eval_bin(const fpts_mesh *m, int pass, int64_t n, const int32_
 hipError_t launch_eval(const fpts_mesh *m, int64_t n, const double *r, int n_fields, int field_n,
                        const double *field, double *out, const int *sorted, const int *elem_off,
                        const int *chunk_off, const int *task_elem, int64_t task_bound,
-                       hipStream_t s, const double *rs)
+                       hipStream_t s, const double *rs, const double *rec)
 {
     EvalArgs a;
     a.r = r;
@@ -685,6 +700,7 @@ hipError_t launch_eval(const fpts_mesh *m, int64_t n, const double *r, int n_fie
     a.chunk_off = chunk_off;
     a.task_elem = task_elem;
     a.rs = rs;
+    a.rec = rec;
     a.f0 = 0;
     if (field_n == m->N) a.basis = m->basis;
     else gll::fill(field_n, a.basis.z, a.basis.w);

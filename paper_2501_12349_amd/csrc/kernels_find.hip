@@ -410,8 +410,8 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_scatter(const int *total_p,
 // loads (task -> cell -> point ids and candidate ids -> coordinates and
 // records): those of the wave's next task are issued while the current one
 // is tested, level by level, so that their latency hides behind the tests.
-// Per point: number of candidates, primary candidate (smallest OBB depth,
-// lowest id on ties), and the primary's bucket count.
+// Per point: primary candidate (smallest OBB depth, lowest id on ties), its
+// rank in the primary's bucket, and whether there are other candidates.
 constexpr int kLocChunk = 32;
 
 __device__ __forceinline__ double read_lane(double v, int l)
@@ -529,11 +529,12 @@ __global__ __launch_bounds__(64) void k_locate_cells(HashView h, int n, int R, c
         }
         if (!l2) ids_of(nxt, nxt.q0, pn, minen);   // a cell without candidates
         if (!l3) data_of(nxt, nxt.q0, pn, minen, xn, rvn);
+        const int k = wave_inc(elem_cnt, prim, has && prim >= 0);
         if (has) {
-            cand[p] = make_int2(cnt, prim);   // one scattered write per point
+            // one scattered write per point
+            cand[p] = make_int2((int)((unsigned)k << 1 | (cnt > 1)), prim);
             if (prim < 0) write_not_found(p, n, R, code, elem, r, dist);
         }
-        const int k = wave_inc(elem_cnt, prim, has && prim >= 0);
         // primary and rank in bin order (coalesced), for the scatter by bins
         if (has) {
             bin_prim[cur.beg + lane] = prim;
@@ -579,37 +580,27 @@ __global__ __launch_bounds__(256) void k_primary_scatter_bins(int n, const int *
 // interior (it would overlap the primary), so the paper's rule -- first
 // INTERIOR candidate in ascending id order -- picks the same element.
 
-__device__ inline bool deep_interior(int32_t cd, const double (&rr)[3], int R)
+__device__ inline bool deep_interior(bool interior, const double (&rr)[3], int R)
 {
-    if (cd != FPTS_INTERIOR) return false;
+    if (!interior) return false;
     double m = 1.0;
     for (int a = 0; a < R; ++a) m = fmin(m, 1.0 - fabs(rr[a]));
     return m > kSettleGuard;
 }
 
-__device__ inline bool settled(int nc, int32_t cd, const double (&rr)[3], int R)
-{
-    return nc <= 1 || deep_interior(cd, rr, R);
-}
-
 // Phase D, marking: every point whose primary result leaves the search open
-// (a cell, a primary and not settled) is appended to ulist, in no particular
-// order, *ucount of them.  The other candidates of the few listed points are
-// then handled by dense wavefronts: tested where they lie among all points,
-// their candidate loops (dependent loads) kept whole wavefronts waiting.
-// A block marks up to kMarkChunk consecutive points, gathers its listed points in
-// LDS and reserves their places with one atomic: device-scope atomics on one
-// address serialise (several ns each), so one per wavefront with a listed
-// point would take longer than the loads.  All of a point's loads are
-// issued at once.
+// (a primary, other candidates and not settled) is appended to ulist, in no
+// particular order, *ucount of them.  The other candidates of the few listed
+// points are then handled by dense wavefronts: tested where they lie among
+// all points, their candidate loops (dependent loads) kept whole wavefronts
+// waiting.  A block marks up to kMarkChunk consecutive points, gathers its
+// listed points in LDS and reserves their places with one atomic:
+// device-scope atomics on one address serialise (some 16 ns each), so one
+// per wavefront with a listed point would take longer than the loads.  Four
+// points' loads per thread are issued at once.
 constexpr int kMarkChunk = 4096;
+constexpr int kMarkAhead = 4;
 
-// With rest.list (fused find + interpolate, volume and surface meshes) the
-// same pass also lists the points the interpolation over the primary list
-// leaves out -- found, but not INTERIOR at least kSettleGuard inside by the
-// primary result (the listed points among them) -- and writes NaN to the
-// interpolated values of NOT_FOUND points, so that the interpolation needs
-// no pass over all points of its own.
 __device__ inline void list_append(bool take, int p, int lane, int *lst, int &lcnt)
 {
     const unsigned long long m = __ballot(take);
@@ -621,12 +612,61 @@ __device__ inline void list_append(bool take, int p, int lane, int *lst, int &lc
     }
 }
 
-__global__ __launch_bounds__(256) void k_unsettled(int n, int R, const int *cellpt,
-                                                  const int2 *cand,
-                                                  const int32_t *code, const double *r,
-                                                  int *ulist, int *ucount, int items,
-                                                  EvalRest rest)
+// Line meshes: the marking pass over the outputs.
+__global__ __launch_bounds__(256) void k_unsettled(int n, const int2 *cand, const int32_t *code,
+                                                  const double *r, int *ulist, int *ucount,
+                                                  int items)
 {
+    __shared__ int lst[kMarkChunk];
+    __shared__ int lcnt, gbase;
+    const int lane = threadIdx.x & 63;
+    if (threadIdx.x == 0) lcnt = 0;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * items * 256 + threadIdx.x;
+    for (int it = 0; it < items; it += kMarkAhead) {
+        int2 cd[kMarkAhead];
+        int32_t co[kMarkAhead];
+        double rr[kMarkAhead];
+#pragma unroll
+        for (int u = 0; u < kMarkAhead; ++u) {
+            const int64_t p = base + (int64_t)(it + u) * 256;
+            const bool in = it + u < items && p < n;
+            cd[u] = in ? cand[p] : make_int2(0, -1);
+            co[u] = in ? code[p] : FPTS_NOT_FOUND;
+            rr[u] = in ? r[p] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < kMarkAhead; ++u) {
+            const double r3[3] = {rr[u], 0.0, 0.0};
+            const bool todo = cd[u].y >= 0 && (cd[u].x & 1) &&
+                              !deep_interior(co[u] == FPTS_INTERIOR, r3, 1);
+            list_append(todo, (int)(base + (int64_t)(it + u) * 256), lane, lst, lcnt);
+        }
+    }
+    __syncthreads();
+    const int cnt = lcnt;
+    if (threadIdx.x == 0 && cnt) gbase = atomicAdd(ucount, cnt);
+    __syncthreads();
+    for (int i = threadIdx.x; i < cnt; i += 256) ulist[gbase + i] = lst[i];
+}
+
+// Volume and surface meshes: the result records of the primary pass are
+// brought into point order -- one 32-byte gather per point, then coalesced
+// writes of the outputs -- and the points marked in the same pass.  With
+// rest.list (fused find + interpolate) the points that the interpolation
+// over the primary list leaves out are listed too -- found, but not INTERIOR
+// at least kSettleGuard inside by the primary result (the listed points
+// among them) -- and the interpolated values of NOT_FOUND points become NaN,
+// so that the interpolation needs no pass over all points of its own.
+// Points without a primary (NOT_FOUND, or kept from a hinted search) hold
+// their results already.
+template <int R>
+__global__ __launch_bounds__(256) void k_settle(int n, const int2 *cand, const int *elem_off,
+                                               const double *rec, int32_t *code, int32_t *elem,
+                                               double *r, double *dist, int *ulist, int *ucount,
+                                               int items, EvalRest rest)
+{
+    typedef double v2 __attribute__((ext_vector_type(2)));
     __shared__ int lst[kMarkChunk], elst[kMarkChunk];
     __shared__ int lcnt, ecnt, gbase, ebase;
     const int lane = threadIdx.x & 63;
@@ -635,32 +675,51 @@ __global__ __launch_bounds__(256) void k_unsettled(int n, int R, const int *cell
         ecnt = 0;
     }
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * items * 256;
-#pragma unroll 4
-    for (int it = 0; it < items; ++it) {
-        const int64_t q = base + it * 256 + threadIdx.x;
-        const int p = (int)q;
-        bool todo = false, other = false;
-        if (q < n) {
-            const int c = cellpt[p];
-            const int2 cd2 = cand[p];
-            const int prim = cd2.y, nc = cd2.x;
-            const int32_t cd = code[p];
-            double rr[3] = {0.0, 0.0, 0.0};
+    const int64_t base = (int64_t)blockIdx.x * items * 256 + threadIdx.x;
+    for (int it = 0; it < items; it += kMarkAhead) {
+        int2 cd[kMarkAhead];
+        v2 lo[kMarkAhead], hi[kMarkAhead];
+        bool in[kMarkAhead];
 #pragma unroll
-            for (int a = 0; a < 3; ++a)
-                if (a < R) rr[a] = r[(size_t)a * n + p];
-            todo = c >= 0 && prim >= 0 && !settled(nc, cd, rr, R);
+        for (int u = 0; u < kMarkAhead; ++u) {
+            const int64_t p = base + (int64_t)(it + u) * 256;
+            in[u] = it + u < items && p < n;
+            cd[u] = in[u] ? cand[p] : make_int2(0, -1);
+        }
+#pragma unroll
+        for (int u = 0; u < kMarkAhead; ++u) {
+            lo[u] = v2{0.0, 0.0};
+            hi[u] = v2{0.0, 0.0};
+            if (cd[u].y >= 0) {
+                const int64_t pos = (int64_t)elem_off[cd[u].y] + ((unsigned)cd[u].x >> 1);
+                const v2 *src = reinterpret_cast<const v2 *>(rec + pos * kRec);
+                lo[u] = src[0];
+                hi[u] = src[1];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kMarkAhead; ++u) {
+            const int64_t q = base + (int64_t)(it + u) * 256;
+            const int p = (int)q;
+            const bool has = cd[u].y >= 0;
+            const bool interior = has && !__builtin_signbit(hi[u][1]);
+            const double rr[3] = {lo[u][0], lo[u][1], R == 3 ? hi[u][0] : 0.0};
+            if (has) {
+                code[p] = interior ? FPTS_INTERIOR : FPTS_BORDER;
+                elem[p] = cd[u].y;
+                dist[p] = fabs(hi[u][1]);
+#pragma unroll
+                for (int a = 0; a < R; ++a) r[(size_t)a * n + p] = rr[a];
+            }
+            const bool deep = deep_interior(interior, rr, R);
+            list_append(has && (cd[u].x & 1) && !deep, p, lane, lst, lcnt);
             if (rest.list) {
-                const bool found = cd != FPTS_NOT_FOUND;
-                other = found && !deep_interior(cd, rr, R);
-                if (!found)
+                list_append(has && !deep, p, lane, elst, ecnt);
+                if (in[u] && !has)
                     for (int f = 0; f < rest.n_fields; ++f)
                         rest.out[(size_t)f * n + p] = __builtin_nan("");
             }
         }
-        list_append(todo, p, lane, lst, lcnt);
-        if (rest.list) list_append(other, p, lane, elst, ecnt);
     }
     __syncthreads();
     const int cnt = lcnt, ec = ecnt;
@@ -1088,18 +1147,35 @@ hipError_t launch_primary_scatter(int64_t n, int64_t nel, const int2 *cand,
     return hipGetLastError();
 }
 
-hipError_t launch_unsettled(const fpts_mesh *m, int64_t n, const int *cellpt, const int2 *cand,
+// a marking block's items per thread: 16 (4096 points) where that still
+// leaves two blocks per CU, else fewer (a block of 16 takes 19 us however few
+// points there are)
+static int mark_items(const fpts_mesh *m, int64_t n)
+{
+    return (int)std::min<int64_t>(std::max<int64_t>(n / ((int64_t)m->cus * 2 * 256), 1),
+                                  kMarkChunk / 256);
+}
+
+hipError_t launch_unsettled(const fpts_mesh *m, int64_t n, const int2 *cand,
                             const int32_t *code, const double *r, int *ulist,
-                            int *ucount, const EvalRest &rest, hipStream_t s)
+                            int *ucount, hipStream_t s)
+{
+    if (n <= 0 || m->R != 1) return n <= 0 ? hipSuccess : hipErrorInvalidValue;
+    const int items = mark_items(m, n);
+    hipLaunchKernelGGL(k_unsettled, dim3(grid_for(n, 256 * items)), dim3(256), 0, s, (int)n, cand,
+                       code, r, ulist, ucount, items);
+    return hipGetLastError();
+}
+
+hipError_t launch_settle(const fpts_mesh *m, int64_t n, const int2 *cand, const int *elem_off,
+                         const double *rec, int32_t *code, int32_t *elem, double *r, double *dist,
+                         int *ulist, int *ucount, const EvalRest &rest, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    // a block's items: 4096 where that still leaves two blocks per CU, else
-    // fewer (a block of 16 items per thread takes 19 us however few points
-    // there are)
-    const int items = (int)std::min<int64_t>(
-        std::max<int64_t>(n / ((int64_t)m->cus * 2 * 256), 1), kMarkChunk / 256);
-    hipLaunchKernelGGL(k_unsettled, dim3(grid_for(n, 256 * items)), dim3(256), 0, s, (int)n, m->R,
-                       cellpt, cand, code, r, ulist, ucount, items, rest);
+    const int items = mark_items(m, n);
+    auto k = m->R == 3 ? k_settle<3> : k_settle<2>;
+    hipLaunchKernelGGL(k, dim3(grid_for(n, 256 * items)), dim3(256), 0, s, (int)n, cand, elem_off,
+                       rec, code, elem, r, dist, ulist, ucount, items, rest);
     return hipGetLastError();
 }
 

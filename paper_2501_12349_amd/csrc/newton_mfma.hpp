@@ -1001,6 +1001,17 @@ __device__ __forceinline__ void add_counters(const Counters &cn, unsigned long l
         atomicAdd(&stats[(blockIdx.x % kStatCopies) * kStats + lane], (unsigned long long)x);
 }
 
+// A pair's result record (NewtonIO::rec).
+template <int R>
+__device__ __forceinline__ void write_record(double *rec, const double (&r)[R], double dist,
+                                             bool inside)
+{
+    typedef double v2 __attribute__((ext_vector_type(2)));
+    v2 *o = reinterpret_cast<v2 *>(rec);
+    o[0] = v2{r[0], r[1]};
+    o[1] = v2{R == 3 ? r[R - 1] : 0.0, inside ? dist : -dist};
+}
+
 // The map at GLL node `node` (packed index i + N j + N^2 k): r, the node's
 // reference point; X, the node itself; dx/dr_d = sum_m phi_m'(z_{a_d})
 // x[.. m ..], an N-term sum along direction d through the node, read from
@@ -1034,7 +1045,7 @@ __device__ __forceinline__ void node_map(const T *xl, int node, T (&r)[R], T (&X
 }
 
 // How a pair's start is given: the packed index of a GLL node per list
-// position (io.node; the nearest node), or a point r (io.start per list
+// position (io.node; the nearest node), or a point r (io.rec per list
 // position, or io.r per item).
 enum { kStartNode = 0, kStartPoint = 1, kStartEither = 2 };
 
@@ -1097,8 +1108,8 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
             for (int c = 0; c < D; ++c) b.x[c] = point_coord<D>(a, it, c);
             if constexpr (START != kStartNode) {
                 if (START == kStartPoint || !io.node) {
-                    const double *src = io.start ? io.start + idx : io.r + it;
-                    const size_t st = io.start ? (size_t)io.start_stride : (size_t)io.ostride;
+                    const double *src = io.rec ? io.rec + (size_t)idx * kRec : io.r + it;
+                    const size_t st = io.rec ? 1 : (size_t)io.ostride;
 #pragma unroll
                     for (int k = 0; k < R; ++k) b.s[k] = src[k * st];
                 }
@@ -1171,31 +1182,32 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
     // A pair is done: results out, lane free.
     auto finish = [&](bool converged) __attribute__((always_inline)) {
         if (FINAL) {
-            if (io.conv) io.conv[item] = converged ? 1 : 0;
             bool inside = true;
 #pragma unroll
             for (int k = 0; k < R; ++k) inside = inside && (fabs(r[k]) < T(1));
             if (R < D) inside = inside && (cur.f < T(a.eps_d));
-            io.code[item] = inside ? FPTS_INTERIOR : FPTS_BORDER;
-            if (io.elem) io.elem[item] = e;
-            io.dist[item] = sqrt((double)cur.f);
-            if (io.rs) {
-                double mg = 1.0;
+            double rr[R];
 #pragma unroll
-                for (int k = 0; k < R; ++k) mg = fmin(mg, 1.0 - fabs((double)r[k]));
-                const bool settles = inside && mg > kSettleGuard;
+            for (int k = 0; k < R; ++k) rr[k] = (double)r[k];
+            if (io.rec) {
+                write_record<R>(io.rec + (size_t)pos * kRec, rr, sqrt((double)cur.f), inside);
+            } else {
+                // (the hinted search of particle tracking)
+                if (io.conv) io.conv[item] = converged ? 1 : 0;
+                io.code[item] = inside ? FPTS_INTERIOR : FPTS_BORDER;
+                if (io.elem) io.elem[item] = e;
+                io.dist[item] = sqrt((double)cur.f);
 #pragma unroll
-                for (int k = 0; k < R; ++k)
-                    io.rs[(size_t)k * io.rs_stride + pos] =
-                        settles ? (double)r[k] : __builtin_nan("");
+                for (int k = 0; k < R; ++k) io.r[(size_t)k * io.ostride + item] = rr[k];
             }
-        }
+        } else {
 #pragma unroll
-        for (int k = 0; k < R; ++k) {
-            if (!FINAL && io.start)   // the FP64 phase's start
-                io.start[(size_t)k * io.start_stride + pos] = (double)r[k];
-            else
-                io.r[(size_t)k * io.ostride + item] = (double)r[k];
+            for (int k = 0; k < R; ++k) {
+                if (io.rec)   // the FP64 phase's start
+                    io.rec[(size_t)pos * kRec + k] = (double)r[k];
+                else
+                    io.r[(size_t)k * io.ostride + item] = (double)r[k];
+            }
         }
         state = S_FREE;
     };
@@ -1464,12 +1476,12 @@ __device__ __forceinline__ int run_element(const NewtonArgs &a, int e, int q0, i
 // of element b, a pair per lane and no refill; a column group takes 16 / NB
 // columns of each element, so that the sweeps and the updates of NB sparse
 // elements cost what those of one do.  Second derivatives in the wave.
-// has: the lane has a pair, of element e; item: where its results go; pos:
-// kFace, its list position (of its park record and of io.rs); node: kResolve,
-// its start node; xs: its point.
+// has: the lane has a pair; item: kResolve, where its results go; pos: kFace,
+// its list position (of its park record and its result record); node:
+// kResolve, its start node; xs: its point.
 template <int D, int R, int N, int KIND, int NB>
 __device__ __forceinline__ void run_few(const NewtonArgs &a, const double *xl, double *tab,
-                                        double *qb, int lane, bool has, int e, int item, int pos,
+                                        double *qb, int lane, bool has, int item, int pos,
                                         int node, const double (&xs)[D], Counters &cn)
 {
     typedef unsigned long long u64;
@@ -1537,26 +1549,19 @@ __device__ __forceinline__ void run_few(const NewtonArgs &a, const double *xl, d
     }
 #pragma unroll
     for (int k = 0; k < R; ++k) q[k] = r[k];
-    auto finish = [&](bool converged) __attribute__((always_inline)) {
+    auto finish = [&]() __attribute__((always_inline)) {
         bool inside = true;
 #pragma unroll
         for (int k = 0; k < R; ++k) inside = inside && (fabs(r[k]) < 1.0);
         if (R < D) inside = inside && (cur.f < a.eps_d);
-        if (io.conv) io.conv[item] = converged ? 1 : 0;
-        io.code[item] = inside ? FPTS_INTERIOR : FPTS_BORDER;
-        if (io.elem) io.elem[item] = e;
-        io.dist[item] = sqrt(cur.f);
-        if (KIND == kFace && io.rs) {
-            double mg = 1.0;
+        if constexpr (KIND == kFace) {
+            write_record<R>(io.rec + (size_t)pos * kRec, r, sqrt(cur.f), inside);
+        } else {
+            io.code[item] = inside ? FPTS_INTERIOR : FPTS_BORDER;
+            io.dist[item] = sqrt(cur.f);
 #pragma unroll
-            for (int k = 0; k < R; ++k) mg = fmin(mg, 1.0 - fabs(r[k]));
-            const bool settles = inside && mg > kSettleGuard;
-#pragma unroll
-            for (int k = 0; k < R; ++k)
-                io.rs[(size_t)k * io.rs_stride + pos] = settles ? r[k] : __builtin_nan("");
+            for (int k = 0; k < R; ++k) io.r[(size_t)k * io.ostride + item] = r[k];
         }
-#pragma unroll
-        for (int k = 0; k < R; ++k) io.r[(size_t)k * io.ostride + item] = r[k];
         state = S_FREE;
     };
     // A lane's place among the lanes of `mask` in its element, and the
@@ -1658,7 +1663,7 @@ __device__ __forceinline__ void run_few(const NewtonArgs &a, const double *xl, d
 #pragma unroll
                     for (int k = 0; k < R; ++k) r[k] = q[k];
                     cur.f = fmax(cur.f - pred, 0.0);
-                    finish(true);
+                    finish();
                 }
             }
         }
@@ -1734,7 +1739,7 @@ __device__ __forceinline__ void run_few(const NewtonArgs &a, const double *xl, d
             for (int c = 0; c < D; ++c) dx[c] = dxn[c];
             hb_ok = false;
         }
-        if (((stepm >> lane) & 1) && pass >= max_iter) finish(false);
+        if (((stepm >> lane) & 1) && pass >= max_iter) finish();
         else if (moved && pass > 0 && on_face(r)) state = S_WAIT;   // next pass: beta = 1
     }
 }
@@ -2279,7 +2284,7 @@ __device__ __forceinline__ void few_body(const NewtonArgs &a)
                 if (j == k) node = bi;
             }
         }
-        run_few<D, R, N, KIND, NB>(a, xl, tab, qb, lane, has, e, item, pos, node, xs, cn);
+        run_few<D, R, N, KIND, NB>(a, xl, tab, qb, lane, has, item, pos, node, xs, cn);
     }
     add_counters(cn, io.stats, lane);
 }
@@ -2348,15 +2353,9 @@ k_resolve_overflow(NewtonArgs a, HashView h)
     la.io.list = ov_item;
     la.io.slot_pt = ov_pt;
     la.io.code = ov_code;
-    la.io.elem = nullptr;
     la.io.r = io.ov_dbl;
     la.io.ostride = G;
     la.io.dist = io.ov_dbl + (size_t)R * G;
-    la.io.start = nullptr;
-    la.io.rs = nullptr;
-    la.io.conv = nullptr;
-    la.io.park_meta = nullptr;
-    la.io.polish = 0;
     if (lane == 0) ov_item[b] = b;
     Counters cn;
     for (int i = b; i < cnt; i += G) {
@@ -2380,7 +2379,7 @@ k_resolve_overflow(NewtonArgs a, HashView h)
             __syncthreads();
             stage_nodes<double, D, R, N>(xl, a.nodes + (size_t)e * D * S::NP, lane);
             const int bi = nearest_staged<D, R, N, kWave>(xl, x, lane);
-            run_few<D, R, N, kResolve, 1>(la, xl, tab, qb, lane, lane == 0, e, b, 0, bi, x, cn);
+            run_few<D, R, N, kResolve, 1>(la, xl, tab, qb, lane, lane == 0, b, 0, bi, x, cn);
             // lane 0, the pair's lane, wrote the result
             int cd = 0;
             double dd = 0.0, rr[R];
