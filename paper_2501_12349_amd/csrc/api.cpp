@@ -220,7 +220,7 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     // an Interpolate in the same workspace leaves them readable.
     w.zero = c.at;
     w.cell_cnt = c.take(I * ncell);
-    w.elem_cnt = c.take(I * m->nel);
+    w.elem_cnt = c.take(I * m->nel * elem_stride(m->nel));
     w.elem_cnt2 = c.take(I * m->nel);
     w.park_cnt = c.take(I * m->nel);
     w.counters = c.take(I * kCounters);
@@ -234,7 +234,7 @@ EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n)
     EvalWs w;
     Cursor c;
     // zeroed before the points are binned: [0, zero_end)
-    w.elem_cnt = c.take(sizeof(int) * m->nel);
+    w.elem_cnt = c.take(sizeof(int) * m->nel * elem_stride(m->nel));
     w.scount = c.take(sizeof(int));
     w.zero_end = c.at;
     w.elem_off = c.take(sizeof(int) * (m->nel + 1));
@@ -347,7 +347,7 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
         chk(launch_locate_cells(m, n, d_pts, pts4, pbin, cell_poff, cell_choff, ncell, task_cell,
                                 w.tb_cell, cand, elem_cnt, rank, bin_prim, d_code,
                                 d_elem, d_r, d_dist, s));
-        UnitScan es{elem_cnt, nel, tmp, elem_off, chunk_off, task_elem};
+        UnitScan es{elem_cnt, nel, tmp, elem_off, chunk_off, task_elem, kChunk, elem_stride(nel)};
         if (len > kChunk) {
             es.off2 = newt_off;
             es.task2 = newt_task;
@@ -637,11 +637,13 @@ int fpts_eval_order(fpts_mesh *m, int64_t n, const int32_t *d_code, const int32_
     };
     {
         Span sp(m, 4, s);
-        chk(launch_zero2(elem_cnt, m->nel, nullptr, 0, s));
+        chk(launch_zero2(elem_cnt, m->nel * elem_stride(m->nel), nullptr, 0, s));
         chk(launch_eval_bin(m, 0, n, d_code, d_elem, nullptr, nullptr, n_fields, d_out, elem_cnt,
                             nullptr, rank, nullptr, s));
         chk(launch_unit_scan(
-            UnitScan{elem_cnt, m->nel, tmp, elem_off, chunk_off, task_elem}, tb, s));
+            UnitScan{elem_cnt, m->nel, tmp, elem_off, chunk_off, task_elem, kChunk,
+                     elem_stride(m->nel)},
+            tb, s));
         chk(launch_eval_bin(m, 1, n, d_code, d_elem, nullptr, nullptr, n_fields, d_out, nullptr,
                             elem_off,
                             rank, sorted, s));
@@ -879,7 +881,8 @@ int fpts_lpt_step(fpts_mesh *m, const fpts_lpt_params *p, int64_t n, int first, 
         Span sp(m, 0, s);
         chk(launch_zero2(at<int>(sub, w.zero), (w.total - w.zero) / sizeof(int), nullptr, 0, s));
         chk(launch_hint(m, 0, n, d_code, d_elem, d_r, cand, elem_cnt, rank, nullptr, s));
-        chk(launch_unit_scan(UnitScan{elem_cnt, m->nel, tmp, elem_off, chunk_off, task_elem},
+        chk(launch_unit_scan(UnitScan{elem_cnt, m->nel, tmp, elem_off, chunk_off, task_elem,
+                                      kChunk, elem_stride(m->nel)},
                              w.scan_blocks, s));
         chk(launch_primary_scatter(n, m->nel, cand, elem_off, rank, sorted, s));
     }
@@ -983,7 +986,9 @@ int fpts_find_eval(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code
         if (split)
             chk(launch_eval_split(m, n, d_elem, erank, elem_cnt, nullptr, nullptr, nullptr,
                                   nullptr, 0, s));
-        chk(launch_unit_scan(UnitScan{elem_cnt, m->nel, tmp, eoff, choff, etask}, tb, s));
+        chk(launch_unit_scan(UnitScan{elem_cnt, m->nel, tmp, eoff, choff, etask, kChunk,
+                                      elem_stride(m->nel)},
+                             tb, s));
         if (split)
             chk(launch_eval_split(m, n, d_elem, erank, elem_cnt, eoff, esorted, slist, scount, 1,
                                   s));

@@ -27,7 +27,7 @@ constexpr int kSparseMax = 4;
 // place point ids at their ranks in their element's bucket.  With `cand`
 // (fused find + interpolate) the points that their primary result settled
 // are left out: the fused pass over Find's primary list has them.
-__global__ __launch_bounds__(256) void k_eval_bin(int pass, int n, int nel, int R,
+__global__ __launch_bounds__(256) void k_eval_bin(int pass, int n, int nel, int es, int R,
                                                  const int32_t *code, const int32_t *elem,
                                                  const double *r, const int2 *cand,
                                                  int n_fields, double *out, int *elem_cnt,
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(256) void k_eval_bin(int pass, int n, int nel, int 
         done = mg > kSettleGuard;
     }
     const bool bin = found && !done;
-    const int k = wave_inc(elem_cnt, e, bin);
+    const int k = wave_inc(elem_cnt, e * es, bin);
     if (in) rank[p] = bin ? k : -1;
     if (in && !found)
         for (int f = 0; f < n_fields; ++f) out[(size_t)f * n + p] = __builtin_nan("");
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256) void k_eval_bin(int pass, int n, int nel, int 
 // k_eval_bin over a list of found points (grid-stride; the loop bound is
 // uniform per wavefront, as wave_inc needs)
 __global__ __launch_bounds__(256) void k_eval_bin_list(int pass, const int *list,
-                                                      const int *count, int nel,
+                                                      const int *count, int nel, int es,
                                                       const int32_t *elem, int *elem_cnt,
                                                       const int *elem_off, int *rank,
                                                       int *sorted)
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void k_eval_bin_list(int pass, const int *list
         const int e = act ? elem[p] : -1;
         const bool ok = act && e >= 0 && e < nel;
         if (pass == 0) {
-            const int k = wave_inc(elem_cnt, e, ok);
+            const int k = wave_inc(elem_cnt, e * es, ok);
             if (act) rank[i] = ok ? k : -1;
         } else if (ok && rank[i] >= 0) {
             sorted[elem_off[e] + rank[i]] = p;
@@ -498,10 +498,10 @@ __global__ __launch_bounds__(256) void k_eval_sparse(EvalArgs a, const int32_t *
 
 // Elements with at most kSparseMax binned points drop out of the bucket
 // counts (their points go to the per-point list).
-__global__ __launch_bounds__(256) void k_eval_dense(int nel, int *elem_cnt)
+__global__ __launch_bounds__(256) void k_eval_dense(int nel, int es, int *elem_cnt)
 {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < nel && elem_cnt[e] <= kSparseMax) elem_cnt[e] = 0;
+    if (e < nel && elem_cnt[e * es] <= kSparseMax) elem_cnt[e * es] = 0;
 }
 
 // Pass 1 with the split: a binned point (rank >= 0) of a dense element goes
@@ -512,7 +512,7 @@ __global__ __launch_bounds__(256) void k_eval_dense(int nel, int *elem_cnt)
 constexpr int kSplitChunk = 4096;
 
 __global__ __launch_bounds__(256) void k_eval_split(int n, const int32_t *elem, const int *rank,
-                                                   const int *dense_cnt, const int *elem_off,
+                                                   const int *dense_cnt, int es, const int *elem_off,
                                                    int *sorted, int *list, int *count)
 {
     __shared__ int lst[kSplitChunk];
@@ -528,7 +528,7 @@ __global__ __launch_bounds__(256) void k_eval_split(int n, const int32_t *elem, 
         if (q < n) {
             const int k = rank[p], e = elem[p];
             if (k >= 0) {
-                if (dense_cnt[e] > 0) sorted[elem_off[e] + k] = p;
+                if (dense_cnt[e * es] > 0) sorted[elem_off[e] + k] = p;
                 else sp = true;
             }
         }
@@ -667,7 +667,7 @@ hipError_t launch_eval_bin_list(const fpts_mesh *m, int pass, const int *list, c
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((cap + 255) / 256,
                                                                  (int64_t)m->cus * 16));
     hipLaunchKernelGGL(k_eval_bin_list, dim3(grid), dim3(256), 0, s, pass, list, count,
-                       (int)m->nel, elem, elem_cnt, elem_off, rank, sorted);
+                       (int)m->nel, elem_stride(m->nel), elem, elem_cnt, elem_off, rank, sorted);
     return hipGetLastError();
 }
 
@@ -678,7 +678,7 @@ hipError_t launch_eval_bin(const fpts_mesh *m, int pass, int64_t n, const int32_
 {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_eval_bin, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, pass,
-                       (int)n, (int)m->nel, m->R, code, elem, r, cand, n_fields, out,
+                       (int)n, (int)m->nel, elem_stride(m->nel), m->R, code, elem, r, cand, n_fields, out,
                        elem_cnt, elem_off, rank, sorted);
     return hipGetLastError();
 }
@@ -737,11 +737,11 @@ hipError_t launch_eval_split(const fpts_mesh *m, int64_t n, const int32_t *elem,
     if (n <= 0) return hipSuccess;
     if (phase == 0) {
         hipLaunchKernelGGL(k_eval_dense, dim3((unsigned)((m->nel + 255) / 256)), dim3(256), 0, s,
-                           (int)m->nel, elem_cnt);
+                           (int)m->nel, elem_stride(m->nel), elem_cnt);
     } else {
         hipLaunchKernelGGL(k_eval_split, dim3((unsigned)((n + kSplitChunk - 1) / kSplitChunk)),
-                           dim3(256), 0, s, (int)n, elem, rank, elem_cnt, elem_off, sorted, list,
-                           count);
+                           dim3(256), 0, s, (int)n, elem, rank, elem_cnt, elem_stride(m->nel),
+                           elem_off, sorted, list, count);
     }
     return hipGetLastError();
 }

@@ -37,7 +37,11 @@ __device__ __forceinline__ int tasks_of(int cnt, int len) { return (cnt + len - 
 
 __device__ __forceinline__ void load_counts(const UnitScan &u, int64_t base, int (&v)[kUsItems])
 {
-    if (base + kUsItems <= u.n) {
+    if (u.stride > 1) {
+#pragma unroll
+        for (int k = 0; k < kUsItems; ++k)
+            v[k] = base + k < u.n ? u.cnt[(base + k) * u.stride] : 0;
+    } else if (base + kUsItems <= u.n) {
         const int4 *p = reinterpret_cast<const int4 *>(u.cnt + base);   // 256-byte aligned arrays
         const int4 x = p[0], y = p[1];
         v[0] = x.x;
@@ -426,7 +430,7 @@ __global__ __launch_bounds__(64) void k_locate_cells(HashView h, int n, int R, c
                                                     const int *pbin, const int *cell_poff,
                                                     const int *cell_choff, int ncell,
                                                     const int *task_cell, int2 *cand,
-                                                    int *elem_cnt, int *rank,
+                                                    int *elem_cnt, int es, int *rank,
                                                     int *bin_prim, int32_t *code, int32_t *elem,
                                                     double *r, double *dist)
 {
@@ -529,7 +533,7 @@ __global__ __launch_bounds__(64) void k_locate_cells(HashView h, int n, int R, c
         }
         if (!l2) ids_of(nxt, nxt.q0, pn, minen);   // a cell without candidates
         if (!l3) data_of(nxt, nxt.q0, pn, minen, xn, rvn);
-        const int k = wave_inc(elem_cnt, prim, has && prim >= 0);
+        const int k = wave_inc(elem_cnt, prim * es, has && prim >= 0);
         if (has) {
             // one scattered write per point
             cand[p] = make_int2((int)((unsigned)k << 1 | (cnt > 1)), prim);
@@ -915,7 +919,7 @@ inline int grid_for(int64_t n, int block) { return (int)((n + block - 1) / block
 // on entry) INTERIOR at least kSettleGuard inside the reference box: no
 // other element can hold them in its interior, so that result is the one
 // the full search gives, and they are kept.
-__global__ __launch_bounds__(256) void k_hint(int pass, int n, int nel, int R,
+__global__ __launch_bounds__(256) void k_hint(int pass, int n, int nel, int es, int R,
                                              const int32_t *code, const int32_t *elem,
                                              const double *r, int2 *cand, int *elem_cnt,
                                              int *rank, int *keep)
@@ -926,7 +930,7 @@ __global__ __launch_bounds__(256) void k_hint(int pass, int n, int nel, int R,
         const int e = in && code[p] == FPTS_INTERIOR ? elem[p] : -1;
         const bool ok = e >= 0 && e < nel;
         if (in) cand[p] = make_int2(ok ? 1 : 0, ok ? e : -1);
-        const int k = wave_inc(elem_cnt, e, ok);
+        const int k = wave_inc(elem_cnt, e * es, ok);
         if (ok) rank[p] = k;
     } else if (in) {
         bool k = cand[p].y >= 0 && code[p] == FPTS_INTERIOR && keep[p] == 1;
@@ -1123,7 +1127,7 @@ hipError_t launch_locate_cells(const fpts_mesh *m, int64_t n, const double *pts,
                        : (pts4 ? k_locate_cells<3, true> : k_locate_cells<3, false>);
     hipLaunchKernelGGL(k, dim3(task_grid(task_bound, m->cus)), dim3(64), 0, s, h, (int)n, m->R,
                        pts, pts4, pbin, cell_poff, cell_choff, (int)ncell, task_cell, cand,
-                       elem_cnt, rank, bin_prim, code, elem, r, dist);
+                       elem_cnt, elem_stride(m->nel), rank, bin_prim, code, elem, r, dist);
     return hipGetLastError();
 }
 
@@ -1227,7 +1231,8 @@ hipError_t launch_hint(const fpts_mesh *m, int pass, int64_t n, const int32_t *c
 {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_hint, dim3(grid_for(n, 256)), dim3(256), 0, s, pass, (int)n,
-                       (int)m->nel, m->R, code, elem, r, cand, elem_cnt, rank, keep);
+                       (int)m->nel, elem_stride(m->nel), m->R, code, elem, r, cand, elem_cnt, rank,
+                       keep);
     return hipGetLastError();
 }
 
