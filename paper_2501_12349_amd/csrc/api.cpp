@@ -95,6 +95,15 @@ int newton_task_len(const fpts_mesh *m, int64_t n, int64_t ncell)
     return (int)std::min<int64_t>(std::max<int64_t>((per + kChunk - 1) / kChunk, 1), 16) * kChunk;
 }
 
+// Points per task of the interpolation at most, likewise (its waves: 16 per
+// CU in the grid); line meshes take kChunk.
+int eval_task_len(const fpts_mesh *m, int64_t n)
+{
+    if (m->R < 2) return kChunk;
+    const int64_t per = n / ((int64_t)m->cus * 16 * 4);
+    return (int)std::min<int64_t>(std::max<int64_t>((per + kChunk - 1) / kChunk, 1), 16) * kChunk;
+}
+
 void clear_events(fpts_mesh *m)
 {
     for (auto &v : m->ev) {
@@ -229,7 +238,7 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     return w;
 }
 
-EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n)
+EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n, bool own)
 {
     EvalWs w;
     Cursor c;
@@ -245,6 +254,9 @@ EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n)
     w.tb_elem = task_bound(n, m->nel);
     w.task_elem = c.take(sizeof(int) * w.tb_elem);
     w.slist = c.take(sizeof(int) * std::max<int64_t>(n, 1));
+    const bool recs = own && m->R >= 2;
+    w.erec = c.take(recs ? sizeof(double) * kRec * n : 1);
+    w.tmp = c.take(recs ? sizeof(double) * 4 * n : 1);
     w.total = c.at;
     return w;
 }
@@ -598,7 +610,7 @@ int fpts_find(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
 size_t fpts_eval_workspace_size(const fpts_mesh *m, int64_t n)
 {
     if (!m || n < 0 || n > INT32_MAX - 1) return 0;
-    return eval_ws_layout(m, n).total;
+    return eval_ws_layout(m, n, true).total;
 }
 
 int fpts_eval(fpts_mesh *m, int64_t n, const int32_t *d_code, const int32_t *d_elem,
@@ -619,7 +631,7 @@ int fpts_eval_order(fpts_mesh *m, int64_t n, const int32_t *d_code, const int32_
     if (n == 0) return FPTS_OK;
     if (!d_code || !d_elem || !d_r || !d_field || !d_out || !d_ws) return FPTS_EINVAL;
     if (((uintptr_t)d_ws & 255) != 0) return FPTS_EINVAL;
-    const EvalWs w = eval_ws_layout(m, n);
+    const EvalWs w = eval_ws_layout(m, n, true);
     if (ws_bytes < w.total) return FPTS_EINVAL;
     if (sticky_error()) return FPTS_EDEVICE;
     hipStream_t s = (hipStream_t)stream;
@@ -630,6 +642,7 @@ int fpts_eval_order(fpts_mesh *m, int64_t n, const int32_t *d_code, const int32_
     int *tmp = at<int>(d_ws, w.scan_tmp);
     int *sorted = at<int>(d_ws, w.sorted);
     int *task_elem = at<int>(d_ws, w.task_elem);
+    double *erec = m->R >= 2 ? at<double>(d_ws, w.erec) : nullptr;
     const int64_t tb = scan_tmp_blocks(m->nel);
     hipError_t e = hipSuccess;
     auto chk = [&](hipError_t x) {
@@ -639,19 +652,28 @@ int fpts_eval_order(fpts_mesh *m, int64_t n, const int32_t *d_code, const int32_
         Span sp(m, 4, s);
         chk(launch_zero2(elem_cnt, m->nel * elem_stride(m->nel), nullptr, 0, s));
         chk(launch_eval_bin(m, 0, n, d_code, d_elem, nullptr, nullptr, n_fields, d_out, elem_cnt,
-                            nullptr, rank, nullptr, s));
+                            nullptr, rank, nullptr, nullptr, s));
         chk(launch_unit_scan(
-            UnitScan{elem_cnt, m->nel, tmp, elem_off, chunk_off, task_elem, kChunk,
+            UnitScan{elem_cnt, m->nel, tmp, elem_off, chunk_off, task_elem, eval_task_len(m, n),
                      elem_stride(m->nel)},
             tb, s));
-        chk(launch_eval_bin(m, 1, n, d_code, d_elem, nullptr, nullptr, n_fields, d_out, nullptr,
-                            elem_off,
-                            rank, sorted, s));
+        chk(launch_eval_bin(m, 1, n, d_code, d_elem, d_r, nullptr, n_fields, d_out, nullptr,
+                            elem_off, rank, sorted, erec, s));
     }
     {
         Span sp(m, 5, s);
-        chk(launch_eval(m, n, d_r, n_fields, field_nodes_1d, d_field, d_out, sorted, elem_off,
-                        chunk_off, task_elem, w.tb_elem, s));
+        EvalList l;
+        l.sorted = sorted;
+        l.elem_off = elem_off;
+        l.chunk_off = chunk_off;
+        l.task_elem = task_elem;
+        l.task_bound = w.tb_elem;
+        l.r = d_r;
+        l.erec = erec;
+        l.tmp = m->R >= 2 ? at<double>(d_ws, w.tmp) : nullptr;
+        l.elem = d_elem;
+        l.rank = rank;
+        chk(launch_eval(m, n, n_fields, field_nodes_1d, d_field, d_out, l, s));
     }
     if (m->profiling) m->prof_eval++;
     return e == hipSuccess ? FPTS_OK : FPTS_EDEVICE;
@@ -800,7 +822,7 @@ size_t fpts_lpt_workspace_size(const fpts_mesh *m, int64_t n)
     if (!m || n < 0 || n > INT32_MAX - 1) return 0;
     const size_t fw = fpts_find_workspace_size(m, n);
     if (fw == 0) return 0;
-    const size_t ew = eval_ws_layout(m, n).total;
+    const size_t ew = eval_ws_layout(m, n, true).total;
     const size_t nn = (size_t)std::max<int64_t>(n, 1);
     return align_up(sizeof(double) * (size_t)m->D * nn) + align_up(sizeof(int) * nn) +
            std::max(fw, ew);
@@ -908,7 +930,7 @@ size_t fpts_find_eval_workspace_size(const fpts_mesh *m, int64_t n)
     const size_t fw = fpts_find_workspace_size(m, n);
     if (fw == 0) return 0;
     const size_t nn = (size_t)std::max<int64_t>(n, 1);
-    return fw + align_up(eval_ws_layout(m, n).total) +
+    return fw + align_up(eval_ws_layout(m, n, false).total) +
            (m->R == 1 ? align_up(sizeof(double) * nn) : 0);
 }
 
@@ -929,7 +951,7 @@ int fpts_find_eval(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code
     // [find workspace][interpolation workspace], and on line meshes [n]
     // results in list order (the other meshes' are in the find workspace)
     const FindWs w = find_ws_layout(m, n);
-    const EvalWs v = eval_ws_layout(m, n);
+    const EvalWs v = eval_ws_layout(m, n, false);
     void *ews = static_cast<char *>(d_ws) + w.total;
     double *rs = m->R == 1 ? at<double>(d_ws, w.total + align_up(v.total)) : nullptr;
     const double *rec = m->R == 1 ? nullptr : at<double>(d_ws, w.rec);
@@ -963,8 +985,27 @@ int fpts_find_eval(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code
         // points the primary pass settled: Find's own element buckets, r in
         // list order (no re-binning, no gather of r)
         Span sp(m, 5, s);
-        chk(launch_eval(m, n, nullptr, n_fields, field_nodes_1d, d_field, d_out, sorted,
-                        elem_off, chunk_off, task_elem, w.tb_elem, s, rs, rec));
+        EvalList l;
+        l.sorted = sorted;
+        l.elem_off = elem_off;
+        l.chunk_off = chunk_off;
+        l.task_elem = task_elem;
+        l.task_bound = w.tb_elem;
+        l.rs = rs;
+        l.rec = rec;
+        if (m->R >= 2) {
+            // the Newton pass's tasks; the park records are no longer
+            // needed, and longer than the values
+            static_assert(sizeof(int4) + sizeof(double) * 3 >= sizeof(double) * 4, "tmp");
+            const int len = newton_task_len(m, n, w.ncell);
+            if (len > kChunk) {
+                l.chunk_off = at<int>(d_ws, w.cell_choff);
+                l.task_elem = at<int>(d_ws, w.task_cell);
+            }
+            l.tmp = at<double>(d_ws, w.park_meta);
+            l.cand = cand;
+        }
+        chk(launch_eval(m, n, n_fields, field_nodes_1d, d_field, d_out, l, s));
     }
     {
         // the rest (settled by the second search, BORDER, NOT_FOUND): the
@@ -981,7 +1022,7 @@ int fpts_find_eval(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code
                                      nullptr, s));
         } else {
             chk(launch_eval_bin(m, 0, n, d_code, d_elem, d_r, cand, n_fields, d_out, elem_cnt,
-                                nullptr, erank, nullptr, s));
+                                nullptr, erank, nullptr, nullptr, s));
         }
         if (split)
             chk(launch_eval_split(m, n, d_elem, erank, elem_cnt, nullptr, nullptr, nullptr,
@@ -997,12 +1038,18 @@ int fpts_find_eval(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code
                                      esorted, s));
         else
             chk(launch_eval_bin(m, 1, n, d_code, d_elem, d_r, cand, n_fields, d_out, nullptr,
-                                eoff, erank, esorted, s));
+                                eoff, erank, esorted, nullptr, s));
     }
     {
         Span sp(m, 5, s);
-        chk(launch_eval(m, n, d_r, n_fields, field_nodes_1d, d_field, d_out, esorted, eoff,
-                        choff, etask, v.tb_elem, s));
+        EvalList l;
+        l.sorted = esorted;
+        l.elem_off = eoff;
+        l.chunk_off = choff;
+        l.task_elem = etask;
+        l.task_bound = v.tb_elem;
+        l.r = d_r;
+        chk(launch_eval(m, n, n_fields, field_nodes_1d, d_field, d_out, l, s));
         if (m->R == 1)
             chk(launch_eval_sparse(m, n, d_r, n_fields, field_nodes_1d, d_field, d_out, d_elem,
                                    slist, scount, s));

@@ -228,7 +228,7 @@ struct FindWs {
 
 struct EvalWs {
     size_t elem_cnt, elem_off, rank, chunk_off, scan_tmp, sorted, task_elem, slist, scount,
-        zero_end, total;
+        zero_end, erec, tmp, total;
     int64_t tb_elem;
 };
 
@@ -410,7 +410,9 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
 
 // workspace layouts (api.cpp)
 FindWs find_ws_layout(const fpts_mesh *m, int64_t n);
-EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n);
+// own: the layout of an Interpolate call of its own, with its point records
+// and values in list order (else: the second pass of the fused call)
+EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n, bool own);
 
 // launchers (kernels_*.hip); all return hipError_t of the last launch
 // zeroes two ranges of ints (counts may be 0) in one launch
@@ -555,13 +557,24 @@ hipError_t launch_eval_bin_list(const fpts_mesh *m, int pass, const int *list, c
 hipError_t launch_eval_bin(const fpts_mesh *m, int pass, int64_t n, const int32_t *code,
                            const int32_t *elem, const double *r, const int2 *cand,
                            int n_fields, double *out, int *elem_cnt, const int *elem_off,
-                           int *rank, int *sorted, hipStream_t s);
+                           int *rank, int *sorted, double *erec, hipStream_t s);
+// A list of points grouped by element (elem_off) and its tasks (chunk_off,
+// task_elem: on line meshes up to kChunk points each, else the even parts of
+// an element's list), where its r comes from (EvalArgs), and optionally tmp
+// [n][4] with what leads from a point to its list position: Find's cand, or
+// the point's elem and rank.
+struct EvalList {
+    const int *sorted = nullptr, *elem_off = nullptr, *chunk_off = nullptr, *task_elem = nullptr;
+    int64_t task_bound = 0;
+    const double *r = nullptr, *rs = nullptr, *rec = nullptr, *erec = nullptr;
+    double *tmp = nullptr;
+    const int2 *cand = nullptr;
+    const int32_t *elem = nullptr;
+    const int *rank = nullptr;
+};
 // field_n: GLL nodes per direction of the field (its own order, 2..kMaxN)
-hipError_t launch_eval(const fpts_mesh *m, int64_t n, const double *r, int n_fields, int field_n,
-                       const double *field, double *out, const int *sorted,
-                       const int *elem_off, const int *chunk_off, const int *task_elem,
-                       int64_t task_bound, hipStream_t s, const double *rs = nullptr,
-                       const double *rec = nullptr);
+hipError_t launch_eval(const fpts_mesh *m, int64_t n, int n_fields, int field_n,
+                       const double *field, double *out, const EvalList &l, hipStream_t s);
 hipError_t launch_nodes32(const fpts_mesh *m, hipStream_t s);
 // score rows of the nearest-node contraction: per element and node j,
 // (-2 x_j, -2 y_j, -2 z_j, |x_j|^2) element-local (D = 2: (-2x, -2y, |x|^2, 0)),

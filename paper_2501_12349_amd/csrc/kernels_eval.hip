@@ -18,13 +18,18 @@
 namespace fpts {
 namespace {
 
+// fields per launch from which, and nodes per direction up to which the
+// values go through list order (launch_eval)
+constexpr int kSpreadFields = 3, kSpreadNodes = 6;
+
 // fused find + interpolate: elements holding at most this many of the
 // remaining points have them interpolated one lane per point
 constexpr int kSparseMax = 4;
 
 // pass 0: count points per element, keep each point's rank in its bucket
 // (-1 for points not binned) and write NaN for NOT_FOUND points; pass 1:
-// place point ids at their ranks in their element's bucket.  With `cand`
+// place point ids (with their r, as records, unless erec is null) at their
+// ranks in their element's bucket.  With `cand`
 // (fused find + interpolate) the points that their primary result settled
 // are left out: the fused pass over Find's primary list has them.
 __global__ __launch_bounds__(256) void k_eval_bin(int pass, int n, int nel, int es, int R,
@@ -32,7 +37,7 @@ __global__ __launch_bounds__(256) void k_eval_bin(int pass, int n, int nel, int 
                                                  const double *r, const int2 *cand,
                                                  int n_fields, double *out, int *elem_cnt,
                                                  const int *elem_off, int *rank,
-                                                 int *sorted)
+                                                 int *sorted, double *erec)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     const bool in = p < n;
@@ -40,7 +45,23 @@ __global__ __launch_bounds__(256) void k_eval_bin(int pass, int n, int nel, int 
         // rank[p] < 0: not binned
         if (!in) return;
         const int k = rank[p], e = elem[p];
-        if (k >= 0) sorted[elem_off[e] + k] = p;
+        if (erec) {
+            // volume and surface meshes: r and the id as one record (a
+            // scattered write of 32 bytes costs what one of 4 does, and the
+            // interpolation then reads its points in order)
+            double rr[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+                if (a < R) rr[a] = r[(size_t)a * n + p];
+            if (k >= 0) {
+                typedef double v2 __attribute__((ext_vector_type(2)));
+                v2 *o = reinterpret_cast<v2 *>(erec + (size_t)(elem_off[e] + k) * kRec);
+                o[0] = v2{rr[0], rr[1]};
+                o[1] = v2{rr[2], __hiloint2double(0, p)};
+            }
+        } else if (k >= 0) {
+            sorted[elem_off[e] + k] = p;
+        }
         return;
     }
     // pass 0, no early exit (wave_inc needs every lane); all of a point's
@@ -121,19 +142,20 @@ struct EvalArgs {
     double *out;            // [n_fields][n]
     const int *sorted;
     const int *elem_off;
-    const int *chunk_off;
-    const int *task_elem;   // task -> element (task grid)
+    const int *chunk_off;   // task offsets per element
+    const int *task_elem;   // task -> element
     Basis basis;
-    // fused mode: `sorted` is the primary list of Find, and r comes from its
-    // results by list position -- rec (records of NewtonIO::rec; the points
-    // that they do not settle are skipped), or on line meshes rs (NaN there
-    // skips the point)
+    // where r comes from, by list position (first one that is not null):
+    // erec, records (r, id) of k_eval_bin; rec, Find's result records of its
+    // primary list (NewtonIO::rec; the points that they do not settle are
+    // skipped); rs, the same of line meshes (NaN skips the point).  Else r
+    const double *erec;
     const double *rec;
     const double *rs;
+    // k_eval_mfma: values by list position, tmp[4 q + f] (k_eval_spread
+    // brings them into point order), instead of out
+    double *tmp;
     int f0;                 // first field of this launch (k_eval_mfma)
-    // k_eval_mfma: walk the elements (every wave at most a few of them)
-    // instead of the task grid
-    int by_elem;
 };
 
 typedef const __attribute__((address_space(4))) double cdouble;
@@ -241,42 +263,59 @@ __global__ __launch_bounds__(64) void k_eval(EvalArgs a)
     }
 }
 
+// Waves per SIMD that k_eval_mfma's registers are allocated for: four where
+// the fields loaded ahead leave the contraction enough of 128, else two (held
+// to four, N = 6 with four fields spills 108 registers and takes 373 instead
+// of 250 us for 3M points).
+template <int N, int FC>
+constexpr int eval_waves_per_eu()
+{
+    return FC * N * N <= 90 ? 4 : 2;
+}
+
 // Interpolation with the first contraction on the matrix cores (quad, hex
-// and surface meshes; FC fields a0.f0 .. a.f0 + FC - 1 per launch).  One
-// wavefront per element (the first of its 64-point tasks in the task grid;
-// the element's other tasks are skipped): the FC fields of the element are
-// staged in LDS once (layout of the Newton kernels' node block, one field
-// per coordinate slot), and its points are taken 64 and then 16 at a time,
-// one per slot of four lanes (slot = lane % 16, quarter g = lane /
-// 16).  Quarter g builds the bases of direction g of its slot's point; then
-// C_f[row][s] = sum_i u_f[i][row] phi_i(r_s) by v_mfma_f64_16x16x4 (A = the
-// element's values, row = (j, k) or j; B = the slots' phi_i), each lane
-// weights its four rows of each tile with phi_j(s) phi_k(t) of its slot
-// (hexes with N = 4, 8: summed over k first, then weighted per j), and the
-// four lanes of a slot are summed.  A point's value depends on its own
-// coordinates and element only, not on the group it lands in.
-// The wave walks the elements e, e + G, ... (G = grid size; each XCD a
-// contiguous range per round) and skips those without points; the fields
-// of its next element are loaded into registers while the current one is
-// contracted, and the bucket offsets of the one after are loaded then too,
-// so that an element's staging does not wait on memory.  (Two waves per
-// SIMD: the prefetched fields take 48 VGPRs; the LDS footprint, 15 KiB per
-// wave for three fields of N = 8, allowed at most ten waves per CU anyway.)
+// and surface meshes; FC fields a.f0 .. a.f0 + FC - 1 per launch).  One
+// wavefront per task, one of the even parts of an element's list (one wave
+// for each element left most of the chip idle where the points crowd: 2M
+// points in the wake of a channel, N = 8, three fields, 679 -> 222 us): the
+// FC fields of the element are staged in LDS once (layout of the Newton
+// kernels' node block, one field per coordinate slot), and the task's points
+// are taken 64 and then 16 at a time, one per slot of four lanes (slot = lane
+// % 16, quarter g = lane / 16).  Quarter g builds the bases of direction g of
+// its slot's point; then C_f[row][s] = sum_i u_f[i][row] phi_i(r_s) on the
+// matrix cores (A = the element's values, row = (j, k) or j; B = the slots'
+// phi_i; tiles of 16 rows, the last rows in tiles of four), each lane weights
+// its rows with phi_j(s) phi_k(t) of its slot (hexes with N = 4, 8: summed
+// over k first, then weighted per j), and the four lanes of a slot are
+// summed.  A point's value depends on its own coordinates and element only,
+// not on the group or task it lands in.
+// The fields of the wave's next task, the next 64 points and the offsets of
+// the task after are loaded while the current ones are contracted.
+// Bound by FP64 arithmetic at large N (N = 8, 5M points, three fields: 450
+// us, with the matrix cores 63% and the vector units another 27% of the time
+// busy, against 240 for the products alone) and by the scattered writes of
+// its values at small N (N = 4, 4M points, one field: 107 us, 37 G/s).
 template <int R, int N, int FC>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void
+__global__ __launch_bounds__(64)
+__attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<N, FC>()))) void
 k_eval_mfma(EvalArgs a)
 {
     typedef newton::Shape<3, R, N> S;
     typedef newton::NodeLds<double, FC, R, N> L;
     typedef newton::Factor<R, N> F;
     typedef newton::V4<double>::type v4;
-    constexpr int NP = S::NP, MT = S::MT, KS = S::KS, ROWS = S::ROWS;
-    constexpr int PER = (NP + 63) / 64;
-    constexpr bool kFullA = (N % 4 == 0) && (ROWS % 16 == 0);
+    constexpr int NP = S::NP, ROWS = S::ROWS, KS = S::KS;
+        constexpr int PER = (NP + 63) / 64;
+    // row tiles: FT of 16 rows, QT of four (a 16-row tile takes as long as
+    // four of those)
+    constexpr int FT = ROWS / 16 + (ROWS % 16 > 12 ? 1 : 0);
+    constexpr int QT = ROWS > 16 * FT ? (ROWS - 16 * FT + 3) / 4 : 0;
+    constexpr bool kFullK = N % 4 == 0;
+    constexpr bool kRows = ROWS >= 16 * FT;   // the 16-row tiles' rows all exist
     extern __shared__ double lds_eval[];
+    const int lane = threadIdx.x, slot = lane & 15, g = lane >> 4;
     double *xl = lds_eval;        // the FC fields, NodeLds layout
     double *tab = xl + L::SIZE;   // [R][N][16] bases of the group's points
-    const int lane = threadIdx.x, slot = lane & 15, g = lane >> 4;
     const int G = gridDim.x, nel = a.nel;
     double v[FC][PER];
     auto load_fields = [&](int en) __attribute__((always_inline)) {
@@ -302,168 +341,281 @@ k_eval_mfma(EvalArgs a)
             }
         __syncthreads();
     };
-    // the points of the staged element: list positions [ebeg, eend)
-    auto points = [&](int ebeg, int eend) __attribute__((always_inline)) {
-        for (int beg = ebeg; beg < eend; beg += kChunk) {
-        const int end = min(eend, beg + kChunk);
+    // the lane's point: list position beg + lane (< end)
+    struct Pt {
+        double r[3], sd;
+        int p;
+    };
+    auto load_point = [&](int beg, int end, Pt &q) __attribute__((always_inline)) {
         const int idx = beg + lane;
-        bool has = idx < end;
-        const int p = has ? a.sorted[idx] : 0;
-        double rr[3] = {0.0, 0.0, 0.0};
-        if (a.rec) {
-            double mg = 1.0, sd = 0.0;
-            if (has) {
-                const double *rc = a.rec + (size_t)idx * kRec;
+        q.p = 0;
+        q.sd = 0.0;
+        q.r[0] = q.r[1] = q.r[2] = 0.0;
+        if (idx >= end) return;
+        if (a.erec || a.rec) {
+            typedef double v2 __attribute__((ext_vector_type(2)));
+            const v2 *src = reinterpret_cast<const v2 *>((a.erec ? a.erec : a.rec) +
+                                                         (size_t)idx * kRec);
+            const v2 lo = src[0], hi = src[1];
+            q.r[0] = lo[0];
+            q.r[1] = lo[1];
+            q.r[2] = hi[0];
+            q.sd = hi[1];
+            if (!a.erec && !a.tmp) q.p = a.sorted[idx];
+        } else {
+            q.p = a.sorted[idx];
 #pragma unroll
-                for (int k = 0; k < R; ++k) {
-                    rr[k] = rc[k];
-                    mg = fmin(mg, 1.0 - fabs(rr[k]));
-                }
-                sd = rc[kRec - 1];
-            }
-            has = has && !__builtin_signbit(sd) && mg > kSettleGuard;
-        } else if (has) {
-#pragma unroll
-            for (int k = 0; k < R; ++k) rr[k] = a.r[(size_t)k * a.n + p];
+            for (int k = 0; k < R; ++k) q.r[k] = a.r[(size_t)k * a.n + q.p];
         }
-        const int ngrp = (end - beg + 15) >> 4;
-        for (int grp = 0; grp < ngrp; ++grp) {
-            const int pl = 16 * grp + slot;   // task position of this slot's point
-            // coordinate g of that point (each coordinate shuffled, then the
-            // quarter's one selected)
-            const double c0 = __shfl(rr[0], pl);
-            const double c1 = R >= 2 ? __shfl(rr[1], pl) : 0.0;
-            const double c2 = R == 3 ? __shfl(rr[2], pl) : 0.0;
-            const double x = g == 0 ? c0 : g == 1 ? c1 : c2;
-            newton::wave_lds_sync();   // the previous group's table reads come first
-            if (g < R) {
-                double pv[N];
-                pv[0] = 1.0;
+    };
+    Pt nx;   // the next points
+    // the points of the staged element: list positions [ebeg, eend), the
+    // first of them in nx
+    auto points = [&](int ebeg, int eend, int nbeg, int nend) __attribute__((always_inline)) {
+#pragma unroll 1
+        for (int beg = ebeg; beg < eend; beg += kChunk) {
+            const int end = min(eend, beg + kChunk);
+            const Pt cur = nx;
+            if (end < eend) load_point(end, eend, nx);
+            else load_point(nbeg, nend, nx);
+            bool has = beg + lane < end;
+            int p = cur.p;
+            if (a.erec) {
+                p = __double2loint(cur.sd);
+            } else if (a.rec) {
+                double mg = 1.0;
 #pragma unroll
-                for (int i = 1; i < N; ++i) pv[i] = pv[i - 1] * (x - a.basis.z[i - 1]);
-                double sv = 1.0;
-#pragma unroll
-                for (int i = N - 1; i >= 0; --i) {
-                    tab[(g * N + i) * 16 + slot] = a.basis.w[i] * (pv[i] * sv);
-                    sv *= x - a.basis.z[i];
-                }
+                for (int k = 0; k < R; ++k) mg = fmin(mg, 1.0 - fabs(cur.r[k]));
+                has = has && !__builtin_signbit(cur.sd) && mg > kSettleGuard;
             }
-            newton::wave_lds_sync();
-            const double *ts = tab + N * 16, *tt = tab + 2 * N * 16;
-            double b0[KS];
+#pragma unroll 1
+            for (int grp = 0; beg + 16 * grp < end; ++grp) {
+                const int first = beg + 16 * grp;   // the group's positions
+                const int pl = 16 * grp + slot;   // the lane with this slot's point
+                // coordinate g of that point (each coordinate shuffled, then
+                // the quarter's one selected)
+                const double c0 = __shfl(cur.r[0], pl);
+                const double c1 = R >= 2 ? __shfl(cur.r[1], pl) : 0.0;
+                const double c2 = R == 3 ? __shfl(cur.r[2], pl) : 0.0;
+                const double x = g == 0 ? c0 : g == 1 ? c1 : c2;
+                newton::wave_lds_sync();   // the previous group's table reads come first
+                if (g < R) {
+                    double pv[N];
+                    pv[0] = 1.0;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const int i = 4 * ks + g;
-                b0[ks] = i < N ? tab[i * 16 + slot] : 0.0;
-            }
-            double X[FC], Z[F::NJ][FC];
+                    for (int i = 1; i < N; ++i) pv[i] = pv[i - 1] * (x - a.basis.z[i - 1]);
+                    double sv = 1.0;
 #pragma unroll
-            for (int f = 0; f < FC; ++f) {
-                X[f] = 0.0;
-#pragma unroll
-                for (int js = 0; js < F::NJ; ++js) Z[js][f] = 0.0;
-            }
-#pragma unroll(MT <= 4 ? MT : 1)
-            for (int m = 0; m < MT; ++m) {
-                v4 acc[FC];
-#pragma unroll
-                for (int f = 0; f < FC; ++f) acc[f] = v4{0, 0, 0, 0};
-                const int arow = 16 * m + slot;
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    const int ai = 4 * ks + g;
-                    const bool aok = kFullA || (arow < ROWS && ai < N);
-#pragma unroll
-                    for (int f = 0; f < FC; ++f)
-                        acc[f] = newton::mfma16(xl[aok ? L::at(f, arow, ai) : 0], b0[ks], acc[f]);
-                }
-#pragma unroll
-                for (int qq = 0; qq < 4; ++qq) {
-                    const int row = newton::out_row(m, g, qq);
-                    if (ROWS % 16 != 0 && row >= ROWS) continue;
-                    if constexpr (F::ON) {
-                        const int k = (16 * m + 4 * qq) / N, js = qq % F::NJ;
-                        const double tv = tt[k * 16 + slot];
-#pragma unroll
-                        for (int f = 0; f < FC; ++f) Z[js][f] = fma(acc[f][qq], tv, Z[js][f]);
-                    } else {
-                        const double w = R == 3 ? ts[(row % N) * 16 + slot] * tt[(row / N) * 16 + slot]
-                                                : ts[row * 16 + slot];
-#pragma unroll
-                        for (int f = 0; f < FC; ++f) X[f] = fma(acc[f][qq], w, X[f]);
+                    for (int i = N - 1; i >= 0; --i) {
+                        tab[(g * N + i) * 16 + slot] = a.basis.w[i] * (pv[i] * sv);
+                        sv *= x - a.basis.z[i];
                     }
                 }
-            }
-            if constexpr (F::ON) {
+                newton::wave_lds_sync();
+                const double *ts = tab + N * 16, *tt = tab + 2 * N * 16;
+                double b0[KS];
 #pragma unroll
-                for (int js = 0; js < F::NJ; ++js) {
-                    const double sv = ts[(g + 4 * js) * 16 + slot];
+                for (int ks = 0; ks < KS; ++ks) {
+                    const int i = 4 * ks + g;
+                    b0[ks] = kFullK || i < N ? tab[i * 16 + slot] : 0.0;
+                }
+                double X[FC], Z[F::NJ][FC];
 #pragma unroll
-                    for (int f = 0; f < FC; ++f) X[f] = fma(Z[js][f], sv, X[f]);
+                for (int f = 0; f < FC; ++f) {
+                    X[f] = 0.0;
+#pragma unroll
+                    for (int js = 0; js < F::NJ; ++js) Z[js][f] = 0.0;
+                }
+                // one contraction row of the lane, weighted into the sums
+                auto weight = [&](int row) __attribute__((always_inline)) {
+                    return R == 3 ? ts[(row % N) * 16 + slot] * tt[(row / N) * 16 + slot]
+                                  : ts[row * 16 + slot];
+                };
+#pragma unroll(FT <= 4 ? (FT > 0 ? FT : 1) : 1)
+                for (int m = 0; m < FT; ++m) {
+                    v4 acc[FC];
+#pragma unroll
+                    for (int f = 0; f < FC; ++f) acc[f] = v4{0, 0, 0, 0};
+                    const int arow = 16 * m + slot;
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) {
+                        const int ai = 4 * ks + g;
+                        const bool aok = (kRows || arow < ROWS) && (kFullK || ai < N);
+#pragma unroll
+                        for (int f = 0; f < FC; ++f)
+                            acc[f] =
+                                newton::mfma16(xl[aok ? L::at(f, arow, ai) : 0], b0[ks], acc[f]);
+                    }
+#pragma unroll
+                    for (int qq = 0; qq < 4; ++qq) {
+                        const int row = newton::out_row(m, g, qq);
+                        if (!kRows && row >= ROWS) continue;
+                        if constexpr (F::ON) {
+                            const int k = (16 * m + 4 * qq) / N, js = qq % F::NJ;
+                            const double tv = tt[k * 16 + slot];
+#pragma unroll
+                            for (int f = 0; f < FC; ++f) Z[js][f] = fma(acc[f][qq], tv, Z[js][f]);
+                        } else {
+                            const double w = weight(row);
+#pragma unroll
+                            for (int f = 0; f < FC; ++f) X[f] = fma(acc[f][qq], w, X[f]);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < QT; ++t) {
+                    const int base = 16 * FT + 4 * t;
+                    const bool whole = base + 4 <= ROWS;
+                    const int arow = base + (slot & 3), row = base + g;
+                    double c[FC];
+#pragma unroll
+                    for (int f = 0; f < FC; ++f) c[f] = 0.0;
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) {
+                        const int ai = 4 * ks + g;
+                        const bool aok = (whole || arow < ROWS) && (kFullK || ai < N);
+#pragma unroll
+                        for (int f = 0; f < FC; ++f)
+                            c[f] = newton::mfma4(xl[aok ? L::at(f, arow, ai) : 0], b0[ks], c[f]);
+                    }
+                    if (whole || row < ROWS) {
+                        const double w = weight(row);
+#pragma unroll
+                        for (int f = 0; f < FC; ++f) X[f] = fma(c[f], w, X[f]);
+                    }
+                }
+                if constexpr (F::ON) {
+#pragma unroll
+                    for (int js = 0; js < F::NJ; ++js) {
+                        const double sv = ts[(g + 4 * js) * 16 + slot];
+#pragma unroll
+                        for (int f = 0; f < FC; ++f) X[f] = fma(Z[js][f], sv, X[f]);
+                    }
+                }
+                newton::slot_sum_all(X);
+                // quarter g writes field g of its slot's point
+                double u = X[0];
+#pragma unroll
+                for (int f = 1; f < FC; ++f) u = g == f ? X[f] : u;
+                if (a.tmp) {
+                    if (g < FC && first + slot < end) a.tmp[(size_t)(first + slot) * 4 + g] = u;
+                } else {
+                    const bool hp = __shfl((int)has, pl) != 0;
+                    const int pp = __shfl(p, pl);
+                    if (hp && g < FC) a.out[(size_t)(a.f0 + g) * a.n + pp] = u;
                 }
             }
-            newton::slot_sum_all(X);
-            const bool hp = __shfl((int)has, pl) != 0;
-            const int pp = __shfl(p, pl);
-            // quarter g writes field g of its slot's point
+        }
+    };
+    const int total = a.chunk_off[nel];
+    // task t's list positions from its element's offsets (loaded a task ahead)
+    struct Offs {
+        int c0, c1, o0, o1;
+    };
+    auto load_offs = [&](int e, Offs &o) __attribute__((always_inline)) {
+        o.c0 = a.chunk_off[e];
+        o.c1 = a.chunk_off[e + 1];
+        o.o0 = a.elem_off[e];
+        o.o1 = a.elem_off[e + 1];
+    };
+    auto range_of = [&](int t, const Offs &o, int &q0, int &q1) __attribute__((always_inline)) {
+        const int k = __builtin_amdgcn_readfirstlane(t - o.c0);
+        const int nt = __builtin_amdgcn_readfirstlane(o.c1 - o.c0);
+        const int b = __builtin_amdgcn_readfirstlane(o.o0);
+        const int cnt = __builtin_amdgcn_readfirstlane(o.o1) - b;
+        const int per = ((cnt + nt - 1) / nt + 15) / 16 * 16;   // whole groups
+        q0 = b + min(cnt, k * per);
+        q1 = b + min(cnt, (k + 1) * per);
+    };
+    int t = task_of_block();
+    if (t >= total) return;
+    // e: the task's element, e1: the next one's, e2: that of the one after,
+    // each loaded a task before its offsets are
+    int q0, q1, e1 = 0, e2 = 0;
+    Offs of;
+    {
+        const int e = __builtin_amdgcn_readfirstlane(a.task_elem[t]);
+        if (t + G < total) e1 = a.task_elem[t + G];
+        if (t + 2 * G < total) e2 = a.task_elem[t + 2 * G];
+        load_offs(e, of);
+        range_of(t, of, q0, q1);
+        load_fields(e);
+        load_point(q0, q1, nx);
+        e1 = __builtin_amdgcn_readfirstlane(e1);
+        if (t + G < total) load_offs(e1, of);
+    }
+    for (;;) {
+        stage_fields();   // loaded during the previous task
+        const int tn = t + G;
+        int n0 = 0, n1 = 0;
+        if (tn < total) {
+            range_of(tn, of, n0, n1);
+            load_fields(e1);
+            e1 = __builtin_amdgcn_readfirstlane(e2);
+            if (tn + G < total) load_offs(e1, of);
+            if (tn + 2 * G < total) e2 = a.task_elem[tn + 2 * G];
+        }
+        if (q0 < q1) points(q0, q1, n0, n1);
+        else load_point(n0, n1, nx);
+        if (tn >= total) break;
+        t = tn;
+        q0 = n0;
+        q1 = n1;
+    }
+}
+
+// Values by list position (tmp[4 q + f], FC fields from f0 on) into point
+// order: a 32-byte gather per point and coalesced writes, instead of a
+// scattered 8-byte write per point and field (some 30 G/s on this GPU).  The
+// list position of point p: elem_off[elem] + rank (rank < 0: not in the
+// list), or, with cand, its place in Find's primary list (points that the
+// list's results do not settle get values that the interpolation of the
+// rest overwrites).
+template <int FC>
+__global__ __launch_bounds__(256) void k_eval_spread(int n, const int2 *cand, const int32_t *elem,
+                                                    const int *rank, const int *elem_off,
+                                                    const double *tmp, int f0, double *out)
+{
+    typedef double v2 __attribute__((ext_vector_type(2)));
+    constexpr int U = 4;
+    const int64_t base = (int64_t)blockIdx.x * U * 256 + threadIdx.x;
+    int64_t pos[U];
 #pragma unroll
-            for (int f = 0; f < FC; ++f)
-                if (hp && g == f) a.out[(size_t)(a.f0 + f) * a.n + pp] = X[f];
-        }
-        }
-    };
-    if (!a.by_elem) {
-        // task grid: the element's first task takes all its points, so that
-        // its fields are staged once (its other tasks have nothing to do)
-        const int total = a.chunk_off[nel];
-        for (int t = task_of_block(); t < total; t += G) {
-            const int e = __builtin_amdgcn_readfirstlane(a.task_elem[t]);
-            if (t != a.chunk_off[e]) continue;
-            load_fields(e);
-            stage_fields();
-            points(a.elem_off[e], a.elem_off[e + 1]);
-        }
-        return;
-    }
-    // element walk: the wave's first element with points from e0 on, in
-    // steps of G (nel when none), its bucket range in o0, o1
-    auto busy_from = [&](int e0, int &o0, int &o1) __attribute__((always_inline)) {
-        int en = e0;
-        for (; en < nel; en += G) {
-            o0 = a.elem_off[en];
-            o1 = a.elem_off[en + 1];
-            if (o1 > o0) break;
-        }
-        return en;
-    };
-    int ebeg = 0, eend = 0;
-    int e = busy_from(task_of_block(), ebeg, eend);
-    if (e < nel) load_fields(e);
-    // offsets of the element after the next, loaded one element ahead
-    int nb = 0, nnb = 0;
-    int en = e + G;
-    if (en < nel) {
-        nb = a.elem_off[en];
-        nnb = a.elem_off[en + 1];
-    }
-    while (e < nel) {
-        stage_fields();   // fields loaded during the previous element
-        // the next element with points: en, whose offsets arrived meanwhile
-        // (past an empty one the search goes on from there)
-        if (en < nel && !(nnb > nb)) en = busy_from(en + G, nb, nnb);
-        const int n0 = nb, n1 = nnb;
-        if (en < nel) {
-            load_fields(en);
-            if (en + G < nel) {
-                nb = a.elem_off[en + G];
-                nnb = a.elem_off[en + G + 1];
+    for (int u = 0; u < U; ++u) {
+        const int64_t p = base + u * 256;
+        int e = -1;
+        unsigned k = 0;
+        if (p < n) {
+            if (cand) {
+                const int2 cd = cand[p];
+                e = cd.y;
+                k = (unsigned)cd.x >> 1;
+            } else {
+                const int rk = rank[p];
+                e = rk < 0 ? -1 : elem[p];
+                k = (unsigned)rk;
             }
         }
-        points(ebeg, eend);
-        e = en;
-        ebeg = n0;
-        eend = n1;
-        en = e + G;
+        pos[u] = e < 0 ? -1 : (int64_t)elem_off[e] + k;
+    }
+    v2 lo[U], hi[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        lo[u] = v2{0.0, 0.0};
+        hi[u] = v2{0.0, 0.0};
+        if (pos[u] >= 0) {
+            const v2 *src = reinterpret_cast<const v2 *>(tmp + pos[u] * 4);
+            lo[u] = src[0];
+            if (FC > 2) hi[u] = src[1];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t p = base + u * 256;
+        if (pos[u] < 0) continue;
+        const double x[4] = {lo[u][0], lo[u][1], hi[u][0], hi[u][1]};
+#pragma unroll
+        for (int f = 0; f < FC; ++f) out[(size_t)(f0 + f) * n + p] = x[f];
     }
 }
 
@@ -647,8 +799,12 @@ EvalFn pick_eval_mfma(int N, size_t *lds)
 template <int R>
 EvalFn pick_eval_mfma_fc(int N, int fc, size_t *lds)
 {
-    return fc == 3 ? pick_eval_mfma<R, 3>(N, lds)
-                   : fc == 2 ? pick_eval_mfma<R, 2>(N, lds) : pick_eval_mfma<R, 1>(N, lds);
+    switch (fc) {
+    case 4: return pick_eval_mfma<R, 4>(N, lds);
+    case 3: return pick_eval_mfma<R, 3>(N, lds);
+    case 2: return pick_eval_mfma<R, 2>(N, lds);
+    default: return pick_eval_mfma<R, 1>(N, lds);
+    }
 }
 
 template <bool LDS>
@@ -674,55 +830,67 @@ hipError_t launch_eval_bin_list(const fpts_mesh *m, int pass, const int *list, c
 hipError_t launch_eval_bin(const fpts_mesh *m, int pass, int64_t n, const int32_t *code,
                            const int32_t *elem, const double *r, const int2 *cand,
                            int n_fields, double *out, int *elem_cnt, const int *elem_off,
-                           int *rank, int *sorted, hipStream_t s)
+                           int *rank, int *sorted, double *erec, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_eval_bin, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, pass,
-                       (int)n, (int)m->nel, elem_stride(m->nel), m->R, code, elem, r, cand, n_fields, out,
-                       elem_cnt, elem_off, rank, sorted);
+                       (int)n, (int)m->nel, elem_stride(m->nel), m->R, code, elem, r, cand,
+                       n_fields, out, elem_cnt, elem_off, rank, sorted, erec);
     return hipGetLastError();
 }
 
-hipError_t launch_eval(const fpts_mesh *m, int64_t n, const double *r, int n_fields, int field_n,
-                       const double *field, double *out, const int *sorted, const int *elem_off,
-                       const int *chunk_off, const int *task_elem, int64_t task_bound,
-                       hipStream_t s, const double *rs, const double *rec)
+hipError_t launch_eval(const fpts_mesh *m, int64_t n, int n_fields, int field_n,
+                       const double *field, double *out, const EvalList &l, hipStream_t s)
 {
-    EvalArgs a;
-    a.r = r;
+    EvalArgs a{};
+    a.r = l.r;
     a.n = (int)n;
     a.nel = (int)m->nel;
     a.n_fields = n_fields;
     a.field = field;
     a.out = out;
-    a.sorted = sorted;
-    a.elem_off = elem_off;
-    a.chunk_off = chunk_off;
-    a.task_elem = task_elem;
-    a.rs = rs;
-    a.rec = rec;
-    a.f0 = 0;
+    a.sorted = l.sorted;
+    a.elem_off = l.elem_off;
+    a.chunk_off = l.chunk_off;
+    a.task_elem = l.task_elem;
+    a.erec = l.erec;
+    a.rec = l.rec;
+    a.rs = l.rs;
     if (field_n == m->N) a.basis = m->basis;
     else gll::fill(field_n, a.basis.z, a.basis.w);
-    const dim3 grid(task_grid(task_bound, m->cus));
-    // the matrix-core kernel walks the elements when every wave has at most
-    // eight of them to visit (many points); else it follows the task grid
-    a.by_elem = (int64_t)grid.x * 8 >= m->nel;
     if (m->R >= 2) {
-        // matrix cores, up to three fields per launch
-        for (int f0 = 0; f0 < n_fields; f0 += 3) {
+        // matrix cores, up to four fields per launch, evenly
+        const int launches = (n_fields + 3) / 4;
+        const dim3 grid((unsigned)std::min<int64_t>(task_grid(l.task_bound, m->cus),
+                                                    (int64_t)m->cus * 16));
+        for (int k = 0, f0 = 0; k < launches; ++k) {
             size_t lds = 0;
-            const int fc = std::min(3, n_fields - f0);
+            const int fc = (n_fields - f0 + launches - k - 1) / (launches - k);
             EvalFn fn = m->R == 3 ? pick_eval_mfma_fc<3>(field_n, fc, &lds)
                                   : pick_eval_mfma_fc<2>(field_n, fc, &lds);
             if (!fn) return hipErrorInvalidValue;
             a.f0 = f0;
+            // three or four fields of up to six nodes per direction go through
+            // list order: a gather per point and coalesced writes take less
+            // than that many scattered writes (some 28 us per 1M values;
+            // N = 6, four fields, 3M points: 250 + 77 us, scattered 360).
+            // At larger N the writes hide behind the arithmetic (N = 8, three
+            // fields, 5M points: 420 + 121 us, scattered 450).
+            const bool spread = l.tmp && fc >= kSpreadFields && field_n <= kSpreadNodes;
+            a.tmp = spread ? l.tmp : nullptr;
             hipLaunchKernelGGL(fn, grid, dim3(64), lds, s, a);
+            if (spread) {
+                auto sp = fc == 4 ? k_eval_spread<4> : k_eval_spread<3>;
+                hipLaunchKernelGGL(sp, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, s,
+                                   (int)n, l.cand, l.elem, l.rank, l.elem_off, l.tmp, f0, out);
+            }
+            f0 += fc;
         }
         return hipGetLastError();
     }
     // line meshes: stage in LDS unless elements hold many points (several
     // tasks each)
+    const dim3 grid(task_grid(l.task_bound, m->cus));
     const bool lds = n <= (int64_t)4 * kChunk * m->nel;
     EvalFn fn = lds ? pick_eval_r<true>(m->R, field_n) : pick_eval_r<false>(m->R, field_n);
     if (!fn) return hipErrorInvalidValue;
