@@ -194,9 +194,9 @@ __device__ inline bool box_pass(P rec, const double *x, double &depth)
 }
 
 // fused find + interpolate: ints zeroed with the find's own counts (zero,
-// zero_n of them, *count among them); unless list is null, the points the
-// pass over the primary list does not interpolate (list, *count of them), and
-// NaN values for NOT_FOUND points
+// zero_n of them, *count among them); unless list is null, the points that
+// their primary result leaves less than deep inside (list, *count of them);
+// unless out is null, NaN values for NOT_FOUND points
 struct EvalRest {
     int *zero = nullptr;
     int64_t zero_n = 0;
@@ -567,6 +567,7 @@ struct EvalList {
     const int *sorted = nullptr, *elem_off = nullptr, *chunk_off = nullptr, *task_elem = nullptr;
     int64_t task_bound = 0;
     const double *r = nullptr, *rs = nullptr, *rec = nullptr, *erec = nullptr;
+    bool deep_only = false;
     double *tmp = nullptr;
     const int2 *cand = nullptr;
     const int32_t *elem = nullptr;

@@ -147,10 +147,12 @@ struct EvalArgs {
     Basis basis;
     // where r comes from, by list position (first one that is not null):
     // erec, records (r, id) of k_eval_bin; rec, Find's result records of its
-    // primary list (NewtonIO::rec; the points that they do not settle are
-    // skipped); rs, the same of line meshes (NaN skips the point).  Else r
+    // primary list (NewtonIO::rec; with deep_only those that are not INTERIOR
+    // at least kSettleGuard inside are skipped); rs, the same of line meshes
+    // (NaN skips the point).  Else r
     const double *erec;
     const double *rec;
+    bool deep_only;
     const double *rs;
     // k_eval_mfma: values by list position, tmp[4 q + f] (k_eval_spread
     // brings them into point order), instead of out
@@ -382,7 +384,7 @@ k_eval_mfma(EvalArgs a)
             int p = cur.p;
             if (a.erec) {
                 p = __double2loint(cur.sd);
-            } else if (a.rec) {
+            } else if (a.rec && a.deep_only) {
                 double mg = 1.0;
 #pragma unroll
                 for (int k = 0; k < R; ++k) mg = fmin(mg, 1.0 - fabs(cur.r[k]));
@@ -855,6 +857,7 @@ hipError_t launch_eval(const fpts_mesh *m, int64_t n, int n_fields, int field_n,
     a.task_elem = l.task_elem;
     a.erec = l.erec;
     a.rec = l.rec;
+    a.deep_only = l.deep_only;
     a.rs = l.rs;
     if (field_n == m->N) a.basis = m->basis;
     else gll::fill(field_n, a.basis.z, a.basis.w);

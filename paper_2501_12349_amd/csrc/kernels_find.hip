@@ -657,11 +657,12 @@ __global__ __launch_bounds__(256) void k_unsettled(int n, const int2 *cand, cons
 // Volume and surface meshes: the result records of the primary pass are
 // brought into point order -- one 32-byte gather per point, then coalesced
 // writes of the outputs -- and the points marked in the same pass.  With
-// rest.list (fused find + interpolate) the points that the interpolation
+// rest.out (fused find + interpolate) the interpolated values of NOT_FOUND
+// points become NaN, and with rest.list the points that the interpolation
 // over the primary list leaves out are listed too -- found, but not INTERIOR
 // at least kSettleGuard inside by the primary result (the listed points
-// among them) -- and the interpolated values of NOT_FOUND points become NaN,
-// so that the interpolation needs no pass over all points of its own.
+// among them) --, so that the interpolation needs no pass over all points of
+// its own.
 // Points without a primary (NOT_FOUND, or kept from a hinted search) hold
 // their results already.
 template <int R>
@@ -717,12 +718,10 @@ __global__ __launch_bounds__(256) void k_settle(int n, const int2 *cand, const i
             }
             const bool deep = deep_interior(interior, rr, R);
             list_append(has && (cd[u].x & 1) && !deep, p, lane, lst, lcnt);
-            if (rest.list) {
-                list_append(has && !deep, p, lane, elst, ecnt);
-                if (in[u] && !has)
-                    for (int f = 0; f < rest.n_fields; ++f)
-                        rest.out[(size_t)f * n + p] = __builtin_nan("");
-            }
+            if (rest.list) list_append(has && !deep, p, lane, elst, ecnt);
+            if (rest.out && in[u] && !has)
+                for (int f = 0; f < rest.n_fields; ++f)
+                    rest.out[(size_t)f * n + p] = __builtin_nan("");
         }
     }
     __syncthreads();
