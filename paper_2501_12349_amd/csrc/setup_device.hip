@@ -99,10 +99,12 @@ __device__ __forceinline__ void side_bounds(const BoundTables &T, double *val, d
             }
             const double *u = val + S::at(sd, c, 0);
 #pragma unroll
-            for (int j = 0; j < N; ++j)
+            for (int j = 0; j < N; ++j) {
 #pragma unroll
                 for (int i = 0; i < N; ++i)
                     a += u[(i * N + j) * S::G * S::PQ] * m0[i] * m1[j];
+                __builtin_amdgcn_sched_barrier(0);
+            }
             mom[id] = a * (q == 0 ? 0.25 : q == 3 ? 2.25 : 0.75);
         } else {
 #pragma unroll
@@ -163,6 +165,7 @@ __device__ __forceinline__ void side_bounds(const BoundTables &T, double *val, d
                         sl[f] += fmin(a, b);
                         sh[f] += fmax(a, b);
                     }
+                    if (j % 2) __builtin_amdgcn_sched_barrier(0);
                 }
             }
 #pragma unroll
@@ -255,16 +258,20 @@ __device__ bool invert_d(int D, const double *A, double *I)
 }
 
 // AABB and OBB record (lo, hi, OBB centre, OBB inverse transform) and
-// centre of every element; one wave per element, striding.  Bound by FP64
+// centre of every element; one wave per element.  Bound by FP64
 // vector arithmetic: for a hex (2N)^2 grid points x N^2 nodes x 18 functions
 // x 2 boxes x 6 operations (no contraction: the host's rounding).  Only the
 // side functions' values are kept in LDS; the nodes stream through it one
 // slab (k) at a time for the centre sums, whose order fixes the rounding (one
-// lane per sum).
+// lane per sum).  Four waves per SIMD: the element's frame waits in LDS, and
+// the scheduling barriers keep the LDS reads of later rows from being hoisted
+// (with 256 registers a wave had its SIMD to itself).  5832 hexes of N = 6:
+// 2840 us when each function was bounded by itself, 687 with 256 registers,
+// 366 now.
 template <int D, int R, int N>
-__global__ __launch_bounds__(kLanes) void k_elem_boxes(const BoundTables *Tg, const double *nodes,
-                                                      int64_t nel, double tol, double *box,
-                                                      double *xc_out)
+__global__ __launch_bounds__(kLanes) __attribute__((amdgpu_waves_per_eu(4))) void
+k_elem_boxes(const BoundTables *Tg, const double *nodes, int64_t nel, double tol, double *box,
+             double *xc_out)
 {
     typedef Sides<D, R, N> S;
     constexpr int NP = S::NP, W = 3 * D + D * D;
@@ -272,67 +279,67 @@ __global__ __launch_bounds__(kLanes) void k_elem_boxes(const BoundTables *Tg, co
     constexpr int PER = (D * SLAB + kLanes - 1) / kLanes;
     static_assert(D * SLAB <= 3 * kMaxN * kMaxN, "slab");
     __shared__ __align__(16) double val[S::VALS];
-    __shared__ double mom[S::NF * S::MOM], slab[D * SLAB], sc[16];
+    __shared__ double mom[S::NF * S::MOM], slab[D * SLAB], sc[16], frame[24];
     const BoundTables &T = *Tg;
     const int lane = threadIdx.x;
-    for (int64_t e = blockIdx.x; e < nel; e += gridDim.x) {
-        const double *xe = nodes + e * D * NP;
-        // centre and centre Jacobian: lane 4 c + q sums coordinate c times
-        // phi phi phi (q = 0) or its derivative along direction q - 1
-        {
-            double pre[PER];
-            auto fetch = [&](int ks) __attribute__((always_inline)) {
+    const int64_t e = blockIdx.x;
+    if (e >= nel) return;
+    const double *xe = nodes + e * D * NP;
+    double *rec = box + e * W;
+    // centre and centre Jacobian: lane 4 c + q sums coordinate c times
+    // phi phi phi (q = 0) or its derivative along direction q - 1
+    {
+        double pre[PER];
+        auto fetch = [&](int ks) __attribute__((always_inline)) {
 #pragma unroll
-                for (int u = 0; u < PER; ++u) {
-                    const int i = u * kLanes + lane;
-                    pre[u] = i < D * SLAB ? xe[i / SLAB * NP + ks * SLAB + i % SLAB] : 0.0;
-                }
-            };
-            const int c = lane >> 2, q = lane & 3;
-            double w0[N], w1[N], acc = 0.0;
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                w0[i] = q == 1 ? T.d0[i] : T.v0[i];
-                w1[i] = q == 2 ? T.d0[i] : T.v0[i];
+            for (int u = 0; u < PER; ++u) {
+                const int i = u * kLanes + lane;
+                pre[u] = i < D * SLAB ? xe[i / SLAB * NP + ks * SLAB + i % SLAB] : 0.0;
             }
-            fetch(0);
+        };
+        const int c = lane >> 2, q = lane & 3;
+        double w0[N], w1[N], acc = 0.0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            w0[i] = q == 1 ? T.d0[i] : T.v0[i];
+            w1[i] = q == 2 ? T.d0[i] : T.v0[i];
+        }
+        fetch(0);
 #pragma unroll 1
-            for (int ks = 0; ks < NSLAB; ++ks) {
-                __syncthreads();
+        for (int ks = 0; ks < NSLAB; ++ks) {
+            __syncthreads();
 #pragma unroll
-                for (int u = 0; u < PER; ++u) {
-                    const int i = u * kLanes + lane;
-                    if (i < D * SLAB) slab[i] = pre[u];
-                }
-                __syncthreads();
-                if (ks + 1 < NSLAB) fetch(ks + 1);
-                const double w2 = q == 3 ? T.d0[ks] : T.v0[ks];
-                if (c < D && q <= R) {
-                    const double *u = slab + c * SLAB;
-                    if constexpr (R == 1) {
+            for (int u = 0; u < PER; ++u) {
+                const int i = u * kLanes + lane;
+                if (i < D * SLAB) slab[i] = pre[u];
+            }
+            __syncthreads();
+            if (ks + 1 < NSLAB) fetch(ks + 1);
+            const double w2 = q == 3 ? T.d0[ks] : T.v0[ks];
+            if (c < D && q <= R) {
+                const double *u = slab + c * SLAB;
+                if constexpr (R == 1) {
 #pragma unroll
-                        for (int i = 0; i < N; ++i) acc += u[i] * w0[i];
-                    } else {
+                    for (int i = 0; i < N; ++i) acc += u[i] * w0[i];
+                } else {
 #pragma unroll
-                        for (int j = 0; j < N; ++j)
+                    for (int j = 0; j < N; ++j) {
 #pragma unroll
-                            for (int i = 0; i < N; ++i) {
-                                double b = w0[i] * w1[j];
-                                if (R == 3) b *= w2;
-                                acc += u[i + N * j] * b;
-                            }
+                        for (int i = 0; i < N; ++i) {
+                            double b = w0[i] * w1[j];
+                            if (R == 3) b *= w2;
+                            acc += u[i + N * j] * b;
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
                     }
                 }
             }
-            __syncthreads();
-            if (lane < 16) sc[lane] = acc;   // lanes without a sum: 0
-            __syncthreads();
         }
-        double xc[3] = {0, 0, 0}, G[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-        for (int c = 0; c < D; ++c) {
-            xc[c] = sc[4 * c];
-            for (int a = 0; a < R; ++a) G[c][a] = sc[4 * c + 1 + a];
-        }
+        __syncthreads();
+        if (lane < 16) sc[lane] = acc;   // lanes without a sum: 0
+        __syncthreads();
+    }
+    {
         double lo[3], hi[3], one[3] = {1, 1, 1};
         for (int idx = lane; idx < S::NS * S::PTS; idx += kLanes) {
             const int sd = idx / S::PTS, k = idx % S::PTS, nd = S::node(sd, k);
@@ -341,7 +348,20 @@ __global__ __launch_bounds__(kLanes) void k_elem_boxes(const BoundTables *Tg, co
         }
         side_bounds<D, R, N>(T, val, mom, lane, lo, hi);
         finish_d(D, R, tol, lo, hi, one);
-        double Jc[9] = {0}, Ji[9] = {0}, len[3] = {1, 1, 1};
+        if (lane == 0)
+            for (int c = 0; c < D; ++c) {
+                rec[c] = lo[c];
+                rec[D + c] = hi[c];
+                xc_out[e * D + c] = sc[4 * c];
+            }
+    }
+    bool inv;
+    {
+        double Jc[9] = {0}, Ji[9] = {0}, len[3] = {1, 1, 1}, G[3][3], xc[3] = {0, 0, 0};
+        for (int c = 0; c < D; ++c) {
+            xc[c] = sc[4 * c];
+            for (int a = 0; a < R; ++a) G[c][a] = sc[4 * c + 1 + a];
+        }
         if (R == D) {
             for (int a = 0; a < D; ++a)
                 for (int b = 0; b < D; ++b) Jc[a * D + b] = G[a][b];
@@ -360,9 +380,7 @@ __global__ __launch_bounds__(kLanes) void k_elem_boxes(const BoundTables *Tg, co
             len[0] = sqrt(t1[0] * t1[0] + t1[1] * t1[1] + t1[2] * t1[2]);
             len[1] = sqrt(t2[0] * t2[0] + t2[1] * t2[1] + t2[2] * t2[2]);
         }
-        double *rec = box + e * W;
-        const bool inv = invert_d(D, Jc, Ji);
-        double tl[3], th[3];
+        inv = invert_d(D, Jc, Ji);
         if (inv) {
             __syncthreads();   // the AABB's reads of val come first
             for (int idx = lane; idx < S::NS * S::PTS; idx += kLanes) {
@@ -378,32 +396,37 @@ __global__ __launch_bounds__(kLanes) void k_elem_boxes(const BoundTables *Tg, co
                     val[S::at(sd, c, k)] = t;
                 }
             }
-            side_bounds<D, R, N>(T, val, mom, lane, tl, th);
-            finish_d(D, R, tol, tl, th, len);
         }
-        if (lane == 0) {
-            for (int c = 0; c < D; ++c) {
-                rec[c] = lo[c];
-                rec[D + c] = hi[c];
-                xc_out[e * D + c] = xc[c];
+        // the frame waits in LDS while the bounds are computed
+        if (lane == 0)
+            for (int a = 0; a < 9; ++a) {
+                frame[a] = Jc[a];
+                frame[9 + a] = Ji[a];
+                if (a < 3) frame[18 + a] = len[a];
             }
-            double *oc = rec + 2 * D, *oA = rec + 3 * D;
-            if (!inv) {
-                for (int c = 0; c < D; ++c) oc[c] = xc[c];
-                for (int a = 0; a < D * D; ++a) oA[a] = 0.0;
-            } else {
-                for (int a = 0; a < D; ++a) {
-                    const double half = 0.5 * (th[a] - tl[a]);
-                    for (int b = 0; b < D; ++b) oA[a * D + b] = Ji[a * D + b] / half;
-                }
-                for (int c = 0; c < D; ++c) {
-                    double s = xc[c];
-                    for (int q = 0; q < D; ++q) s += Jc[c * D + q] * 0.5 * (th[q] + tl[q]);
-                    oc[c] = s;
-                }
-            }
-        }
         __syncthreads();
+    }
+    double *oc = rec + 2 * D, *oA = rec + 3 * D;
+    if (!inv) {
+        if (lane == 0) {
+            for (int c = 0; c < D; ++c) oc[c] = sc[4 * c];
+            for (int a = 0; a < D * D; ++a) oA[a] = 0.0;
+        }
+        return;
+    }
+    double tl[3], th[3];
+    side_bounds<D, R, N>(T, val, mom, lane, tl, th);
+    finish_d(D, R, tol, tl, th, frame + 18);
+    if (lane == 0) {
+        for (int a = 0; a < D; ++a) {
+            const double half = 0.5 * (th[a] - tl[a]);
+            for (int b = 0; b < D; ++b) oA[a * D + b] = frame[9 + a * D + b] / half;
+        }
+        for (int c = 0; c < D; ++c) {
+            double s = sc[4 * c];
+            for (int q = 0; q < D; ++q) s += frame[c * D + q] * 0.5 * (th[q] + tl[q]);
+            oc[c] = s;
+        }
     }
 }
 
@@ -470,14 +493,40 @@ __global__ __launch_bounds__(256) void k_map(MapView v, const double *box, int64
             }
 }
 
-// each cell's element list in ascending id (the host registers elements in
-// ascending order)
+// Each cell's element list in ascending id (the host registers elements in
+// ascending order).  A list of up to kSortWide elements is held by kSortLanes
+// lanes, and each element goes where the number of smaller ones says; longer
+// lists are sorted by insertion.  (One lane per cell and insertion throughout,
+// a chain of dependent loads and stores, took 66 us for 5832 elements.)
+constexpr int kSortLanes = 16, kSortPer = 4, kSortWide = kSortLanes * kSortPer;
 __global__ __launch_bounds__(256) void k_map_sort(const int *off, int64_t ncell, int *cell_el)
 {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncell) return;
+    const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kSortLanes;
+    if (c >= ncell) return;   // whole groups of lanes
+    const int l = threadIdx.x % kSortLanes, first = (threadIdx.x & 63) / kSortLanes * kSortLanes;
     const int b = off[c], n = off[c + 1] - b;
     int *a = cell_el + b;
+    if (n <= kSortWide) {
+        int x[kSortPer], below[kSortPer];
+#pragma unroll
+        for (int k = 0; k < kSortPer; ++k) {
+            const int i = l + k * kSortLanes;
+            x[k] = i < n ? a[i] : 0;
+            below[k] = 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kSortPer; ++k)
+            for (int t = 0; t < min(kSortLanes, n - k * kSortLanes); ++t) {
+                const int y = __shfl(x[k], first + t);
+#pragma unroll
+                for (int q = 0; q < kSortPer; ++q) below[q] += y < x[q];
+            }
+#pragma unroll
+        for (int k = 0; k < kSortPer; ++k)
+            if (l + k * kSortLanes < n) a[below[k]] = x[k];
+        return;
+    }
+    if (l != 0) return;
     for (int i = 1; i < n; ++i) {
         const int x = a[i];
         int j = i - 1;
@@ -527,7 +576,7 @@ int device_setup(fpts_mesh *m, hipStream_t s)
     if (hipMemcpyAsync(dt.p, &bt, sizeof(bt), hipMemcpyHostToDevice, s) != hipSuccess)
         return FPTS_EDEVICE;
     // boxes and centres
-    const int grid = (int)std::min<int64_t>(m->nel, (int64_t)m->cus * 16);
+    const int grid = (int)m->nel;
     const BoxKernel kb = D == 2 ? (R == 2 ? pick_boxes<2, 2>(N) : pick_boxes<2, 1>(N))
                          : R == 3 ? pick_boxes<3, 3>(N)
                                   : R == 2 ? pick_boxes<3, 2>(N) : pick_boxes<3, 1>(N);
@@ -596,8 +645,8 @@ int device_setup(fpts_mesh *m, hipStream_t s)
     m->cell_el.resize(std::max<int64_t>(nnz, 1));
     hipLaunchKernelGGL(k_map, dim3(eg), dim3(256), 0, s, v, m->d_box, (int64_t)m->nel, 1, nullptr,
                        m->d_cell_off, fill.p, m->d_cell_el);
-    hipLaunchKernelGGL(k_map_sort, dim3((int)((ncell + 255) / 256)), dim3(256), 0, s,
-                       m->d_cell_off, ncell, m->d_cell_el);
+    hipLaunchKernelGGL(k_map_sort, dim3((int)((ncell * kSortLanes + 255) / 256)), dim3(256), 0,
+                       s, m->d_cell_off, ncell, m->d_cell_el);
     m->max_cell = 0;
     for (int64_t c = 0; c < ncell; ++c)
         m->max_cell = std::max(m->max_cell, m->cell_off[c + 1] - m->cell_off[c]);
