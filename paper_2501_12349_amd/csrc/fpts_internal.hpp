@@ -558,6 +558,30 @@ hipError_t launch_eval_bin(const fpts_mesh *m, int pass, int64_t n, const int32_
                            const int32_t *elem, const double *r, const int2 *cand,
                            int n_fields, double *out, int *elem_cnt, const int *elem_off,
                            int *rank, int *sorted, double *erec, hipStream_t s);
+// A request of a serving batch: its arrays (the caller's) and the n points'
+// place off in the batch's.
+struct BatchReq {
+    const double *pts;
+    int32_t *code, *elem;
+    double *r, *dist, *out;
+    int64_t n, off;
+};
+constexpr int kBatchReqs = 16;   // of one launch
+struct BatchReqs {
+    int count;
+    BatchReq q[kBatchReqs];
+};
+// The batch's arrays ([..][n], component-major like each request's); which =
+// 0: the requests' points into pts; 1: the results out to the requests.
+struct BatchArrays {
+    double *pts;
+    const int32_t *code, *elem;
+    const double *r, *dist, *out;
+    int64_t n;
+    int D, R, n_fields;
+};
+hipError_t launch_batch_copy(int which, const BatchArrays &b, const BatchReqs &reqs,
+                             hipStream_t s);
 // A list of points grouped by element (elem_off) and its tasks (chunk_off,
 // task_elem: on line meshes up to kChunk points each, else the even parts of
 // an element's list), where its r comes from (EvalArgs), and optionally tmp

@@ -150,6 +150,12 @@ size_t batch_bytes(const fpts_server *s, int mesh, int64_t ntot, size_t nreq)
     return b;
 }
 
+using fpts::BatchArrays;
+using fpts::BatchReq;
+using fpts::BatchReqs;
+using fpts::kBatchReqs;
+using fpts::launch_batch_copy;
+
 // Enqueue one batch on its stream.  Runs without the server lock: the
 // requests and the mesh entry are passed by address (taken under the lock;
 // deque elements do not move), and nothing here writes shared state.
@@ -167,9 +173,17 @@ bool launch(fpts_server *s, const Batch &b, const std::vector<const Req *> &rq,
     char *ws;
     size_t wsb = batch_ws(me, n);
     bool ok = true;
-    auto cp = [&](void *dst, const void *src, size_t bytes) {
-        if (bytes && hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, st) != hipSuccess)
-            ok = false;
+    BatchArrays arr{};
+    auto copy = [&](int which) {
+        for (size_t k = 0; k < rq.size() && ok; k += kBatchReqs) {
+            BatchReqs reqs{};
+            reqs.count = (int)std::min<size_t>(rq.size() - k, kBatchReqs);
+            for (int i = 0; i < reqs.count; ++i) {
+                const Req &q = *rq[k + i];
+                reqs.q[i] = BatchReq{q.pts, q.code, q.elem, q.r, q.dist, q.out, q.n, q.offset};
+            }
+            ok = launch_batch_copy(which, arr, reqs, st) == hipSuccess;
+        }
     };
     for (const Req *q : rq)
         if (hipStreamWaitEvent(st, q->ready, 0) != hipSuccess) ok = false;
@@ -195,11 +209,8 @@ bool launch(fpts_server *s, const Batch &b, const std::vector<const Req *> &rq,
         p += up(sizeof(double) * n);
         out = reinterpret_cast<double *>(p);
         ws = base;
-        for (const Req *qp : rq) {
-            const Req &q = *qp;
-            for (int d = 0; d < D; ++d)
-                cp(pts_b + d * n + q.offset, q.pts + d * q.n, sizeof(double) * q.n);
-        }
+        arr = BatchArrays{pts_b, code, elem, r, dist, out, n, D, R, nf};
+        copy(0);
         pts = pts_b;
     }
     if (!ok) return false;
@@ -211,18 +222,7 @@ bool launch(fpts_server *s, const Batch &b, const std::vector<const Req *> &rq,
                FPTS_OK) {
         return false;
     }
-    if (b.reqs.size() > 1) {
-        for (const Req *qp : rq) {
-            const Req &q = *qp;
-            cp(q.code, code + q.offset, sizeof(int32_t) * q.n);
-            cp(q.elem, elem + q.offset, sizeof(int32_t) * q.n);
-            cp(q.dist, dist + q.offset, sizeof(double) * q.n);
-            for (int k = 0; k < R; ++k)
-                cp(q.r + k * q.n, r + k * n + q.offset, sizeof(double) * q.n);
-            for (int f = 0; f < nf; ++f)
-                cp(q.out + f * q.n, out + f * n + q.offset, sizeof(double) * q.n);
-        }
-    }
+    if (b.reqs.size() > 1) copy(1);
     return ok && hipEventRecord(s->done_ev[b.stream], st) == hipSuccess;
 }
 
