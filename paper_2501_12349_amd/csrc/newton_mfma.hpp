@@ -2289,6 +2289,16 @@ __device__ __forceinline__ void few_body(const NewtonArgs &a)
     add_counters(cn, io.stats, lane);
 }
 
+// Waves per SIMD of the Newton and resolve kernels (the launch takes four times
+// as many blocks per CU).  Two parameters leave room for three, with a few
+// spilled registers at most, which cover more of each other's latencies
+// (k_newton, surface, N = 7, 2M points 485 -> 431 us; quads, N = 6, 1.5M
+// points 213 -> 179; k_newton_resolve, surface, N = 6, 1M points 135 -> 90;
+// at N = 10 it spills, 216 -> 238, and stays at two).  Three parameters need
+// all 256 registers (N = 4 at three waves: 2251 instead of 768 us).
+constexpr int newton_waves(int R) { return R == 2 ? 3 : 2; }
+constexpr int resolve_waves(int R, int N) { return R == 2 && N <= 9 ? 3 : 2; }
+
 // (at least three waves per SIMD: the register budget then stays within the
 // 256 VGPRs, and the compiler gives the MFMA results VGPRs, not AGPRs that
 // the selection would first have to copy out)
@@ -2299,18 +2309,22 @@ k_nearest(NewtonArgs a)
     nearest_body<D, R, N, MIXED>(a);
 }
 template <int D, int R, int N>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_newton(NewtonArgs a)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(
+    newton_waves(R), newton_waves(R)))) void
+k_newton(NewtonArgs a)
 {
     newton_body<double, D, R, N, kPrimary>(a);
 }
 template <int D, int R, int N>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(
+    newton_waves(R), newton_waves(R)))) void
 k_newton_polish(NewtonArgs a)
 {
     newton_body<double, D, R, N, kPolish>(a);
 }
 template <int D, int R, int N>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(
+    resolve_waves(R, N), resolve_waves(R, N)))) void
 k_newton_resolve(NewtonArgs a)
 {
     few_body<D, R, N, kResolve>(a);
@@ -2517,8 +2531,9 @@ hipError_t launch_newton_kind(const fpts_mesh *m, bool mixed, int64_t n, const d
         // starts given as points (the FP32 phase's results, or the hinted
         // search of particle tracking) take the warm-start kernel
         const KernelFn kn = resolve || (io.node && !mixed) ? k.newton : k.warm;
-        hipLaunchKernelGGL(kn, dim3(m->cus * 8), dim3(64), resolve ? k.lds_few : k.lds_newton, s,
-                           a);
+        const int waves = resolve ? resolve_waves(m->R, m->N) : newton_waves(m->R);
+        hipLaunchKernelGGL(kn, dim3(m->cus * 4 * waves), dim3(64),
+                           resolve ? k.lds_few : k.lds_newton, s, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
