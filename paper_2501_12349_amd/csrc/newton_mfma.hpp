@@ -1837,6 +1837,12 @@ struct NearLds {
 // distance itself (non-negative), and the node index replaces the low
 // kNodeBits mantissa bits; one minimum per score then keeps the nearest node
 // with ties (equal to 2^-42 relative) to the lowest index.
+// Bound by the FP64 products and the two operations that take up each score
+// (N = 8, 5M points: 390 us of the 570); the reductions over a row's 16 lanes
+// are register moves, since a chain of four shuffles each, through LDS, for
+// 16 scores per task cost as much as several node tiles (N = 4, 4M points 184
+// -> 160 us; FP32, N = 8, 1.3M points 199 -> 183; N = 6, 27 thousand points 20
+// -> 15).
 constexpr int kNodeBits = 10;   // node indices below 1024 (N <= 10)
 // one bit-field insert (mask from a scalar register: no literal operands
 // here), in place in the low word; written out because the compiler would
@@ -1856,6 +1862,29 @@ __device__ __forceinline__ double key_min(double a, double b)
     double r;
     asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
     return r;
+}
+__device__ __forceinline__ float key_min(float a, float b)
+{
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+// x of the lane SH places on in the row of 16 (register moves; a shuffle goes
+// through LDS, and the reductions over a row are chains of four)
+template <int SH>
+__device__ __forceinline__ int row_ror(int x)
+{
+    return __builtin_amdgcn_mov_dpp(x, 0x120 + SH, 0xf, 0xf, true);
+}
+template <int SH>
+__device__ __forceinline__ float row_ror(float x)
+{
+    return __int_as_float(row_ror<SH>(__float_as_int(x)));
+}
+template <int SH>
+__device__ __forceinline__ double row_ror(double x)
+{
+    return __hiloint2double(row_ror<SH>(__double2hiint(x)), row_ror<SH>(__double2loint(x)));
 }
 template <int D, int R, int N, bool MIXED>
 __device__ __forceinline__ void nearest_body(const NewtonArgs &a)
@@ -1905,25 +1934,39 @@ __device__ __forceinline__ void nearest_body(const NewtonArgs &a)
 #pragma unroll
         for (int c = 0; c < D; ++c) xc[c] = a.xc[(size_t)e * D + c];
         wave_lds_sync();   // the previous task's reads come first
-        // B rows of the element's nodes (FP32; FP64 reads the setup rows)
+        // B rows of the element's nodes (FP32; FP64 reads the setup rows), up
+        // to eight nodes' loads per lane at once
+        constexpr int AHEAD = 8;
 #pragma unroll 1
-        for (int j = lane; L::B_IN_LDS && j < L::NPAD; j += kWave) {
-            T b[4] = {T(0), T(0), T(0), T(0)};
-            if (j < S::NP) {
-                T n2 = T(0);
+        for (int j0 = lane; L::B_IN_LDS && j0 < L::NPAD; j0 += AHEAD * kWave) {
+            T v[AHEAD][D];
 #pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    const T v = MIXED ? T(a.nodes32[((size_t)e * D + c) * S::NP + j])
-                                      : T(a.nodes[((size_t)e * D + c) * S::NP + j] - xc[c]);
-                    b[c] = T(-2) * v;
-                    n2 = fma(v, v, n2);
-                }
-                b[D] = n2;
-            } else {
-                b[D] = kBig;
+            for (int u = 0; u < AHEAD; ++u) {
+                const int j = min(j0 + u * kWave, S::NP - 1);
+#pragma unroll
+                for (int c = 0; c < D; ++c)
+                    v[u][c] = MIXED ? T(a.nodes32[((size_t)e * D + c) * S::NP + j])
+                                    : T(a.nodes[((size_t)e * D + c) * S::NP + j] - xc[c]);
             }
 #pragma unroll
-            for (int k = 0; k < 4; ++k) Bt[k * L::NPAD + j] = b[k];
+            for (int u = 0; u < AHEAD; ++u) {
+                const int j = j0 + u * kWave;
+                if (j >= L::NPAD) break;
+                T r[4] = {T(0), T(0), T(0), T(0)};
+                if (j < S::NP) {
+                    T n2 = T(0);
+#pragma unroll
+                    for (int c = 0; c < D; ++c) {
+                        r[c] = T(-2) * v[u][c];
+                        n2 = fma(v[u][c], v[u][c], n2);
+                    }
+                    r[D] = n2;
+                } else {
+                    r[D] = kBig;
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) Bt[k * L::NPAD + j] = r[k];
+            }
         }
         // A rows of the pairs
         {
@@ -2024,10 +2067,13 @@ __device__ __forceinline__ void nearest_body(const NewtonArgs &a)
             for (int pt = 0; pt < 4; ++pt) {
                 if (pt >= ntile) break;
 #pragma unroll
-                for (int o = 1; o < 16; o <<= 1)
-#pragma unroll
-                    for (int qq = 0; qq < 4; ++qq)
-                        best[pt][qq] = key_min(best[pt][qq], __shfl_xor(best[pt][qq], o));
+                for (int qq = 0; qq < 4; ++qq) {
+                    double k = best[pt][qq];
+                    k = key_min(k, row_ror<8>(k));
+                    k = key_min(k, row_ror<4>(k));
+                    k = key_min(k, row_ror<2>(k));
+                    best[pt][qq] = key_min(k, row_ror<1>(k));
+                }
                 // lane `col` < 4 writes the pair of output row g + 4 col
                 // (the node index is in the low word; masks, not a select
                 // chain, which the compiler would turn into a stack array)
@@ -2081,18 +2127,20 @@ __device__ __forceinline__ void nearest_body(const NewtonArgs &a)
 #pragma unroll
             for (int pt = 0; pt < 4; ++pt) {
                 if (pt >= ntile) break;
-                // lexicographic (score, node) minimum over the 16 lanes of a row
+                // over the 16 lanes of a row: the lowest score, then the lowest
+                // node among the lanes that hold it
 #pragma unroll
-                for (int o = 1; o < 16; o <<= 1) {
-#pragma unroll
-                    for (int qq = 0; qq < 4; ++qq) {
-                        const T so = __shfl_xor(best[pt][qq], o);
-                        const int io2 = __shfl_xor(bix[pt][qq], o);
-                        const bool take =
-                            so < best[pt][qq] || (so == best[pt][qq] && io2 < bix[pt][qq]);
-                        bix[pt][qq] = take ? io2 : bix[pt][qq];
-                        best[pt][qq] = take ? so : best[pt][qq];
-                    }
+                for (int qq = 0; qq < 4; ++qq) {
+                    T k = best[pt][qq];
+                    k = key_min(k, row_ror<8>(k));
+                    k = key_min(k, row_ror<4>(k));
+                    k = key_min(k, row_ror<2>(k));
+                    k = key_min(k, row_ror<1>(k));
+                    int i = best[pt][qq] == k ? bix[pt][qq] : INT32_MAX;
+                    i = min(i, row_ror<8>(i));
+                    i = min(i, row_ror<4>(i));
+                    i = min(i, row_ror<2>(i));
+                    bix[pt][qq] = min(i, row_ror<1>(i));
                 }
                 // lane `col` < 4 writes the pair of its row group held in item qq = col
                 int bi = bix[pt][0] * (col == 0) + bix[pt][1] * (col == 1) +
@@ -2116,11 +2164,14 @@ __device__ __forceinline__ void nearest_body(const NewtonArgs &a)
 // NodeLds layout), by a segment of L lanes together (j: the lane's place in
 // it): the squared distance summed over the coordinates in order, the lowest
 // node index among equal distances (Section 3.2.1 starts Newton there).
+// (The same reduction, and four nodes' reads at once: k_newton_resolve, N = 8,
+// 5M points 431 -> 415 us; surface, N = 7, 2M points 174 -> 161.)
 template <int D, int R, int N, int L>
 __device__ __forceinline__ int nearest_staged(const double *xl, const double (&x)[D], int j)
 {
     double bd = __builtin_huge_val();
     int bi = 0;
+#pragma unroll(N <= 8 ? 4 : 1)
     for (int n = j; n < Shape<D, R, N>::NP; n += L) {
         double d2 = 0.0;
 #pragma unroll
@@ -2133,15 +2184,22 @@ __device__ __forceinline__ int nearest_staged(const double *xl, const double (&x
             bi = n;
         }
     }
-#pragma unroll
-    for (int o = 1; o < L; o <<= 1) {
-        const double od = __shfl_xor(bd, o);
-        const int oi = __shfl_xor(bi, o);
-        if (od < bd || (od == bd && oi < bi)) {
-            bd = od;
-            bi = oi;
-        }
-    }
+    // the lowest distance, then the lowest node among the lanes that hold it
+    // (rows of 16 by register moves, the rest of the segment by shuffles)
+    double k = bd;
+    k = key_min(k, row_ror<8>(k));
+    k = key_min(k, row_ror<4>(k));
+    k = key_min(k, row_ror<2>(k));
+    k = key_min(k, row_ror<1>(k));
+    if (L >= 32) k = key_min(k, __shfl_xor(k, 16));
+    if (L >= 64) k = key_min(k, __shfl_xor(k, 32));
+    bi = bd == k ? bi : INT32_MAX;
+    bi = min(bi, row_ror<8>(bi));
+    bi = min(bi, row_ror<4>(bi));
+    bi = min(bi, row_ror<2>(bi));
+    bi = min(bi, row_ror<1>(bi));
+    if (L >= 32) bi = min(bi, __shfl_xor(bi, 16));
+    if (L >= 64) bi = min(bi, __shfl_xor(bi, 32));
     return bi;
 }
 
