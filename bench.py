@@ -52,13 +52,23 @@ def eval_flops(D, R, N, h2):
     return con + basis + obj
 
 
+def node_starts(stats):
+    """FP64 map evaluations of the primary pass at the pairs' start nodes,
+    which take the node and rows of the differentiation matrix instead of a
+    sweep (in mixed mode the FP32 phase makes them)."""
+    return 0 if stats["evals_fp32"] else min(stats["pairs"], stats["evals"])
+
+
 def newton_flops(stats, D, R, N):
     """FLOPs of one k_newton launch from its exact counters: every map
     evaluation the iteration needs (first derivatives at each query point,
-    second derivatives where a face pass needs them), FP32 and FP64."""
-    f = stats["evals"] * eval_flops(D, R, N, False)
-    f += stats["evals_h2"] * (eval_flops(D, R, N, True) - eval_flops(D, R, N, False))
-    f += stats["evals_fp32"] * eval_flops(D, R, N, False)
+    second derivatives where a face pass needs them), FP32 and FP64; at a
+    start node D R dot products of length N and the objective terms."""
+    full = eval_flops(D, R, N, False)
+    at_node = 2 * D * R * N + 2 * D * (1 + R + R * R)
+    n64, n32 = node_starts(stats), stats.get("evals_fp32_node", 0)
+    f = (stats["evals"] - n64 + stats["evals_fp32"] - n32) * full + (n64 + n32) * at_node
+    f += stats["evals_h2"] * (eval_flops(D, R, N, True) - full)
     return float(f)
 
 
@@ -72,7 +82,8 @@ def slot_use(stats):
     """Fraction of busy pair slots per sweep (16 slots per wavefront)."""
     out = {}
     if stats["sweeps"]:
-        out["sweep1"] = round(stats["evals"] / (16.0 * stats["sweeps"]), 4)
+        swept = stats["evals"] - node_starts(stats)
+        out["sweep1"] = round(swept / (16.0 * stats["sweeps"]), 4)
     if stats["sweeps_h2"]:
         out["sweep2"] = round(stats["evals_h2"] / (16.0 * stats["sweeps_h2"]), 4)
     if stats["sweeps_fp32"]:

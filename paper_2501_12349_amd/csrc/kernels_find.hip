@@ -3,7 +3,8 @@
 // OBB tests (eqs. eq_AABB_test, eq_OBB_test); the primary candidate of each
 // point is bucketed by element for Newton; points the primary does not
 // settle get their other candidates in a second pass and the selection rule
-// of Section 3.2.  Also the scan and fill kernels used by find and eval.
+// of Section 3.2.  Also the scans used by find and eval and the copies of a
+// serving batch.
 #include "fpts_internal.hpp"
 
 namespace fpts {
