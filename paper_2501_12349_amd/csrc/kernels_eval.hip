@@ -265,21 +265,22 @@ __global__ __launch_bounds__(64) void k_eval(EvalArgs a)
     }
 }
 
-// Waves per SIMD that k_eval_mfma's registers are allocated for: four where
-// the fields loaded ahead leave the contraction enough of 128, else two (held
-// to four, N = 6 with four fields spills 108 registers and takes 373 instead
-// of 250 us for 3M points).
-template <int N, int FC>
+// Waves per SIMD of k_eval_mfma: four where the fields loaded ahead leave the
+// contraction enough of 128 registers, else two, with all they can use (N = 6,
+// four fields, 3M points: 250 us so, 373 held to four with 108 spilled
+// registers; N = 8, three fields, 5M points: 423 us, 468 with three waves, which
+// get in each other's way with their scattered writes).
+template <int R, int N, int FC>
 constexpr int eval_waves_per_eu()
 {
-    return FC * N * N <= 90 ? 4 : 2;
+    return (R == 2 ? FC * N <= 30 : FC * N * N <= 90) ? 4 : 2;
 }
 
 // Interpolation with the first contraction on the matrix cores (quad, hex
 // and surface meshes; FC fields a.f0 .. a.f0 + FC - 1 per launch).  One
 // wavefront per task, one of the even parts of an element's list (one wave
 // for each element left most of the chip idle where the points crowd: 2M
-// points in the wake of a channel, N = 8, three fields, 679 -> 222 us): the
+// points in the wake of a channel, N = 8, three fields, 679 -> 201 us): the
 // FC fields of the element are staged in LDS once (layout of the Newton
 // kernels' node block, one field per coordinate slot), and the task's points
 // are taken 64 and then 16 at a time, one per slot of four lanes (slot = lane
@@ -293,13 +294,14 @@ constexpr int eval_waves_per_eu()
 // not on the group or task it lands in.
 // The fields of the wave's next task, the next 64 points and the offsets of
 // the task after are loaded while the current ones are contracted.
-// Bound by FP64 arithmetic at large N (N = 8, 5M points, three fields: 450
+// Bound by FP64 arithmetic at large N (N = 8, 5M points, three fields: 423
 // us, with the matrix cores 63% and the vector units another 27% of the time
 // busy, against 240 for the products alone) and by the scattered writes of
 // its values at small N (N = 4, 4M points, one field: 107 us, 37 G/s).
 template <int R, int N, int FC>
 __global__ __launch_bounds__(64)
-__attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<N, FC>()))) void
+__attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<R, N, FC>(),
+                                   eval_waves_per_eu<R, N, FC>()))) void
 k_eval_mfma(EvalArgs a)
 {
     typedef newton::Shape<3, R, N> S;
@@ -878,7 +880,7 @@ hipError_t launch_eval(const fpts_mesh *m, int64_t n, int n_fields, int field_n,
             // than that many scattered writes (some 28 us per 1M values;
             // N = 6, four fields, 3M points: 250 + 77 us, scattered 360).
             // At larger N the writes hide behind the arithmetic (N = 8, three
-            // fields, 5M points: 420 + 121 us, scattered 450).
+            // fields, 5M points: 420 + 121 us, scattered 423).
             const bool spread = l.tmp && fc >= kSpreadFields && field_n <= kSpreadNodes;
             a.tmp = spread ? l.tmp : nullptr;
             hipLaunchKernelGGL(fn, grid, dim3(64), lds, s, a);
