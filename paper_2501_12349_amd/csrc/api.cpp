@@ -172,7 +172,8 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     // exact bound (their kernel has no overflow path).
     const int64_t cmax = n * (int64_t)std::max(m->max_cell - 1, 1);
     w.cap2 = std::max<int64_t>(1, m->R == 1 ? cmax : std::min<int64_t>(cmax, n));
-    w.bin_shift = bin_shift(ncell);
+    w.bin_shift = bin_shift(n, ncell);
+    w.cell_stride = w.bin_shift < 0 ? elem_stride(ncell) : 1;
     w.bin_hist_n = w.bin_shift < 0 ? 0 : bin_hist_size(n, ncell, w.bin_shift);
     w.scan_blocks = scan_tmp_blocks(
         std::max<int64_t>(std::max<int64_t>(std::max<int64_t>(n, m->nel), ncell), w.bin_hist_n));
@@ -228,7 +229,7 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     // zeroed at the start of a call: [zero, total).  The counters stay last:
     // an Interpolate in the same workspace leaves them readable.
     w.zero = c.at;
-    w.cell_cnt = c.take(I * ncell);
+    w.cell_cnt = c.take(I * ncell * w.cell_stride);
     w.elem_cnt = c.take(I * m->nel * elem_stride(m->nel));
     w.elem_cnt2 = c.take(I * m->nel);
     w.park_cnt = c.take(I * m->nel);
@@ -349,12 +350,14 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
                 UnitScan{cell_cnt, ncell, tmp, cell_poff, cell_choff, task_cell}, tb, s));
             chk(launch_bin_scatter(n, npairs, pairs, rank, cell_poff, pbin, m->cus, s));
         } else {
-            chk(launch_cell_bin(m, 0, n, d_pts, pts4, keep, cellpt, cell_cnt, nullptr, rank,
+            const int cs = w.cell_stride;
+            chk(launch_cell_bin(m, 0, n, d_pts, pts4, keep, cellpt, cell_cnt, cs, nullptr, rank,
                                 nullptr, cand, d_code, d_elem, d_r, d_dist, s));
-            chk(launch_unit_scan(
-                UnitScan{cell_cnt, ncell, tmp, cell_poff, cell_choff, task_cell}, tb, s));
-            chk(launch_cell_bin(m, 1, n, d_pts, nullptr, keep, cellpt, nullptr, cell_poff, rank,
-                                pbin, nullptr, d_code, d_elem, d_r, d_dist, s));
+            chk(launch_unit_scan(UnitScan{cell_cnt, ncell, tmp, cell_poff, cell_choff, task_cell,
+                                          kChunk, cs},
+                                 tb, s));
+            chk(launch_cell_bin(m, 1, n, d_pts, nullptr, keep, cellpt, nullptr, cs, cell_poff,
+                                rank, pbin, nullptr, d_code, d_elem, d_r, d_dist, s));
         }
         chk(launch_locate_cells(m, n, d_pts, pts4, pbin, cell_poff, cell_choff, ncell, task_cell,
                                 w.tb_cell, cand, elem_cnt, rank, bin_prim, d_code,

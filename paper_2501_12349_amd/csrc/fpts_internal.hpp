@@ -223,6 +223,7 @@ struct FindWs {
     int64_t park_state_cap;  // parked pairs whose iteration state is saved
     int64_t ov_grid;        // blocks of the overflow search (its scratch)
     int bin_shift;          // phase A without per-point atomics: bucket shift, or -1
+    int cell_stride;        // ints between the cells' counters (elem_stride)
     int64_t bin_hist_n;     // entries of its bucket histograms (nb * ntile)
 };
 
@@ -441,11 +442,11 @@ int64_t scan_tmp_blocks(int64_t n);
 // (keep may be null) are left out and keep their results; pass 0 also
 // writes the coordinates packed per point to pts4 unless it is null
 hipError_t launch_cell_bin(const fpts_mesh *m, int pass, int64_t n, const double *pts,
-                           double *pts4, const int *keep, int *cellpt, int *cell_cnt,
+                           double *pts4, const int *keep, int *cellpt, int *cell_cnt, int cs,
                            const int *cell_poff, int *rank, int *pbin, int2 *cand,
                            int32_t *code, int32_t *elem, double *r, double *dist, hipStream_t s);
-// Phase A without per-point atomics (meshes with at most kBinMaxCells
-// cells; bin_shift returns -1 beyond): cells grouped into buckets of
+// Phase A without per-point atomics (many points, at most kBinMaxCells
+// cells; bin_shift returns -1 else): cells grouped into buckets of
 // 2^shift cells, at most kBinMaxBuckets of them.  tiles: as pass 0 of
 // launch_cell_bin, and each tile's bucket histogram into bh[bucket * ntile
 // + tile] (bh is then scanned in place, its total at bh[nb * ntile]); coarse: (cell, id) pairs sorted by bucket from the
@@ -454,7 +455,7 @@ hipError_t launch_cell_bin(const fpts_mesh *m, int pass, int64_t n, const double
 // id of pair i.
 constexpr int64_t kBinMaxCells = (int64_t)1 << 24;
 constexpr int kBinMaxBuckets = 4096;
-int bin_shift(int64_t ncell);
+int bin_shift(int64_t n, int64_t ncell);
 // entries of bh: buckets times tiles
 int64_t bin_hist_size(int64_t n, int64_t ncell, int shift);
 inline int64_t bin_cells(const fpts_mesh *m)

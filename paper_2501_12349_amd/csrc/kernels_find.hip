@@ -249,13 +249,13 @@ __device__ inline int bin_point(const HashView &h, int p, int n, int R, const do
     return c;
 }
 
-// Phase A with one atomic per point (meshes with more than kBinMaxCells
-// cells).  pass 0: bin_point and the count per cell; pass 1: scatter point
+// Phase A with one atomic per point (bin_shift: few points, or more than
+// kBinMaxCells cells); the cells' counters lie cs ints apart.  pass 0: bin_point and the count per cell; pass 1: scatter point
 // ids into their cell's bucket.
 template <int D>
 __global__ __launch_bounds__(256) void k_cell_bin(HashView h, int pass, int n, int R,
                                                  const double *pts, double *pts4, const int *keep,
-                                                 int *cellpt, int *cell_cnt,
+                                                 int *cellpt, int *cell_cnt, int cs,
                                                  const int *cell_poff, int *rank,
                                                  int *pbin, int2 *cand, int32_t *code,
                                                  int32_t *elem, double *r, double *dist)
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(256) void k_cell_bin(HashView h, int pass, int n, i
     if (pass == 0) {
         const int c =
             in ? bin_point<D>(h, p, n, R, pts, pts4, keep, cellpt, cand, code, elem, r, dist) : -1;
-        const int k = wave_inc(cell_cnt, c, c >= 0);
+        const int k = wave_inc(cell_cnt, c * cs, c >= 0);
         if (c >= 0) rank[p] = k;
     } else {
         const int c = in ? cellpt[p] : -1;
@@ -1034,7 +1034,7 @@ hipError_t launch_park_bin(int pass, const int4 *meta, const int *total, int64_t
 }
 
 hipError_t launch_cell_bin(const fpts_mesh *m, int pass, int64_t n, const double *pts,
-                           double *pts4, const int *keep, int *cellpt, int *cell_cnt,
+                           double *pts4, const int *keep, int *cellpt, int *cell_cnt, int cs,
                            const int *cell_poff, int *rank, int *pbin, int2 *cand,
                            int32_t *code, int32_t *elem, double *r, double *dist, hipStream_t s)
 {
@@ -1043,13 +1043,20 @@ hipError_t launch_cell_bin(const fpts_mesh *m, int pass, int64_t n, const double
     const int grid = grid_for(n, 256);
     auto k = m->D == 2 ? k_cell_bin<2> : k_cell_bin<3>;
     hipLaunchKernelGGL(k, dim3(grid), dim3(256), 0, s, h, pass, (int)n, m->R, pts, pts4, keep,
-                       cellpt, cell_cnt, cell_poff, rank, pbin, cand, code, elem, r, dist);
+                       cellpt, cell_cnt, cs, cell_poff, rank, pbin, cand, code, elem, r, dist);
     return hipGetLastError();
 }
 
-int bin_shift(int64_t ncell)
+// Up to kCellBinPoints points go to their cells with one atomic each: three
+// launches instead of six (of 3 to 5 us each; find + interpolate of 1000 points
+// 121 -> 111 us), and with the counters spread over at least 512 cache lines a
+// few thousand atomics take a few microseconds.  Beyond, points that crowd in
+// cells of one line would wait for each other's atomics, 16 ns each.
+constexpr int64_t kCellBinPoints = 4096;
+
+int bin_shift(int64_t n, int64_t ncell)
 {
-    if (ncell > kBinMaxCells) return -1;
+    if (n <= kCellBinPoints || ncell > kBinMaxCells) return -1;
     // buckets of at least 512 cells: a tile's run per bucket is then tens
     // of pairs long (whole cache lines) at a few points per cell
     int shift = 9;
