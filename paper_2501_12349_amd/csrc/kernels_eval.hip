@@ -309,17 +309,22 @@ k_eval_mfma(EvalArgs a)
     typedef newton::Factor<R, N> F;
     typedef newton::V4<double>::type v4;
     constexpr int NP = S::NP, ROWS = S::ROWS, KS = S::KS;
-        constexpr int PER = (NP + 63) / 64;
+    constexpr int PER = (NP + 63) / 64;
     // row tiles: FT of 16 rows, QT of four (a 16-row tile takes as long as
     // four of those)
     constexpr int FT = ROWS / 16 + (ROWS % 16 > 12 ? 1 : 0);
     constexpr int QT = ROWS > 16 * FT ? (ROWS - 16 * FT + 3) / 4 : 0;
     constexpr bool kFullK = N % 4 == 0;
     constexpr bool kRows = ROWS >= 16 * FT;   // the 16-row tiles' rows all exist
+    // what the A operand's padding reads: a zero of its own, behind the tables.
+    // (A field's value there, times the zero of the B operand, would carry a
+    // NaN or an infinity of one field into the others.)
+    constexpr int kZero = L::SIZE + R * N * 16;
     extern __shared__ double lds_eval[];
     const int lane = threadIdx.x, slot = lane & 15, g = lane >> 4;
     double *xl = lds_eval;        // the FC fields, NodeLds layout
     double *tab = xl + L::SIZE;   // [R][N][16] bases of the group's points
+    if (N % 4 && lane == 0) xl[kZero] = 0.0;   // (read after stage_fields' barriers)
     const int G = gridDim.x, nel = a.nel;
     double v[FC][PER];
     auto load_fields = [&](int en) __attribute__((always_inline)) {
@@ -447,8 +452,8 @@ k_eval_mfma(EvalArgs a)
                         const bool aok = (kRows || arow < ROWS) && (kFullK || ai < N);
 #pragma unroll
                         for (int f = 0; f < FC; ++f)
-                            acc[f] =
-                                newton::mfma16(xl[aok ? L::at(f, arow, ai) : 0], b0[ks], acc[f]);
+                            acc[f] = newton::mfma16(xl[aok ? L::at(f, arow, ai) : kZero],
+                                                    b0[ks], acc[f]);
                     }
 #pragma unroll
                     for (int qq = 0; qq < 4; ++qq) {
@@ -480,7 +485,8 @@ k_eval_mfma(EvalArgs a)
                         const bool aok = (whole || arow < ROWS) && (kFullK || ai < N);
 #pragma unroll
                         for (int f = 0; f < FC; ++f)
-                            c[f] = newton::mfma4(xl[aok ? L::at(f, arow, ai) : 0], b0[ks], c[f]);
+                            c[f] = newton::mfma4(xl[aok ? L::at(f, arow, ai) : kZero], b0[ks],
+                                                 c[f]);
                     }
                     if (whole || row < ROWS) {
                         const double w = weight(row);
@@ -784,7 +790,8 @@ EvalFn pick_eval_mfma(int N, size_t *lds)
     switch (N) {
 #define FPTS_CASE(NN)                                                                      \
     case NN:                                                                               \
-        *lds = sizeof(double) * (newton::NodeLds<double, FC, R, NN>::SIZE + R * NN * 16);  \
+        *lds = sizeof(double) * (newton::NodeLds<double, FC, R, NN>::SIZE + R * NN * 16 +  \
+                                 (NN % 4 ? 1 : 0));                                        \
         return k_eval_mfma<R, NN, FC>;
         FPTS_CASE(2)
         FPTS_CASE(3)
