@@ -290,6 +290,10 @@ struct NodeLds {
     static constexpr int P = (ROT || N % 2) ? N : N + 1;
     static constexpr int RP = S::ROWS * P;               // per coordinate
     static constexpr int SIZE = D * RP;
+    // values from one node block to the next where a wave holds several: whole
+    // 16-byte words, as stage() writes them (SIZE is odd for D = 3 and odd N)
+    static constexpr int STRIDE = (SIZE * (int)sizeof(T) + 15) / 16 * 16 / (int)sizeof(T);
+    static_assert(STRIDE * sizeof(T) % 16 == 0, "node blocks start on 16 bytes");
     static constexpr bool PLAIN = !ROT && P == N;        // the global layout
     __device__ static __forceinline__ int at(int c, int row, int i)
     {
@@ -379,7 +383,7 @@ __device__ __forceinline__ void basis_table(T x, T *tab, int slot, bool write)
 // N <= 8 stay within 20 KB, so that eight waves fit a CU.
 template <typename T, int D, int R, int N>
 struct Lds {
-    static constexpr int NODES = NodeLds<T, D, R, N>::SIZE;
+    static constexpr int NODES = NodeLds<T, D, R, N>::STRIDE;
     static constexpr int TAB = (R == 3 ? 6 : 4) * N * 16;
     static constexpr int QB = 64 * R;
     static_assert(16 * (R + D) <= QB, "sweep 2 points");
@@ -463,7 +467,7 @@ __device__ __forceinline__ void sweep1(const T *xl, T *tab, const T *qb, int cg,
     typedef typename V4<T>::type v4;
     constexpr int FT = NB > 1 ? 0 : C::FT, QT = NB > 1 ? (S::ROWS + 3) / 4 : C::QT;
     const int slot = lane & 15, g = lane >> 4;
-    if (NB > 1) xl += slot / (16 / NB) * NL::SIZE;
+    if (NB > 1) xl += slot / (16 / NB) * NL::STRIDE;
     // per-column tables [direction][kind][i][column] (kinds phi, phi'): lane
     // quarter g builds direction g of its column, so the R tables of all 16
     // columns are built at once
@@ -683,7 +687,7 @@ __device__ __forceinline__ void sweep2(const T *xl, T *tab, const T *qb, int lan
     typedef typename V4<T>::type v4;
     typedef NodeLds<T, D, R, N> NL;
     const int slot = lane & 15, g = lane >> 4;
-    if (NB > 1) xl += slot / (16 / NB) * NL::SIZE;
+    if (NB > 1) xl += slot / (16 / NB) * NL::STRIDE;
     wave_lds_sync();   // qb is written
     T q[R], dx[D];
 #pragma unroll
@@ -1539,7 +1543,7 @@ __device__ __forceinline__ void run_few(const NewtonArgs &a, const double *xl, d
         // the start is a node: evaluated from the node block
         if (has) {
             double X[D], Gm[D][R];
-            node_map<double, D, R, N>(xl + b * NL::SIZE, node, r, X, Gm);
+            node_map<double, D, R, N>(xl + b * NL::STRIDE, node, r, X, Gm);
             objective<double, D, R>(xs, X, Gm, cur, dx);
             state = S_STEP;
         }
@@ -1746,15 +1750,17 @@ __device__ __forceinline__ void run_few(const NewtonArgs &a, const double *xl, d
 
 // Copies COUNT values of an element block from global memory to LDS (one
 // wave), issuing every load before the first store, then waits for the
-// workgroup.
+// workgroup.  lds starts on 16 bytes; src on a value (an element's block of an
+// odd number of values puts the next one between 16-byte words).
 template <typename T, int COUNT>
 __device__ __forceinline__ void stage(T *lds, const T *src, int lane)
 {
     typedef __attribute__((ext_vector_type(4))) unsigned int u4;
+    typedef u4 __attribute__((aligned(4))) u4_at_value;   // (a float's alignment)
     constexpr int WORDS = COUNT * (int)sizeof(T) / 16;
     constexpr int PER = (WORDS + kWave - 1) / kWave;
     constexpr int BATCH = 4;   // 16-byte loads in flight per lane
-    const u4 *s = reinterpret_cast<const u4 *>(src);
+    const u4_at_value *s = reinterpret_cast<const u4_at_value *>(src);
     u4 *d = reinterpret_cast<u4 *>(lds);
 #pragma unroll 1
     for (int k0 = 0; k0 < PER; k0 += BATCH) {
@@ -2289,7 +2295,7 @@ __device__ __forceinline__ void few_body(const NewtonArgs &a)
     constexpr int NB = few_elems(R, N), L = few_lanes(R, N);
     extern __shared__ double lds_raw[];
     double *xl = lds_raw;
-    double *tab = xl + NB * NL::SIZE;
+    double *tab = xl + NB * NL::STRIDE;
     double *qb = tab + Lds<double, D, R, N>::TAB;
     const int lane = threadIdx.x, b = lane / L, j = lane % L;
     const NewtonIO &io = a.io;
@@ -2323,7 +2329,7 @@ __device__ __forceinline__ void few_body(const NewtonArgs &a)
         for (int u = 0; u < NB; ++u) {
             const int eu = __builtin_amdgcn_readlane(e, u * L);
             if (eu >= 0)
-                stage_nodes<double, D, R, N>(xl + u * NL::SIZE, a.nodes + (size_t)eu * D * S::NP,
+                stage_nodes<double, D, R, N>(xl + u * NL::STRIDE, a.nodes + (size_t)eu * D * S::NP,
                                              lane);
         }
         int node = 0;
@@ -2338,7 +2344,7 @@ __device__ __forceinline__ void few_body(const NewtonArgs &a)
                 double x[D];
 #pragma unroll
                 for (int d = 0; d < D; ++d) x[d] = __shfl(xs[d], b * L + k);
-                const int bi = nearest_staged<D, R, N, L>(xl + b * NL::SIZE, x, j);
+                const int bi = nearest_staged<D, R, N, L>(xl + b * NL::STRIDE, x, j);
                 if (j == k) node = bi;
             }
         }
@@ -2520,7 +2526,7 @@ Kernels pick_kernels(int N, bool resolve)
         k.lds_newton32 = Lds<float, D, R, NN>::bytes();                                     \
         k.lds_newton = Lds<double, D, R, NN>::bytes();                                      \
         k.lds_few = k.lds_newton + sizeof(double) * (few_elems(R, NN) - 1) *                \
-                                       NodeLds<double, D, R, NN>::SIZE;                     \
+                                       NodeLds<double, D, R, NN>::STRIDE;                   \
         break;
     switch (N) {
         FPTS_CASE(2)
