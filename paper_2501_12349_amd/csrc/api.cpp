@@ -175,8 +175,13 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     w.bin_shift = bin_shift(n, ncell);
     w.cell_stride = w.bin_shift < 0 ? elem_stride(ncell) : 1;
     w.bin_hist_n = w.bin_shift < 0 ? 0 : bin_hist_size(n, ncell, w.bin_shift);
+    // No array gets smaller as n grows, so that a workspace made for n points
+    // holds for fewer, also where a smaller n takes another path: the tile
+    // histograms by their largest size up to n, the cells' counters always as
+    // far apart as the path of few points has them.
+    const int64_t hist = w.bin_shift < 0 ? 0 : bin_hist_bound(n, ncell, w.bin_shift);
     w.scan_blocks = scan_tmp_blocks(
-        std::max<int64_t>(std::max<int64_t>(std::max<int64_t>(n, m->nel), ncell), w.bin_hist_n));
+        std::max<int64_t>(std::max<int64_t>(std::max<int64_t>(n, m->nel), ncell), hist));
     const size_t I = sizeof(int);
     w.cell_poff = c.take(I * (ncell + 1));
     w.cell_choff = c.take(I * (ncell + 1));
@@ -224,12 +229,12 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     w.ov_grid = (int64_t)m->cus * 3;
     w.ov_int = c.take(I * 3 * w.ov_grid);
     w.ov_dbl = c.take(sizeof(double) * (m->R + 1) * w.ov_grid);
-    w.bin_hist = c.take(I * (w.bin_hist_n + 1));
+    w.bin_hist = c.take(I * (hist + 1));
     w.bin_pairs = c.take(w.bin_shift < 0 ? 1 : sizeof(int2) * n);
     // zeroed at the start of a call: [zero, total).  The counters stay last:
     // an Interpolate in the same workspace leaves them readable.
     w.zero = c.at;
-    w.cell_cnt = c.take(I * ncell * w.cell_stride);
+    w.cell_cnt = c.take(I * ncell * elem_stride(ncell));
     w.elem_cnt = c.take(I * m->nel * elem_stride(m->nel));
     w.elem_cnt2 = c.take(I * m->nel);
     w.park_cnt = c.take(I * m->nel);

@@ -458,6 +458,9 @@ constexpr int kBinMaxBuckets = 4096;
 int bin_shift(int64_t n, int64_t ncell);
 // entries of bh: buckets times tiles
 int64_t bin_hist_size(int64_t n, int64_t ncell, int shift);
+// the most of them for any number of points up to n (a workspace made for n
+// points has to hold for fewer)
+int64_t bin_hist_bound(int64_t n, int64_t ncell, int shift);
 inline int64_t bin_cells(const fpts_mesh *m)
 {
     int64_t c = 1;

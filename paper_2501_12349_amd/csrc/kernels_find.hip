@@ -1068,12 +1068,15 @@ int bin_shift(int64_t n, int64_t ncell)
 // below so that some three blocks per CU have work, as long as the bucket
 // histograms (one per tile) stay below an eighth of the points.  (At 4
 // million points 8 items took the tile pass from 74 to 64 us, but the pass
-// that writes the shorter runs from 26 to 33.)
+// that writes the shorter runs from 26 to 33.)  The second condition, once
+// met, holds for every larger n, so that the items grow with n at the ends of
+// the ranges only.
+static int64_t bin_items_end(int items) { return (int64_t)kBinThreads * items * 768; }
 static int bin_items(int64_t n, int nb)
 {
     int items = kBinItems;
-    while (items > 4 && n < (int64_t)kBinThreads * items * 768 &&
-           (n / (kBinThreads * items / 2) + 1) * nb <= n / 8)
+    while (items > 4 && n < bin_items_end(items) &&
+           nb * (n + kBinThreads / 2 * items) <= kBinThreads / 16 * items * n)
         items /= 2;
     return items;
 }
@@ -1089,6 +1092,15 @@ int64_t bin_hist_size(int64_t n, int64_t ncell, int shift)
 {
     const int nb = bin_buckets(ncell, shift);
     return nb * tiles_for(n, bin_items(n, nb));
+}
+int64_t bin_hist_bound(int64_t n, int64_t ncell, int shift)
+{
+    // the histograms shrink where the items grow: the last size before it
+    int64_t most = bin_hist_size(n, ncell, shift);
+    for (int items = kBinItems; items > 4; items /= 2)
+        if (n >= bin_items_end(items))
+            most = std::max(most, bin_hist_size(bin_items_end(items) - 1, ncell, shift));
+    return most;
 }
 
 // a grid of at least `blocks` blocks, a multiple of the XCD count
