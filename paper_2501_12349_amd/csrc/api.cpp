@@ -173,12 +173,12 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     const int64_t cmax = n * (int64_t)std::max(m->max_cell - 1, 1);
     w.cap2 = std::max<int64_t>(1, m->R == 1 ? cmax : std::min<int64_t>(cmax, n));
     w.bin_shift = bin_shift(n, ncell);
-    w.cell_stride = w.bin_shift < 0 ? elem_stride(ncell) : 1;
+    w.cell_stride = w.bin_shift < 0 ? elem_stride(ncell, n) : 1;
     w.bin_hist_n = w.bin_shift < 0 ? 0 : bin_hist_size(n, ncell, w.bin_shift);
-    // No array gets smaller as n grows, so that a workspace made for n points
-    // holds for fewer, also where a smaller n takes another path: the tile
-    // histograms by their largest size up to n, the cells' counters always as
-    // far apart as the path of few points has them.
+    // The total never gets smaller as n grows, so that a workspace made for n
+    // points holds for fewer, also where a smaller n takes another path: the
+    // tile histograms take their largest size up to n, the cells' counters
+    // always that of the path of few points.
     const int64_t hist = w.bin_shift < 0 ? 0 : bin_hist_bound(n, ncell, w.bin_shift);
     w.scan_blocks = scan_tmp_blocks(
         std::max<int64_t>(std::max<int64_t>(std::max<int64_t>(n, m->nel), ncell), hist));
@@ -186,10 +186,19 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     w.cell_poff = c.take(I * (ncell + 1));
     w.cell_choff = c.take(I * (ncell + 1));
     w.cellpt = c.take(I * n);
-    w.pbin = c.take(I * n);
     w.cand = c.take(sizeof(int2) * n);
     w.rank = c.take(I * n);
+    // the result records (Newton writes the first ones) lie where the binning
+    // by cell has its pairs and places
+    const size_t bin = c.at;
+    w.pbin = c.take(I * n);
     w.bin_prim = c.take(I * n);
+    w.bin_hist = c.take(I * (hist + 1));
+    w.bin_pairs = c.take(w.bin_shift < 0 ? 1 : sizeof(int2) * n);
+    const size_t bin_end = c.at;
+    c.at = bin;
+    w.rec = c.take(m->R >= 2 ? sizeof(double) * kRec * n : 1);
+    c.at = std::max(c.at, bin_end);
     w.elem_off = c.take(I * (m->nel + 1));
     w.chunk_off = c.take(I * (m->nel + 1));
     w.sorted = c.take(I * n);
@@ -212,7 +221,8 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     w.task_elem2 = c.take(I * w.tb_elem2);
     w.scan_tmp = c.take(I * w.scan_blocks);
     w.pts4 = c.take(m->R >= 2 ? sizeof(double) * pt_stride(m->D) * n : 1);
-    w.rec = c.take(m->R >= 2 ? sizeof(double) * kRec * n : 1);
+    // used from the Newton pass on
+    const size_t late = c.at;
     // parked pairs of the primary pass (at most one per point)
     w.park_meta = c.take(sizeof(int4) * n);
     w.park_r = c.take(sizeof(double) * (m->R + 1) * n);
@@ -229,13 +239,17 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     w.ov_grid = (int64_t)m->cus * 3;
     w.ov_int = c.take(I * 3 * w.ov_grid);
     w.ov_dbl = c.take(sizeof(double) * (m->R + 1) * w.ov_grid);
-    w.bin_hist = c.take(I * (hist + 1));
-    w.bin_pairs = c.take(w.bin_shift < 0 ? 1 : sizeof(int2) * n);
     // zeroed at the start of a call: [zero, total).  The counters stay last:
-    // an Interpolate in the same workspace leaves them readable.
-    w.zero = c.at;
-    w.cell_cnt = c.take(I * ncell * elem_stride(ncell));
-    w.elem_cnt = c.take(I * m->nel * elem_stride(m->nel));
+    // an Interpolate in the same workspace leaves them readable.  The counts
+    // per cell and per element are scanned before the Newton pass: they lie at
+    // the end of what is used from then on.
+    const size_t late_end = c.at;
+    const size_t cells = align_up(I * ncell * elem_stride(ncell, std::min(n, kCellBinPoints)));
+    const size_t elems = align_up(I * m->nel * elem_stride(m->nel, n));
+    w.zero = late_end - std::min(late_end - late, cells + elems);
+    w.cell_cnt = w.zero;
+    w.elem_cnt = w.cell_cnt + cells;
+    c.at = std::max(late_end, w.elem_cnt + elems);
     w.elem_cnt2 = c.take(I * m->nel);
     w.park_cnt = c.take(I * m->nel);
     w.counters = c.take(I * kCounters);
@@ -244,25 +258,27 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     return w;
 }
 
-EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n, bool own)
+EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n, EvalWsKind kind)
 {
     EvalWs w;
     Cursor c;
+    w.stride = kind == kEvalSmall ? 1 : elem_stride(m->nel, n);
     // zeroed before the points are binned: [0, zero_end)
-    w.elem_cnt = c.take(sizeof(int) * m->nel * elem_stride(m->nel));
+    w.elem_cnt = c.take(sizeof(int) * m->nel * w.stride);
     w.scount = c.take(sizeof(int));
     w.zero_end = c.at;
     w.elem_off = c.take(sizeof(int) * (m->nel + 1));
     w.rank = c.take(sizeof(int) * std::max<int64_t>(n, 1));
     w.chunk_off = c.take(sizeof(int) * (m->nel + 1));
     w.scan_tmp = c.take(sizeof(int) * scan_tmp_blocks(m->nel));
-    w.sorted = c.take(sizeof(int) * std::max<int64_t>(n, 1));
+    // (the records hold the point ids, too; arrays without use take no room)
+    const bool recs = kind == kEvalOwn && m->R >= 2;
+    w.sorted = recs ? c.at : c.take(sizeof(int) * n);
     w.tb_elem = task_bound(n, m->nel);
     w.task_elem = c.take(sizeof(int) * w.tb_elem);
-    w.slist = c.take(sizeof(int) * std::max<int64_t>(n, 1));
-    const bool recs = own && m->R >= 2;
-    w.erec = c.take(recs ? sizeof(double) * kRec * n : 1);
-    w.tmp = c.take(recs ? sizeof(double) * 4 * n : 1);
+    w.slist = kind == kEvalFused ? c.take(sizeof(int) * n) : c.at;
+    w.erec = recs ? c.take(sizeof(double) * kRec * n) : c.at;
+    w.tmp = recs ? c.take(sizeof(double) * 4 * n) : c.at;
     w.total = c.at;
     return w;
 }
@@ -367,7 +383,8 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
         chk(launch_locate_cells(m, n, d_pts, pts4, pbin, cell_poff, cell_choff, ncell, task_cell,
                                 w.tb_cell, cand, elem_cnt, rank, bin_prim, d_code,
                                 d_elem, d_r, d_dist, s));
-        UnitScan es{elem_cnt, nel, tmp, elem_off, chunk_off, task_elem, kChunk, elem_stride(nel)};
+        UnitScan es{elem_cnt, nel,       tmp,    elem_off,
+                    chunk_off, task_elem, kChunk, elem_stride(nel, n)};
         if (len > kChunk) {
             es.off2 = newt_off;
             es.task2 = newt_task;
@@ -618,7 +635,7 @@ int fpts_find(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
 size_t fpts_eval_workspace_size(const fpts_mesh *m, int64_t n)
 {
     if (!m || n < 0 || n > INT32_MAX - 1) return 0;
-    return eval_ws_layout(m, n, true).total;
+    return eval_ws_layout(m, n, kEvalOwn).total;
 }
 
 int fpts_eval(fpts_mesh *m, int64_t n, const int32_t *d_code, const int32_t *d_elem,
@@ -639,7 +656,11 @@ int fpts_eval_order(fpts_mesh *m, int64_t n, const int32_t *d_code, const int32_
     if (n == 0) return FPTS_OK;
     if (!d_code || !d_elem || !d_r || !d_field || !d_out || !d_ws) return FPTS_EINVAL;
     if (((uintptr_t)d_ws & 255) != 0) return FPTS_EINVAL;
-    const EvalWs w = eval_ws_layout(m, n, true);
+    // without room for the records the points are read through their ids and
+    // the values written where they go, at the same bits
+    EvalWs w = eval_ws_layout(m, n, kEvalOwn);
+    const bool recs = m->R >= 2 && ws_bytes >= w.total;
+    if (ws_bytes < w.total) w = eval_ws_layout(m, n, kEvalSmall);
     if (ws_bytes < w.total) return FPTS_EINVAL;
     if (sticky_error()) return FPTS_EDEVICE;
     hipStream_t s = (hipStream_t)stream;
@@ -650,7 +671,7 @@ int fpts_eval_order(fpts_mesh *m, int64_t n, const int32_t *d_code, const int32_
     int *tmp = at<int>(d_ws, w.scan_tmp);
     int *sorted = at<int>(d_ws, w.sorted);
     int *task_elem = at<int>(d_ws, w.task_elem);
-    double *erec = m->R >= 2 ? at<double>(d_ws, w.erec) : nullptr;
+    double *erec = recs ? at<double>(d_ws, w.erec) : nullptr;
     const int64_t tb = scan_tmp_blocks(m->nel);
     hipError_t e = hipSuccess;
     auto chk = [&](hipError_t x) {
@@ -658,15 +679,14 @@ int fpts_eval_order(fpts_mesh *m, int64_t n, const int32_t *d_code, const int32_
     };
     {
         Span sp(m, 4, s);
-        chk(launch_zero2(elem_cnt, m->nel * elem_stride(m->nel), nullptr, 0, s));
+        chk(launch_zero2(elem_cnt, m->nel * w.stride, nullptr, 0, s));
         chk(launch_eval_bin(m, 0, n, d_code, d_elem, nullptr, nullptr, n_fields, d_out, elem_cnt,
-                            nullptr, rank, nullptr, nullptr, s));
-        chk(launch_unit_scan(
-            UnitScan{elem_cnt, m->nel, tmp, elem_off, chunk_off, task_elem, eval_task_len(m, n),
-                     elem_stride(m->nel)},
-            tb, s));
+                            w.stride, nullptr, rank, nullptr, nullptr, s));
+        chk(launch_unit_scan(UnitScan{elem_cnt, m->nel, tmp, elem_off, chunk_off, task_elem,
+                                      eval_task_len(m, n), w.stride},
+                             tb, s));
         chk(launch_eval_bin(m, 1, n, d_code, d_elem, d_r, nullptr, n_fields, d_out, nullptr,
-                            elem_off, rank, sorted, erec, s));
+                            w.stride, elem_off, rank, sorted, erec, s));
     }
     {
         Span sp(m, 5, s);
@@ -678,7 +698,7 @@ int fpts_eval_order(fpts_mesh *m, int64_t n, const int32_t *d_code, const int32_
         l.task_bound = w.tb_elem;
         l.r = d_r;
         l.erec = erec;
-        l.tmp = m->R >= 2 ? at<double>(d_ws, w.tmp) : nullptr;
+        l.tmp = recs ? at<double>(d_ws, w.tmp) : nullptr;
         l.elem = d_elem;
         l.rank = rank;
         chk(launch_eval(m, n, n_fields, field_nodes_1d, d_field, d_out, l, s));
@@ -830,7 +850,7 @@ size_t fpts_lpt_workspace_size(const fpts_mesh *m, int64_t n)
     if (!m || n < 0 || n > INT32_MAX - 1) return 0;
     const size_t fw = fpts_find_workspace_size(m, n);
     if (fw == 0) return 0;
-    const size_t ew = eval_ws_layout(m, n, true).total;
+    const size_t ew = eval_ws_layout(m, n, kEvalSmall).total;
     const size_t nn = (size_t)std::max<int64_t>(n, 1);
     return align_up(sizeof(double) * (size_t)m->D * nn) + align_up(sizeof(int) * nn) +
            std::max(fw, ew);
@@ -912,7 +932,7 @@ int fpts_lpt_step(fpts_mesh *m, const fpts_lpt_params *p, int64_t n, int first, 
         chk(launch_zero2(at<int>(sub, w.zero), (w.total - w.zero) / sizeof(int), nullptr, 0, s));
         chk(launch_hint(m, 0, n, d_code, d_elem, d_r, cand, elem_cnt, rank, nullptr, s));
         chk(launch_unit_scan(UnitScan{elem_cnt, m->nel, tmp, elem_off, chunk_off, task_elem,
-                                      kChunk, elem_stride(m->nel)},
+                                      kChunk, elem_stride(m->nel, n)},
                              w.scan_blocks, s));
         chk(launch_primary_scatter(n, m->nel, cand, elem_off, rank, sorted, s));
     }
@@ -938,7 +958,7 @@ size_t fpts_find_eval_workspace_size(const fpts_mesh *m, int64_t n)
     const size_t fw = fpts_find_workspace_size(m, n);
     if (fw == 0) return 0;
     const size_t nn = (size_t)std::max<int64_t>(n, 1);
-    return fw + align_up(eval_ws_layout(m, n, false).total) +
+    return fw + align_up(eval_ws_layout(m, n, kEvalFused).total) +
            (m->R == 1 ? align_up(sizeof(double) * nn) : 0);
 }
 
@@ -959,7 +979,7 @@ int fpts_find_eval(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code
     // [find workspace][interpolation workspace], and on line meshes [n]
     // results in list order (the other meshes' are in the find workspace)
     const FindWs w = find_ws_layout(m, n);
-    const EvalWs v = eval_ws_layout(m, n, false);
+    const EvalWs v = eval_ws_layout(m, n, kEvalFused);
     void *ews = static_cast<char *>(d_ws) + w.total;
     double *rs = m->R == 1 ? at<double>(d_ws, w.total + align_up(v.total)) : nullptr;
     const double *rec = m->R == 1 ? nullptr : at<double>(d_ws, w.rec);
@@ -1036,27 +1056,26 @@ int fpts_find_eval(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code
         const bool split = m->R == 1;
         Span sp(m, 4, s);
         if (listed) {
-            chk(launch_eval_bin_list(m, 0, slist, scount, n, d_elem, elem_cnt, nullptr, erank,
-                                     nullptr, s));
+            chk(launch_eval_bin_list(m, 0, slist, scount, n, d_elem, elem_cnt, v.stride, nullptr,
+                                     erank, nullptr, s));
         } else {
             chk(launch_eval_bin(m, 0, n, d_code, d_elem, d_r, cand, n_fields, d_out, elem_cnt,
-                                nullptr, erank, nullptr, nullptr, s));
+                                v.stride, nullptr, erank, nullptr, nullptr, s));
         }
         if (split)
-            chk(launch_eval_split(m, n, d_elem, erank, elem_cnt, nullptr, nullptr, nullptr,
-                                  nullptr, 0, s));
-        chk(launch_unit_scan(UnitScan{elem_cnt, m->nel, tmp, eoff, choff, etask, kChunk,
-                                      elem_stride(m->nel)},
-                             tb, s));
+            chk(launch_eval_split(m, n, d_elem, erank, elem_cnt, v.stride, nullptr, nullptr,
+                                  nullptr, nullptr, 0, s));
+        chk(launch_unit_scan(
+            UnitScan{elem_cnt, m->nel, tmp, eoff, choff, etask, kChunk, v.stride}, tb, s));
         if (split)
-            chk(launch_eval_split(m, n, d_elem, erank, elem_cnt, eoff, esorted, slist, scount, 1,
-                                  s));
+            chk(launch_eval_split(m, n, d_elem, erank, elem_cnt, v.stride, eoff, esorted, slist,
+                                  scount, 1, s));
         else if (listed)
-            chk(launch_eval_bin_list(m, 1, slist, scount, n, d_elem, nullptr, eoff, erank,
-                                     esorted, s));
+            chk(launch_eval_bin_list(m, 1, slist, scount, n, d_elem, nullptr, v.stride, eoff,
+                                     erank, esorted, s));
         else
             chk(launch_eval_bin(m, 1, n, d_code, d_elem, d_r, cand, n_fields, d_out, nullptr,
-                                eoff, erank, esorted, nullptr, s));
+                                v.stride, eoff, erank, esorted, nullptr, s));
     }
     {
         Span sp(m, 5, s);

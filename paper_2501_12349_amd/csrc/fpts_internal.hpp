@@ -38,7 +38,8 @@ struct HashView {
     const double *box;     // [nel][box_words(D)]
 };
 
-// Byte offsets of the find workspace for n points (every array 256-aligned).
+// Byte offsets of the find workspace for n points (every array 256-aligned;
+// arrays that are never in use at the same time share their place).
 // Phase A bins points by cell of the local map, phase B tests each cell's
 // candidates and picks a primary candidate per point, phase C runs Newton on
 // the primaries, phase D runs the remaining candidates of the points the
@@ -120,11 +121,13 @@ __host__ __device__ inline void rodrigues_frame(int D, double tx, double ty, dou
 // 16 ns each, so that 32 counters a line make a mesh of a few thousand
 // elements count 10 G/s where 512 lines or more count 26 G/s (2 million
 // particles over 3888 elements: location 284 -> 155 us, counting pass of the
-// interpolation 203 -> 108 us, spread over one line per counter).
-inline int elem_stride(int64_t nel)
+// interpolation 203 -> 108 us, spread over one line per counter).  At most three
+// ints per point that counts: the workspace of a call of few points stays small,
+// and a thousand points on 64 lines wait for each other some 0.2 us.
+inline int elem_stride(int64_t nel, int64_t n)
 {
     int s = 1;
-    while (s < 32 && nel * s < 16384) s *= 2;
+    while (s < 32 && nel * s < 16384 && 2 * nel * s <= 3 * n) s *= 2;
     return s;
 }
 
@@ -231,6 +234,7 @@ struct EvalWs {
     size_t elem_cnt, elem_off, rank, chunk_off, scan_tmp, sorted, task_elem, slist, scount,
         zero_end, erec, tmp, total;
     int64_t tb_elem;
+    int stride;             // ints between the elements' counters (elem_stride)
 };
 
 // Where one Newton launch reads its work and writes its results.
@@ -411,9 +415,11 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
 
 // workspace layouts (api.cpp)
 FindWs find_ws_layout(const fpts_mesh *m, int64_t n);
-// own: the layout of an Interpolate call of its own, with its point records
-// and values in list order (else: the second pass of the fused call)
-EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n, bool own);
+// The interpolation's: of the second pass of the fused call; of an Interpolate
+// call of its own, with point records and values in list order; of such a call
+// in a workspace that does not hold those.
+enum EvalWsKind { kEvalFused, kEvalOwn, kEvalSmall };
+EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n, EvalWsKind kind);
 
 // launchers (kernels_*.hip); all return hipError_t of the last launch
 // zeroes two ranges of ints (counts may be 0) in one launch
@@ -455,6 +461,7 @@ hipError_t launch_cell_bin(const fpts_mesh *m, int pass, int64_t n, const double
 // id of pair i.
 constexpr int64_t kBinMaxCells = (int64_t)1 << 24;
 constexpr int kBinMaxBuckets = 4096;
+constexpr int64_t kCellBinPoints = 4096;   // up to these: one atomic per point
 int bin_shift(int64_t n, int64_t ncell);
 // entries of bh: buckets times tiles
 int64_t bin_hist_size(int64_t n, int64_t ncell, int shift);
@@ -542,8 +549,8 @@ hipError_t launch_newton(const fpts_mesh *m, int precision, int64_t n, const dou
 // zeroes the counts of elements with few points, phase 1 places every binned
 // point (bucket at its rank, or the list, *count entries)
 hipError_t launch_eval_split(const fpts_mesh *m, int64_t n, const int32_t *elem, const int *rank,
-                             int *elem_cnt, const int *elem_off, int *sorted, int *list,
-                             int *count, int phase, hipStream_t s);
+                             int *elem_cnt, int es, const int *elem_off, int *sorted,
+                             int *list, int *count, int phase, hipStream_t s);
 // interpolation of the listed points, one lane per point
 hipError_t launch_eval_sparse(const fpts_mesh *m, int64_t n, const double *r, int n_fields,
                               int field_n, const double *field, double *out,
@@ -556,12 +563,13 @@ hipError_t launch_eval_sparse(const fpts_mesh *m, int64_t n, const double *r, in
 // and found (no NaN writes): pass 0 counts per element and keeps each entry's
 // rank, pass 1 places the points
 hipError_t launch_eval_bin_list(const fpts_mesh *m, int pass, const int *list, const int *count,
-                                int64_t cap, const int32_t *elem, int *elem_cnt,
+                                int64_t cap, const int32_t *elem, int *elem_cnt, int es,
                                 const int *elem_off, int *rank, int *sorted, hipStream_t s);
 hipError_t launch_eval_bin(const fpts_mesh *m, int pass, int64_t n, const int32_t *code,
                            const int32_t *elem, const double *r, const int2 *cand,
-                           int n_fields, double *out, int *elem_cnt, const int *elem_off,
-                           int *rank, int *sorted, double *erec, hipStream_t s);
+                           int n_fields, double *out, int *elem_cnt, int es,
+                           const int *elem_off, int *rank, int *sorted, double *erec,
+                           hipStream_t s);
 // A request of a serving batch: its arrays (the caller's) and the n points'
 // place off in the batch's.
 struct BatchReq {

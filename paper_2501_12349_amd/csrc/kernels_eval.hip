@@ -827,26 +827,27 @@ EvalFn pick_eval_r(int R, int N)
 }  // namespace
 
 hipError_t launch_eval_bin_list(const fpts_mesh *m, int pass, const int *list, const int *count,
-                                int64_t cap, const int32_t *elem, int *elem_cnt,
+                                int64_t cap, const int32_t *elem, int *elem_cnt, int es,
                                 const int *elem_off, int *rank, int *sorted, hipStream_t s)
 {
     if (cap <= 0) return hipSuccess;
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((cap + 255) / 256,
                                                                  (int64_t)m->cus * 16));
     hipLaunchKernelGGL(k_eval_bin_list, dim3(grid), dim3(256), 0, s, pass, list, count,
-                       (int)m->nel, elem_stride(m->nel), elem, elem_cnt, elem_off, rank, sorted);
+                       (int)m->nel, es, elem, elem_cnt, elem_off, rank, sorted);
     return hipGetLastError();
 }
 
 hipError_t launch_eval_bin(const fpts_mesh *m, int pass, int64_t n, const int32_t *code,
                            const int32_t *elem, const double *r, const int2 *cand,
-                           int n_fields, double *out, int *elem_cnt, const int *elem_off,
-                           int *rank, int *sorted, double *erec, hipStream_t s)
+                           int n_fields, double *out, int *elem_cnt, int es,
+                           const int *elem_off, int *rank, int *sorted, double *erec,
+                           hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_eval_bin, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, pass,
-                       (int)n, (int)m->nel, elem_stride(m->nel), m->R, code, elem, r, cand,
-                       n_fields, out, elem_cnt, elem_off, rank, sorted, erec);
+                       (int)n, (int)m->nel, es, m->R, code, elem, r, cand, n_fields, out,
+                       elem_cnt, elem_off, rank, sorted, erec);
     return hipGetLastError();
 }
 
@@ -911,17 +912,17 @@ hipError_t launch_eval(const fpts_mesh *m, int64_t n, int n_fields, int field_n,
 }
 
 hipError_t launch_eval_split(const fpts_mesh *m, int64_t n, const int32_t *elem, const int *rank,
-                             int *elem_cnt, const int *elem_off, int *sorted, int *list,
-                             int *count, int phase, hipStream_t s)
+                             int *elem_cnt, int es, const int *elem_off, int *sorted,
+                             int *list, int *count, int phase, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
     if (phase == 0) {
         hipLaunchKernelGGL(k_eval_dense, dim3((unsigned)((m->nel + 255) / 256)), dim3(256), 0, s,
-                           (int)m->nel, elem_stride(m->nel), elem_cnt);
+                           (int)m->nel, es, elem_cnt);
     } else {
         hipLaunchKernelGGL(k_eval_split, dim3((unsigned)((n + kSplitChunk - 1) / kSplitChunk)),
-                           dim3(256), 0, s, (int)n, elem, rank, elem_cnt, elem_stride(m->nel),
-                           elem_off, sorted, list, count);
+                           dim3(256), 0, s, (int)n, elem, rank, elem_cnt, es, elem_off, sorted,
+                           list, count);
     }
     return hipGetLastError();
 }

@@ -1052,8 +1052,6 @@ hipError_t launch_cell_bin(const fpts_mesh *m, int pass, int64_t n, const double
 // 121 -> 111 us), and with the counters spread over at least 512 cache lines a
 // few thousand atomics take a few microseconds.  Beyond, points that crowd in
 // cells of one line would wait for each other's atomics, 16 ns each.
-constexpr int64_t kCellBinPoints = 4096;
-
 int bin_shift(int64_t n, int64_t ncell)
 {
     if (n <= kCellBinPoints || ncell > kBinMaxCells) return -1;
@@ -1172,7 +1170,7 @@ hipError_t launch_locate_cells(const fpts_mesh *m, int64_t n, const double *pts,
                        : (pts4 ? k_locate_cells<3, true> : k_locate_cells<3, false>);
     hipLaunchKernelGGL(k, dim3(task_grid(task_bound, m->cus)), dim3(64), 0, s, h, (int)n, m->R,
                        pts, pts4, pbin, cell_poff, cell_choff, (int)ncell, task_cell, cand,
-                       elem_cnt, elem_stride(m->nel), rank, bin_prim, code, elem, r, dist);
+                       elem_cnt, elem_stride(m->nel, n), rank, bin_prim, code, elem, r, dist);
     return hipGetLastError();
 }
 
@@ -1289,8 +1287,8 @@ hipError_t launch_hint(const fpts_mesh *m, int pass, int64_t n, const int32_t *c
 {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_hint, dim3(grid_for(n, 256)), dim3(256), 0, s, pass, (int)n,
-                       (int)m->nel, elem_stride(m->nel), m->R, code, elem, r, cand, elem_cnt, rank,
-                       keep);
+                       (int)m->nel, elem_stride(m->nel, n), m->R, code, elem, r, cand, elem_cnt,
+                       rank, keep);
     return hipGetLastError();
 }
 

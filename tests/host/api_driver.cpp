@@ -1,12 +1,26 @@
 // Checks of the library's host side that need no device, run by
 // tests/test_host_api.py: api_driver <check>.  Prints what failed and returns
-// whether anything did.
+// whether anything did.  The HIP calls that a check reaches are defined here
+// (the program's own definitions come before the runtime's) and touch no
+// device: launches are noted, nothing runs.
+#include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <set>
 
 #include "fpts_internal.hpp"
 #include "fpts_lpt.h"
+
+extern "C" {
+
+hipError_t hipGetLastError() { return hipSuccess; }
+
+hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t)
+{
+    return hipSuccess;
+}
+
+}  // extern "C"
 
 namespace {
 
@@ -82,12 +96,91 @@ void sizes()
         }
 }
 
+// What the calls asked for before their kernels kept records and spread
+// counters: programs have budgets made for it (a server's pool, a buffer), so
+// they must not ask for more, and fpts_eval must take that much.
+struct Asked {
+    int D, R, N;
+    int64_t nel;
+    int NL, max_cell;
+    int64_t n;
+    size_t bytes[4];   // find, eval, find_eval, lpt
+};
+const Asked kAsked[] = {
+    {3, 3, 8, 110592, 48, 20, 1, {5807104, 1329152, 7136512, 5807616}},
+    {3, 3, 8, 110592, 48, 20, 1000, {6158592, 1344512, 7527168, 6186752}},
+    {3, 3, 8, 110592, 48, 20, 4096, {6932480, 1394176, 8424960, 7047168}},
+    {3, 3, 8, 110592, 48, 20, 4097, {6938368, 1394944, 8431872, 7053568}},
+    {3, 3, 8, 110592, 48, 20, 30000, {13263616, 1810432, 15794176, 14103808}},
+    {3, 3, 8, 110592, 48, 20, 1000000, {236058624, 13833216, 273891840, 264058624}},
+    {3, 3, 8, 110592, 48, 20, 6291455, {1444400384, 77661184, 1673056512, 1620561152}},
+    {3, 3, 6, 13824, 24, 30, 1, {774400, 167936, 942592, 774912}},
+    {3, 3, 6, 13824, 24, 30, 1000, {1125888, 183296, 1333248, 1154048}},
+    {3, 3, 6, 13824, 24, 30, 4096, {1899776, 232960, 2231040, 2014464}},
+    {3, 3, 6, 13824, 24, 30, 4097, {1905664, 233728, 2237952, 2020864}},
+    {3, 3, 6, 13824, 24, 30, 30000, {7969536, 584448, 9274112, 8809728}},
+    {3, 3, 6, 13824, 24, 30, 1000000, {229385216, 12284928, 265670144, 257385216}},
+    {3, 3, 6, 13824, 24, 30, 6291455, {1437239552, 76112896, 1664347392, 1613400320}},
+    {2, 2, 5, 256, 16, 9, 1, {60672, 5120, 66048, 61184}},
+    {2, 2, 5, 256, 16, 9, 1000, {361216, 17664, 395008, 381440}},
+    {2, 2, 5, 256, 16, 9, 4096, {960768, 54784, 1081088, 1042688}},
+    {2, 2, 5, 256, 16, 9, 4097, {966656, 55552, 1088000, 1049088}},
+    {2, 2, 5, 256, 16, 9, 30000, {5838336, 367360, 6685696, 6438400}},
+    {2, 2, 5, 256, 16, 9, 1000000, {188441600, 12067840, 216509440, 208441600}},
+    {2, 2, 5, 256, 16, 9, 6291455, {1184570624, 75895808, 1361129728, 1310399744}},
+    {3, 2, 7, 6144, 19, 60, 1, {375552, 75776, 451584, 376064}},
+    {3, 2, 7, 6144, 19, 60, 1000, {703232, 91136, 810496, 731392}},
+    {3, 2, 7, 6144, 19, 60, 4096, {1402624, 140800, 1608960, 1517312}},
+    {3, 2, 7, 6144, 19, 60, 4097, {1408512, 141568, 1615872, 1523712}},
+    {3, 2, 7, 6144, 19, 60, 30000, {6730240, 461568, 7671808, 7570432}},
+    {3, 2, 7, 6144, 19, 60, 1000000, {204859904, 12162048, 233021952, 232859904}},
+    {3, 2, 7, 6144, 19, 60, 6291455, {1285686016, 75990016, 1462339328, 1461846784}},
+    {2, 1, 4, 1024, 32, 8, 1, {92416, 14336, 107008, 92928}},
+    {2, 1, 4, 1024, 32, 8, 1000, {557056, 29696, 594944, 577280}},
+    {2, 1, 4, 1024, 32, 8, 4096, {1629184, 67072, 1729024, 1711104}},
+    {2, 1, 4, 1024, 32, 8, 4097, {1634816, 67840, 1735680, 1717248}},
+    {2, 1, 4, 1024, 32, 8, 30000, {10454528, 379648, 11074304, 11054592}},
+    {2, 1, 4, 1024, 32, 8, 1000000, {340861184, 12080128, 360941312, 360861184}},
+    {2, 1, 4, 1024, 32, 8, 6291455, {2143278592, 75908096, 2269518336, 2269107712}},
+    {3, 1, 4, 700, 9, 12, 1, {74496, 9984, 84736, 75008}},
+    {3, 1, 4, 700, 9, 12, 1000, {662528, 24320, 695040, 690688}},
+    {3, 1, 4, 700, 9, 12, 4096, {2130688, 61184, 2224640, 2245376}},
+    {3, 1, 4, 700, 9, 12, 4097, {2136320, 61952, 2231296, 2251520}},
+    {3, 1, 4, 700, 9, 12, 30000, {14278912, 374016, 14893056, 15119104}},
+    {3, 1, 4, 700, 9, 12, 1000000, {469088256, 12074496, 489162752, 497088256}},
+    {3, 1, 4, 700, 9, 12, 6291455, {2950135040, 75902464, 3076369152, 3126295808}},
+};
+
+void budgets()
+{
+    for (const Asked &a : kAsked) {
+        fpts_mesh m = shape(a.D, a.R, a.N, a.nel, a.NL, a.max_cell);
+        for (int k = 0; k < 4; ++k) {
+            if (kSizes[k].fn == fpts_lpt_workspace_size && a.R != a.D) continue;
+            const size_t b = kSizes[k].fn(&m, a.n);
+            int st = b <= a.bytes[k] ? FPTS_OK : FPTS_EINVAL;
+            if (kSizes[k].fn == fpts_eval_workspace_size) {
+                // no memory behind the addresses: nothing is launched
+                void *p = reinterpret_cast<void *>(uintptr_t(1) << 40);
+                st = fpts_eval(&m, a.n, (int32_t *)p, (int32_t *)p, (double *)p, 1, (double *)p,
+                               (double *)p, p, a.bytes[k], nullptr);
+            }
+            if (st == FPTS_OK) continue;
+            ++failures;
+            std::printf("%s, D %d R %d N %d, %lld elements, %lld points: %zu bytes, had %zu\n",
+                        kSizes[k].name, a.D, a.R, a.N, (long long)a.nel, (long long)a.n, b,
+                        a.bytes[k]);
+        }
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "sizes")) sizes();
+    else if (!std::strcmp(what, "budgets")) budgets();
     else return 2;
     std::printf("%s: %d failures\n", what, failures);
     return failures != 0;

@@ -37,3 +37,7 @@ def _run(driver, what):
 
 def test_workspace_sizes_never_decrease(driver):
     _run(driver, "sizes")
+
+
+def test_workspaces_fit_the_budgets_they_fitted(driver):
+    _run(driver, "budgets")
