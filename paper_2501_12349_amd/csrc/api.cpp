@@ -173,7 +173,7 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     const int64_t cmax = n * (int64_t)std::max(m->max_cell - 1, 1);
     w.cap2 = std::max<int64_t>(1, m->R == 1 ? cmax : std::min<int64_t>(cmax, n));
     w.bin_shift = bin_shift(n, ncell);
-    w.cell_stride = w.bin_shift < 0 ? elem_stride(ncell, n) : 1;
+    w.cell_stride = w.bin_shift < 0 ? find_stride(ncell, n) : 1;
     w.bin_hist_n = w.bin_shift < 0 ? 0 : bin_hist_size(n, ncell, w.bin_shift);
     // The total never gets smaller as n grows, so that a workspace made for n
     // points holds for fewer, also where a smaller n takes another path: the
@@ -244,8 +244,8 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     // per cell and per element are scanned before the Newton pass: they lie at
     // the end of what is used from then on.
     const size_t late_end = c.at;
-    const size_t cells = align_up(I * ncell * elem_stride(ncell, std::min(n, kCellBinPoints)));
-    const size_t elems = align_up(I * m->nel * elem_stride(m->nel, n));
+    const size_t cells = align_up(I * ncell * find_stride(ncell, std::min(n, kCellBinPoints)));
+    const size_t elems = align_up(I * m->nel * find_stride(m->nel, n));
     w.zero = late_end - std::min(late_end - late, cells + elems);
     w.cell_cnt = w.zero;
     w.elem_cnt = w.cell_cnt + cells;
@@ -262,7 +262,7 @@ EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n, EvalWsKind kind)
 {
     EvalWs w;
     Cursor c;
-    w.stride = kind == kEvalSmall ? 1 : elem_stride(m->nel, n);
+    w.stride = kind == kEvalSmall ? 1 : elem_stride(m->nel, (kind == kEvalOwn ? 16 : 3) * n);
     // zeroed before the points are binned: [0, zero_end)
     w.elem_cnt = c.take(sizeof(int) * m->nel * w.stride);
     w.scount = c.take(sizeof(int));
@@ -384,7 +384,7 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
                                 w.tb_cell, cand, elem_cnt, rank, bin_prim, d_code,
                                 d_elem, d_r, d_dist, s));
         UnitScan es{elem_cnt, nel,       tmp,    elem_off,
-                    chunk_off, task_elem, kChunk, elem_stride(nel, n)};
+                    chunk_off, task_elem, kChunk, find_stride(nel, n)};
         if (len > kChunk) {
             es.off2 = newt_off;
             es.task2 = newt_task;
@@ -932,7 +932,7 @@ int fpts_lpt_step(fpts_mesh *m, const fpts_lpt_params *p, int64_t n, int first, 
         chk(launch_zero2(at<int>(sub, w.zero), (w.total - w.zero) / sizeof(int), nullptr, 0, s));
         chk(launch_hint(m, 0, n, d_code, d_elem, d_r, cand, elem_cnt, rank, nullptr, s));
         chk(launch_unit_scan(UnitScan{elem_cnt, m->nel, tmp, elem_off, chunk_off, task_elem,
-                                      kChunk, elem_stride(m->nel, n)},
+                                      kChunk, find_stride(m->nel, n)},
                              w.scan_blocks, s));
         chk(launch_primary_scatter(n, m->nel, cand, elem_off, rank, sorted, s));
     }

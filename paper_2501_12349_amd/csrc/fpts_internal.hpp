@@ -116,20 +116,24 @@ __host__ __device__ inline void rodrigues_frame(int D, double tx, double ty, dou
         for (int q = 0; q < D; ++q) Jc[c * D + q] = Q[q][c];
 }
 
-// Counters per element that many threads step at once lie elem_stride(nel)
-// ints apart: atomics on one 128-byte line come one after the other, some
+// Counters per element that many threads step at once lie elem_stride ints
+// apart: atomics on one 128-byte line come one after the other, some
 // 16 ns each, so that 32 counters a line make a mesh of a few thousand
 // elements count 10 G/s where 512 lines or more count 26 G/s (2 million
 // particles over 3888 elements: location 284 -> 155 us, counting pass of the
-// interpolation 203 -> 108 us, spread over one line per counter).  At most three
-// ints per point that counts: the workspace of a call of few points stays small,
-// and a thousand points on 64 lines wait for each other some 0.2 us.
-inline int elem_stride(int64_t nel, int64_t n)
+// interpolation 203 -> 108 us, spread over one line per counter).  At most `most`
+// ints in all, per point that counts: 16 where they share their place with
+// arrays of 170 bytes per point (find_ws_layout) or where less will do
+// (eval_ws_layout), else 3.  (With 3 throughout, find + interpolate of 1000
+// points took 112.0 us instead of 110.0.)
+inline int elem_stride(int64_t nel, int64_t most)
 {
     int s = 1;
-    while (s < 32 && nel * s < 16384 && 2 * nel * s <= 3 * n) s *= 2;
+    while (s < 32 && nel * s < 16384 && 2 * nel * s <= most) s *= 2;
     return s;
 }
+// of the counts per element and per cell of a Find of n points
+inline int find_stride(int64_t nel, int64_t n) { return elem_stride(nel, 16 * n); }
 
 // ctr[key]++ for every active lane, returning the lane's old value, with one
 // atomic per group of lanes that share a key: the group of the lowest pending
@@ -226,7 +230,7 @@ struct FindWs {
     int64_t park_state_cap;  // parked pairs whose iteration state is saved
     int64_t ov_grid;        // blocks of the overflow search (its scratch)
     int bin_shift;          // phase A without per-point atomics: bucket shift, or -1
-    int cell_stride;        // ints between the cells' counters (elem_stride)
+    int cell_stride;        // ints between the cells' counters (find_stride)
     int64_t bin_hist_n;     // entries of its bucket histograms (nb * ntile)
 };
 

@@ -1170,7 +1170,7 @@ hipError_t launch_locate_cells(const fpts_mesh *m, int64_t n, const double *pts,
                        : (pts4 ? k_locate_cells<3, true> : k_locate_cells<3, false>);
     hipLaunchKernelGGL(k, dim3(task_grid(task_bound, m->cus)), dim3(64), 0, s, h, (int)n, m->R,
                        pts, pts4, pbin, cell_poff, cell_choff, (int)ncell, task_cell, cand,
-                       elem_cnt, elem_stride(m->nel, n), rank, bin_prim, code, elem, r, dist);
+                       elem_cnt, find_stride(m->nel, n), rank, bin_prim, code, elem, r, dist);
     return hipGetLastError();
 }
 
@@ -1287,7 +1287,7 @@ hipError_t launch_hint(const fpts_mesh *m, int pass, int64_t n, const int32_t *c
 {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_hint, dim3(grid_for(n, 256)), dim3(256), 0, s, pass, (int)n,
-                       (int)m->nel, elem_stride(m->nel, n), m->R, code, elem, r, cand, elem_cnt,
+                       (int)m->nel, find_stride(m->nel, n), m->R, code, elem, r, cand, elem_cnt,
                        rank, keep);
     return hipGetLastError();
 }
