@@ -270,8 +270,8 @@ __device__ bool invert_d(int D, const double *A, double *I)
 // 366 now.
 template <int D, int R, int N>
 __global__ __launch_bounds__(kLanes) __attribute__((amdgpu_waves_per_eu(4))) void
-k_elem_boxes(const BoundTables *Tg, const double *nodes, int64_t nel, double tol, double *box,
-             double *xc_out)
+k_elem_boxes(const BoundTables *Tg, const double *nodes, int64_t e0, int64_t nel, double tol,
+             double *box, double *xc_out)
 {
     typedef Sides<D, R, N> S;
     constexpr int NP = S::NP, W = 3 * D + D * D;
@@ -282,7 +282,7 @@ k_elem_boxes(const BoundTables *Tg, const double *nodes, int64_t nel, double tol
     __shared__ double mom[S::NF * S::MOM], slab[D * SLAB], sc[16], frame[24];
     const BoundTables &T = *Tg;
     const int lane = threadIdx.x;
-    const int64_t e = blockIdx.x;
+    const int64_t e = e0 + blockIdx.x;
     if (e >= nel) return;
     const double *xe = nodes + e * D * NP;
     double *rec = box + e * W;
@@ -499,9 +499,10 @@ __global__ __launch_bounds__(256) void k_map(MapView v, const double *box, int64
 // lists are sorted by insertion.  (One lane per cell and insertion throughout,
 // a chain of dependent loads and stores, took 66 us for 5832 elements.)
 constexpr int kSortLanes = 16, kSortPer = 4, kSortWide = kSortLanes * kSortPer;
-__global__ __launch_bounds__(256) void k_map_sort(const int *off, int64_t ncell, int *cell_el)
+__global__ __launch_bounds__(256) void k_map_sort(const int *off, int64_t c0, int64_t ncell,
+                                                 int *cell_el)
 {
-    const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kSortLanes;
+    const int64_t c = c0 + ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kSortLanes;
     if (c >= ncell) return;   // whole groups of lanes
     const int l = threadIdx.x % kSortLanes, first = (threadIdx.x & 63) / kSortLanes * kSortLanes;
     const int b = off[c], n = off[c + 1] - b;
@@ -538,8 +539,13 @@ __global__ __launch_bounds__(256) void k_map_sort(const int *off, int64_t ncell,
     }
 }
 
-typedef void (*BoxKernel)(const BoundTables *, const double *, int64_t, double, double *,
+typedef void (*BoxKernel)(const BoundTables *, const double *, int64_t, int64_t, double, double *,
                           double *);
+
+// Blocks of one launch at most, of up to 256 threads: a launch takes fewer than
+// 2^32 threads, and a mesh may have more elements times 64 (or cells times
+// kSortLanes) than that.
+constexpr int64_t kLaunchBlocks = (int64_t)1 << 23;
 template <int D, int R>
 BoxKernel pick_boxes(int N)
 {
@@ -576,14 +582,16 @@ int device_setup(fpts_mesh *m, hipStream_t s)
     if (hipMemcpyAsync(dt.p, &bt, sizeof(bt), hipMemcpyHostToDevice, s) != hipSuccess)
         return FPTS_EDEVICE;
     // boxes and centres
-    const int grid = (int)m->nel;
     const BoxKernel kb = D == 2 ? (R == 2 ? pick_boxes<2, 2>(N) : pick_boxes<2, 1>(N))
                          : R == 3 ? pick_boxes<3, 3>(N)
                                   : R == 2 ? pick_boxes<3, 2>(N) : pick_boxes<3, 1>(N);
     if (!kb) return FPTS_EINVAL;
-    hipLaunchKernelGGL(kb, dim3(grid), dim3(kLanes), 0, s, dt.p, m->d_nodes, (int64_t)m->nel,
-                       m->p.bbox_tol, m->d_box, m->d_xc);
-    if (hipGetLastError() != hipSuccess) return FPTS_EDEVICE;
+    for (int64_t e0 = 0; e0 < m->nel; e0 += kLaunchBlocks) {
+        const int64_t grid = std::min<int64_t>(m->nel - e0, kLaunchBlocks);
+        hipLaunchKernelGGL(kb, dim3((unsigned)grid), dim3(kLanes), 0, s, dt.p, m->d_nodes, e0,
+                           (int64_t)m->nel, m->p.bbox_tol, m->d_box, m->d_xc);
+        if (hipGetLastError() != hipSuccess) return FPTS_EDEVICE;
+    }
     // union box
     const int ublocks = (int)std::min<int64_t>((m->nel + 255) / 256, 1024);
     DevBuf<double> part;
@@ -645,8 +653,12 @@ int device_setup(fpts_mesh *m, hipStream_t s)
     m->cell_el.resize(std::max<int64_t>(nnz, 1));
     hipLaunchKernelGGL(k_map, dim3(eg), dim3(256), 0, s, v, m->d_box, (int64_t)m->nel, 1, nullptr,
                        m->d_cell_off, fill.p, m->d_cell_el);
-    hipLaunchKernelGGL(k_map_sort, dim3((int)((ncell * kSortLanes + 255) / 256)), dim3(256), 0,
-                       s, m->d_cell_off, ncell, m->d_cell_el);
+    constexpr int64_t kCells = 256 / kSortLanes;   // of a block
+    for (int64_t c0 = 0; c0 < ncell; c0 += kLaunchBlocks * kCells) {
+        const int64_t grid = std::min((ncell - c0 + kCells - 1) / kCells, kLaunchBlocks);
+        hipLaunchKernelGGL(k_map_sort, dim3((unsigned)grid), dim3(256), 0, s, m->d_cell_off, c0,
+                           ncell, m->d_cell_el);
+    }
     m->max_cell = 0;
     for (int64_t c = 0; c < ncell; ++c)
         m->max_cell = std::max(m->max_cell, m->cell_off[c + 1] - m->cell_off[c]);

@@ -7,16 +7,65 @@
 #include <cstdio>
 #include <cstring>
 #include <set>
+#include <vector>
 
 #include "fpts_internal.hpp"
 #include "fpts_lpt.h"
+
+struct Launch {
+    const void *kernel;
+    uint64_t blocks, threads;   // threads of a block
+};
+static std::vector<Launch> launches;
+static int copies_back = 0;   // the copies to the host until one fails
+static std::vector<double> first_back;   // what the first one brings
 
 extern "C" {
 
 hipError_t hipGetLastError() { return hipSuccess; }
 
-hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t)
+static dim3 call_grid, call_block;
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t, hipStream_t)
 {
+    call_grid = g;
+    call_block = b;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *shared, hipStream_t *s)
+{
+    *g = call_grid;
+    *b = call_block;
+    *shared = 0;
+    *s = nullptr;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *kernel, dim3 g, dim3 b, void **, size_t, hipStream_t)
+{
+    launches.push_back({kernel, (uint64_t)g.x * g.y * g.z, (uint64_t)b.x * b.y * b.z});
+    return hipSuccess;
+}
+
+hipError_t hipMalloc(void **p, size_t)
+{
+    // an address that nothing is read from
+    *p = reinterpret_cast<void *>(uintptr_t(1) << 40);
+    return hipSuccess;
+}
+
+hipError_t hipFree(void *) { return hipSuccess; }
+
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+
+hipError_t hipMemcpyAsync(void *dst, const void *, size_t bytes, hipMemcpyKind kind, hipStream_t)
+{
+    if (kind != hipMemcpyDeviceToHost) return hipSuccess;
+    if (copies_back-- <= 0) return hipErrorInvalidValue;
+    if (!first_back.empty() && bytes % (first_back.size() * sizeof(double)) == 0) {
+        const size_t w = first_back.size();
+        for (size_t i = 0; i < bytes / sizeof(double); ++i)
+            static_cast<double *>(dst)[i] = first_back[i % w];
+        first_back.clear();
+    }
     return hipSuccess;
 }
 
@@ -174,6 +223,45 @@ void budgets()
     }
 }
 
+// The device setup's launches take fewer than 2^32 threads each, and enough
+// together, for the most elements and cells that fpts_setup lets in.
+void setup_launches(int64_t nel, int NL, int copies, uint64_t threads, uint64_t needed)
+{
+    fpts_mesh m = shape(2, 1, 2, nel, NL, 1);
+    m.p.bbox_tol = 0.1;
+    launches.clear();
+    copies_back = copies;
+    first_back = {0.0, 0.0, 1.0, 1.0};   // the union box
+    (void)fpts::device_setup(&m, nullptr);
+    uint64_t most = 0;
+    for (const Launch &l : launches) {
+        if (l.blocks * l.threads >= (uint64_t(1) << 32) || l.blocks > INT32_MAX) {
+            ++failures;
+            std::printf("%lld elements, %d^2 cells: a launch of %llu blocks of %llu threads\n",
+                        (long long)nel, NL, (unsigned long long)l.blocks,
+                        (unsigned long long)l.threads);
+        }
+        uint64_t sum = 0;   // of this kernel's launches
+        for (const Launch &k : launches)
+            if (k.kernel == l.kernel) sum += k.blocks * k.threads;
+        if (l.threads == threads) most = sum > most ? sum : most;
+    }
+    if (most < needed) {
+        ++failures;
+        std::printf("%lld elements, %d^2 cells: %llu threads of %llu needed\n", (long long)nel, NL,
+                    (unsigned long long)most, (unsigned long long)needed);
+    }
+}
+
+void setups()
+{
+    // (the copy of the union box ends the first two)
+    setup_launches((int64_t(1) << 26) + 77, 1, 0, 64, ((uint64_t(1) << 26) + 77) * 64);
+    setup_launches(INT32_MAX / 2, 1, 0, 64, uint64_t(INT32_MAX / 2) * 64);
+    setup_launches(5, 16400, 2, 256, uint64_t(16400) * 16400 * 16);
+    setup_launches(5, 3, 2, 256, 9 * 16);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -181,6 +269,7 @@ int main(int argc, char **argv)
     const char *what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "sizes")) sizes();
     else if (!std::strcmp(what, "budgets")) budgets();
+    else if (!std::strcmp(what, "setups")) setups();
     else return 2;
     std::printf("%s: %d failures\n", what, failures);
     return failures != 0;

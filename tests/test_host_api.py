@@ -41,3 +41,7 @@ def test_workspace_sizes_never_decrease(driver):
 
 def test_workspaces_fit_the_budgets_they_fitted(driver):
     _run(driver, "budgets")
+
+
+def test_device_setup_launches_of_large_meshes(driver):
+    _run(driver, "setups")
