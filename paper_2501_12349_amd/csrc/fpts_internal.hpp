@@ -72,12 +72,18 @@ inline int64_t task_bound(int64_t n, int64_t nunit, int len = kChunk)
     return n / len + std::min<int64_t>(n, nunit) + 1;
 }
 
-// Grid size (blocks) for a task bound: a multiple of the XCD count, at most
-// 64 blocks per CU; blocks loop over tasks t, t + G, ...
+// a grid of at least `blocks` blocks, a multiple of the XCD count (the kernels
+// that divide work among the XCDs take no other)
+inline unsigned xcd_grid(int64_t blocks)
+{
+    return (unsigned)((std::max<int64_t>(blocks, 1) + kXcd - 1) / kXcd * kXcd);
+}
+
+// Grid size (blocks) for a task bound: at most 64 blocks per CU; blocks loop
+// over tasks t, t + G, ...
 inline int64_t task_grid(int64_t bound, int cus)
 {
-    const int64_t g = std::min<int64_t>(bound, (int64_t)cus * 64);
-    return (std::max<int64_t>(g, 1) + kXcd - 1) / kXcd * kXcd;
+    return xcd_grid(std::min<int64_t>(bound, (int64_t)cus * 64));
 }
 
 __device__ __forceinline__ int task_of_block()

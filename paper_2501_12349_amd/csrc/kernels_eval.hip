@@ -874,8 +874,7 @@ hipError_t launch_eval(const fpts_mesh *m, int64_t n, int n_fields, int field_n,
     if (m->R >= 2) {
         // matrix cores, up to four fields per launch, evenly
         const int launches = (n_fields + 3) / 4;
-        const dim3 grid((unsigned)std::min<int64_t>(task_grid(l.task_bound, m->cus),
-                                                    (int64_t)m->cus * 16));
+        const dim3 grid(xcd_grid(std::min<int64_t>(l.task_bound, (int64_t)m->cus * 16)));
         for (int k = 0, f0 = 0; k < launches; ++k) {
             size_t lds = 0;
             const int fc = (n_fields - f0 + launches - k - 1) / (launches - k);

@@ -1101,12 +1101,6 @@ int64_t bin_hist_bound(int64_t n, int64_t ncell, int shift)
     return most;
 }
 
-// a grid of at least `blocks` blocks, a multiple of the XCD count
-static unsigned xcd_grid(int64_t blocks)
-{
-    return (unsigned)((std::max<int64_t>(blocks, 1) + kXcd - 1) / kXcd * kXcd);
-}
-
 hipError_t launch_bin_tiles(const fpts_mesh *m, int64_t n, const double *pts, double *pts4,
                             const int *keep, int *cellpt, int2 *cand,
                             int32_t *code, int32_t *elem, double *r, double *dist, int shift,

@@ -2588,7 +2588,8 @@ hipError_t launch_newton_kind(const fpts_mesh *m, bool mixed, int64_t n, const d
     if (which & 2) {
         if (k.newton32) {
             // three waves per SIMD, as the kernel's register budget allows
-            hipLaunchKernelGGL(k.newton32, dim3(m->cus * 12), dim3(64), k.lds_newton32, s, a);
+            hipLaunchKernelGGL(k.newton32, dim3(xcd_grid((int64_t)m->cus * 12)), dim3(64),
+                               k.lds_newton32, s, a);
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
@@ -2596,14 +2597,15 @@ hipError_t launch_newton_kind(const fpts_mesh *m, bool mixed, int64_t n, const d
         // search of particle tracking) take the warm-start kernel
         const KernelFn kn = resolve || (io.node && !mixed) ? k.newton : k.warm;
         const int waves = resolve ? resolve_waves(m->R, m->N) : newton_waves(m->R);
-        hipLaunchKernelGGL(kn, dim3(m->cus * 4 * waves), dim3(64),
+        hipLaunchKernelGGL(kn, dim3(xcd_grid((int64_t)m->cus * 4 * waves)), dim3(64),
                            resolve ? k.lds_few : k.lds_newton, s, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if (which & 4) {
         if (!k.face) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k.face, dim3(m->cus * 8), dim3(64), k.lds_few, s, a);
+        hipLaunchKernelGGL(k.face, dim3(xcd_grid((int64_t)m->cus * 8)), dim3(64), k.lds_few, s,
+                           a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

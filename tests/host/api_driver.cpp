@@ -3,6 +3,8 @@
 // whether anything did.  The HIP calls that a check reaches are defined here
 // (the program's own definitions come before the runtime's) and touch no
 // device: launches are noted, nothing runs.
+#include <dlfcn.h>
+
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -262,6 +264,49 @@ void setups()
     setup_launches(5, 3, 2, 256, 9 * 16);
 }
 
+// Kernels of one-wave blocks divide their tasks among the XCDs: their grids are
+// multiples of eight also on a device whose number of CUs is not.
+void grids()
+{
+    void *p = reinterpret_cast<void *>(uintptr_t(1) << 40);
+    const int kinds[][3] = {{3, 3, 6}, {3, 3, 8}, {2, 2, 5}, {3, 2, 7}, {3, 2, 10}, {2, 1, 4}};
+    for (int cus : {256, 33, 19, 1})
+        for (auto &k : kinds)
+            for (int precision : {FPTS_FP64, FPTS_MIXED})
+                for (int64_t n : {1, 1000, 3000000}) {
+                    // (enough cells that no scan of them takes a block of one wave)
+                    fpts_mesh m = shape(k[0], k[1], k[2], 5000, k[0] == 3 ? 18 : 80, 12);
+                    m.cus = cus;
+                    m.near_npad = (m.NP + 31) / 32 * 32;
+                    m.p.max_iter = 50;
+                    launches.clear();
+                    const int st =
+                        fpts_find_eval(&m, n, (double *)p, (int32_t *)p, (int32_t *)p, (double *)p,
+                                       (double *)p, precision, 3, k[2], (double *)p, (double *)p, p,
+                                       fpts_find_eval_workspace_size(&m, n), nullptr);
+                    int waves = 0;
+                    for (const Launch &l : launches) {
+                        Dl_info info;
+                        const bool named = dladdr(l.kernel, &info) && info.dli_sname;
+                        // (a block per point, no division)
+                        if (named && std::strstr(info.dli_sname, "overflow")) continue;
+                        if (l.threads != 64) continue;
+                        ++waves;
+                        if (l.blocks % 8 == 0) continue;
+                        ++failures;
+                        std::printf("%d CUs, D %d R %d N %d, %lld points: %llu blocks of %s\n", cus,
+                                    k[0], k[1], k[2], (long long)n, (unsigned long long)l.blocks,
+                                    named ? info.dli_sname : "?");
+                    }
+                    if (st != FPTS_OK || waves < 4) {
+                        ++failures;
+                        std::printf("%d CUs, D %d R %d N %d, %lld points: status %d, %d launches of "
+                                    "one-wave blocks\n",
+                                    cus, k[0], k[1], k[2], (long long)n, st, waves);
+                    }
+                }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -270,6 +315,7 @@ int main(int argc, char **argv)
     if (!std::strcmp(what, "sizes")) sizes();
     else if (!std::strcmp(what, "budgets")) budgets();
     else if (!std::strcmp(what, "setups")) setups();
+    else if (!std::strcmp(what, "grids")) grids();
     else return 2;
     std::printf("%s: %d failures\n", what, failures);
     return failures != 0;

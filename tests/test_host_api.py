@@ -45,3 +45,7 @@ def test_workspaces_fit_the_budgets_they_fitted(driver):
 
 def test_device_setup_launches_of_large_meshes(driver):
     _run(driver, "setups")
+
+
+def test_grids_are_multiples_of_the_xcd_count(driver):
+    _run(driver, "grids")
