@@ -53,9 +53,9 @@ def eval_flops(D, R, N, h2):
 
 
 def node_starts(stats):
-    """FP64 map evaluations of the primary pass at the pairs' start nodes,
-    which take the node and rows of the differentiation matrix instead of a
-    sweep (in mixed mode the FP32 phase makes them)."""
+    """FP64 map evaluations of a pass at the pairs' start nodes, which take the
+    node and rows of the differentiation matrix instead of a sweep (in mixed
+    mode the FP32 phase makes those of the primary pass)."""
     return 0 if stats["evals_fp32"] else min(stats["pairs"], stats["evals"])
 
 

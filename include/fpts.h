@@ -235,9 +235,9 @@ int fpts_find_eval_noalloc(fpts_mesh *m, int64_t n, const double *d_pts, int32_t
  * summed.  Passes and evaluations of a pair that moved to the face kernel
  * are counted where they ran; its pair is counted once, in pass 1.  A sweep
  * is one evaluation of the map by a whole wavefront at up to 16 pairs at
- * once.  Evaluations at start nodes (the first of every primary pair searched
- * in FP64 from its nearest node; evals_fp32_node in mixed mode) take no sweep,
- * so (evals - those) / (16 sweeps) is the fraction of busy pair slots.
+ * once.  Evaluations at start nodes take no sweep: the first of every pair of
+ * pass 2, and of pass 1 in FP64 mode (evals_fp32_node of the FP32 ones in mixed
+ * mode).  (evals - those) / (16 sweeps) is the fraction of busy pair slots.
  * FPTS_EINVAL for another pass. */
 typedef struct fpts_find_stats {
     int64_t pairs;          /* (point, element) pairs searched */

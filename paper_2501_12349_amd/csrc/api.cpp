@@ -82,8 +82,9 @@ constexpr int kSlotTotal = 4;   // 64-bit running total of the second search's s
 constexpr int kHintPasses = 8;  // Newton passes of the hinted search
 
 // Pairs per task of the primary Newton pass at most, a multiple of kChunk:
-// about four tasks for each of the launch's waves (8 per CU), so that the
-// last ones to finish leave little of the chip idle; an element's queue is
+// about four tasks for each of 8 waves per CU (the launch has as many, 12 on
+// meshes of two parameters: some three tasks each), so that the last ones to
+// finish leave little of the chip idle; an element's queue is
 // kept whole below that (its nodes are staged, and its last pairs drained
 // with lanes idle, once).  kChunk for line meshes, whose kernel takes
 // 64-pair tasks, and where the arrays of the cells' tasks would not hold
@@ -237,7 +238,7 @@ FindWs find_ws_layout(const fpts_mesh *m, int64_t n)
     w.park_task = c.take(I * w.tb_park);
     w.olist = c.take(I * n);
     w.ov_grid = (int64_t)m->cus * 3;
-    w.ov_int = c.take(I * 3 * w.ov_grid);
+    w.ov_int = c.take(I * w.ov_grid);
     w.ov_dbl = c.take(sizeof(double) * (m->R + 1) * w.ov_grid);
     // zeroed at the start of a call: [zero, total).  The counters stay last:
     // an Interpolate in the same workspace leaves them readable.  The counts
@@ -447,7 +448,7 @@ int find_impl(fpts_mesh *m, int64_t n, const double *d_pts, int32_t *d_code, int
     }
     {   // phase D: other candidates of unsettled points, then the selection rule
         Span sp(m, 3, s);
-        // counters[0]: listed points, counters[1]: slots handed out
+        // counters[0]: listed points
         const EvalRest none{};
         if (m->R >= 2)
             chk(launch_settle(m, n, cand, elem_off, rec, d_code, d_elem, d_r, d_dist, ulist,

@@ -313,8 +313,8 @@ struct NewtonIO {
     // step ends the iteration (one FP64 evaluation per pair)
     int polish;
     // overflow search (which & 8): list = overflowed points, *ocount of
-    // them; their cells and primaries; per-block scratch ov_int [3][grid]
-    // and ov_dbl [R + 1][grid]; code/elem/r/dist are the final outputs
+    // them; their cells and primaries; per-block scratch ov_int [grid] and
+    // ov_dbl [R + 1][grid]; code/elem/r/dist are the final outputs
     const int *ocount;
     const int *cellpt;
     const int2 *cand;

@@ -207,8 +207,6 @@ __device__ inline int cell_of(const HashView &h, const double *x)
     return cell;
 }
 
-typedef const __attribute__((address_space(4))) double cdouble;
-
 __device__ inline void write_not_found(int p, int n, int R, int32_t *code, int32_t *elem,
                                        double *r, double *dist)
 {
@@ -910,7 +908,6 @@ __global__ __launch_bounds__(256) void k_select2(int n, int R, const int *ulist,
 }
 
 inline int grid_for(int64_t n, int block) { return (int)((n + block - 1) / block); }
-
 
 // Search hints (points that move a little between searches): pass 0 takes
 // the previous element of every point whose previous code was INTERIOR as

@@ -291,8 +291,8 @@ hipError_t launch_newton_line(const fpts_mesh *m, int64_t n, const double *pts,
     a.max_iter = io.max_iter > 0 ? io.max_iter : m->p.max_iter;
     a.tol = m->p.newton_tol;
     a.eps_d = m->p.surf_eps_d;
-    // phase C calls the start (which 1) and the iteration (which 2) apart;
-    // the second call recomputes nothing but reads the start back
+    // phase C asks for the start and the iteration in one launch (which 3);
+    // the iteration alone (2) reads its starts from r
     a.which = which & 3;
     hipLaunchKernelGGL(fn, dim3(task_grid(io.task_bound, m->cus)), dim3(64), 0, s, a);
     return hipGetLastError();

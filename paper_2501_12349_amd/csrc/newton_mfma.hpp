@@ -70,7 +70,13 @@ __device__ __forceinline__ double mfma4(double a, double b, double c)
 {
     return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ float mfma4(float, float, float c) { return c; }   // FP64 covers only
+// (FP32 has no 4-row form of this shape; its cover is of 16-row tiles only)
+template <typename T>
+__device__ T mfma4(T, T, T)
+{
+    static_assert(std::is_same<T, double>::value, "4-row tiles are FP64");
+    return T(0);
+}
 
 template <typename T> __device__ inline T eps_of();
 template <> __device__ inline double eps_of<double>() { return DBL_EPSILON; }
@@ -102,16 +108,6 @@ template <> __device__ __forceinline__ double sqrt_scale<double>(double x)
 template <> __device__ __forceinline__ float sqrt_scale<float>(float x)
 {
     return __builtin_amdgcn_sqrtf(x);
-}
-
-template <typename T> __device__ __forceinline__ T xor_shfl(T v, int m);
-template <> __device__ __forceinline__ double xor_shfl<double>(double v, int m)
-{
-    return __shfl_xor(v, m);
-}
-template <> __device__ __forceinline__ float xor_shfl<float>(float v, int m)
-{
-    return __shfl_xor(v, m);
 }
 
 // Orders LDS accesses between the lanes of a wave (every workgroup here is
@@ -2410,9 +2406,9 @@ k_newton32(NewtonArgs a)
 // array (more candidate pairs than the workspace holds): one wavefront per
 // point, its other candidates in ascending id order, each started from its
 // nearest node (squared distances to every node of the element, ties to the
-// lowest index) and iterated by the same code as the pass kernels, on a
-// one-pair queue; then the selection rule of Section 3.2 over the primary
-// and them.  One pair per wavefront: a path for rare overloads only.
+// lowest index) and iterated by the code of the resolve kernel, with one lane's
+// pair; then the selection rule of Section 3.2 over the primary and them.  One
+// pair per wavefront: a path for rare overloads only.
 template <int D, int R, int N>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 k_resolve_overflow(NewtonArgs a, HashView h)
@@ -2425,16 +2421,13 @@ k_resolve_overflow(NewtonArgs a, HashView h)
     const int lane = threadIdx.x, b = blockIdx.x, G = gridDim.x;
     const NewtonIO &io = a.io;
     const int cnt = *io.ocount;
-    // this block's one-pair queue: item b of the scratch outputs
-    int *ov_item = io.ov_int, *ov_pt = io.ov_int + G, *ov_code = io.ov_int + 2 * G;
+    // a pair's result goes to item b of the block's scratch
+    int *ov_code = io.ov_int;
     NewtonArgs la = a;
-    la.io.list = ov_item;
-    la.io.slot_pt = ov_pt;
     la.io.code = ov_code;
     la.io.r = io.ov_dbl;
     la.io.ostride = G;
     la.io.dist = io.ov_dbl + (size_t)R * G;
-    if (lane == 0) ov_item[b] = b;
     Counters cn;
     for (int i = b; i < cnt; i += G) {
         const int p = io.list[i];
@@ -2442,7 +2435,6 @@ k_resolve_overflow(NewtonArgs a, HashView h)
         double x[D];
 #pragma unroll
         for (int d = 0; d < D; ++d) x[d] = point_coord<D>(a, p, d);
-        if (lane == 0) ov_pt[b] = p;
         // the primary's result is the best so far
         int bcode = io.code[p], belem = prim;
         double bdist = io.dist[p], br[R];
@@ -2552,9 +2544,9 @@ Kernels pick_kernels(int N, bool resolve)
 // the FP64 kernel); which & 4 runs the face kernel over the parked pairs
 // (io.list = their list positions binned by element, io.elem_off / chunk_off
 // / task_elem their buckets and tasks).  io.counter must be zero
-// (kNewtonCounters ints).  A list with io.slot_pt set (other candidates) selects the *_resolve
-// kernels, whose Newton strides over the 64-pair tasks like the nearest-node
-// kernel.
+// (kNewtonCounters ints).  A list with io.slot_pt set (other candidates) selects
+// the *_resolve kernels, whose waves stride over tasks of up to few_lanes pairs,
+// like those of the face kernel.
 template <int D, int R>
 hipError_t launch_newton_kind(const fpts_mesh *m, bool mixed, int64_t n, const double *pts,
                               const NewtonIO &io, int which, hipStream_t s)
