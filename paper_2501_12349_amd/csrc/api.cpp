@@ -263,7 +263,7 @@ EvalWs eval_ws_layout(const fpts_mesh *m, int64_t n, EvalWsKind kind)
 {
     EvalWs w;
     Cursor c;
-    w.stride = kind == kEvalSmall ? 1 : elem_stride(m->nel, (kind == kEvalOwn ? 16 : 3) * n);
+    w.stride = elem_stride(m->nel, (kind == kEvalOwn ? 16 : kind == kEvalFused ? 3 : 1) * n);
     // zeroed before the points are binned: [0, zero_end)
     w.elem_cnt = c.take(sizeof(int) * m->nel * w.stride);
     w.scount = c.take(sizeof(int));

@@ -18,9 +18,11 @@
 namespace fpts {
 namespace {
 
-// fields per launch from which, and nodes per direction up to which the
-// values go through list order (launch_eval)
+// fields per launch from which, nodes per direction up to which and points
+// from which the values go through list order (launch_eval; the points for an
+// Interpolate call and for the first pass of the fused call)
 constexpr int kSpreadFields = 3, kSpreadNodes = 6;
+constexpr int64_t kSpreadPoints = 2500000, kSpreadFusedPoints = 500000;
 
 // fused find + interpolate: elements holding at most this many of the
 // remaining points have them interpolated one lane per point
@@ -883,12 +885,21 @@ hipError_t launch_eval(const fpts_mesh *m, int64_t n, int n_fields, int field_n,
             if (!fn) return hipErrorInvalidValue;
             a.f0 = f0;
             // three or four fields of up to six nodes per direction go through
-            // list order: a gather per point and coalesced writes take less
-            // than that many scattered writes (some 28 us per 1M values;
-            // N = 6, four fields, 3M points: 250 + 77 us, scattered 360).
-            // At larger N the writes hide behind the arithmetic (N = 8, three
-            // fields, 5M points: 420 + 121 us, scattered 423).
-            const bool spread = l.tmp && fc >= kSpreadFields && field_n <= kSpreadNodes;
+            // list order where the points are many: a gather per point and
+            // coalesced writes take less than that many scattered writes (some
+            // 28 us per 1M values; N = 6, four fields, 3M points: 250 + 77 us,
+            // scattered 360).  At larger N the writes hide behind the arithmetic
+            // (N = 8, three fields, 5M points: 420 + 121 us, scattered 423), with
+            // two fields the gather costs as much (N = 4, 2M points: call 237 us,
+            // 214), and where the values of few points stay in the caches
+            // scattered writes cost little: geometric means of the calls' times
+            // over N = 2 to 6, list order against scattered, hexes (and quads) of
+            // 512 to 90000 elements: 100 thousand points 1.16 (1.16), 1 million
+            // 1.05 (1.05), 3 million 0.98 (0.91).  The fused call's first pass
+            // (four fields, N = 4): 200 thousand points 1.01, 1 million 0.98, 4
+            // million 0.92 (quads 1.01, 0.96, 0.84).
+            const bool spread = l.tmp && fc >= kSpreadFields && field_n <= kSpreadNodes &&
+                                n >= (l.cand ? kSpreadFusedPoints : kSpreadPoints);
             a.tmp = spread ? l.tmp : nullptr;
             hipLaunchKernelGGL(fn, grid, dim3(64), lds, s, a);
             if (spread) {
