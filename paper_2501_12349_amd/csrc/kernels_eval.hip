@@ -278,6 +278,12 @@ constexpr int eval_waves_per_eu()
     return (R == 2 ? FC * N <= 30 : FC * N * N <= 90) ? 4 : 2;
 }
 
+// Fields of a launch at most: four, but three on hexes of ten nodes per
+// direction, where the products of four spill 14 registers (13824 elements, four
+// fields in one launch and in two: 3M points 2011 and 1710 us, 20 thousand 219
+// and 175; on 512 elements, 20 thousand points 45 and 53).
+constexpr int most_fields(int R, int N) { return R == 3 && N == 10 ? 3 : 4; }
+
 // Interpolation with the first contraction on the matrix cores (quad, hex
 // and surface meshes; FC fields a.f0 .. a.f0 + FC - 1 per launch).  One
 // wavefront per task, one of the even parts of an element's list (one wave
@@ -792,9 +798,12 @@ EvalFn pick_eval_mfma(int N, size_t *lds)
     switch (N) {
 #define FPTS_CASE(NN)                                                                      \
     case NN:                                                                               \
-        *lds = sizeof(double) * (newton::NodeLds<double, FC, R, NN>::SIZE + R * NN * 16 +  \
-                                 (NN % 4 ? 1 : 0));                                        \
-        return k_eval_mfma<R, NN, FC>;
+        if constexpr (FC <= most_fields(R, NN)) {                                          \
+            *lds = sizeof(double) * (newton::NodeLds<double, FC, R, NN>::SIZE +            \
+                                     R * NN * 16 + (NN % 4 ? 1 : 0));                      \
+            return k_eval_mfma<R, NN, FC>;                                                 \
+        }                                                                                  \
+        return nullptr;
         FPTS_CASE(2)
         FPTS_CASE(3)
         FPTS_CASE(4)
@@ -874,8 +883,9 @@ hipError_t launch_eval(const fpts_mesh *m, int64_t n, int n_fields, int field_n,
     if (field_n == m->N) a.basis = m->basis;
     else gll::fill(field_n, a.basis.z, a.basis.w);
     if (m->R >= 2) {
-        // matrix cores, up to four fields per launch, evenly
-        const int launches = (n_fields + 3) / 4;
+        // matrix cores, up to most_fields per launch, evenly
+        const int most = most_fields(m->R, field_n);
+        const int launches = (n_fields + most - 1) / most;
         const dim3 grid(xcd_grid(std::min<int64_t>(l.task_bound, (int64_t)m->cus * 16)));
         for (int k = 0, f0 = 0; k < launches; ++k) {
             size_t lds = 0;
