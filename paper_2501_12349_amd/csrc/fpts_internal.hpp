@@ -465,10 +465,10 @@ hipError_t launch_cell_bin(const fpts_mesh *m, int pass, int64_t n, const double
 // cells; bin_shift returns -1 else): cells grouped into buckets of
 // 2^shift cells, at most kBinMaxBuckets of them.  tiles: as pass 0 of
 // launch_cell_bin, and each tile's bucket histogram into bh[bucket * ntile
-// + tile] (bh is then scanned in place, its total at bh[nb * ntile]); coarse: (cell, id) pairs sorted by bucket from the
-// scanned bh; rank: each pair's rank in its cell (cell_cnt zeroed before,
-// complete after), *total pairs; scatter: pbin[cell_poff[c] + rank[i]] =
-// id of pair i.
+// + tile] (bh is then scanned in place, its total at bh[nb * ntile]); coarse:
+// (cell, id) pairs sorted by bucket from the scanned bh; rank: each pair's rank
+// in its cell (cell_cnt zeroed before, complete after), *total pairs; scatter:
+// pbin[cell_poff[c] + rank[i]] = id of pair i.
 constexpr int64_t kBinMaxCells = (int64_t)1 << 24;
 constexpr int kBinMaxBuckets = 4096;
 constexpr int64_t kCellBinPoints = 4096;   // up to these: one atomic per point
@@ -500,8 +500,6 @@ hipError_t launch_bin_scatter(int64_t n, const int *total, const int2 *pairs, co
 hipError_t launch_hint(const fpts_mesh *m, int pass, int64_t n, const int32_t *code,
                        const int32_t *elem, const double *r, int2 *cand, int *elem_cnt,
                        int *rank, int *keep, hipStream_t s);
-// phase B: candidates of each point from its cell's list (one wave per 64
-// points of one cell), primary = deepest inside its OBB
 // Parked pairs binned by element, over the *total list positions q (at most
 // cap) of which those with node[q] < 0 hold one: pass 0 counts them per
 // element (elem_cnt, zeroed before) and keeps each one's rank (node[q] = -2 -
@@ -509,6 +507,8 @@ hipError_t launch_hint(const fpts_mesh *m, int pass, int64_t n, const int32_t *c
 hipError_t launch_park_bin(int pass, const int4 *meta, const int *total, int64_t cap,
                            int *node, int *elem_cnt, const int *elem_off, int *sorted, int cus,
                            hipStream_t s);
+// phase B: candidates of each point from its cell's list (one wave per 64
+// points of one cell), primary = deepest inside its OBB
 // (counts primaries per element; in bin order, bin_prim[i] and rank[i] are
 // the primary of the point at bin position i and its rank in that bucket)
 hipError_t launch_locate_cells(const fpts_mesh *m, int64_t n, const double *pts,

@@ -271,7 +271,13 @@ __global__ __launch_bounds__(64) void k_eval(EvalArgs a)
 // contraction enough of 128 registers, else two, with all they can use (N = 6,
 // four fields, 3M points: 250 us so, 373 held to four with 108 spilled
 // registers; N = 8, three fields, 5M points: 423 us, 468 with three waves, which
-// get in each other's way with their scattered writes).
+// get in each other's way with their scattered writes).  Calls of 2M points, N = 3
+// to 10, one to four fields, each with two, three and four waves: the rule's choice
+// is the fastest or within 3 % of it, but for quads of N = 9 and 10 with four
+// fields (266 us, 248 with four waves; 270, 258).  On either side of its lines:
+// hexes, N = 7, one field 230 us (248 with two waves), two 283 (313 with four);
+// N = 9 and 10, one field 346 (391), 466 (492); quads, N = 10, three fields 224
+// (250), N = 8, four 237 (234).
 template <int R, int N, int FC>
 constexpr int eval_waves_per_eu()
 {

@@ -248,8 +248,8 @@ __device__ inline int bin_point(const HashView &h, int p, int n, int R, const do
 }
 
 // Phase A with one atomic per point (bin_shift: few points, or more than
-// kBinMaxCells cells); the cells' counters lie cs ints apart.  pass 0: bin_point and the count per cell; pass 1: scatter point
-// ids into their cell's bucket.
+// kBinMaxCells cells); the cells' counters lie cs ints apart.  pass 0: bin_point
+// and the count per cell; pass 1: scatter point ids into their cell's bucket.
 template <int D>
 __global__ __launch_bounds__(256) void k_cell_bin(HashView h, int pass, int n, int R,
                                                  const double *pts, double *pts4, const int *keep,
@@ -1045,10 +1045,13 @@ hipError_t launch_cell_bin(const fpts_mesh *m, int pass, int64_t n, const double
 }
 
 // Up to kCellBinPoints points go to their cells with one atomic each: three
-// launches instead of six (of 3 to 5 us each; find + interpolate of 1000 points
-// 121 -> 111 us), and with the counters spread over at least 512 cache lines a
-// few thousand atomics take a few microseconds.  Beyond, points that crowd in
-// cells of one line would wait for each other's atomics, 16 ns each.
+// launches instead of six (of 3 to 5 us each), and with the counters spread over
+// at least 512 cache lines a few thousand atomics take a few microseconds.  The
+// line is a cautious one: find + interpolate took 7 to 16 us less so at every
+// size measured, 500 to 32000 points, all over the mesh or all in one cell (256
+// quads, N = 5: 1000 points 104 against 115 us, 4000 109 and 121, 16000 122 and
+// 132; 512 hexes, N = 8: 160 and 172, 193 and 205, 249 and 263); beyond, points
+// that crowd in cells of one line wait for each other's atomics, 16 ns each.
 int bin_shift(int64_t n, int64_t ncell)
 {
     if (n <= kCellBinPoints || ncell > kBinMaxCells) return -1;
