@@ -1047,7 +1047,7 @@ hipError_t launch_cell_bin(const fpts_mesh *m, int pass, int64_t n, const double
 // Up to kCellBinPoints points go to their cells with one atomic each: three
 // launches instead of six (of 3 to 5 us each), and with the counters spread over
 // at least 512 cache lines a few thousand atomics take a few microseconds.  The
-// line is a cautious one: find + interpolate took 7 to 16 us less so at every
+// line is a cautious one: find + interpolate took 5 to 17 us less so at every
 // size measured, 500 to 32000 points, all over the mesh or all in one cell (256
 // quads, N = 5: 1000 points 104 against 115 us, 4000 109 and 121, 16000 122 and
 // 132; 512 hexes, N = 8: 160 and 172, 193 and 205, 249 and 263); beyond, points
